@@ -14,10 +14,20 @@ static inline int cdiv(size_t a, int b) { return (int)((a + b - 1) / b); }
 //   y_u = alpha u - mu Lap u + (p_ij - p_{i-1,j}) / h + dt/h^2 (J^T K' J u)
 //   y_v = alpha v - mu Lap v + (p_ij - p_{i,j-1}) / h + dt/h^2 (J^T K' J v)
 //   y_p = -(u_{i+1,j} - u_ij + v_{i,j+1} - v_ij) / h
-// The IB term arrives as the nodal forces F = K' J u (k_ib_force) and is
-// gathered through the face -> (point, slot) lists, so no atomics are used.
+// The IB term comes in one of two forms (IBM), neither with atomics:
+// 2: the level's explicit Galerkin rows.  The stencil's threads leave the
+//    velocity rows that hold IB entries to the launch's last work-groups,
+//    where 16 or 64 lanes share a row: its entries, its stencil and its store.
+//    One launch does what interpolation, spring forces and the gather of
+//    form 1 do in three, each of them a chain of dependent loads: with the
+//    first Gram-Schmidt pass (FP64, two vectors) 6.2 us against 21.5 at 64^2
+//    (128 points), 5.1 against 20.6 at 256^2 (1024 points), 18.8 against 24.9
+//    at 512^2 (8192 points).
+// 1: the nodal forces F = K' J u (k_ib_force), gathered through the face ->
+//    (point, slot) lists, for levels whose explicit rows are too large
+//    (kIbRowsMaxEntries).
 // The transposed form evaluates -D^T p and G^T u directly; the IB block is
-// the same J^T K' J chain with J standing in for S^T (S = J^* / h^2).
+// symmetric (S = J^* / h^2).
 // ---------------------------------------------------------------------------
 // Rows per thread: grids below 2048 keep one point per thread (their fields
 // stay in the caches, and more waves hide the latency); larger grids march
@@ -36,11 +46,12 @@ __device__ __forceinline__ void store_out(T* p, T v) {
   else *p = v;
 }
 
-// Rows j0 .. j0+RJ-1 (those below N) of column i; emit(c0, y_u, y_v, y_p)
-// receives each point's three rows.
+// Rows j0 .. j0+RJ-1 (those below N) of column i; emit(c0, flag, y_u, y_v,
+// y_p) receives each point's three rows (flag: which of its velocity rows
+// belong to the IB rows' work-groups).
 template <typename T, bool TRANS, bool RESID, int IBM, int RJ, typename Emit>
 __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __restrict__ b,
-                                            const T* __restrict__ F, const T* __restrict__ Gib,
+                                            const T* __restrict__ F, const unsigned char* __restrict__ ibflag,
                                             const FootView<T>& fx, const FootView<T>& fy, int N, int M,
                                             const StokesCoef<T>& c, int i, int j0, Emit emit) {
   const size_t n = (size_t)N * N;
@@ -52,8 +63,6 @@ __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __
   const int jm0 = j0 == 0 ? N - 1 : j0 - 1;
   T ud = u[(size_t)jm0 * N + i], vd = v[(size_t)jm0 * N + i], pd = p[(size_t)jm0 * N + i];
   T uc = u[(size_t)j0 * N + i], vc = v[(size_t)j0 * N + i], pc = p[(size_t)j0 * N + i];
-  // the precomputed Galerkin rows already carry the factor dt/h^2
-  const T ibs = IBM == 2 ? T(1) : c.ibs;
 #pragma unroll
   for (int r = 0; r < RJ; ++r) {
     const int j = j0 + r;
@@ -64,10 +73,8 @@ __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __
     const T ut = u[ct], vt = v[ct];
     const T ul = u[row + im], ur = u[row + ip], vl = v[row + im], vr = v[row + ip], pl = p[row + im];
     T ibu = 0, ibv = 0;
-    if (IBM == 2) {
-      ibu = Gib[c0];
-      ibv = Gib[n + c0];
-    } else if (IBM == 1) {
+    const int flag = IBM == 2 ? ibflag[c0] : 0;
+    if (IBM == 1) {
       const int a0 = fx.sp_ptr[c0], a1 = fx.sp_ptr[c0 + 1];
       for (int e = a0; e < a1; ++e) ibu += fx.sw[e] * F[fx.sp_ent[e] >> 4];
       const int b0 = fy.sp_ptr[c0], b1 = fy.sp_ptr[c0 + 1];
@@ -77,15 +84,15 @@ __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __
     const T lapv = vl + vr + vd + vt - T(4) * vc;
     T yu, yv, yp;
     if (!TRANS) {
-      yu = c.alpha * uc - c.beta * lapu + c.gi * (pc - pl) + ibs * ibu;
-      yv = c.alpha * vc - c.beta * lapv + c.gi * (pc - pd) + ibs * ibv;
+      yu = c.alpha * uc - c.beta * lapu + c.gi * (pc - pl) + c.ibs * ibu;
+      yv = c.alpha * vc - c.beta * lapv + c.gi * (pc - pd) + c.ibs * ibv;
       yp = -c.gi * (ur - uc + vt - vc);
     } else {
       // (-D^T p) on the x-face (i, j): D maps the face to cells (i, j) with -1/h
       // and (i-1, j) with +1/h.  G^T u on cell (i, j): G maps the cell to faces
       // (i, j) with +1/h and (i+1, j) with -1/h (likewise in y).
-      yu = c.alpha * uc - c.beta * lapu - c.gi * (pl - pc) + ibs * ibu;
-      yv = c.alpha * vc - c.beta * lapv - c.gi * (pd - pc) + ibs * ibv;
+      yu = c.alpha * uc - c.beta * lapu - c.gi * (pl - pc) + c.ibs * ibu;
+      yv = c.alpha * vc - c.beta * lapv - c.gi * (pd - pc) + c.ibs * ibv;
       yp = c.gi * (uc - ur + vc - vt);
     }
     if (RESID) {
@@ -93,7 +100,7 @@ __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __
       yv = b[n + c0] - yv;
       yp = b[2 * n + c0] - yp;
     }
-    emit(c0, yu, yv, yp);
+    emit(c0, flag, yu, yv, yp);
     if (r + 1 < RJ) {
       ud = uc;
       vd = vc;
@@ -105,23 +112,95 @@ __device__ __forceinline__ void apply_strip(const T* __restrict__ w, const T* __
   }
 }
 
+// One explicit IB row r = comp N^2 + (j N + i), its LANES lanes (sub) sharing
+// the entries: the lane sums by a butterfly in a fixed order, the stencil
+// added by every lane alike.
+template <typename T, bool TRANS, bool RESID, int LANES>
+__device__ __forceinline__ T apply_ib_row(const T* __restrict__ w, const T* __restrict__ b, const IbRows<T>& R, int N,
+                                          const StokesCoef<T>& c, int r, int sub) {
+  const int n = N * N, comp = r >= n ? 1 : 0, q = r - comp * n;
+  const int i = q % N, j = q / N, o = comp * n;
+  const int im = i == 0 ? N - 1 : i - 1, ip = i == N - 1 ? 0 : i + 1;
+  const int jm = j == 0 ? N - 1 : j - 1, jp = j == N - 1 ? 0 : j + 1;
+  const T* p = w + 2 * (size_t)n;
+  const T xc = w[r], xl = w[o + j * N + im], xr = w[o + j * N + ip], xd = w[o + jm * N + i], xt = w[o + jp * N + i];
+  const T pc = p[q], pb = p[comp ? jm * N + i : j * N + im];
+  const CsrT<T> t = comp ? R.tv : R.tu;
+  const int lo = t.ptr[q], hi = t.ptr[q + 1];
+  T a = 0;
+  int k = lo + sub;
+  for (; k + 3 * LANES < hi; k += 4 * LANES) {   // four gathers in flight
+    const T p0 = t.val[k] * w[t.col[k]], p1 = t.val[k + LANES] * w[t.col[k + LANES]];
+    const T p2 = t.val[k + 2 * LANES] * w[t.col[k + 2 * LANES]], p3 = t.val[k + 3 * LANES] * w[t.col[k + 3 * LANES]];
+    a += (p0 + p1) + (p2 + p3);
+  }
+  for (; k < hi; k += LANES) a += t.val[k] * w[t.col[k]];
+#pragma unroll
+  for (int off = LANES / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, LANES);
+  const T lap = xl + xr + xd + xt - T(4) * xc;
+  const T gp = TRANS ? -c.gi * (pb - pc) : c.gi * (pc - pb);
+  const T y = c.alpha * xc - c.beta * lap + gp + a;
+  return RESID ? b[r] - y : y;
+}
+
+// IB-row work-group blk of nrb: rows blk, blk + nrb, ... of row groups of
+// 256 / LANES; emit(r, y) once per row (lane sub = 0)
+template <typename T, bool TRANS, bool RESID, int LANES, typename Emit>
+__device__ __forceinline__ void apply_ib_rows(const T* __restrict__ w, const T* __restrict__ b, const IbRows<T>& R,
+                                              int N, const StokesCoef<T>& c, int blk, int nrb, int tid, Emit emit) {
+  const int grp = tid / LANES, sub = tid % LANES;
+  for (int g = blk * (256 / LANES) + grp; g < R.n; g += nrb * (256 / LANES)) {
+    const int r = R.rows[g];
+    const T y = apply_ib_row<T, TRANS, RESID, LANES>(w, b, R, N, c, r, sub);
+    if (sub == 0) emit(r, y);
+  }
+}
+
+// work-groups of the stencil part, and of the explicit IB rows: one row group
+// each up to 1024 work-groups (a 512^2 annulus level with 2.35 M entries:
+// 28.4 us with 256 of them, 22.8 with 512, 18.8 with 1024, 19.5 with 2048,
+// whose partial sums the next kernel pays for)
+static inline int strip_blocks(int N) {
+  const int rj = apply_rows(N);
+  const dim3 blk = apply_block(rj);
+  const int rows = (int)blk.y * rj;
+  return ((N + (int)blk.x - 1) / (int)blk.x) * ((N + rows - 1) / rows);
+}
+static inline int ib_row_blocks(int nrows, int lanes) {
+  if (nrows <= 0) return 0;
+  const int g = cdiv((size_t)nrows * lanes, 256);
+  return g < 1024 ? g : 1024;
+}
+int apply_blocks(int N, int nrows, int lanes) { return strip_blocks(N) + ib_row_blocks(nrows, lanes); }
+
+// grid: strip_blocks(N) work-groups of the stencil, then the IB rows' (x);
+// systems (z; batched launches, which take no IB rows here)
 template <typename T, bool TRANS, bool RESID, int IBM, int RJ>
 __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __restrict__ y,
                                                const T* __restrict__ b, const T* __restrict__ F,
-                                               const T* __restrict__ Gib, FootView<T> fx,
+                                               IbRows<T> R, FootView<T> fx,
                                                FootView<T> fy, int N, int M, StokesCoef<T> c,
-                                               size_t bs) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j0 = (blockIdx.y * blockDim.y + threadIdx.y) * RJ;
+                                               size_t bs, int nsb) {
+  if (IBM == 2 && (int)blockIdx.x >= nsb) {
+    const int tid = threadIdx.y * blockDim.x + threadIdx.x, blk = blockIdx.x - nsb, nrb = gridDim.x - nsb;
+    auto emit = [&](int r, T v) { y[r] = v; };
+    if (R.lanes == 16) apply_ib_rows<T, TRANS, RESID, 16>(w, b, R, N, c, blk, nrb, tid, emit);
+    else apply_ib_rows<T, TRANS, RESID, 64>(w, b, R, N, c, blk, nrb, tid, emit);
+    return;
+  }
+  const int gx = (N + (int)blockDim.x - 1) / (int)blockDim.x;
+  const int i = ((int)blockIdx.x % gx) * blockDim.x + threadIdx.x;
+  const int j0 = (((int)blockIdx.x / gx) * blockDim.y + threadIdx.y) * RJ;
   if (i >= N || j0 >= N) return;
   // batched launches: system blockIdx.z, systems bs apart
   w += blockIdx.z * bs;
   y += blockIdx.z * bs;
   if (RESID) b += blockIdx.z * bs;
   const size_t n = (size_t)N * N;
-  apply_strip<T, TRANS, RESID, IBM, RJ>(w, b, F, Gib, fx, fy, N, M, c, i, j0, [&](size_t c0, T yu, T yv, T yp) {
-    store_out<RJ>(y + c0, yu);
-    store_out<RJ>(y + n + c0, yv);
+  apply_strip<T, TRANS, RESID, IBM, RJ>(w, b, F, R.flag, fx, fy, N, M, c, i, j0,
+                                        [&](size_t c0, int flag, T yu, T yv, T yp) {
+    if (IBM != 2 || !(flag & 1)) store_out<RJ>(y + c0, yu);
+    if (IBM != 2 || !(flag & 2)) store_out<RJ>(y + n + c0, yv);
     store_out<RJ>(y + 2 * n + c0, yp);
   });
 }
@@ -134,131 +213,148 @@ __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __res
 template <typename T, bool RESID, int IBM, int RJ>
 __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* __restrict__ y,
                                                     const T* __restrict__ b, const T* __restrict__ F,
-                                                    const T* __restrict__ Gib, FootView<T> fx, FootView<T> fy,
+                                                    IbRows<T> R, FootView<T> fx, FootView<T> fy,
                                                     int N, int M, StokesCoef<T> c, const T* __restrict__ V,
-                                                    int nvec, size_t vstride, double* __restrict__ partial) {
+                                                    int nvec, size_t vstride, double* __restrict__ partial, int nsb) {
   __shared__ double red[9][4];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j0 = (blockIdx.y * blockDim.y + threadIdx.y) * RJ;
-  const bool live = i < N && j0 < N;
   const size_t n = (size_t)N * N;
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x, wave = tid >> 6, lane = tid & 63;
   double d[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) d[q] = 0.0;
-  if (live)
-    apply_strip<T, false, RESID, IBM, RJ>(w, b, F, Gib, fx, fy, N, M, c, i, j0, [&](size_t c0, T yu, T yv, T yp) {
-      store_out<RJ>(y + c0, yu);
-      store_out<RJ>(y + n + c0, yv);
-      store_out<RJ>(y + 2 * n + c0, yp);
-      if (V) {
+  // adds one entry's products to the thread's sums
+  auto dot = [&](size_t k, T v) {
+    if (V) {
 #pragma unroll
-        for (int q = 0; q < 9; ++q)
-          if (q < nvec) {
-            const T* vq = V + (size_t)q * vstride;
-            d[q] += (double)vq[c0] * (double)yu + (double)vq[n + c0] * (double)yv + (double)vq[2 * n + c0] * (double)yp;
-          }
-      } else {
-        d[0] += (double)yu * (double)yu + (double)yv * (double)yv + (double)yp * (double)yp;
-      }
-    });
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x, wave = tid >> 6, lane = tid & 63;
+      for (int q = 0; q < 9; ++q)
+        if (q < nvec) d[q] += (double)V[(size_t)q * vstride + k] * (double)v;
+    } else {
+      d[0] += (double)v * (double)v;
+    }
+  };
+  if (IBM == 2 && (int)blockIdx.x >= nsb) {
+    const int blk = blockIdx.x - nsb, nrb = gridDim.x - nsb;
+    auto emit = [&](int r, T v) {
+      y[r] = v;
+      dot((size_t)r, v);
+    };
+    if (R.lanes == 16) apply_ib_rows<T, false, RESID, 16>(w, b, R, N, c, blk, nrb, tid, emit);
+    else apply_ib_rows<T, false, RESID, 64>(w, b, R, N, c, blk, nrb, tid, emit);
+  } else {
+    const int gx = (N + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int i = ((int)blockIdx.x % gx) * blockDim.x + threadIdx.x;
+    const int j0 = (((int)blockIdx.x / gx) * blockDim.y + threadIdx.y) * RJ;
+    if (i < N && j0 < N)
+      apply_strip<T, false, RESID, IBM, RJ>(w, b, F, R.flag, fx, fy, N, M, c, i, j0,
+                                            [&](size_t c0, int flag, T yu, T yv, T yp) {
+        if (IBM != 2 || !(flag & 1)) {
+          store_out<RJ>(y + c0, yu);
+          dot(c0, yu);
+        }
+        if (IBM != 2 || !(flag & 2)) {
+          store_out<RJ>(y + n + c0, yv);
+          dot(n + c0, yv);
+        }
+        store_out<RJ>(y + 2 * n + c0, yp);
+        dot(2 * n + c0, yp);
+      });
+  }
 #pragma unroll
   for (int q = 0; q < 9; ++q) {
-    if (q >= nvec) break;
-    double a = d[q];
+    if (q < nvec) {
+      double a = d[q];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (lane == 0) red[q][wave] = a;
+      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+      if (lane == 0) red[q][wave] = a;
+    }
   }
   __syncthreads();
   if (tid < nvec)
-    partial[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * nvec + tid] =
-        (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+    partial[(size_t)blockIdx.x * nvec + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
 }
 
-
 template <typename T, int IBM, int RJ>
-static void launch_apply_r(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
+static void launch_apply_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                            FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose,
                            hipStream_t s, int nsys, size_t bs) {
   const dim3 blk = apply_block(RJ);
-  dim3 grd((N + blk.x - 1) / blk.x, (N + blk.y * RJ - 1) / (blk.y * RJ), nsys);
+  const int nsb = strip_blocks(N);
+  const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0), 1, nsys);
   if (b) {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, bs);
+      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, bs);
+      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
   } else {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, bs);
+      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, bs);
+      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
   }
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T, int IBM>
-static void launch_apply_m(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
+static void launch_apply_m(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                            FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose,
                            hipStream_t s, int nsys = 1, size_t bs = 0) {
-  if (apply_rows(N) == 4) launch_apply_r<T, IBM, 4>(w, y, b, F, G, fx, fy, N, M, c, transpose, s, nsys, bs);
-  else launch_apply_r<T, IBM, 1>(w, y, b, F, G, fx, fy, N, M, c, transpose, s, nsys, bs);
+  if (apply_rows(N) == 4) launch_apply_r<T, IBM, 4>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, nsys, bs);
+  else launch_apply_r<T, IBM, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, nsys, bs);
 }
 
-// IB source: G (precomputed dt/h^2 J^T K' J u rows) if non-null, else the
-// forces F gathered through the spreading lists if non-null, else none.
 template <typename T>
-void launch_apply(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
+static void check_ib_rows(const IbRows<T>& R) {
+  if (R.n > 0 && R.lanes != 16 && R.lanes != 64) throw Error(IBMG_ERR_ARG, "IB rows take 16 or 64 lanes");
+}
+
+template <typename T>
+void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                   FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s) {
-  if (G)
-    launch_apply_m<T, 2>(w, y, b, F, G, fx, fy, N, M, c, transpose, s);
+  check_ib_rows(R);
+  if (R.n > 0)
+    launch_apply_m<T, 2>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
   else if (F)
-    launch_apply_m<T, 1>(w, y, b, F, G, fx, fy, N, M, c, transpose, s);
+    launch_apply_m<T, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
   else
-    launch_apply_m<T, 0>(w, y, b, F, G, fx, fy, N, M, c, transpose, s);
+    launch_apply_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
 }
 
 template <typename T, int IBM, int RJ>
-static void launch_apply_dots_r(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
+static void launch_apply_dots_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                                 FootView<T> fy, int N, int M, StokesCoef<T> c, const T* V, int nvec,
                                 size_t vstride, double* partial, hipStream_t s) {
   const dim3 blk = apply_block(RJ);
-  dim3 grd((N + blk.x - 1) / blk.x, (N + blk.y * RJ - 1) / (blk.y * RJ));
+  const int nsb = strip_blocks(N);
+  const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0));
   if (b)
-    IBMG_KLAUNCH((k_apply_dots<T, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, V, nvec,
-                       vstride, partial);
+    IBMG_KLAUNCH((k_apply_dots<T, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, V, nvec,
+                       vstride, partial, nsb);
   else
-    IBMG_KLAUNCH((k_apply_dots<T, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, G, fx, fy, N, M, c, V, nvec,
-                       vstride, partial);
+    IBMG_KLAUNCH((k_apply_dots<T, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, V, nvec,
+                       vstride, partial, nsb);
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T, int IBM>
-static void launch_apply_dots_m(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
+static void launch_apply_dots_m(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                                 FootView<T> fy, int N, int M, StokesCoef<T> c, const T* V, int nvec,
                                 size_t vstride, double* partial, hipStream_t s) {
-  if (apply_rows(N) == 4) launch_apply_dots_r<T, IBM, 4>(w, y, b, F, G, fx, fy, N, M, c, V, nvec, vstride, partial, s);
-  else launch_apply_dots_r<T, IBM, 1>(w, y, b, F, G, fx, fy, N, M, c, V, nvec, vstride, partial, s);
-}
-
-int apply_blocks(int N) {
-  const int rj = apply_rows(N);
-  const dim3 blk = apply_block(rj);
-  const int rows = (int)blk.y * rj;
-  return ((N + (int)blk.x - 1) / (int)blk.x) * ((N + rows - 1) / rows);
+  if (apply_rows(N) == 4) launch_apply_dots_r<T, IBM, 4>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+  else launch_apply_dots_r<T, IBM, 1>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
 }
 
 template <typename T>
-void launch_apply_dots(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx, FootView<T> fy,
+void launch_apply_dots(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy,
                        int N, int M, StokesCoef<T> c, const T* V, int nvec, size_t vstride, double* partial,
                        hipStream_t s) {
   if (nvec < 1 || nvec > 9) throw Error(IBMG_ERR_ARG, "fused dots take 1..9 vectors");
-  if (G)
-    launch_apply_dots_m<T, 2>(w, y, b, F, G, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+  check_ib_rows(R);
+  if (R.n > 0)
+    launch_apply_dots_m<T, 2>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
   else if (F)
-    launch_apply_dots_m<T, 1>(w, y, b, F, G, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 1>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
   else
-    launch_apply_dots_m<T, 0>(w, y, b, F, G, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
 }
 
 // Stencil part of L_IB (or the residual) for nsys systems of one grid size,
@@ -268,7 +364,7 @@ void launch_apply_batch(const T* w, T* y, const T* b, int N, StokesCoef<T> c, in
                         hipStream_t s) {
   if (nsys <= 0) return;
   FootView<T> none{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  launch_apply_m<T, 0>(w, y, b, nullptr, nullptr, none, none, N, 0, c, false, s, nsys, bs);
+  launch_apply_m<T, 0>(w, y, b, nullptr, IbRows<T>{}, none, none, N, 0, c, false, s, nsys, bs);
 }
 
 // Explicit IB rows: one wave per listed row, lanes over its entries, the
@@ -871,7 +967,7 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
 // Explicit instantiations.
 // ---------------------------------------------------------------------------
 #define IBMG_INST_GRID(T)                                                                         \
-  template void launch_apply<T>(const T*, T*, const T*, const T*, const T*, FootView<T>,          \
+  template void launch_apply<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,         \
                                 FootView<T>, int, int, StokesCoef<T>, bool, hipStream_t);         \
   template void launch_restrict<T>(const T*, T*, int, hipStream_t);                               \
   template void launch_restrict_norm<T>(const T*, T*, int, double*, hipStream_t);                 \
@@ -886,7 +982,7 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
   template void launch_combine<T>(T*, const T*, int, size_t, const double*, size_t, hipStream_t); \
   template void launch_block_sums<T>(const T*, int, double*, int, hipStream_t);                   \
   template void launch_subtract_means<T>(T*, int, const double*, int, hipStream_t);               \
-  template void launch_apply_dots<T>(const T*, T*, const T*, const T*, const T*, FootView<T>,     \
+  template void launch_apply_dots<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,    \
                                      FootView<T>, int, int, StokesCoef<T>, const T*, int, size_t,  \
                                      double*, hipStream_t);                                        \
   template void launch_apply_batch<T>(const T*, T*, const T*, int, StokesCoef<T>, int, size_t,    \

@@ -293,24 +293,38 @@ constexpr int kMaxNloc = 2 * kMaxBoxSide * (kMaxBoxSide + 1) + kMaxBoxSide * kMa
 // ---------------------------------------------------------------------------
 // grid ops
 template <typename T>
-void launch_apply(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx,
-                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s);
-// L_IB w (b != null: b - L_IB w) with the first Gram-Schmidt pass fused:
-// partial[blk * nvec + q] = block sums of V_q . y (V = null: nvec = 1, y . y)
-// over apply_blocks(N) blocks; nvec <= 9
-template <typename T>
-void launch_apply_dots(const T* w, T* y, const T* b, const T* F, const T* G, FootView<T> fx, FootView<T> fy,
-                       int N, int M, StokesCoef<T> c, const T* V, int nvec, size_t vstride, double* partial,
-                       hipStream_t s);
-int apply_blocks(int N);
-template <typename T>
 struct CsrT {
   const int* ptr;
   const int* col;
   const T* val;
 };
+// A level's explicit IB rows (Galerkin rows of both velocity components,
+// columns over [u | v]): the rows that hold entries, as comp N^2 + face, and
+// per face the bits 1 (its u row is one of them) and 2 (its v row).
 template <typename T>
-void launch_ib_spmv(const T* x, T* G, CsrT<T> tu, CsrT<T> tv, int N, hipStream_t s);
+struct IbRows {
+  const int* rows;            // [n]
+  const unsigned char* flag;  // [N*N]
+  CsrT<T> tu, tv;
+  int n;
+  int lanes;                  // lanes per row: 16 or 64
+};
+// y = L_IB w or b - L_IB w (b != null), or the transposed product.  The IB
+// term comes from the explicit rows (R.n > 0), else from the nodal forces F
+// (F != null), else there is none.
+template <typename T>
+void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
+                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s);
+// L_IB w (b != null: b - L_IB w) with the first Gram-Schmidt pass fused:
+// partial[blk * nvec + q] = block sums of V_q . y (V = null: nvec = 1, y . y)
+// over apply_blocks(N, R) blocks; nvec <= 9
+template <typename T>
+void launch_apply_dots(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy,
+                       int N, int M, StokesCoef<T> c, const T* V, int nvec, size_t vstride, double* partial,
+                       hipStream_t s);
+// blocks of launch_apply_dots on an N x N level with nrows explicit IB rows
+// of `lanes` lanes each (0: none)
+int apply_blocks(int N, int nrows, int lanes);
 template <typename T>
 void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s);
 // the same, and partial[0..restrict_blocks(Nc)) = per-block sums of the

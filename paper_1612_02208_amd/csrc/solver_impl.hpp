@@ -27,9 +27,16 @@ constexpr int kMaxNu = 8;
 constexpr int kMaxRestart = 64;
 constexpr int kScalY = 1;     // scal[1..16]: least-squares solution
 constexpr int kScalTmp = 20;  // scal[20..]: second Gram-Schmidt pass
-// Levels whose longest face -> point list exceeds this use the explicit
-// Galerkin IB rows (one wave per row) for the IB term.
-constexpr int kSpmvListThreshold = 24;
+// The IB term of L_IB w comes from a level's explicit Galerkin rows (in the
+// operator's own launch) up to this many entries.  Beyond the bare stencil the
+// rows cost about 4.2 to 5.9 us per million entries (12 bytes each, FP64), the
+// other form (interpolate, spring forces, gather: three launches) about 15 us
+// at any size measured: 512^2 annulus, FP64, 2.35 M entries 18.8 against 24.9
+// us, 4.6 M (tangent springs) 36.3 against 24.2.  IBMG_NO_IB_ROWS in the
+// environment takes the other form on every level.
+constexpr size_t kIbRowsMaxEntries = 3500000;
+// lanes per explicit row: a wave where rows are long (crowded coarse levels)
+constexpr int kIbLongRow = 96;
 // partial-sum buffers: two of kPartStride doubles (blocks x vectors)
 constexpr size_t kPartStride = (size_t)256 * 65;
 // the outer solve's Gram-Schmidt passes: up to kOuterBlocks blocks of up to
@@ -66,11 +73,12 @@ template <typename T>
 struct Level {
   int N = 0;
   CompFoot f[2];
-  // IB term from the explicit Galerkin rows (wave per row) instead of the
-  // interpolate / spring / spread chain: chosen where points crowd the faces
-  bool use_spmv = false;
-  DBuf<double> Gd;
-  DBuf<T> Gt;
+  // rows of the IB term (comp N^2 + face) and the faces' flags; ib_lanes = 0:
+  // the IB term of L_IB w by interpolation, spring forces and the gather
+  std::vector<int> ib_rows;
+  int ib_lanes = 0;
+  DBuf<int> d_ib_rows;
+  DBuf<unsigned char> d_ib_flag;
   StokesCoef<double> cd{};
   StokesCoef<T> ct{};
   // restricted additive Schwarz
@@ -347,12 +355,33 @@ class Solver final : public SolverBase {
         for (size_t r = 0; r + 1 < f.sp_ptr.size(); ++r)
           f.max_list = std::max(f.max_list, f.sp_ptr[r + 1] - f.sp_ptr[r]);
       }
-      lev.use_spmv = std::max(lev.f[0].max_list, lev.f[1].max_list) > kSpmvListThreshold;
+      list_ib_rows(lev, s);
       if (l >= 1 && (d_.smoother == IBMG_RAS || d_.smoother == IBMG_RMS)) classify_boxes(lev);
       if (l >= 1 && d_.smoother == IBMG_RMS) colour_boxes(lev);
       if (l >= 1 && d_.smoother == IBMG_SC) sc_structure(lev, s);
     }
     mark("box classes");
+  }
+
+  // The level's rows with IB entries, the faces' flags and the lanes a row
+  // gets in the operator's launch (0: too many entries, see kIbRowsMaxEntries).
+  void list_ib_rows(Level<T>& lev, hipStream_t s) {
+    const int nn = lev.N * lev.N;
+    const size_t nnz = lev.f[0].tcol.size() + lev.f[1].tcol.size();
+    lev.ib_rows.clear();
+    lev.ib_lanes = 0;
+    // (a member of a batch applies its operator through the batch's own rows)
+    if (defer_coarse_ || nnz == 0 || nnz > kIbRowsMaxEntries || std::getenv("IBMG_NO_IB_ROWS")) return;
+    std::vector<unsigned char> flag(nn, 0);
+    for (int c = 0; c < 2; ++c)
+      for (int q = 0; q < nn; ++q)
+        if (lev.f[c].tptr[q + 1] > lev.f[c].tptr[q]) {
+          lev.ib_rows.push_back(c * nn + q);
+          flag[q] |= (unsigned char)(1 << c);
+        }
+    lev.ib_lanes = nnz > (size_t)kIbLongRow * lev.ib_rows.size() ? 64 : 16;
+    lev.d_ib_rows.upload(lev.ib_rows, s);
+    lev.d_ib_flag.upload(flag, s);
   }
 
   // Points in cell order (row-major by the finest x-window base, ties in
@@ -629,10 +658,15 @@ class Solver final : public SolverBase {
                         parts, acc, tb, lev.int_x.p, lev.int_x.n, sym ? &sy : nullptr);
   }
 
+  // blocks of the fused operator + dots kernel on a level
+  static int dot_blocks(const Level<T>& lev) {
+    return apply_blocks(lev.N, lev.ib_lanes ? (int)lev.ib_rows.size() : 0, lev.ib_lanes);
+  }
+
   // partial-sum buffers of a level: the reductions' blocks x vectors, and the
   // fused operator kernel's blocks x (nu + 1) vectors
   static size_t part_stride(const Level<T>& lev) {
-    return std::max(kPartStride, (size_t)apply_blocks(lev.N) * (kMaxNu + 1));
+    return std::max(kPartStride, (size_t)dot_blocks(lev) * (kMaxNu + 1));
   }
 
   // Interior product form per Schwarz level: time the pipelined XCD-ordered
@@ -1177,10 +1211,6 @@ class Solver final : public SolverBase {
       }
       lev.F.alloc(4 * (size_t)std::max(M_, 1));   // forces [2][M] then J u [2][M]
       if (l >= 1 && d_.smoother == IBMG_RMS) lev.rr.alloc(n);
-      if (lev.use_spmv) {
-        lev.Gd.alloc(2 * (size_t)lev.N * lev.N);
-        if (std::is_same<T, float>::value) lev.Gt.alloc(2 * (size_t)lev.N * lev.N);
-      }
       lev.H.alloc((size_t)(kMaxNu + 1) * kMaxNu);
       lev.scal.alloc(64);
       lev.part.alloc(2 * part_stride(lev));
@@ -1210,50 +1240,41 @@ class Solver final : public SolverBase {
     else return StokesCoef<float>{(float)lev.cd.alpha, (float)lev.cd.beta, (float)lev.cd.gi, (float)lev.cd.ibs};
   }
 
+  // the level's explicit IB rows, or its nodal forces K' J x formed in F (Fp)
+  template <typename U>
+  IbRows<U> ib_source(Level<T>& lev, const U* x, U* F, const U** Fp, hipStream_t s) {
+    *Fp = nullptr;
+    if (lev.ib_lanes)
+      return IbRows<U>{lev.d_ib_rows.p, lev.d_ib_flag.p, csr<U>(lev.f[0]), csr<U>(lev.f[1]), (int)lev.ib_rows.size(),
+                       lev.ib_lanes};
+    if (M_ > 0 && E_ > 0) {
+      const size_t nn = (size_t)lev.N * lev.N;
+      launch_ib_force<U>(x, x + nn, fview<U>(lev.f[0]), fview<U>(lev.f[1]), sview<U>(), lev.N,
+                         F + 2 * (size_t)std::max(M_, 1), F, s);
+      *Fp = F;
+    }
+    return IbRows<U>{};
+  }
+
   // y = L_IB^l x (b != null: y = b - L_IB^l x)
   template <typename U>
   void op(int l, const U* x, U* y, const U* b, bool trans, U* F, hipStream_t s) {
     Level<T>& lev = levels_[l];
-    const size_t nn = (size_t)lev.N * lev.N;
-    const U* Fp = nullptr;
-    const U* Gp = nullptr;
-    if (M_ > 0 && E_ > 0) {
-      if (lev.use_spmv) {
-        U* G = gbuf<U>(lev);
-        launch_ib_spmv<U>(x, G, csr<U>(lev.f[0]), csr<U>(lev.f[1]), lev.N, s);
-        Gp = G;
-      } else {
-        launch_ib_force<U>(x, x + nn, fview<U>(lev.f[0]), fview<U>(lev.f[1]), sview<U>(), lev.N,
-                           F + 2 * (size_t)std::max(M_, 1), F, s);
-        Fp = F;
-      }
-    }
-    launch_apply<U>(x, y, b, Fp, Gp, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev),
-                    trans, s);
+    const U* Fp;
+    const IbRows<U> R = ib_source<U>(lev, x, F, &Fp, s);
+    launch_apply<U>(x, y, b, Fp, R, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), trans, s);
   }
 
   // y = L_IB^l x (b != null: y = b - L_IB^l x) with the first Gram-Schmidt
-  // pass fused into the operator kernel: partial holds apply_blocks(N)
+  // pass fused into the operator kernel: partial holds dot_blocks(lev)
   // blocks of the dots V_q . y, q < nvec (V = null: y . y)
   template <typename U>
   void op_dots(int l, const U* x, U* y, const U* b, const U* V, int nvec, size_t vstride, double* partial, U* F,
                hipStream_t s) {
     Level<T>& lev = levels_[l];
-    const size_t nn = (size_t)lev.N * lev.N;
-    const U* Fp = nullptr;
-    const U* Gp = nullptr;
-    if (M_ > 0 && E_ > 0) {
-      if (lev.use_spmv) {
-        U* G = gbuf<U>(lev);
-        launch_ib_spmv<U>(x, G, csr<U>(lev.f[0]), csr<U>(lev.f[1]), lev.N, s);
-        Gp = G;
-      } else {
-        launch_ib_force<U>(x, x + nn, fview<U>(lev.f[0]), fview<U>(lev.f[1]), sview<U>(), lev.N,
-                           F + 2 * (size_t)std::max(M_, 1), F, s);
-        Fp = F;
-      }
-    }
-    launch_apply_dots<U>(x, y, b, Fp, Gp, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), V, nvec,
+    const U* Fp;
+    const IbRows<U> R = ib_source<U>(lev, x, F, &Fp, s);
+    launch_apply_dots<U>(x, y, b, Fp, R, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), V, nvec,
                          vstride, partial, s);
   }
 
@@ -1264,12 +1285,6 @@ class Solver final : public SolverBase {
     else
       return CsrT<float>{f.d_tptr.p, f.d_tcol.p, f.tvalf.p};
   }
-  template <typename U>
-  U* gbuf(Level<T>& lev) {
-    if constexpr (std::is_same<U, double>::value) return lev.Gd.p;
-    else return lev.Gt.p;
-  }
-
   // ------------------------------------------------------- V-cycle pieces
   void basic_smoother(int l, const T* v, T* z, hipStream_t s) {
     Level<T>& lev = levels_[l];
@@ -1335,7 +1350,7 @@ class Solver final : public SolverBase {
     double* beta = lev.scal.p;
     double* pa = lev.part.p;
     double* pb = lev.part.p + part_stride(lev);
-    const int nab = apply_blocks(lev.N);  // blocks of the fused operator + dots kernel
+    const int nab = dot_blocks(lev);  // blocks of the fused operator + dots kernel
     T* V = lev.V.p;
     T* Z = lev.Z.p;
     if (w_zero && b_nblk > 0) {
@@ -1782,7 +1797,7 @@ class Solver final : public SolverBase {
       by = 2.0 * (double)n * ts;
       fl = 0;
       ms = time_launches([&] {
-        launch_apply<T>(lev.r.p, lev.t.p, nullptr, nullptr, nullptr, fview<T>(lev.f[0]), fview<T>(lev.f[1]), lev.N,
+        launch_apply<T>(lev.r.p, lev.t.p, nullptr, nullptr, IbRows<T>{}, fview<T>(lev.f[0]), fview<T>(lev.f[1]), lev.N,
                         M_, coef<T>(lev), false, s);
       }, reps, s);
     } else if (kernel == IBMG_KERNEL_RESTRICT || kernel == IBMG_KERNEL_PROLONG) {
@@ -1828,7 +1843,7 @@ class Solver final : public SolverBase {
       // least squares well posed, so repeated launches see the same values
       require(level >= 1, "the smoothing kernels run on levels >= 1");
       const int k = nu_;
-      const int nblk = dots_blocks(n, 1024), nab = apply_blocks(lev.N), ldh = kMaxNu + 1;
+      const int nblk = dots_blocks(n, 1024), nab = dot_blocks(lev), ldh = kMaxNu + 1;
       double* pa = lev.part.p;
       double* pb = lev.part.p + part_stride(lev);
       T* V = lev.V.p;
