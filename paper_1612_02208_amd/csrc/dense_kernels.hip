@@ -770,29 +770,6 @@ __global__ void __launch_bounds__(256) k_ras_ib(const T* __restrict__ r, T* __re
 // of its column phase, which belongs to owned row q of an earlier chunk.
 // The box's partials: the chunk's row sums per slice at sym_part_off(c,
 // ks), its column sums after them (each column in one slice).
-// Sum over the 16 lanes of a DPP row (every lane of the row ends with the
-// same bits): swap neighbours and pairs within quads, then mirror within
-// halves and within the row, adding after each step.
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-template <typename T>
-__device__ __forceinline__ T row16_sum(T p) {
-  p += dpp_move<0xB1>(p);    // quad_perm [1,0,3,2]
-  p += dpp_move<0x4E>(p);    // quad_perm [2,3,0,1]
-  p += dpp_move<0x141>(p);   // row_half_mirror
-  p += dpp_move<0x140>(p);   // row_mirror
-  return p;
-}
-
 template <typename T>
 __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, BoxGeom g, const T* __restrict__ inv,
                                                     const int* __restrict__ boxes, const int* __restrict__ perm,

@@ -205,32 +205,31 @@ __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __res
   });
 }
 
-// The same (non-transposed) with the first Gram-Schmidt dot products fused:
-// partial[blk * nvec + q] = this block's sum of V_q . y over its rows
-// (V = null: nvec = 1 and the sum of y . y), each thread's points summed in
-// row order, then reduced over the block's four waves by shuffles and shared
-// memory in a fixed order; blk = the block's linear index.
-template <typename T, bool RESID, int IBM, int RJ>
+// The same (L_IB w) with the first Gram-Schmidt dot products fused:
+// partial[blk * nvec + q] = this block's sum of u_q . y over its rows (u_0 =
+// u0, u_q = V + q vstride; NV = nvec), with NV = 1 also u_0 . u_0 (two sums per
+// block); each thread's points summed in row order, then over the block in a
+// fixed order; blk = the block's linear index.
+template <typename T, int IBM, int RJ, int NV>
 __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* __restrict__ y,
-                                                    const T* __restrict__ b, const T* __restrict__ F,
-                                                    IbRows<T> R, FootView<T> fx, FootView<T> fy,
-                                                    int N, int M, StokesCoef<T> c, const T* __restrict__ V,
-                                                    int nvec, size_t vstride, double* __restrict__ partial, int nsb) {
-  __shared__ double red[9][4];
+                                                    const T* __restrict__ F, IbRows<T> R, FootView<T> fx,
+                                                    FootView<T> fy, int N, int M, StokesCoef<T> c,
+                                                    const T* __restrict__ u0, const T* __restrict__ V,
+                                                    size_t vstride, double* __restrict__ partial, int nsb) {
+  constexpr int NS = NV == 1 ? 2 : NV;   // sums per block
+  __shared__ double red[NS * 4];
   const size_t n = (size_t)N * N;
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  double d[9];
+  const int tid = threadIdx.y * blockDim.x + threadIdx.x;
+  double d[NS];
 #pragma unroll
-  for (int q = 0; q < 9; ++q) d[q] = 0.0;
+  for (int q = 0; q < NS; ++q) d[q] = 0.0;
   // adds one entry's products to the thread's sums
   auto dot = [&](size_t k, T v) {
-    if (V) {
+    const double a = (double)u0[k];
+    d[0] += a * (double)v;
+    if constexpr (NV == 1) d[1] += a * a;
 #pragma unroll
-      for (int q = 0; q < 9; ++q)
-        if (q < nvec) d[q] += (double)V[(size_t)q * vstride + k] * (double)v;
-    } else {
-      d[0] += (double)v * (double)v;
-    }
+    for (int q = 1; q < NV; ++q) d[q] += (double)V[(size_t)q * vstride + k] * (double)v;
   };
   if (IBM == 2 && (int)blockIdx.x >= nsb) {
     const int blk = blockIdx.x - nsb, nrb = gridDim.x - nsb;
@@ -238,14 +237,14 @@ __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* 
       y[r] = v;
       dot((size_t)r, v);
     };
-    if (R.lanes == 16) apply_ib_rows<T, false, RESID, 16>(w, b, R, N, c, blk, nrb, tid, emit);
-    else apply_ib_rows<T, false, RESID, 64>(w, b, R, N, c, blk, nrb, tid, emit);
+    if (R.lanes == 16) apply_ib_rows<T, false, false, 16>(w, nullptr, R, N, c, blk, nrb, tid, emit);
+    else apply_ib_rows<T, false, false, 64>(w, nullptr, R, N, c, blk, nrb, tid, emit);
   } else {
     const int gx = (N + (int)blockDim.x - 1) / (int)blockDim.x;
     const int i = ((int)blockIdx.x % gx) * blockDim.x + threadIdx.x;
     const int j0 = (((int)blockIdx.x / gx) * blockDim.y + threadIdx.y) * RJ;
     if (i < N && j0 < N)
-      apply_strip<T, false, RESID, IBM, RJ>(w, b, F, R.flag, fx, fy, N, M, c, i, j0,
+      apply_strip<T, false, false, IBM, RJ>(w, nullptr, F, R.flag, fx, fy, N, M, c, i, j0,
                                             [&](size_t c0, int flag, T yu, T yv, T yp) {
         if (IBM != 2 || !(flag & 1)) {
           store_out<RJ>(y + c0, yu);
@@ -259,18 +258,10 @@ __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* 
         dot(2 * n + c0, yp);
       });
   }
+  block_totals<NS>(d, red, tid);
+  if (tid == 0)
 #pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    if (q < nvec) {
-      double a = d[q];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-      if (lane == 0) red[q][wave] = a;
-    }
-  }
-  __syncthreads();
-  if (tid < nvec)
-    partial[(size_t)blockIdx.x * nvec + tid] = (red[tid][0] + red[tid][1]) + (red[tid][2] + red[tid][3]);
+    for (int q = 0; q < NS; ++q) partial[(size_t)blockIdx.x * NS + q] = d[q];
 }
 
 template <typename T, int IBM, int RJ>
@@ -319,42 +310,47 @@ void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootVie
     launch_apply_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
 }
 
-template <typename T, int IBM, int RJ>
-static void launch_apply_dots_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
-                                FootView<T> fy, int N, int M, StokesCoef<T> c, const T* V, int nvec,
-                                size_t vstride, double* partial, hipStream_t s) {
-  const dim3 blk = apply_block(RJ);
-  const int nsb = strip_blocks(N);
-  const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0));
-  if (b)
-    IBMG_KLAUNCH((k_apply_dots<T, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, V, nvec,
-                       vstride, partial, nsb);
-  else
-    IBMG_KLAUNCH((k_apply_dots<T, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, V, nvec,
-                       vstride, partial, nsb);
-  IBMG_LAUNCH_CHECK();
+template <typename T, int IBM, int RJ, int NV>
+static void launch_apply_dots_n(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
+                                StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
+                                hipStream_t s) {
+  if constexpr (NV > 8) {
+    throw Error(IBMG_ERR_ARG, "fused dots take 1..8 vectors");
+  } else {
+    if (nvec != NV) {
+      launch_apply_dots_n<T, IBM, RJ, NV + 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+      return;
+    }
+    const int nsb = strip_blocks(N);
+    const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0));
+    IBMG_KLAUNCH((k_apply_dots<T, IBM, RJ, NV>), grd, apply_block(RJ), 0, s, w, y, F, R, fx, fy, N, M, c, u0, V, vstride,
+                 partial, nsb);
+    IBMG_LAUNCH_CHECK();
+  }
 }
 
 template <typename T, int IBM>
-static void launch_apply_dots_m(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
-                                FootView<T> fy, int N, int M, StokesCoef<T> c, const T* V, int nvec,
-                                size_t vstride, double* partial, hipStream_t s) {
-  if (apply_rows(N) == 4) launch_apply_dots_r<T, IBM, 4>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
-  else launch_apply_dots_r<T, IBM, 1>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+static void launch_apply_dots_m(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
+                                StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
+                                hipStream_t s) {
+  if (apply_rows(N) == 4)
+    launch_apply_dots_n<T, IBM, 4, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+  else
+    launch_apply_dots_n<T, IBM, 1, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
 }
 
 template <typename T>
-void launch_apply_dots(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy,
-                       int N, int M, StokesCoef<T> c, const T* V, int nvec, size_t vstride, double* partial,
+void launch_apply_dots(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
+                       StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
                        hipStream_t s) {
-  if (nvec < 1 || nvec > 9) throw Error(IBMG_ERR_ARG, "fused dots take 1..9 vectors");
+  if (nvec < 1 || nvec > 8) throw Error(IBMG_ERR_ARG, "fused dots take 1..8 vectors");
   check_ib_rows(R);
   if (R.n > 0)
-    launch_apply_dots_m<T, 2>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 2>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
   else if (F)
-    launch_apply_dots_m<T, 1>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
   else
-    launch_apply_dots_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 0>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
 }
 
 // Stencil part of L_IB (or the residual) for nsys systems of one grid size,
@@ -393,50 +389,17 @@ void launch_ib_rows(const T* x, T* y, const int* rows, const int* ptr, const int
 
 // ---------------------------------------------------------------------------
 // Restriction (Sec. 3.2): R_u = P_u^T / 4 (adjoint of the Raviart-Thomas
-// prolongation), R_p = mean of the four fine cells.  With partial (single
-// system, 64 x 4 blocks) each block also stores the sum of squares of its
-// coarse values at partial[block], the first norm the coarse level's
-// smoother needs: a wave butterfly, then (w0 + w1) + (w2 + w3).
+// prolongation), R_p = mean of the four fine cells.
 // ---------------------------------------------------------------------------
 template <typename T>
-__device__ __forceinline__ void restrict_point(const T* __restrict__ f, T* __restrict__ cz, int Nc, int i, int j,
-                                               double& sq) {
-  const int Nf = 2 * Nc;
-  const size_t nf = (size_t)Nf * Nf, nc = (size_t)Nc * Nc;
-  f += blockIdx.z * 3 * nf;
-  cz += blockIdx.z * 3 * nc;
-  auto at = [&](int comp, int I, int J) -> T {
-    I = I < 0 ? I + Nf : (I >= Nf ? I - Nf : I);
-    J = J < 0 ? J + Nf : (J >= Nf ? J - Nf : J);
-    return f[comp * nf + (size_t)J * Nf + I];
-  };
-  const int I = 2 * i, J = 2 * j;
-  const T ru = T(0.25) * (at(0, I, J) + at(0, I, J + 1)) +
-               T(0.125) * (at(0, I - 1, J) + at(0, I - 1, J + 1) + at(0, I + 1, J) + at(0, I + 1, J + 1));
-  const T rv = T(0.25) * (at(1, I, J) + at(1, I + 1, J)) +
-               T(0.125) * (at(1, I, J - 1) + at(1, I + 1, J - 1) + at(1, I, J + 1) + at(1, I + 1, J + 1));
-  const T rp = T(0.25) * (at(2, I, J) + at(2, I + 1, J) + at(2, I, J + 1) + at(2, I + 1, J + 1));
-  const size_t o = (size_t)j * Nc + i;
-  cz[o] = ru;
-  cz[nc + o] = rv;
-  cz[2 * nc + o] = rp;
-  sq = (double)ru * (double)ru + (double)rv * (double)rv + (double)rp * (double)rp;
-}
-
-template <typename T>
-__global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc, double* __restrict__ partial) {
+__global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y * blockDim.y + threadIdx.y;
-  double sq = 0.0;
-  if (i < Nc && j < Nc) restrict_point<T>(f, cz, Nc, i, j, sq);
-  if (!partial) return;
-  __shared__ double red[4];
-  const int tid = threadIdx.y * blockDim.x + threadIdx.x, wave = tid >> 6, lane = tid & 63;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
-  if (lane == 0) red[wave] = sq;
-  __syncthreads();
-  if (tid == 0) partial[blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (i >= Nc || j >= Nc) return;
+  const size_t nf = (size_t)4 * Nc * Nc, nc = (size_t)Nc * Nc;
+  f += blockIdx.z * 3 * nf;
+  restrict_point<T>(cz + blockIdx.z * 3 * nc, Nc, i, j,
+                    [&](int comp, int I, int J) -> T { return f[comp * nf + (size_t)J * 2 * Nc + I]; });
 }
 
 template <typename T>
@@ -444,23 +407,13 @@ void launch_restrict_batch(const T* fine, T* coarse, int Nc, int nsys, hipStream
   if (nsys <= 0) return;
   dim3 blk(64, 4);
   dim3 grd((Nc + 63) / 64, (Nc + 3) / 4, nsys);
-  IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc, nullptr);
+  IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc);
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s) {
   launch_restrict_batch<T>(fine, coarse, Nc, 1, s);
-}
-
-int restrict_blocks(int Nc) { return ((Nc + 63) / 64) * ((Nc + 3) / 4); }
-
-template <typename T>
-void launch_restrict_norm(const T* fine, T* coarse, int Nc, double* partial, hipStream_t s) {
-  dim3 blk(64, 4);
-  dim3 grd((Nc + 63) / 64, (Nc + 3) / 4, 1);
-  IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc, partial);
-  IBMG_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------------------
@@ -774,51 +727,6 @@ void launch_combine(T* x, const T* Z, int k, size_t stride, const double* y, siz
   IBMG_LAUNCH_CHECK();
 }
 
-// ---------------------------------------------------------------------------
-// Least squares min || beta e1 - H y || for a (k+1) x k Hessenberg matrix
-// (column-major, leading dimension ldh) by Givens rotations; k <= 16.
-// Zero pivots (exact breakdown) give zero components.
-// ---------------------------------------------------------------------------
-__global__ void k_small_ls(const double* __restrict__ H, int ldh, int k, const double* __restrict__ beta,
-                           double* __restrict__ y) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double R[17][16];
-  double g[17];
-  double cs[16], sn[16];
-  for (int j = 0; j < k; ++j)
-    for (int i = 0; i <= k; ++i) R[i][j] = H[i + (size_t)j * ldh];
-  for (int i = 0; i <= k; ++i) g[i] = 0.0;
-  g[0] = beta[0];
-  for (int j = 0; j < k; ++j) {
-    for (int i = 0; i < j; ++i) {
-      const double a = R[i][j], b = R[i + 1][j];
-      R[i][j] = cs[i] * a + sn[i] * b;
-      R[i + 1][j] = -sn[i] * a + cs[i] * b;
-    }
-    const double a = R[j][j], b = R[j + 1][j];
-    const double d = sqrt(a * a + b * b);
-    double c = 1.0, s = 0.0;
-    if (d != 0.0) { c = a / d; s = b / d; }
-    cs[j] = c;
-    sn[j] = s;
-    R[j][j] = d;
-    R[j + 1][j] = 0.0;
-    const double gj = g[j];
-    g[j] = c * gj;
-    g[j + 1] = -s * gj;
-  }
-  for (int j = k - 1; j >= 0; --j) {
-    double a = g[j];
-    for (int m = j + 1; m < k; ++m) a -= R[j][m] * y[m];
-    y[j] = R[j][j] != 0.0 ? a / R[j][j] : 0.0;
-  }
-}
-
-void launch_small_ls(double* H, int ldh, int k, const double* beta, double* y, hipStream_t s) {
-  IBMG_KLAUNCH(k_small_ls, dim3(1), dim3(64), 0, s, H, ldh, k, beta, y);
-  IBMG_LAUNCH_CHECK();
-}
-
 // Outer FGMRES: rotate column k of H (rows 0..k+1) by the stored rotations,
 // form rotation k, update g and write |g[k+1]| to res.  Batched: system
 // blockIdx.x (H hstride apart; cs, sn, g rstride apart; res[s]), inactive
@@ -970,7 +878,6 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
   template void launch_apply<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,         \
                                 FootView<T>, int, int, StokesCoef<T>, bool, hipStream_t);         \
   template void launch_restrict<T>(const T*, T*, int, hipStream_t);                               \
-  template void launch_restrict_norm<T>(const T*, T*, int, double*, hipStream_t);                 \
   template void launch_prolong_add<T>(const T*, T*, int, hipStream_t);                            \
   template void launch_fill<T>(T*, T, size_t, hipStream_t);                                       \
   template void launch_axpy<T>(T*, const T*, size_t, hipStream_t);                                \
@@ -982,8 +889,8 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
   template void launch_combine<T>(T*, const T*, int, size_t, const double*, size_t, hipStream_t); \
   template void launch_block_sums<T>(const T*, int, double*, int, hipStream_t);                   \
   template void launch_subtract_means<T>(T*, int, const double*, int, hipStream_t);               \
-  template void launch_apply_dots<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,    \
-                                     FootView<T>, int, int, StokesCoef<T>, const T*, int, size_t,  \
+  template void launch_apply_dots<T>(const T*, T*, const T*, IbRows<T>, FootView<T>, FootView<T>, \
+                                     int, int, StokesCoef<T>, const T*, const T*, int, size_t,     \
                                      double*, hipStream_t);                                        \
   template void launch_apply_batch<T>(const T*, T*, const T*, int, StokesCoef<T>, int, size_t,    \
                                       hipStream_t);                                               \

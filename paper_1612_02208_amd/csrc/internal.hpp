@@ -260,6 +260,53 @@ __device__ __forceinline__ size_t seg_len(const BSeg& g, int s) {
 }
 __device__ __forceinline__ bool seg_on(const BSeg& g, int s) { return !g.active || g.active[s] != 0; }
 
+// A lane's value after a DPP move within its row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+// Sum over the 16 lanes of a DPP row (every lane of the row ends with the
+// same bits): swap neighbours and pairs within quads, then mirror within
+// halves and within the row, adding after each step.
+template <typename T>
+__device__ __forceinline__ T row16_sum(T p) {
+  p += dpp_move<0xB1>(p);    // quad_perm [1,0,3,2]
+  p += dpp_move<0x4E>(p);    // quad_perm [2,3,0,1]
+  p += dpp_move<0x141>(p);   // row_half_mirror
+  p += dpp_move<0x140>(p);   // row_mirror
+  return p;
+}
+// Sum over a wave's 64 lanes, the same bits in every lane.
+template <typename T>
+__device__ __forceinline__ T wave_sum(T p) {
+  p = row16_sum(p);
+  p += __shfl_xor(p, 16, 64);
+  p += __shfl_xor(p, 32, 64);
+  return p;
+}
+// K per-thread values summed over a block of 256 threads; every thread ends
+// with the K totals.  red: 4 K doubles of shared memory.  One barrier: red
+// must not be reused without another.
+template <int K>
+__device__ __forceinline__ void block_totals(double (&v)[K], double* red, int tid) {
+  const int wave = tid >> 6, lane = tid & 63;
+#pragma unroll
+  for (int q = 0; q < K; ++q) {
+    const double a = wave_sum(v[q]);
+    if (lane == 0) red[q * 4 + wave] = a;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < K; ++q) v[q] = (red[q * 4] + red[q * 4 + 1]) + (red[q * 4 + 2] + red[q * 4 + 3]);
+}
+
 // Sums of nv <= K per-thread values over a block of 256 threads, in the same
 // fixed order in every block (deterministic): a butterfly over the 64 lanes
 // of each wave (every lane ends with identical bits), then the four wave
@@ -282,6 +329,23 @@ __device__ __forceinline__ void block_sums256(const double (&v)[K], int nv, doub
   __syncthreads();
   if (tid < nv) out[tid] = (red[tid * 4] + red[tid * 4 + 1]) + (red[tid * 4 + 2] + red[tid * 4 + 3]);
   __syncthreads();
+}
+
+// The restriction's coarse point (i, j) of an Nc x Nc grid (Sec. 3.2) from the
+// fine values at(comp, I, J), 0 <= I, J < 2 Nc
+template <typename T, typename At>
+__device__ __forceinline__ void restrict_point(T* __restrict__ cz, int Nc, int i, int j, At at) {
+  const int Nf = 2 * Nc, I = 2 * i, J = 2 * j;
+  const int Im = I == 0 ? Nf - 1 : I - 1, Jm = J == 0 ? Nf - 1 : J - 1;   // I + 1 and J + 1 never wrap
+  const T ru = T(0.25) * (at(0, I, J) + at(0, I, J + 1)) +
+               T(0.125) * (at(0, Im, J) + at(0, Im, J + 1) + at(0, I + 1, J) + at(0, I + 1, J + 1));
+  const T rv = T(0.25) * (at(1, I, J) + at(1, I + 1, J)) +
+               T(0.125) * (at(1, I, Jm) + at(1, I + 1, Jm) + at(1, I, J + 1) + at(1, I + 1, J + 1));
+  const T rp = T(0.25) * (at(2, I, J) + at(2, I + 1, J) + at(2, I, J + 1) + at(2, I + 1, J + 1));
+  const size_t nc = (size_t)Nc * Nc, o = (size_t)j * Nc + i;
+  cz[o] = ru;
+  cz[nc + o] = rv;
+  cz[2 * nc + o] = rp;
 }
 
 // Largest RAS box: b + 2 o <= 32 cells per side
@@ -315,23 +379,18 @@ struct IbRows {
 template <typename T>
 void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                   FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s);
-// L_IB w (b != null: b - L_IB w) with the first Gram-Schmidt pass fused:
-// partial[blk * nvec + q] = block sums of V_q . y (V = null: nvec = 1, y . y)
-// over apply_blocks(N, R) blocks; nvec <= 9
+// y = L_IB w with the first Gram-Schmidt pass fused: the dots u_q . y of
+// nvec <= 8 basis vectors (u_0 = u0, u_q = V + q vstride), nvec per block,
+// over apply_blocks blocks; with nvec = 1 a second sum, u_0 . u_0, follows
 template <typename T>
-void launch_apply_dots(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy,
-                       int N, int M, StokesCoef<T> c, const T* V, int nvec, size_t vstride, double* partial,
+void launch_apply_dots(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
+                       StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
                        hipStream_t s);
 // blocks of launch_apply_dots on an N x N level with nrows explicit IB rows
 // of `lanes` lanes each (0: none)
 int apply_blocks(int N, int nrows, int lanes);
 template <typename T>
 void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s);
-// the same, and partial[0..restrict_blocks(Nc)) = per-block sums of the
-// squared coarse values (launch_scale_red reduces them)
-template <typename T>
-void launch_restrict_norm(const T* fine, T* coarse, int Nc, double* partial, hipStream_t s);
-int restrict_blocks(int Nc);
 template <typename T>
 void launch_prolong_add(const T* coarse, T* fine, int Nc, hipStream_t s);
 template <typename Ts, typename Td>
@@ -359,7 +418,6 @@ void launch_scale(const T* t, T* v, const double* denom, size_t n, hipStream_t s
 template <typename T>
 void launch_combine(T* x, const T* Z, int k, size_t stride, const double* y, size_t n,
                     hipStream_t s);
-void launch_small_ls(double* H, int ldh, int k, const double* beta, double* y, hipStream_t s);
 void launch_givens(double* H, int ldh, int k, double* cs, double* sn, double* g, double* res,
                    hipStream_t s);
 void launch_backsolve(const double* H, int ldh, int k, const double* g, double* y, hipStream_t s);
@@ -384,25 +442,34 @@ void launch_upd_norm(T* t, const T* V, int k, size_t stride, size_t n, const dou
 template <typename T>
 void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout,
                       hipStream_t s);
-// npart != null: H[k][k-1] = sqrt(sum of the nnblk partials at npart),
-// stored into H by the kernel.  pass2: npart holds launch_upd_dots_n's
-// partials of the last column instead (its second-pass coefficients and the
-// squared norm before them, k + 1 per block), added to that column inside
-// the kernel
-template <typename T>
-void launch_combine_ls(T* x, const T* Z, int k, size_t stride, size_t n, double* H, int ldh,
-                       const double* beta, double* yout, hipStream_t s, bool assign = false,
-                       const double* npart = nullptr, int nnblk = 0, bool pass2 = false);
-// launch_upd_dots whose partials also carry |t|^2 of the updated t (k + 1
-// values per block, the norm last; k <= 8)
-template <typename T>
-void launch_upd_dots_n(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
-                       double* hcol, double* pout, hipStream_t s, int nblk_in = 0);
 // from those partials: t = (t - V h2) / |t - V h2| with the norm taken as
 // sqrt(|t|^2 - |h2|^2); hcol[0..k) += h2, hcol[k] = the norm
 template <typename T>
 void launch_scale_upd(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk_in,
                       double* hcol, hipStream_t s);
+
+// Smoothing FGMRES (krylov_kernels.hip): the state block S of one smoothing
+// step (kGsScal doubles) and the launches after each operator application.
+constexpr int kGsScal = 192;
+// partial-sum blocks of launch_gs_update
+int gs_blocks(size_t n);
+// t = L z_{k-1} becomes the next basis vector u_k: t -= its projection on the
+// k earlier ones (first pass, from launch_apply_dots' nd blocks at pd), with
+// the second pass's sums u_q . u_k, q < k, and |u_k|^2 left in pout (k + 1 per
+// block, gs_blocks(n) blocks).  pu: the previous call's pout (k > 1).
+template <typename T>
+void launch_gs_update(T* t, const T* u0, const T* V, int k, size_t stride, size_t n, const double* pd, int nd,
+                      const double* pu, double* S, double* pout, hipStream_t s);
+// the least squares, then x += sum_q y_q Z_q (assign: x = ...)
+template <typename T>
+void launch_gs_combine(T* x, const T* Z, int k, size_t stride, size_t n, const double* pu, double* S, bool assign,
+                       hipStream_t s);
+// the same with x assigned on a grid of 2 Nc x 2 Nc points, and the
+// restriction of the residual r = u_0 - sum_q y_q L z_q to the coarse grid;
+// r comes from the Arnoldi relation (a combination of u_0 .. u_k)
+template <typename T>
+void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k, size_t stride, int Nc,
+                                const double* pu, double* S, T* coarse, hipStream_t s);
 
 // immersed boundary
 void launch_fp_fine(const double* X, int M, int N, int comp, const int* base, const int* mask,

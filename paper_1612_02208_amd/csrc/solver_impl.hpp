@@ -26,7 +26,6 @@ namespace detail {
 constexpr int kMaxNu = 8;
 constexpr int kMaxRestart = 64;
 constexpr int kScalY = 1;     // scal[1..16]: least-squares solution
-constexpr int kScalTmp = 20;  // scal[20..]: second Gram-Schmidt pass
 // The IB term of L_IB w comes from a level's explicit Galerkin rows (in the
 // operator's own launch) up to this many entries.  Beyond the bare stencil the
 // rows cost about 4.2 to 5.9 us per million entries (12 bytes each, FP64), the
@@ -111,7 +110,7 @@ struct Level {
   DBuf<T> Y;
   // work vectors
   DBuf<T> w, b, r, t, V, Z, F;
-  DBuf<double> H, scal, part;
+  DBuf<double> scal, part;   // the smoothing step's state, its partial sums
   // Schur-complement smoother
   std::unique_ptr<ScLevel<T>> sc;
 };
@@ -666,7 +665,7 @@ class Solver final : public SolverBase {
   // partial-sum buffers of a level: the reductions' blocks x vectors, and the
   // fused operator kernel's blocks x (nu + 1) vectors
   static size_t part_stride(const Level<T>& lev) {
-    return std::max(kPartStride, (size_t)dot_blocks(lev) * (kMaxNu + 1));
+    return (size_t)std::max({dot_blocks(lev), gs_blocks(3 * (size_t)lev.N * lev.N), 1024}) * (kMaxNu + 1);
   }
 
   // Interior product form per Schwarz level: time the pipelined XCD-ordered
@@ -1211,9 +1210,8 @@ class Solver final : public SolverBase {
       }
       lev.F.alloc(4 * (size_t)std::max(M_, 1));   // forces [2][M] then J u [2][M]
       if (l >= 1 && d_.smoother == IBMG_RMS) lev.rr.alloc(n);
-      lev.H.alloc((size_t)(kMaxNu + 1) * kMaxNu);
-      lev.scal.alloc(64);
-      lev.part.alloc(2 * part_stride(lev));
+      lev.scal.alloc(kGsScal);
+      lev.part.alloc(3 * part_stride(lev));
     }
   }
 
@@ -1265,16 +1263,16 @@ class Solver final : public SolverBase {
     launch_apply<U>(x, y, b, Fp, R, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), trans, s);
   }
 
-  // y = L_IB^l x (b != null: y = b - L_IB^l x) with the first Gram-Schmidt
-  // pass fused into the operator kernel: partial holds dot_blocks(lev)
-  // blocks of the dots V_q . y, q < nvec (V = null: y . y)
+  // y = L_IB^l x with the first Gram-Schmidt pass fused into the operator
+  // kernel: partial holds dot_blocks(lev) blocks of the dots u_q . y, q < nvec
+  // (u_0 = u0, u_q = V + q vstride; with nvec = 1 also u_0 . u_0)
   template <typename U>
-  void op_dots(int l, const U* x, U* y, const U* b, const U* V, int nvec, size_t vstride, double* partial, U* F,
+  void op_dots(int l, const U* x, U* y, const U* u0, const U* V, int nvec, size_t vstride, double* partial, U* F,
                hipStream_t s) {
     Level<T>& lev = levels_[l];
     const U* Fp;
     const IbRows<U> R = ib_source<U>(lev, x, F, &Fp, s);
-    launch_apply_dots<U>(x, y, b, Fp, R, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), V, nvec,
+    launch_apply_dots<U>(x, y, Fp, R, fview<U>(lev.f[0]), fview<U>(lev.f[1]), lev.N, M_, coef<U>(lev), u0, V, nvec,
                          vstride, partial, s);
   }
 
@@ -1316,11 +1314,12 @@ class Solver final : public SolverBase {
                lev.int_tb, lev.use_sym);
   }
 
-  // w <- w + e, e = nu FGMRES iterations (CGS2) on L e = b - L w from e = 0.
-  // With w_zero, w is not read (the result is stored into it) and b_nblk > 0
-  // says the level's partial-sum buffer already holds b_nblk block sums of
-  // |b|^2 (left there by the restriction that produced b).
-  void smooth_t(int l, T* w, const T* b, int nu, bool w_zero, hipStream_t s, int b_nblk = 0) {
+  // w <- w + e, e = nu FGMRES iterations (classical Gram-Schmidt twice) on
+  // L e = b - L w from e = 0, on an unnormalised basis (krylov_kernels.hip).
+  // With w_zero, w is not read (the result is stored into it); crs != null
+  // (w_zero only) also leaves the restriction of b - L w there, and the return
+  // value says whether it did (the Richardson steps do not).
+  bool smooth_t(int l, T* w, const T* b, int nu, bool w_zero, hipStream_t s, T* crs = nullptr) {
     Level<T>& lev = levels_[l];
     const size_t n = 3 * (size_t)lev.N * lev.N;
     if (d_.sweep_kind == IBMG_SWEEP_RICHARDSON) {
@@ -1335,64 +1334,36 @@ class Solver final : public SolverBase {
         basic_smoother(l, lev.r.p, lev.t.p, s);
         launch_axpy<T>(w, lev.t.p, n, s);
       }
-      return;
+      return false;
     }
-    const int nblk = dots_blocks(n, 1024);  // at most nu + 1 vectors
-    const int ldh = kMaxNu + 1;
-    const T* r0;
-    if (w_zero) {
-      r0 = b;
-    } else {
-      // r = b - L w with its squared norm's block sums
-      op_dots<T>(l, w, lev.r.p, b, nullptr, 1, 0, lev.part.p, lev.F.p, s);
-      r0 = lev.r.p;
-    }
-    double* beta = lev.scal.p;
-    double* pa = lev.part.p;
-    double* pb = lev.part.p + part_stride(lev);
-    const int nab = dot_blocks(lev);  // blocks of the fused operator + dots kernel
     T* V = lev.V.p;
     T* Z = lev.Z.p;
-    if (w_zero && b_nblk > 0) {
-      launch_scale_red<T>(r0, V, n, pa, b_nblk, beta, s);
-    } else if (w_zero) {
-      launch_dots<T>(r0, 1, n, r0, n, pa, nblk, s);
-      launch_scale_red<T>(r0, V, n, pa, nblk, beta, s);
-    } else {
-      launch_scale_red<T>(r0, V, n, pa, nab, beta, s);
+    const T* u0 = b;
+    if (!w_zero) {
+      op<T>(l, w, V, b, false, lev.F.p, s);
+      u0 = V;
     }
+    double* pd = lev.part.p;
+    double* pu[2] = {lev.part.p + part_stride(lev), lev.part.p + 2 * part_stride(lev)};
+    const int nd = dot_blocks(lev);
     for (int k = 0; k < nu; ++k) {
-      T* vk = V + (size_t)k * n;
+      const T* uk = k == 0 ? u0 : V + (size_t)k * n;
       T* zk = Z + (size_t)k * n;
       T* t = V + (size_t)(k + 1) * n;
-      basic_smoother(l, vk, zk, s);
-      // t = L z with the pass-1 dots V_q . t; pass 2 and the norm follow
-      op_dots<T>(l, zk, t, nullptr, V, k + 1, n, pa, lev.F.p, s);
-      double* hcol = lev.H.p + (size_t)k * ldh;
-      // pass 2's dots with |t|^2 beside them: t - V h2 is orthogonal to the
-      // orthonormal basis, so its norm is sqrt(|t|^2 - |h2|^2) and the
-      // update, the norm and the normalisation take one more sweep
-      launch_upd_dots_n<T>(t, V, k + 1, n, n, pa, nblk, hcol, pb, s, nab);
-      // the last basis vector is never read: the least-squares kernel takes
-      // its coefficients and norm from these partials
-      if (k + 1 < nu) launch_scale_upd<T>(t, V, k + 1, n, n, pb, nblk, hcol, s);
+      basic_smoother(l, uk, zk, s);
+      op_dots<T>(l, zk, t, u0, V, k + 1, n, pd, lev.F.p, s);
+      launch_gs_update<T>(t, u0, V, k + 1, n, n, pd, nd, pu[(k + 1) & 1], lev.scal.p, pu[k & 1], s);
     }
-    launch_combine_ls<T>(w, Z, nu, n, n, lev.H.p, ldh, beta, lev.scal.p + kScalY, s, w_zero, pb, nblk, true);
+    const double* pl = pu[(nu - 1) & 1];
+    if (crs) launch_gs_combine_restrict<T>(w, Z, u0, V, nu, n, lev.N / 2, pl, lev.scal.p, crs, s);
+    else launch_gs_combine<T>(w, Z, nu, n, n, pl, lev.scal.p, w_zero, s);
+    return crs != nullptr;
   }
 
-  // Classical Gram-Schmidt twice against V[0..k): h (first pass + second
-  // pass) into hcol[0..k); the partial sums of ||t||^2 are left in pa for
-  // launch_scale_red, which stores ||t|| and normalises t.
-  template <typename U>
-  void orthogonalise(const U* V, int k, size_t n, U* t, double* hcol, double* pa, double* pb,
-                     int nblk, hipStream_t s) {
-    launch_dots<U>(V, k, n, t, n, pa, nblk, s);
-    launch_upd_dots<U>(t, V, k, n, n, pa, nblk, hcol, pb, s);
-    launch_upd_norm<U>(t, V, k, n, n, pb, nblk, hcol, pa, s);
-  }
-
-  // The same for the outer solve's long vectors, on up to kOuterBlocks
-  // blocks: one block folds each pass's partial sums (the pass-1 dots, then
+  // Classical Gram-Schmidt twice against V[0..k) for the outer solve's long
+  // vectors: h (first pass + second pass) into hcol[0..k), the partial sums of
+  // |t|^2 left in opart_ for launch_scale_red.  On up to kOuterBlocks blocks:
+  // one block folds each pass's partial sums (the pass-1 dots, then
   // the pass-2 dots) before the next kernel, so that kernel's blocks read k
   // values instead of every block's k partials.
   void orthogonalise_outer(const double* V, int k, size_t n, double* t, double* hcol, int nblk, hipStream_t s) {
@@ -1405,24 +1376,19 @@ class Solver final : public SolverBase {
     launch_upd_norm<double>(t, V, k, n, n, ofold_.p + 72, nblk, hcol, pa, s, 1);
   }
 
-  // w = MG(0, b) on level l (Alg. 1); b_nblk as for smooth_t
-  void mg(int l, const T* b, T* w, hipStream_t s, int b_nblk = 0) {
+  // w = MG(0, b) on level l (Alg. 1)
+  void mg(int l, const T* b, T* w, hipStream_t s) {
     if (l == 0) {
       launch_coarse_apply<T>(inv0_.p, n0_, b, w, s);
       return;
     }
     Level<T>& lev = levels_[l];
     Level<T>& crs = levels_[l - 1];
-    smooth_t(l, w, b, d_.nu1, true, s, b_nblk);
-    op<T>(l, w, lev.r.p, b, false, lev.F.p, s);
-    int c_nblk = 0;
-    if (l - 1 >= 1 && restrict_blocks(crs.N) <= (int)part_stride(crs)) {
-      launch_restrict_norm<T>(lev.r.p, crs.b.p, crs.N, crs.part.p, s);
-      c_nblk = restrict_blocks(crs.N);
-    } else {
+    if (!smooth_t(l, w, b, d_.nu1, true, s, crs.b.p)) {
+      op<T>(l, w, lev.r.p, b, false, lev.F.p, s);
       launch_restrict<T>(lev.r.p, crs.b.p, crs.N, s);
     }
-    mg(l - 1, crs.b.p, crs.w.p, s, c_nblk);
+    mg(l - 1, crs.b.p, crs.w.p, s);
     launch_prolong_add<T>(crs.w.p, w, crs.N, s);
     smooth_t(l, w, b, d_.nu2, false, s);
   }
@@ -1838,30 +1804,36 @@ class Solver final : public SolverBase {
       }
     } else if (kernel >= IBMG_KERNEL_APPLY_DOTS && kernel <= IBMG_KERNEL_SCALE_UPD) {
       // one smoothing step's Krylov kernels with the basis at its largest
-      // (k = nu vectors): zero first-pass dots leave t as it is, unit
-      // partial norms give a unit scale, and a diagonal Hessenberg keeps the
-      // least squares well posed, so repeated launches see the same values
+      // (k = nu vectors), and the outer solve's (and the batched smoothing's)
+      // kernels of a normalised basis: zero dots leave t as it is and unit
+      // norms keep the small algebra well posed, so repeated launches see the
+      // same values
       require(level >= 1, "the smoothing kernels run on levels >= 1");
       const int k = nu_;
-      const int nblk = dots_blocks(n, 1024), nab = dot_blocks(lev), ldh = kMaxNu + 1;
+      const int nblk = dots_blocks(n, 1024), nd = dot_blocks(lev);
+      const size_t ps = part_stride(lev);
       double* pa = lev.part.p;
-      double* pb = lev.part.p + part_stride(lev);
+      double* pb = lev.part.p + ps;
+      double* pc = lev.part.p + 2 * ps;
+      double* S = lev.scal.p;
       T* V = lev.V.p;
       T* Z = lev.Z.p;
       T* t = V + (size_t)k * n;
       launch_fill<T>(V, T(1), (size_t)(k + 1) * n, s);
       launch_fill<T>(Z, T(1), (size_t)k * n, s);
-      launch_fill<double>(pa, 0.0, 2 * part_stride(lev), s);
-      launch_fill<double>(lev.H.p, 0.0, (size_t)(kMaxNu + 1) * kMaxNu, s);
-      launch_fill<double>(lev.scal.p, 1.0, 1, s);
-      for (int q = 0; q < k; ++q) launch_fill<double>(lev.H.p + (size_t)q * ldh + q, 1.0, 1, s);
-      double* hcol = lev.H.p + (size_t)(k - 1) * ldh;
+      launch_fill<double>(pa, 0.0, 3 * ps, s);
+      launch_fill<double>(S, 0.0, kGsScal, s);
+      launch_fill<double>(S, 1.0, k, s);                                           // D_q
+      for (int q = 0; q < k; ++q) launch_fill<double>(S + 96 + 9 * q + q, 1.0, 1, s);   // H_qq
+      if (k == 1) launch_fill<double>(pa + 1, 1.0, 1, s);                          // u_0 . u_0
+      else launch_fill<double>(pb + k - 1, 1.0, 1, s);                             // |u_{k-1}|^2
+      double* hcol = S + 96;
       if (kernel == IBMG_KERNEL_APPLY_DOTS) {
         by = (double)(k + 2) * n * ts;
-        ms = time_launches([&] { op_dots<T>(level, Z, lev.t.p, nullptr, V, k, n, pa, lev.F.p, s); }, reps, s);
+        ms = time_launches([&] { op_dots<T>(level, Z, lev.t.p, V, V, k, n, pa, lev.F.p, s); }, reps, s);
       } else if (kernel == IBMG_KERNEL_UPD_DOTS) {
         by = (double)(k + 2) * n * ts;
-        ms = time_launches([&] { launch_upd_dots_n<T>(t, V, k, n, n, pb, nblk, hcol, pa, s, nab); }, reps, s);
+        ms = time_launches([&] { launch_gs_update<T>(t, V, V, k, n, n, pa, nd, pb, S, pc, s); }, reps, s);
       } else if (kernel == IBMG_KERNEL_SCALE_UPD) {
         // zero second-pass dots and a unit |t|^2 in every block's partials:
         // t keeps its values and is scaled by the same factor each launch
@@ -1871,17 +1843,16 @@ class Solver final : public SolverBase {
         ms = time_launches([&] { launch_scale_upd<T>(t, V, k, n, n, pb, nblk, hcol, s); }, reps, s);
       } else if (kernel == IBMG_KERNEL_UPD_NORM) {
         by = (double)(k + 2) * n * ts;
+        launch_fill<double>(pb, 0.0, (size_t)nblk * k, s);
         ms = time_launches([&] { launch_upd_norm<T>(t, V, k, n, n, pb, nblk, hcol, pa, s); }, reps, s);
       } else if (kernel == IBMG_KERNEL_SCALE_RED) {
         by = 2.0 * n * ts;
         launch_fill<double>(pb, 1.0, (size_t)nblk, s);
-        ms = time_launches([&] { launch_scale_red<T>(t, lev.t.p, n, pb, nblk, lev.scal.p + kScalTmp, s); },
-                           reps, s);
+        ms = time_launches([&] { launch_scale_red<T>(t, lev.t.p, n, pb, nblk, hcol, s); }, reps, s);
       } else {
         by = (double)(k + 2) * n * ts;
-        ms = time_launches([&] {
-          launch_combine_ls<T>(lev.w.p, Z, k, n, n, lev.H.p, ldh, lev.scal.p, lev.scal.p + kScalY, s, false);
-        }, reps, s);
+        launch_fill<double>(pc + k, 1.0, 1, s);                                    // |u_k|^2
+        ms = time_launches([&] { launch_gs_combine<T>(lev.w.p, Z, k, n, n, pc, S, false, s); }, reps, s);
       }
     } else {
       require(false, "unknown kernel");
