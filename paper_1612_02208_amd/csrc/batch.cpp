@@ -60,22 +60,22 @@ class BatchSolver final : public BatchBase {
     std::stable_sort(order_.begin(), order_.end(), [&](int a, int b) { return d[a].N > d[b].N; });
     for (int p = 0; p < nsys; ++p) sys_.emplace_back(new Solver<T>(d[order_[p]], s, true));
     {
-      // every system's bordered coarsest system has the same size (shared
-      // coarse_N and rho): they are inverted a group at a time, one launch
-      // per group of up to 1 GiB of augmented matrices
-      const int nn = sys_[0]->nn0_;
-      const size_t stride = (size_t)nn * 2 * nn;
+      // every system's coarsest matrix has the same size (shared coarse_N):
+      // they are swept a group at a time, one run of sweeps per group of up
+      // to 1 GiB of matrices
+      const int n0 = sys_[0]->n0_;
+      const size_t stride = (size_t)n0 * n0;
       const int grp = (int)std::max<size_t>(1, std::min<size_t>(nsys, ((size_t)1 << 27) / stride));
-      DBuf<double> augs(stride * grp);
+      DBuf<double> mats(stride * grp), work(Solver<T>::sweep_work(n0, grp));
       for (int p0 = 0; p0 < nsys; p0 += grp) {
         const int cnt = std::min(grp, nsys - p0);
         for (int p = p0; p < p0 + cnt; ++p) {
-          require(sys_[p]->nn0_ == nn && sys_[p]->aug0_.n == stride, "coarsest systems differ in size");
-          IBMG_HIP(hipMemcpyAsync(augs.p + (p - p0) * stride, sys_[p]->aug0_.p, stride * sizeof(double),
+          require(sys_[p]->n0_ == n0 && sys_[p]->aug0_.n == stride, "coarsest systems differ in size");
+          IBMG_HIP(hipMemcpyAsync(mats.p + (p - p0) * stride, sys_[p]->aug0_.p, stride * sizeof(double),
                                   hipMemcpyDeviceToDevice, s));
         }
-        launch_coarse_invert(augs.p, nn, cnt, stride, s);
-        for (int p = p0; p < p0 + cnt; ++p) sys_[p]->finish_coarse(augs.p + (p - p0) * stride, s);
+        launch_gj_invert(mats.p, n0, cnt, work.p, work.p + (size_t)cnt * 3 * n0 * kGjNb, s);
+        for (int p = p0; p < p0 + cnt; ++p) sys_[p]->finish_coarse(mats.p + (p - p0) * stride, s);
         IBMG_HIP(hipStreamSynchronize(s));
       }
       for (int p = 0; p < nsys; ++p) sys_[p]->check_breakdown(s, true);

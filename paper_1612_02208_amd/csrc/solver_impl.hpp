@@ -1014,25 +1014,54 @@ class Solver final : public SolverBase {
     IBMG_HIP(hipStreamSynchronize(s));
   }
 
+  // doubles of the sweeps' workspace for cnt matrices of n unknowns
+  static size_t sweep_work(size_t n, size_t cnt) { return cnt * (3 * n * kGjNb + (size_t)kGjNb * kGjNb); }
+
+  // Springs shorter than their rest length (tangent model): the velocity
+  // blocks may be indefinite, so the coarsest elimination pivots.
+  bool compressed() const {
+    if (!tangent_) return false;
+    for (int e = 0; e < E_; ++e) {
+      double dx = X_[2 * ends_[2 * e + 1]] - X_[2 * ends_[2 * e]], dy = X_[2 * ends_[2 * e + 1] + 1] - X_[2 * ends_[2 * e] + 1];
+      dx -= std::nearbyint(dx);
+      dy -= std::nearbyint(dy);
+      if (rest_[e] > std::hypot(dx, dy)) return true;
+    }
+    return false;
+  }
+
   void build_coarse(hipStream_t s) {
     Level<T>& lev = levels_[0];
     const int N = lev.N;
-    const int nb = d_.rho == 0.0 ? 3 : 1;
     n0_ = 3 * N * N;
-    const int nn = n0_ + nb;
-    nn0_ = nn;
-    DBuf<double> aug((size_t)nn * 2 * nn);
-    launch_fill<double>(aug.p, 0.0, aug.n, s);
-    launch_coarse_assemble(N, lev.cd, lev.f[0].d_tptr.p, lev.f[0].d_tcol.p, lev.f[0].tval.p,
-                           lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p, nb, aug.p, s);
-    if (defer_coarse_) {
-      aug0_ = std::move(aug);
+    const CoarseShift sh = coarse_shift(lev.cd, d_.rho == 0.0);
+    auto assemble_sym = [&](double* mat) {
+      launch_fill<double>(mat, 0.0, (size_t)n0_ * n0_, s);
+      launch_coarse_assemble_sym(N, lev.cd, lev.f[0].d_tptr.p, lev.f[0].d_tcol.p, lev.f[0].tval.p, lev.f[1].d_tptr.p,
+                                 lev.f[1].d_tcol.p, lev.f[1].tval.p, sh, mat, s);
+    };
+    if (defer_coarse_) {   // (linear springs: no pivoting)
+      aug0_.alloc((size_t)n0_ * n0_);
+      assemble_sym(aug0_.p);
       IBMG_HIP(hipStreamSynchronize(s));
       return;
     }
-    // The inversion is one work-group's latency-bound loop: it runs on a
+    // The inversion is a chain of small latency-bound launches: it runs on a
     // second stream (default priority) beside the box inversions and is
     // joined by join_coarse before anything reads the inverse.
+    const bool pivot = compressed();
+    const int nb = d_.rho == 0.0 ? 3 : 1, nn = n0_ + nb;
+    const size_t mat = pivot ? (size_t)nn * 2 * nn : (size_t)n0_ * n0_;
+    // (a tangent handle's rebuilds may change between the two)
+    const size_t swept = (size_t)n0_ * n0_ + sweep_work(n0_, 1);
+    DBuf<double> aug(tangent_ ? std::max(swept, (size_t)nn * 2 * nn) : swept);
+    if (pivot) {
+      launch_fill<double>(aug.p, 0.0, mat, s);
+      launch_coarse_assemble(N, lev.cd, lev.f[0].d_tptr.p, lev.f[0].d_tcol.p, lev.f[0].tval.p,
+                             lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p, nb, aug.p, s);
+    } else {
+      assemble_sym(aug.p);
+    }
     inv0_.alloc((size_t)n0_ * n0_);
     if (!dry_run() && !side_) {
       IBMG_HIP(hipStreamCreateWithFlags(&side_, hipStreamNonBlocking));
@@ -1041,8 +1070,14 @@ class Solver final : public SolverBase {
     }
     IBMG_HIP(hipEventRecord(ev_fork_, s));
     IBMG_HIP(hipStreamWaitEvent(side_, ev_fork_, 0));
-    launch_coarse_invert(aug.p, nn, 1, 0, side_);
-    launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
+    if (pivot) {
+      launch_coarse_invert(aug.p, nn, 1, 0, side_);
+      launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
+    } else {
+      double* work = aug.p + mat;
+      launch_gj_invert(aug.p, n0_, 1, work, work + 3 * (size_t)n0_ * kGjNb, side_);
+      launch_coarse_extract_sym(aug.p, N, sh, inv0_.p, side_);
+    }
     IBMG_HIP(hipEventRecord(ev_join_, side_));
     coarse_aug_ = std::move(aug);
   }
@@ -1055,10 +1090,11 @@ class Solver final : public SolverBase {
     coarse_aug_.release();
   }
 
-  // the coarsest inverse from the caller's inverted copy of aug0_
-  void finish_coarse(const double* inverted, hipStream_t s) {
+  // the coarsest inverse from the caller's swept copy of aug0_
+  void finish_coarse(const double* swept, hipStream_t s) {
+    Level<T>& lev = levels_[0];
     inv0_.alloc((size_t)n0_ * n0_);
-    launch_coarse_extract(inverted, nn0_, n0_, inv0_.p, s);
+    launch_coarse_extract_sym(swept, lev.N, coarse_shift(lev.cd, d_.rho == 0.0), inv0_.p, s);
     aug0_.release();
     defer_coarse_ = false;
   }
@@ -1152,7 +1188,7 @@ class Solver final : public SolverBase {
     for (auto& grp : groups) {
       const int n = grp.first;
       const auto& items = grp.second;
-      const size_t per = ((size_t)n * n + 3 * (size_t)n * kGjNb + (size_t)kGjNb * kGjNb) * sizeof(double);
+      const size_t per = ((size_t)n * n + sweep_work(n, 1)) * sizeof(double);
       const size_t cap = std::min<size_t>(std::max<size_t>(1, budget / per), 512);
       const size_t nbatch = (items.size() + cap - 1) / cap;
       const int batch = (int)((items.size() + nbatch - 1) / nbatch);
@@ -1915,8 +1951,7 @@ class Solver final : public SolverBase {
   bool defer_coarse_ = false;   // a member of a batch: the batch inverts the coarsest system
   bool valid_ = true;
   double setup_ms_ = 0.0;   // wall time of the latest build_all (device work included)
-  int nn0_ = 0;          // size of the bordered coarsest system
-  DBuf<double> aug0_;    // its assembled [A | I] while the inversion is deferred
+  DBuf<double> aug0_;    // the assembled coarsest matrix while its inversion is deferred
 
   static bool graphs_enabled() {
     const char* e = std::getenv("IBMG_GRAPH");
