@@ -317,10 +317,11 @@ ibmg_status ibmg_sc_info(const ibmg_handle* h, int32_t level, double* lam, int32
  *   IBMG_KERNEL_RAS_IB        Schwarz boxes with their own inverse (k_ras_ib):
  *                             n_ib (nown nloc + nloc + nown) values, 2 n_ib nown
  *                             nloc flops
- *   IBMG_KERNEL_RAS_INTERIOR  interior boxes on the matrix cores
- *                             (k_ras_interior, one launch): the shared inverse
- *                             once plus n_int (nloc + nown) values, 2 n_int nown
- *                             nloc flops
+ *   IBMG_KERNEL_RAS_INTERIOR  interior boxes on the matrix cores (k_ras_int,
+ *                             the shared inverse split by the box's two
+ *                             reflections): the four class matrices once plus
+ *                             n_int (nloc + nown) values, 2 n_int 4 R K flops (R
+ *                             row and K column orbits)
  *   IBMG_KERNEL_STENCIL       the Stokes stencil k_apply (no IB term): 6 N^2
  *                             values
  *   IBMG_KERNEL_RAS_BATCH     (batch handles) the persistent batched Schwarz

@@ -8,6 +8,8 @@
 // jj in [0, m]; cells 2m(m+1) + jj*m + ii.  Owned unknowns (b x b cells with
 // their left x-face and bottom y-face) are ordered x-faces, y-faces, cells,
 // each (oj, oi) row-major.
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace ibmg {
@@ -862,25 +864,21 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, Box
   for (int q = cb + tid; q < (ce < ntr ? ce : ntr); q += 256) pb[64 * ks + q] = tcol[q];
 }
 
-// z[owned rows] (=, or += with acc) the sum of a split launch's slices, in
-// slice order, for the IB boxes (pa: ksa slices of na boxes) and the interior
-// boxes (pb: ksb slices of nb boxes) of one sweep in one launch; slice sl of
-// box b holds row `row` at p[(sl * n + b) * nch * 64 + row].  A list that was
-// not split has n = 0.
-// The symmetric IB list (ps: partials of ns boxes, kss column slices) comes
-// first: owned row r = 64 c + i is chunk c's row sums i of its slices, in
-// slice order, plus the column sums at r of every later chunk, added in
-// chunk order.
+// z[owned rows] (=, or += with acc) from the partial sums of one sweep's IB
+// launch.  Split chunked form (na boxes in ks slices): slice sl of box b holds
+// row `row` at pa[(sl * na + b) * nch * 64 + row], added in slice order.
+// Symmetric form (ps: partials of ns boxes, kss column slices): owned row
+// r = 64 c + i is chunk c's row sums i of its slices, in slice order, plus the
+// column sums at r of every later chunk, added in chunk order.
 template <typename T>
-__global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ ba, int na, int ksa,
-                          const T* __restrict__ pb, const int* __restrict__ bb, int nb, int ksb,
+__global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ boxes, int na, int ks,
                           const T* __restrict__ ps, int ns, int kss, T* __restrict__ z, BoxGeom g, bool acc) {
   const int nown_pad = g.nch * 64;
-  const size_t t0 = (size_t)ns * g.nown;
-  const size_t ta = (size_t)na * g.nown, tot = t0 + ta + (size_t)nb * g.nown;
+  const size_t tot = (size_t)(ns > 0 ? ns : na) * g.nown;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
-    if (t < t0) {
-      const int b = (int)(t / g.nown), row = (int)(t % g.nown);
+    const int b = (int)(t / g.nown), row = (int)(t % g.nown);
+    T a = 0;
+    if (ns > 0) {
       const int cr = row >> 6;
       const T* pp = ps + (size_t)b * sym_part_off(g.nch, kss);
       const T* pr = pp + sym_part_off(cr, kss) + (row & 63);
@@ -888,7 +886,7 @@ __global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ ba, 
       // eight at a time, added one by one in that order
       const int m = kss + (g.nch - cr - 1);
       auto val = [&](int i) { return i < kss ? pr[64 * i] : pp[sym_part_off(cr + 1 + i - kss, kss) + 64 * kss + row]; };
-      T a = pr[0];
+      a = pr[0];
       for (int i0 = 1; i0 < m; i0 += 8) {
         T v[8];
 #pragma unroll
@@ -897,25 +895,17 @@ __global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ ba, 
         for (int j = 0; j < 8; ++j)
           if (i0 + j < m) a += v[j];
       }
-      const size_t o = own_glob(g, ba[b], row);
-      z[o] = acc ? z[o] + a : a;
-      continue;
-    }
-    const bool first = t - t0 < ta;
-    const size_t u = first ? t - t0 : t - t0 - ta;
-    const int b = (int)(u / g.nown), row = (int)(u % g.nown);
-    const T* p = first ? pa : pb;
-    const int n = first ? na : nb, ks = first ? ksa : ksb;
-    T a = 0;
-    for (int s0 = 0; s0 < ks; s0 += 8) {
-      T v[8];
+    } else {
+      for (int s0 = 0; s0 < ks; s0 += 8) {
+        T v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = s0 + j < ks ? p[((size_t)(s0 + j) * n + b) * nown_pad + row] : T(0);
+        for (int j = 0; j < 8; ++j) v[j] = s0 + j < ks ? pa[((size_t)(s0 + j) * na + b) * nown_pad + row] : T(0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (s0 + j < ks) a += v[j];
+        for (int j = 0; j < 8; ++j)
+          if (s0 + j < ks) a += v[j];
+      }
     }
-    const size_t o = own_glob(g, (first ? ba : bb)[b], row);
+    const size_t o = own_glob(g, boxes[b], row);
     z[o] = acc ? z[o] + a : a;
   }
 }
@@ -931,19 +921,200 @@ int ras_ib_ksplit(const BoxGeom& g, int n_ib) {
 
 // ---------------------------------------------------------------------------
 // Interior boxes share one inverse (translation invariance of the periodic
-// stencil away from the structure), so they form one dense contraction
-//   Z[64-row chunk, 32 boxes] = M[chunk, :] X[:, boxes]
-// on the matrix cores: wave w owns rows 16w..16w+15 of the chunk and two
-// 16 x 16 output tiles (boxes 0-15, 16-31), accumulated with 16x16x4 MFMA
-// steps.  A fragments stream straight from the chunk layout (16 contiguous
-// rows per reduction index), B fragments come from the boxes' residuals,
-// gathered 64 reduction indices at a time into LDS.
+// stencil away from the structure), and their matrix commutes with the box's
+// two reflections: x -> -x takes x-face (ii, jj) to (m - ii, jj) with a sign
+// change of u, and y-face or cell (ii, jj) to (m - 1 - ii, jj); y -> -y
+// likewise with v.  So the product splits into the four parity classes
+// (+-, +-) of the residual: with the orbits {k, Xk, Yk, XYk} of local
+// unknowns,
+//   class sums  q_ab[k] = r_k + a s_X r_Xk + b s_Y r_Yk + a b s_XY r_XYk,
+//   products    Z_ab = M_ab q_ab over one representative per orbit,
+//   results     z_k = sum_ab Z_ab,  z_Xk = s_X sum a Z_ab, ...
+// M_ab[k, l] = 1/4 sum over l's distinct images g l of a^i b^j s_g M[k, g l].
+// At 16 x 16/4 that is 4 x 208 x 456 multiply-adds a box instead of 768 x
+// 1776, at 8 x 8/2 4 x 64 x 120 instead of 192 x 456, from a 3.0 MB (0.25 MB)
+// matrix that stays in the caches, and few enough to need no reduction slices.
+//
+// Work-group = 16 boxes x one 16-row tile, wave = class x part of the chunk (KS
+// parts).  The boxes' residuals are gathered 64 KS orbits at a time (a thread
+// reads an orbit's four values of one box), split into classes and staged in
+// LDS as the 16x16x4 MFMA's B operand; A streams from the class matrices, laid
+// out [class][row tile][k][16 rows] so that a wave reads contiguous runs.  The
+// next chunk's values load during the MFMAs.  The parts' and classes' results
+// meet in LDS and each thread writes its row's owned images.
+// Bound by the gathers' latency (one trip per chunk) on few boxes, by their
+// address arithmetic beside the MFMAs on many: 852 boxes of 16 x 16/4 38.5 us
+// FP64 (22.1 FP32) against 89.7 (58.4) for the dense product with its slices'
+// sum launch; 188 boxes 16.5 against 31; 896 boxes of 8 x 8/2 6.7 against 22.
+// ---------------------------------------------------------------------------
+template <typename T, int KS>
+__global__ void __launch_bounds__(256 * KS) k_ras_int(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
+                                                      IntClassView C, const int* __restrict__ boxes, int nlist,
+                                                      bool acc_mode) {
+  constexpr int KC = 64 * KS, NT = 256 * KS, GPT = 4, AS = 16;
+  using acc_t = typename Mfma<T>::acc_t;
+  __shared__ T Xs[4][KC][17];   // [class][orbit of the chunk][box]
+  __shared__ int bid[16];
+  __shared__ int kcode[kIntMaxOrbits];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kq = lane >> 4, bl = lane & 15;
+  const int cls = wave & 3, kp = (wave >> 2) * 64;   // the wave's class and part of the chunk
+  const int bt = blockIdx.x * 16, rt = blockIdx.y, N = g.N, m = g.m, nn = N * N;
+  if (tid < 16) bid[tid] = bt + tid < nlist ? boxes[bt + tid] : -1;
+  for (int k = tid; k < C.Kp; k += NT) kcode[k] = k < C.K ? C.kcode[k] : -1;
+  // a thread's orbit within a chunk and its four boxes are fixed, the boxes
+  // the same for its whole wave
+  int xb[GPT], yb[GPT];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < GPT; ++u) {
+    const int pid = __builtin_amdgcn_readfirstlane(bid[(tid + u * NT) / KC]);
+    xb[u] = pid >= 0 ? (pid % g.npd) * g.b - g.o : -N;   // -N: no box
+    yb[u] = pid >= 0 ? (pid / g.npd) * g.b - g.o : 0;
+  }
+  const T* Ma = static_cast<const T*>(C.M) + (((size_t)cls * C.nrt + rt) * C.Kp + kp + kq) * 16 + bl;
+  acc_t acc{0, 0, 0, 0};
+  T gx[GPT][4], ga[AS];
+  auto wrap = [&](int a) { return a < 0 ? a + N : (a >= N ? a - N : a); };
+  auto gather = [&](int k0) {
+    const int code = kcode[k0 + tid % KC];
+    const int comp = code >> 24, ii = code & 0xfff, jj = (code >> 12) & 0xfff;
+    const int mi = (comp == 0 ? m : m - 1) - ii, mj = (comp == 1 ? m : m - 1) - jj;
+    const int oe = jj * N + ii, ox = jj * N + mi, oy = mj * N + ii, oxy = mj * N + mi;
+    const T* rc = r + (size_t)(comp < 0 ? 0 : comp) * nn;
+#pragma unroll
+    for (int u = 0; u < GPT; ++u) {
+      const int x0 = xb[u], y0 = yb[u];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) gx[u][q] = T(0);
+      if (x0 >= 0 && y0 >= 0 && x0 + m < N && y0 + m < N) {   // clear of the periodic edges
+        const int at = y0 * N + x0;
+        if (code >= 0) {
+          gx[u][0] = rc[at + oe];
+          gx[u][1] = rc[at + ox];
+          gx[u][2] = rc[at + oy];
+          gx[u][3] = rc[at + oxy];
+        }
+      } else if (x0 > -N && code >= 0) {
+        const int xe = wrap(x0 + ii), xm = wrap(x0 + mi), ye = wrap(y0 + jj) * N, ym = wrap(y0 + mj) * N;
+        gx[u][0] = rc[ye + xe];
+        gx[u][1] = rc[ye + xm];
+        gx[u][2] = rc[ym + xe];
+        gx[u][3] = rc[ym + xm];
+      }
+    }
+  };
+  // the signs of the images: u changes under X, v under Y
+  auto stage = [&](int k0) {
+    const int kk = tid % KC, comp = kcode[k0 + kk] >> 24;
+    const T sx = comp == 0 ? T(-1) : T(1), sy = comp == 1 ? T(-1) : T(1);
+#pragma unroll
+    for (int u = 0; u < GPT; ++u) {
+      const int b = (tid + u * NT) / KC;
+      const T e = gx[u][0], x = sx * gx[u][1], y = sy * gx[u][2], xy = sx * sy * gx[u][3];
+      const T ep = e + x, em = e - x, yp = y + xy, ym = y - xy;
+      Xs[0][kk][b] = ep + yp;
+      Xs[1][kk][b] = em + ym;
+      Xs[2][kk][b] = ep - yp;
+      Xs[3][kk][b] = em - ym;
+    }
+  };
+  auto load_a = [&](int k0) {
+#pragma unroll
+    for (int s = 0; s < AS; ++s) ga[s] = Ma[(size_t)k0 * 16 + s * 64];
+  };
+  gather(0);
+  load_a(0);
+  for (int k0 = 0; k0 < C.Kp; k0 += KC) {
+    stage(k0);
+    __syncthreads();
+    T a[AS];
+#pragma unroll
+    for (int s = 0; s < AS; ++s) a[s] = ga[s];
+    if (k0 + KC < C.Kp) {
+      gather(k0 + KC);
+      load_a(k0 + KC);
+    }
+#pragma unroll
+    for (int s = 0; s < AS; ++s) acc = Mfma<T>::mma(a[s], Xs[cls][kp + 4 * s + kq][bl], acc);
+    __syncthreads();
+  }
+  // the parts' and classes' results: Xs[class][16 part + row][box]
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Xs[cls][kp / 4 + Mfma<T>::row(kq, v)][bl] = acc[v];
+  __syncthreads();
+  if (tid < 256) {
+    const int row = tid % 16, b = tid / 16;
+    const int k = rt * 16 + row, pid = bid[b];
+    if (k >= C.R || pid < 0) return;
+    const int code = C.rcode[k], comp = (code >> 24) & 3, ii = code & 0xfff, jj = (code >> 12) & 0xfff, own = code >> 26;
+    const int mi = (comp == 0 ? m : m - 1) - ii, mj = (comp == 1 ? m : m - 1) - jj;
+    const int x0 = (pid % g.npd) * g.b - g.o, y0 = (pid / g.npd) * g.b - g.o;
+    const T sx = comp == 0 ? T(-1) : T(1), sy = comp == 1 ? T(-1) : T(1);
+    T zc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      zc[q] = Xs[q][row][b];
+#pragma unroll
+      for (int p = 1; p < KS; ++p) zc[q] += Xs[q][16 * p + row][b];
+    }
+    const T p = zc[0] + zc[2], q = zc[1] + zc[3], d = zc[0] - zc[2], e = zc[1] - zc[3];
+    auto put = [&](int i, int j, T v) {   // an owned image: inside the grid, no wrap
+      T* zp = z + (size_t)comp * nn + (size_t)(y0 + j) * N + x0 + i;
+      *zp = acc_mode ? *zp + v : v;
+    };
+    if (own & 1) put(ii, jj, p + q);
+    if (own & 2) put(mi, jj, sx * (p - q));
+    if (own & 4) put(ii, mj, sy * (d + e));
+    if (own & 8) put(mi, mj, sx * sy * (d - e));
+  }
+}
 
-// Reference tile width of the single-system interior product: the number of
-// reduction slices is derived from it, so the sums (and the results) do not
-// depend on the tile width a level runs with (16 or 32, picked by timing).
-constexpr int kIntTile = 32;
+// The class matrices of the swept interior box matrix (-A^{-1} in the tiles on
+// or below the diagonal); kl: the four images' local indices of every orbit,
+// rl: the local index of every row representative.
+template <typename T>
+__global__ void k_extract_classes(const double* __restrict__ mat, int nloc, IntClassView C, const int* __restrict__ kl,
+                                  const int* __restrict__ rl, T* __restrict__ out) {
+  const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
+  for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
+    const int rr = (int)(t % 16);
+    const size_t t1 = t / 16;
+    const int k = (int)(t1 % C.Kp);
+    const int rt = (int)(t1 / C.Kp % C.nrt), cls = (int)(t1 / C.Kp / C.nrt), row = rt * 16 + rr;
+    double v = 0.0;
+    if (row < C.R && k < C.K) {
+      const int lr = rl[row], comp = C.kcode[k] >> 24;
+      const int e = kl[4 * k], x = kl[4 * k + 1], y = kl[4 * k + 2], xy = kl[4 * k + 3];
+      auto at = [&](int j) {
+        return -((lr >> 6) >= (j >> 6) ? mat[(size_t)lr * nloc + j] : mat[(size_t)j * nloc + lr]);
+      };
+      const double cx = (comp == 0 ? -1.0 : 1.0) * (cls & 1 ? -1.0 : 1.0), cy = (comp == 1 ? -1.0 : 1.0) * (cls & 2 ? -1.0 : 1.0);
+      v = at(e);
+      if (x != e) v += cx * at(x);
+      if (y != e) v += cy * at(y);
+      if (xy != e && xy != x && xy != y) v += cx * cy * at(xy);
+      v *= 0.25;
+    }
+    out[t] = (T)v;
+  }
+}
 
+template <typename T>
+void launch_extract_classes(const double* mat, int nloc, IntClassView C, const int* kl, const int* rl, T* out,
+                            hipStream_t s) {
+  const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
+  int grid = cdiv(tot, 256);
+  if (grid > 4096) grid = 4096;
+  IBMG_KLAUNCH((k_extract_classes<T>), dim3(grid), dim3(256), 0, s, mat, nloc, C, kl, rl, out);
+  IBMG_LAUNCH_CHECK();
+}
+template void launch_extract_classes<double>(const double*, int, IntClassView, const int*, const int*, double*, hipStream_t);
+template void launch_extract_classes<float>(const double*, int, IntClassView, const int*, const int*, float*, hipStream_t);
+
+// ---------------------------------------------------------------------------
+// Interior tiles of the batched sweep (below): Z[64-row chunk, boxes] = M[chunk,
+// :] X[:, boxes] on the matrix cores, M in 64-row chunks.
+// ---------------------------------------------------------------------------
 // Gathers of a box's local residual.  The level's local-unknown table holds
 // nloc codes (comp << 24 | jj << 12 | ii) followed by nloc linear offsets
 // comp N^2 + jj N + ii.  A box whose enlarged region (corner x0, y0, faces up
@@ -1256,324 +1427,32 @@ __device__ __forceinline__ void ras_int_gemm(const T* __restrict__ r, T* __restr
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_ras_interior_g(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                        const T* __restrict__ M, const int* __restrict__ boxes,
-                                                        int nlist, const int* __restrict__ loc_tab,
-                                                        T* __restrict__ part, int ksplit, bool acc) {
-  __shared__ GemmSmem<T> sm;
-  ras_int_gemm<T>(r, z, g, 0, g.npd * g.npd, M, boxes, nlist, blockIdx.x, blockIdx.y, blockIdx.z, ksplit, loc_tab,
-                  nullptr, part, sm, acc);
+static void launch_interior(const T* r, T* z, BoxGeom g, const IntClassView& C, const int* boxes, int n, bool acc,
+                            hipStream_t s) {
+  if (C.Kp > kIntMaxOrbits || C.Kp % 128) throw Error(IBMG_ERR_ARG, "class matrices padded to whole chunks");
+  const dim3 grid((n + 15) / 16, C.nrt);
+  // two parts shorten a work-group's chain of chunks (188 boxes of 16 x 16/4,
+  // 156 work-groups: 16.5 us against 22.2 FP64, 11.2 against 16.7 FP32); once
+  // the work-groups fill the device their size costs more (852 boxes, 702
+  // work-groups: 46.6 against 38.5 FP64, 22.1 against 24.7 FP32; 3584 boxes of
+  // 8 x 8/2, 896 work-groups: 20.6 against 16.9, 13.1 against 12.3)
+  if ((int)(grid.x * grid.y) >= (sizeof(T) == 8 ? 512 : 768))
+    IBMG_KLAUNCH((k_ras_int<T, 1>), grid, dim3(256), 0, s, r, z, g, C, boxes, n, acc);
+  else
+    IBMG_KLAUNCH((k_ras_int<T, 2>), grid, dim3(512), 0, s, r, z, g, C, boxes, n, acc);
+  IBMG_LAUNCH_CHECK();
 }
-
-template <typename T, int TB>
-__global__ void __launch_bounds__(256) k_ras_interior(const T* __restrict__ r, T* __restrict__ z,
-                                                      BoxGeom g, const T* __restrict__ M,
-                                                      const int* __restrict__ boxes, int nlist,
-                                                      const int* __restrict__ loc_tab,
-                                                      T* __restrict__ part, int ksplit, bool acc) {
-  __shared__ IntTileSmem<T, TB> sm;
-  ras_int_tile<T, TB>(r, z, g, 0, g.npd * g.npd, M, boxes, nlist, blockIdx.x, blockIdx.y, blockIdx.z, ksplit,
-                      loc_tab, nullptr, part, sm, acc);
-}
-
-// Pipelined form of the interior product: a work-group owns a 64-row chunk,
-// 64 boxes and one reduction slice; wave w the chunk's rows 16w..16w+15
-// against all 64 boxes (four 16 x 16 output tiles), its inverse fragments
-// loading straight into registers.  The boxes' gathered residuals pass
-// through two LDS buffers, 32 reduction indices at a time: the next step's
-// inverse fragments and gathers load while the MFMAs read the current
-// buffer, and one barrier per step hands the buffers over.  The grid is one
-// dimensional and remapped so that the work-groups one XCD receives (the
-// hardware deals them to the eight XCDs in turn) form a contiguous run of
-// tasks, chunk-major: each XCD's L2 then serves few chunks of the shared
-// inverse.  Slices and the order of every output's MFMA steps are those of
-// the tile kernels above, so the sums agree bit for bit.
-constexpr int kPipeKC = 32;
-
-template <typename T>
-struct PipeSmem {
-  T Xs[2][kPipeKC][65];   // [buffer][reduction index][box]
-  size_t base[64];
-  long long lin[64];
-  int bid[64], bx0[64], by0[64];
-  int ltab[kIntLinTab];
-};
-
-// Task of work-group wg of nwg: XCD x = wg mod 8 receives wg = x, x + 8, ...;
-// those map to the run [x q + min(x, rem), ...) of length q + (x < rem),
-// q = nwg / 8, rem = nwg mod 8, a bijection onto [0, nwg).
-__device__ __forceinline__ int xcd_task(int wg, int nwg) {
-  const int q = nwg >> 3, rem = nwg & 7, x = wg & 7, u = wg >> 3;
-  return x * q + (x < rem ? x : rem) + u;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_ras_interior_p(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                        const T* __restrict__ M, const int* __restrict__ boxes,
-                                                        int nlist, const int* __restrict__ loc_tab,
-                                                        T* __restrict__ part, int ksplit, bool acc_mode) {
-  constexpr int TB = 64, KC = kPipeKC, GPT = KC * TB / 256, AS = KC / 4, NT = TB / 16;
-  __shared__ PipeSmem<T> sm;
-  using acc_t = typename Mfma<T>::acc_t;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int ntb = (nlist + TB - 1) / TB;
-  const int task = xcd_task(blockIdx.x, gridDim.x);
-  const int tile = task % ntb, cs = task / ntb;
-  const int kslice = cs % ksplit, chunk = cs / ksplit;
-  const int bt = tile * TB;
-  if (tid < TB) {
-    const int b = bt + tid;
-    const int pid = b < nlist ? boxes[b] : -1;
-    sm.bid[tid] = pid;
-    sm.base[tid] = 0;
-    sm.bx0[tid] = pid >= 0 ? (pid % g.npd) * g.b - g.o : 0;
-    sm.by0[tid] = pid >= 0 ? (pid / g.npd) * g.b - g.o : 0;
-    sm.lin[tid] = box_lin(g, 0, sm.bx0[tid], sm.by0[tid]);
-  }
-  // the slice: 64-column chunks [c0, c1) of the reduction index, as above
-  const int nchunk = (g.nloc + 63) / 64;
-  const int per = (nchunk + ksplit - 1) / ksplit;
-  const int c0 = kslice * per;
-  const int c1 = c0 + per < nchunk ? c0 + per : nchunk;
-  const int kb = c0 * 64, kspan = c1 > c0 ? (c1 - c0) * 64 : 0;
-  const bool ltab_lds = kspan <= kIntLinTab;
-  if (ltab_lds)
-    for (int k = tid; k < kspan; k += 256) sm.ltab[k] = kb + k < g.nloc ? loc_tab[g.nloc + kb + k] : 0;
-  __syncthreads();
-  const T* Mrow = M + (size_t)chunk * g.nloc * 64 + 16 * wave + (lane & 15);
-  const int kq = lane >> 4, bl = lane & 15;
-  acc_t acc[NT];
-#pragma unroll
-  for (int q = 0; q < NT; ++q) acc[q] = acc_t{0, 0, 0, 0};
-  // as in the tile kernels: fixed reduction index and boxes per thread, the
-  // boxes' linear starts in registers, one offset read per step
-  long long glin[GPT];
-  bool gslow = false;
-#pragma unroll
-  for (int u = 0; u < GPT; ++u) {
-    const int b = (tid + u * 256) / KC;
-    glin[u] = sm.bid[b] >= 0 ? sm.lin[b] : -2;
-    gslow |= sm.bid[b] >= 0 && (!ltab_lds || sm.lin[b] < 0);
-  }
-  auto gather = [&](int j0, T* gxo) {
-    const int jk = j0 + tid % KC;
-    const bool in = jk < g.nloc;
-    const int off = in && ltab_lds ? sm.ltab[jk - kb] : 0;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      T val = 0;
-      if (in && glin[u] >= 0 && ltab_lds) {
-        val = r[glin[u] + off];
-      } else if (in && gslow && glin[u] != -2) {
-        const int b = (tid + u * 256) / KC;
-        val = box_value<T>(r, g, loc_tab, jk, 0, sm.lin[b], sm.bx0[b], sm.by0[b]);
-      }
-      gxo[u] = val;
-    }
-  };
-  auto load_a = [&](int j0, T* gao) {
-    if (j0 + KC <= g.nloc) {
-      const T* Mj = Mrow + (size_t)(j0 + kq) * 64;
-#pragma unroll
-      for (int s = 0; s < AS; ++s) gao[s] = Mj[(size_t)s * 256];
-    } else {
-#pragma unroll
-      for (int s = 0; s < AS; ++s) {
-        const int jk = j0 + 4 * s + kq;
-        gao[s] = jk < g.nloc ? Mrow[(size_t)jk * 64] : (T)0;
-      }
-    }
-  };
-  auto stage = [&](int buf, const T* gxi) {
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int t = tid + u * 256;
-      sm.Xs[buf][t % KC][t / KC] = gxi[u];
-    }
-  };
-  const int nsteps = kspan / KC;
-  T ga[AS], gx[GPT];
-  if (nsteps > 0) {
-    load_a(kb, ga);
-    gather(kb, gx);
-    stage(0, gx);
-  }
-  __syncthreads();
-  for (int st = 0; st < nsteps; ++st) {
-    const int buf = st & 1;
-    T a[AS];
-#pragma unroll
-    for (int s = 0; s < AS; ++s) a[s] = ga[s];
-    const bool more = st + 1 < nsteps;
-    if (more) {
-      load_a(kb + (st + 1) * KC, ga);
-      gather(kb + (st + 1) * KC, gx);
-    }
-#pragma unroll
-    for (int s = 0; s < AS; ++s) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q) acc[q] = Mfma<T>::mma(a[s], sm.Xs[buf][4 * s + kq][16 * q + bl], acc[q]);
-    }
-    if (more) stage(buf ^ 1, gx);
-    __syncthreads();
-  }
-  const int nown_pad = g.nch * 64;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int row = chunk * 64 + 16 * wave + Mfma<T>::row(kq, v);
-    if (row >= g.nown) continue;
-    if (ksplit == 1) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        const int bb = 16 * q + bl;
-        if (sm.bid[bb] >= 0) {
-          const size_t o = own_glob(g, sm.bid[bb], row);
-          z[o] = acc_mode ? z[o] + acc[q][v] : acc[q][v];
-        }
-      }
-    } else {
-      T* pp = part + (size_t)kslice * nlist * nown_pad;
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-        if (bt + 16 * q + bl < nlist) pp[(size_t)(bt + 16 * q + bl) * nown_pad + row] = acc[q][v];
-    }
-  }
-}
-
-// Reduction slices for the interior product: enough blocks to cover the
-// device (>= 768) while every slice keeps at least two column chunks.
-int ras_interior_ksplit(const BoxGeom& g, int n_int) {
-  if (n_int <= 0) return 1;
-  const int tiles = (n_int + kIntTile - 1) / kIntTile;
-  const int nchunk = (g.nloc + 63) / 64;
-  int ks = 1;
-  while (ks < 8 && tiles * g.nch * ks < 768 && nchunk / (2 * ks) >= 2) ks *= 2;
-  return ks;
-}
-
-// ---------------------------------------------------------------------------
-// Interior product on gathered operands: the boxes' local residuals are
-// gathered once into X[k][box] (nloc x nbp, boxes padded to 128), then
-// Z = M X runs as 64-row x 128-box tiles on the matrix cores: four waves of
-// 2 x 4 16x16x4 tiles, the reduction staged through LDS 32 indices at a time.
-// The reduction slices and the order of each output's MFMA steps are those
-// of the tile kernels above, so the results are the same.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256) k_int_gather(const T* __restrict__ r, T* __restrict__ X, BoxGeom g,
-                                                    const int* __restrict__ boxes, int nlist, int nbp,
-                                                    const int* __restrict__ loc_tab) {
-  const size_t tot = (size_t)g.nloc * nbp;
-  for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
-    const int k = (int)(t / nbp), b = (int)(t % nbp);
-    T v = 0;
-    if (b < nlist) {
-      const int pid = boxes[b];
-      const int x0 = (pid % g.npd) * g.b - g.o, y0 = (pid / g.npd) * g.b - g.o;
-      v = box_value<T>(r, g, loc_tab, k, 0, box_lin(g, 0, x0, y0), x0, y0);
-    }
-    X[t] = v;
-  }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_int_gemm(const T* __restrict__ M, const T* __restrict__ X, T* __restrict__ z,
-                                                  BoxGeom g, const int* __restrict__ boxes, int nlist, int nbp,
-                                                  T* __restrict__ part, int ksplit, bool acc_mode) {
-  constexpr int KC = 32;
-  __shared__ T As[KC][64];
-  __shared__ T Bs[KC][128];
-  using acc_t = typename Mfma<T>::acc_t;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wr = wave & 1, wb = wave >> 1, kq = lane >> 4, ln = lane & 15;
-  const int chunk = blockIdx.x, B0 = blockIdx.y * 128, kslice = blockIdx.z;
-  const int nchunk = (g.nloc + 63) / 64;
-  const int per = (nchunk + ksplit - 1) / ksplit;
-  const int c0 = kslice * per, c1 = c0 + per < nchunk ? c0 + per : nchunk;
-  const int kb = c0 * 64, ke = c1 * 64;   // reduction indices beyond nloc read as zero
-  const T* Mc = M + (size_t)chunk * g.nloc * 64;
-  acc_t acc[2][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
-  T ga[8], gb[16];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = tid + 256 * u, kk = t >> 6, row = t & 63, k = k0 + kk;
-      ga[u] = k < g.nloc ? Mc[(size_t)k * 64 + row] : (T)0;
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int t = tid + 256 * u, kk = t >> 7, c = t & 127, k = k0 + kk;
-      gb[u] = k < g.nloc ? X[(size_t)k * nbp + B0 + c] : (T)0;
-    }
-  };
-  if (kb < ke) load(kb);
-  for (int k0 = kb; k0 < ke; k0 += KC) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int t = tid + 256 * u;
-      As[t >> 6][t & 63] = ga[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int t = tid + 256 * u;
-      Bs[t >> 7][t & 127] = gb[u];
-    }
-    __syncthreads();
-    if (k0 + KC < ke) load(k0 + KC);   // in flight during the MFMAs below
-#pragma unroll
-    for (int st = 0; st < KC / 4; ++st) {
-      const int kk = 4 * st + kq;
-      const T a0 = As[kk][32 * wr + ln], a1 = As[kk][32 * wr + 16 + ln];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const T bv = Bs[kk][64 * wb + 16 * b + ln];
-        acc[0][b] = Mfma<T>::mma(a0, bv, acc[0][b]);
-        acc[1][b] = Mfma<T>::mma(a1, bv, acc[1][b]);
-      }
-    }
-    __syncthreads();
-  }
-  const int nown_pad = g.nch * 64;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = chunk * 64 + 32 * wr + 16 * a + Mfma<T>::row(kq, v);
-        const int box = B0 + 64 * wb + 16 * b + ln;
-        if (row >= g.nown || box >= nlist) continue;
-        if (ksplit == 1) {
-          const size_t o = own_glob(g, boxes[box], row);
-          z[o] = acc_mode ? z[o] + acc[a][b][v] : acc[a][b][v];
-        } else {
-          part[((size_t)kslice * nlist + box) * nown_pad + row] = acc[a][b][v];
-        }
-      }
-}
-
-// nloc x (boxes rounded up to 128): the gathered operand of the product
-size_t int_gather_elems(const BoxGeom& g, int n_int) { return (size_t)g.nloc * (size_t)((n_int + 127) / 128 * 128); }
 
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
-                      const T* shared_inv, const int* int_boxes, int n_int, const int* loc_tab,
-                      T* part, hipStream_t s, int parts, bool acc, int tb, T* xg, size_t xg_elems,
-                      const SymIB* sym) {
-  // slices of a split IB launch first in part, those of the interior product
-  // after them; one sum launch finishes both (and the symmetric IB partials)
+                      const IntClassView& cls, const int* int_boxes, int n_int,
+                      T* part, hipStream_t s, int parts, bool acc, const SymIB* sym) {
+  // slices of a split IB launch go to part; one sum launch adds them (or the
+  // symmetric IB partials)
   const bool do_ib = (parts & 1) && n_ib > 0, do_int = (parts & 2) && n_int > 0;
   const bool use_sym = do_ib && sym != nullptr;
   const int ks_ib = do_ib && !use_sym ? ras_ib_ksplit(g, n_ib) : 1;
   const int ks_sym = use_sym ? ras_ib_ksplit(g, n_ib) : 1;
-  const int ks_int = do_int ? ras_interior_ksplit(g, n_int) : 1;
-  const size_t nown_pad = (size_t)g.nch * 64;
-  T* ipart = part;
-  T* tpart = part + (ks_ib > 1 ? (size_t)ks_ib * n_ib * nown_pad : 0);
   T* spart = use_sym ? static_cast<T*>(sym->part) : nullptr;
   if (use_sym) {
     if (g.nown % 64) throw Error(IBMG_ERR_ARG, "symmetric storage needs whole 64-row chunks");
@@ -1584,42 +1463,18 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
   } else if (do_ib) {
     const size_t lds = (((size_t)g.nloc + 3) & ~(size_t)3) * sizeof(T) + 256 * sizeof(T);
     IBMG_KLAUNCH((k_ras_ib<T>), dim3(n_ib, g.nch, ks_ib), dim3(256), lds, s, r, z, g, inv, ib_boxes, acc,
-                       ipart);
+                       part);
     IBMG_LAUNCH_CHECK();
   }
   if (do_int) {
-    const int ks = ks_int;
-    if (tb == 128 && xg && xg_elems >= int_gather_elems(g, n_int)) {
-      const int nbp = (n_int + 127) / 128 * 128;
-      const size_t tot = (size_t)g.nloc * nbp;
-      int grid = cdiv(tot, 256);
-      if (grid > 8192) grid = 8192;
-      IBMG_KLAUNCH((k_int_gather<T>), dim3(grid), dim3(256), 0, s, r, xg, g, int_boxes, n_int, nbp, loc_tab);
-      IBMG_LAUNCH_CHECK();
-      IBMG_KLAUNCH((k_int_gemm<T>), dim3(g.nch, nbp / 128, ks), dim3(256), 0, s, shared_inv, xg, z, g,
-                         int_boxes, n_int, nbp, tpart, ks, acc);
-    } else if (tb == kIntFormPipe) {
-      const long long nwg = (long long)((n_int + 63) / 64) * g.nch * ks;
-      if (nwg > 0x7fffffffLL) throw Error(IBMG_ERR_ARG, "interior product grid too large");
-      IBMG_KLAUNCH((k_ras_interior_p<T>), dim3((unsigned)nwg), dim3(256), 0, s, r, z, g, shared_inv, int_boxes,
-                   n_int, loc_tab, tpart, ks, acc);
-    } else if (tb == 64)
-      IBMG_KLAUNCH((k_ras_interior_g<T>), dim3((n_int + 63) / 64, g.nch, ks), dim3(256), 0, s, r, z, g,
-                         shared_inv, int_boxes, n_int, loc_tab, tpart, ks, acc);
-    else if (tb == 16)
-      IBMG_KLAUNCH((k_ras_interior<T, 16>), dim3((n_int + 15) / 16, g.nch, ks), dim3(256), 0, s, r, z, g,
-                         shared_inv, int_boxes, n_int, loc_tab, tpart, ks, acc);
-    else
-      IBMG_KLAUNCH((k_ras_interior<T, 32>), dim3((n_int + 31) / 32, g.nch, ks), dim3(256), 0, s, r, z, g,
-                         shared_inv, int_boxes, n_int, loc_tab, tpart, ks, acc);
-    IBMG_LAUNCH_CHECK();
+    if (!cls.M || g.nown != 3 * g.b * g.b) throw Error(IBMG_ERR_ARG, "interior boxes without class matrices");
+    launch_interior<T>(r, z, g, cls, int_boxes, n_int, acc, s);
   }
-  const int na = ks_ib > 1 ? n_ib : 0, nb = ks_int > 1 ? n_int : 0, ns = use_sym ? n_ib : 0;
-  if (na + nb + ns > 0) {
-    int grid = cdiv((size_t)(na + nb + ns) * g.nown, 256);
+  const int na = ks_ib > 1 ? n_ib : 0, ns = use_sym ? n_ib : 0;
+  if (na + ns > 0) {
+    int grid = cdiv((size_t)(na + ns) * g.nown, 256);
     if (grid > 4096) grid = 4096;
-    IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, ipart, ib_boxes, na, ks_ib, tpart, int_boxes, nb,
-                       ks_int, spart, ns, ks_sym, z, g, acc);
+    IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, part, ib_boxes, na, ks_ib, spart, ns, ks_sym, z, g, acc);
     IBMG_LAUNCH_CHECK();
   }
 }
@@ -2013,11 +1868,11 @@ template void launch_asm_apply<double>(const double*, double*, BoxGeom, const do
                                        hipStream_t);
 template void launch_asm_apply<float>(const float*, float*, BoxGeom, const float*, const int*, float*, hipStream_t);
 template void launch_ras_apply<double>(const double*, double*, BoxGeom, const double*, const int*, int,
-                                       const double*, const int*, int, const int*, double*,
-                                       hipStream_t, int, bool, int, double*, size_t, const SymIB*);
+                                       const IntClassView&, const int*, int, double*, hipStream_t, int, bool,
+                                       const SymIB*);
 template void launch_ras_apply<float>(const float*, float*, BoxGeom, const float*, const int*, int,
-                                      const float*, const int*, int, const int*, float*,
-                                      hipStream_t, int, bool, int, float*, size_t, const SymIB*);
+                                      const IntClassView&, const int*, int, float*, hipStream_t, int, bool,
+                                      const SymIB*);
 template void launch_extract_sym<double>(const double*, int, BoxGeom, const int*, double*, hipStream_t);
 template void launch_extract_sym<float>(const double*, int, BoxGeom, const int*, float*, hipStream_t);
 template void launch_coarse_apply<double>(const double*, int, const double*, double*, hipStream_t);

@@ -534,14 +534,6 @@ void launch_extract_owned(const double* mats, int count, BoxGeom g, T* out, hipS
 // (boxes in a fixed order per unknown).
 template <typename T>
 void launch_asm_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* box_inv, T* Y, hipStream_t s);
-// parts: bit 0 = IB boxes (k_ras_ib), bit 1 = interior boxes
-// (k_ras_interior); the smoother launches both, and one k_ras_sum adds the
-// slices of whichever was split.
-// acc: add the local solutions to z on the owned sets instead of storing them;
-// tb: interior product form (16 or 32 boxes per tile, 64: register-blocked
-// 64 x 64 tiles, 128: residuals gathered into xg (at least
-// int_gather_elems(g, n_int) elements) and 64 x 128 tiles; results do not
-// depend on it)
 // Symmetric storage of the IB boxes' owned rows (restricted sweep): chunk c
 // keeps the owned columns of tiles 0..c and every non-owned column, in the
 // permuted local order perm (owned unknowns first, in owned order); the
@@ -558,22 +550,29 @@ int sym_part_len(const BoxGeom& g, int n_ib);
 template <typename T>
 void launch_extract_sym(const double* mats, int count, BoxGeom g, const int* perm, T* out, hipStream_t s);
 
-// sym != null: the IB boxes run from the symmetric storage (parts & 1),
-// their rows summed with the interior slices in one launch
+// The interior boxes' shared inverse in its four parity classes (k_ras_int):
+// M (T[4][nrt][Kp][16]), the orbits' representatives kcode[K] and the rows'
+// rcode[R] (comp << 24 | jj << 12 | ii; rcode with the owned images' bits 1 e,
+// 2 X, 4 Y, 8 XY above at 26), nrt = 16-row tiles, Kp = K rounded up to 128.
+struct IntClassView {
+  const void* M;
+  const int *kcode, *rcode;
+  int K, Kp, R, nrt;
+};
+// the most orbits a box has (b + 2 o <= 32), padded to whole chunks
+constexpr int kIntMaxOrbits = 896;
+template <typename T>
+void launch_extract_classes(const double* mat, int nloc, IntClassView C, const int* kl, const int* rl, T* out,
+                            hipStream_t s);
+
+// One restricted Schwarz sweep (parts: bit 0 = IB boxes, bit 1 = interior
+// boxes); acc: add the local solutions to z on the owned sets instead of
+// storing them.  sym != null: the IB boxes run from the symmetric storage.
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
-                      const T* shared_inv, const int* int_boxes, int n_int, const int* loc_tab,
-                      T* part, hipStream_t s, int parts = 3, bool acc = false, int tb = 32, T* xg = nullptr,
-                      size_t xg_elems = 0, const SymIB* sym = nullptr);
-size_t int_gather_elems(const BoxGeom& g, int n_int);
-// reduction slices of the interior-box product (part holds ksplit * n_int * nch * 64)
-int ras_interior_ksplit(const BoxGeom& g, int n_int);
-// interior product forms (launch_ras_apply's tb): 16, 32 = boxes per tile of
-// the narrow kernels, 64 = register-blocked tiles, 128 = gathered operand,
-// kIntFormPipe = the pipelined XCD-ordered 64-box tiles
-constexpr int kIntFormPipe = 1;
-// column slices of the IB-box kernel (part holds ksplit * n_ib * nch * 64,
-// followed by the interior product's slices when both are launched)
+                      const IntClassView& cls, const int* int_boxes, int n_int, T* part, hipStream_t s, int parts = 3,
+                      bool acc = false, const SymIB* sym = nullptr);
+// column slices of the IB-box kernel (part holds ksplit * n_ib * nch * 64)
 int ras_ib_ksplit(const BoxGeom& g, int n_ib);
 void launch_coarse_assemble(int N, StokesCoef<double> c, const int* tptr_u, const int* tcol_u,
                             const double* tval_u, const int* tptr_v, const int* tcol_v,

@@ -86,10 +86,14 @@ struct Level {
   std::vector<int> uniq;  // unique box ids (IB boxes, then one interior representative)
   std::vector<int> ib_list, int_list;
   std::vector<int> loc_tab;  // local unknown -> (comp << 24) | (jj << 12) | ii, then -> comp N^2 + jj N + ii
-  DBuf<int> d_ib, d_int, d_loc;
+  DBuf<int> d_ib, d_int;
   DBuf<T> inv;            // [n_unique][nch][nloc][64]
-  DBuf<T> int_part;       // reduction slices of the interior-box product
-  DBuf<T> int_x;          // gathered residuals of the interior boxes (product form 128)
+  DBuf<T> ib_part;        // column slices of the IB boxes' product
+  // the interior boxes' shared inverse in its four parity classes (k_ras_int)
+  std::vector<int> kcode, rcode, klocal, rlocal;
+  DBuf<int> d_kcode, d_rcode, d_klocal, d_rlocal;
+  DBuf<T> cls;
+  IntClassView clsv{};
   // symmetric storage of the IB boxes' owned rows (restricted additive
   // sweep): the permuted local order, the storage, the per-box partials
   bool use_sym = false;
@@ -100,7 +104,6 @@ struct Level {
   // [int_off[c], int_off[c+1])
   int ncolour = 0;
   std::vector<int> box_colour, ib_off, int_off;
-  int int_tb = 32;        // interior tile width, picked by timing at set-up
   DBuf<T> rr;             // residual between colours
   // summed combination (IBMG_COMBINE_SUM): g.nown = nloc, every row of every
   // box inverse is kept; box_inv maps a box id to its inverse (IB boxes their
@@ -202,8 +205,6 @@ class Solver final : public SolverBase {
     build_numeric(s, mark);
     check_breakdown(s);
     mark("breakdown scan");
-    if (!defer_coarse_) tune_interior(s);
-    mark("interior tuning");
     IBMG_HIP(hipStreamSynchronize(s));
     setup_ms_ = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_begin).count();
   }
@@ -245,6 +246,7 @@ class Solver final : public SolverBase {
     for (int l = 1; l <= L_ && !coarse_only; ++l) {
       Level<T>& lev = levels_[l];
       if (lev.inv.n) scan(lev.inv.p, lev.inv.n, ("the box inverses of level " + std::to_string(l)).c_str());
+      if (lev.cls.n) scan(lev.cls.p, lev.cls.n, ("the interior box inverse of level " + std::to_string(l)).c_str());
       if (lev.inv_sym.n) scan(lev.inv_sym.p, lev.inv_sym.n, ("the IB box inverses of level " + std::to_string(l)).c_str());
       if (lev.sc)
         if (!(std::isfinite(lev.sc->lamA) && lev.sc->lamA > 0.0 && std::isfinite(lev.sc->lamM) && lev.sc->lamM > 0.0))
@@ -627,13 +629,6 @@ class Solver final : public SolverBase {
 
   size_t box_stride(const Level<T>& lev) const { return (size_t)lev.g.nch * lev.g.nloc * 64; }
 
-  // elements of the interior product's slice buffer for cnt boxes
-  static size_t interior_part_need(const BoxGeom& g, int cnt) {
-    if (cnt <= 0) return 0;
-    const int ks = ras_interior_ksplit(g, cnt);
-    return ks > 1 ? (size_t)ks * cnt * g.nch * 64 : 0;
-  }
-
   // elements of the IB-box kernel's slice buffer for cnt boxes
   static size_t ib_part_need(const BoxGeom& g, int cnt) {
     if (cnt <= 0) return 0;
@@ -642,19 +637,16 @@ class Solver final : public SolverBase {
   }
 
   // Every Schwarz launch goes through here: the slice buffer must hold the
-  // launch's column slices (IB boxes) followed by its reduction slices
-  // (interior).
+  // launch's column slices.
   // sym: the IB boxes (the level's whole list) from the symmetric copy
   void ras_launch(Level<T>& lev, const T* r, T* z, const T* inv, const int* ib, int n_ib, const int* in, int n_int,
-                  hipStream_t s, int parts, bool acc, int tb, bool sym = false) {
-    require(lev.int_part.n >= ib_part_need(lev.g, (parts & 1) ? n_ib : 0) +
-                                   interior_part_need(lev.g, (parts & 2) ? n_int : 0),
-            "Schwarz slice buffer too small");
+                  hipStream_t s, int parts, bool acc, bool sym = false) {
+    require(lev.ib_part.n >= ib_part_need(lev.g, (parts & 1) ? n_ib : 0), "Schwarz slice buffer too small");
     require(!sym || (lev.use_sym && n_ib == lev.n_ib), "symmetric IB storage is for the whole IB list");
     const SymIB sy = sym_of(lev);
     require(sym || !lev.use_sym || !(parts & 1) || n_ib == 0, "the IB boxes of this level are in symmetric storage");
-    launch_ras_apply<T>(r, z, lev.g, inv, ib, n_ib, shared_inv(lev), in, n_int, lev.d_loc.p, lev.int_part.p, s,
-                        parts, acc, tb, lev.int_x.p, lev.int_x.n, sym ? &sy : nullptr);
+    launch_ras_apply<T>(r, z, lev.g, inv, ib, n_ib, lev.clsv, in, n_int, lev.ib_part.p, s, parts, acc,
+                        sym ? &sy : nullptr);
   }
 
   // blocks of the fused operator + dots kernel on a level
@@ -668,49 +660,39 @@ class Solver final : public SolverBase {
     return (size_t)std::max({dot_blocks(lev), gs_blocks(3 * (size_t)lev.N * lev.N), 1024}) * (kMaxNu + 1);
   }
 
-  // Interior product form per Schwarz level: time the pipelined XCD-ordered
-  // 64-box tiles, the 16- and 32-box tiles, the register-blocked 64-box form
-  // and the gathered 128-box form (HIP events, on the level's work vectors)
-  // and keep the fastest.  All compute the same sums in the same order.
-  // IBMG_INTERIOR_FORM=1|16|32|64|128 in the environment fixes the form
-  // instead (1 = pipelined; where the level supports it).
-  void tune_interior(hipStream_t s) {
-    if (d_.smoother != IBMG_RAS && d_.smoother != IBMG_RMS) return;
-    if (dry_run() || d_.combine == IBMG_COMBINE_SUM) return;
-    int forced = 0;
-    if (const char* e = std::getenv("IBMG_INTERIOR_FORM")) forced = std::atoi(e);
-    for (int l = 1; l <= L_; ++l) {
-      Level<T>& lev = levels_[l];
-      const int n_int = (int)lev.int_list.size();
-      if (n_int == 0) continue;
-      if (forced == 16 || forced == 32 || forced == 64 || forced == kIntFormPipe ||
-          (forced == 128 && lev.int_x.n >= int_gather_elems(lev.g, n_int))) {
-        lev.int_tb = forced;
-        continue;
-      }
-      // a rebuild at moved points keeps a level's earlier pick while its
-      // interior box count stays within an eighth of the count it was timed
-      // at (the forms give the same bits, so only speed is at stake)
-      if ((int)int_forms_.size() > l && int_forms_[l].first > 0 &&
-          8 * std::abs(n_int - int_forms_[l].first) <= int_forms_[l].first &&
-          (int_forms_[l].second != 128 || lev.int_x.n >= int_gather_elems(lev.g, n_int))) {
-        lev.int_tb = int_forms_[l].second;
-        continue;
-      }
-      launch_fill<T>(lev.r.p, T(1), 3 * (size_t)lev.N * lev.N, s);
-      double best = 1e300;
-      for (int tb : {kIntFormPipe, 32, 16, 64, 128}) {
-        if (tb == 128 && lev.int_x.n < int_gather_elems(lev.g, n_int)) continue;
-        const double ms = time_launches([&] {
-          ras_launch(lev, lev.r.p, lev.t.p, lev.inv.p, lev.d_ib.p, lev.n_ib, lev.d_int.p, n_int, s, 2, false, tb);
-        }, 5, s);
-        if (ms < best) {
-          best = ms;
-          lev.int_tb = tb;
+  // Orbits of a box's local unknowns under its two reflections (k_ras_int):
+  // one representative per orbit for the columns, and for the rows every orbit
+  // that holds an owned unknown, represented by an owned one.
+  void class_tables(Level<T>& lev) {
+    const BoxGeom& g = lev.g;
+    const int m = g.m, nu = m * (m + 1);
+    auto local = [&](int c, int i, int j) { return c == 0 ? j * (m + 1) + i : (c == 1 ? nu + j * m + i : 2 * nu + j * m + i); };
+    auto owned = [&](int i, int j) { return i >= g.o && i < g.o + g.b && j >= g.o && j < g.o + g.b; };
+    lev.kcode.clear();
+    lev.klocal.clear();
+    lev.rcode.clear();
+    lev.rlocal.clear();
+    for (int c = 0; c < 3; ++c) {
+      const int mx = c == 0 ? m : m - 1, my = c == 1 ? m : m - 1;   // images: mx - i, my - j
+      for (int j = 0; 2 * j <= my; ++j)
+        for (int i = 0; 2 * i <= mx; ++i) {
+          lev.kcode.push_back((c << 24) | (j << 12) | i);
+          for (int l : {local(c, i, j), local(c, mx - i, j), local(c, i, my - j), local(c, mx - i, my - j)})
+            lev.klocal.push_back(l);
+          // an owned image e of the orbit, and which of its images are owned
+          // (each unknown once)
+          for (const auto& e : {std::pair<int, int>{i, j}, {mx - i, j}, {i, my - j}, {mx - i, my - j}}) {
+            if (!owned(e.first, e.second)) continue;
+            const int a = e.first, b = e.second, xa = mx - a, yb = my - b;
+            int bits = 1;
+            if (xa != a && owned(xa, b)) bits |= 2;
+            if (yb != b && owned(a, yb)) bits |= 4;
+            if (xa != a && yb != b && owned(xa, yb)) bits |= 8;
+            lev.rcode.push_back((bits << 26) | (c << 24) | (b << 12) | a);
+            lev.rlocal.push_back(local(c, a, b));
+            break;
+          }
         }
-      }
-      if ((int)int_forms_.size() <= l) int_forms_.resize(l + 1, {0, 0});
-      int_forms_[l] = {n_int, lev.int_tb};
     }
   }
 
@@ -1104,7 +1086,6 @@ class Solver final : public SolverBase {
     const BoxGeom& g = lev.g;
     lev.d_ib.upload(lev.ib_list, s);
     lev.d_int.upload(lev.int_list, s);
-    lev.d_loc.upload(lev.loc_tab, s);
     if (lev.sum_mode) {
       std::vector<int> bi((size_t)g.npd * g.npd, lev.n_ib);
       for (int i = 0; i < lev.n_ib; ++i) bi[lev.ib_list[i]] = i;
@@ -1114,19 +1095,29 @@ class Solver final : public SolverBase {
       return;
     }
     {
-      // column slices of the IB boxes followed by the reduction slices of
-      // the interior product: the whole lists (additive sweep, tuning,
+      // column slices of the IB boxes: the whole list (additive sweep,
       // single-kernel timing) and each colour's ranges (multiplicative sweep)
-      size_t need = interior_part_need(g, (int)lev.int_list.size()) + ib_part_need(g, lev.n_ib);
+      size_t need = ib_part_need(g, lev.n_ib);
       if (d_.smoother == IBMG_RMS)
-        for (int c = 0; c < lev.ncolour; ++c)
-          need = std::max(need, interior_part_need(g, lev.int_off[c + 1] - lev.int_off[c]) +
-                                    ib_part_need(g, lev.ib_off[c + 1] - lev.ib_off[c]));
-      if (lev.int_part.n < need) lev.int_part.alloc(need);
+        for (int c = 0; c < lev.ncolour; ++c) need = std::max(need, ib_part_need(g, lev.ib_off[c + 1] - lev.ib_off[c]));
+      if (lev.ib_part.n < need) lev.ib_part.alloc(need);
     }
-    // the gathered operand of the 128-box product form, up to 512 MB a level
-    const size_t xe = int_gather_elems(g, (int)lev.int_list.size());
-    if (!lev.int_list.empty() && xe * sizeof(T) <= ((size_t)512 << 20)) lev.int_x.alloc(xe);
+    if (has_classes(lev)) {
+      class_tables(lev);
+      lev.d_kcode.upload(lev.kcode, s);
+      lev.d_rcode.upload(lev.rcode, s);
+      lev.d_klocal.upload(lev.klocal, s);
+      lev.d_rlocal.upload(lev.rlocal, s);
+      IntClassView& v = lev.clsv;
+      v.K = (int)lev.kcode.size();
+      v.Kp = (v.K + 127) / 128 * 128;
+      v.R = (int)lev.rcode.size();
+      v.nrt = (v.R + 15) / 16;
+      lev.cls.alloc((size_t)4 * v.nrt * v.Kp * 16);
+      v.M = lev.cls.p;
+      v.kcode = lev.d_kcode.p;
+      v.rcode = lev.d_rcode.p;
+    }
     // The additive sweep of a single system streams the IB boxes' owned
     // rows from a symmetric copy (lower owned tiles only; whole 64-row
     // chunks) on levels with enough IB boxes: at least 256 (box, chunk)
@@ -1134,8 +1125,7 @@ class Solver final : public SolverBase {
     // two in FP32 (measured: below that the symmetric form's uneven slices
     // and longer sums cost more than its fewer bytes save).  The chunked
     // copy (lev.inv) serves the other levels, the multiplicative sweep and
-    // the batched form; on a symmetric level it holds the interior boxes'
-    // shared inverse alone.
+    // the batched form.
     lev.use_sym = d_.smoother == IBMG_RAS && !defer_coarse_ && lev.n_ib > 0 && g.nown % 64 == 0 &&
                   lev.n_ib * g.nch >= 256 && ras_ib_ksplit(g, lev.n_ib) <= (sizeof(T) == 8 ? 4 : 2) &&
                   std::getenv("IBMG_NO_SYM") == nullptr;
@@ -1157,16 +1147,19 @@ class Solver final : public SolverBase {
       lev.inv_sym.alloc((size_t)lev.n_ib * sym_box_stride(g));
       lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g, lev.n_ib));
     }
-    lev.inv.alloc((size_t)(lev.n_unique - inv_base(lev)) * box_stride(lev));
+    lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
   }
 
   SymIB sym_of(Level<T>& lev) { return SymIB{lev.inv_sym.p, lev.d_perm.p, lev.sym_part.p}; }
 
-  // first unique box whose owned rows lev.inv holds in chunks (the IB boxes
-  // of a symmetric level live in inv_sym only)
+  // The unique boxes [inv_base, inv_end) whose owned rows lev.inv holds in
+  // chunks: the IB boxes unless they are in symmetric storage, and the
+  // interior boxes' shared inverse where no parity classes hold it.
   static int inv_base(const Level<T>& lev) { return lev.use_sym ? lev.n_ib : 0; }
-  // the interior boxes' shared inverse
-  T* shared_inv(Level<T>& lev) { return lev.inv.p + (size_t)(lev.n_ib - inv_base(lev)) * box_stride(lev); }
+  int inv_end(const Level<T>& lev) const { return has_classes(lev) ? lev.n_ib : lev.n_unique; }
+  // the single-system restricted sweeps take the interior boxes in parity
+  // classes; the summed combination and the batched form read whole rows
+  bool has_classes(const Level<T>& lev) const { return !lev.sum_mode && !defer_coarse_ && !lev.int_list.empty(); }
 
   // The unique box inverses of every Schwarz level: assembled per level,
   // inverted in batches that mix levels whose boxes have the same number of
@@ -1215,11 +1208,13 @@ class Solver final : public SolverBase {
         launch_gj_invert(mats.p, n, cnt, work.p, dinv.p, s);
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
-          const int skip = std::min(count, std::max(0, inv_base(lev) - u0));
-          if (count > skip)
-            launch_extract_owned<T>(mats.p + (slot + skip) * n * n, count - skip, lev.g,
-                                    lev.inv.p + (size_t)(u0 + skip - inv_base(lev)) * box_stride(lev), s,
-                                    lev.sum_mode);
+          const int c0 = std::max(u0, inv_base(lev)), c1 = std::min(u0 + count, inv_end(lev));
+          if (c1 > c0)
+            launch_extract_owned<T>(mats.p + (slot + (c0 - u0)) * n * n, c1 - c0, lev.g,
+                                    lev.inv.p + (size_t)(c0 - inv_base(lev)) * box_stride(lev), s, lev.sum_mode);
+          if (has_classes(lev) && u0 + count > lev.n_ib)   // the interior representative comes last
+            launch_extract_classes<T>(mats.p + (slot + (lev.n_ib - u0)) * n * n, n, lev.clsv, lev.d_klocal.p,
+                                      lev.d_rlocal.p, lev.cls.p, s);
           // unique indices below n_ib are the IB boxes
           const int nsym = lev.use_sym ? std::min(count, std::max(0, lev.n_ib - u0)) : 0;
           if (nsym > 0)
@@ -1342,12 +1337,12 @@ class Solver final : public SolverBase {
         }
         const int i0 = lev.ib_off[c], k0 = lev.int_off[c];
         ras_launch(lev, rc, z, lev.inv.p + (size_t)i0 * box_stride(lev), lev.d_ib.p + i0, lev.ib_off[c + 1] - i0,
-                   lev.d_int.p + k0, lev.int_off[c + 1] - k0, s, 3, true, lev.int_tb);
+                   lev.d_int.p + k0, lev.int_off[c + 1] - k0, s, 3, true);
       }
       return;
     }
     ras_launch(lev, v, z, lev.inv.p, lev.d_ib.p, lev.n_ib, lev.d_int.p, (int)lev.int_list.size(), s, 3, false,
-               lev.int_tb, lev.use_sym);
+               lev.use_sym);
   }
 
   // w <- w + e, e = nu FGMRES iterations (classical Gram-Schmidt twice) on
@@ -1758,12 +1753,11 @@ class Solver final : public SolverBase {
 
   // One kernel of level `level`, launched alone on the level's work vectors
   // (filled with ones): IB-box Schwarz (k_ras_ib), interior-box Schwarz
-  // (k_ras_interior, one reduction slice when the product is split) or the
-  // stencil k_apply.  Algorithmic work per launch: every IB box streams its
-  // owned rows of the inverse (nown x nloc), gathers nloc values and writes
-  // nown; the interior product reads the shared inverse once and each box's
-  // nloc values and writes nown, 2 nown nloc flops per box; the stencil reads
-  // and writes the three fields once.
+  // (k_ras_int) or the stencil k_apply.  Algorithmic work per launch: every IB
+  // box streams its owned rows of the inverse (nown x nloc), gathers nloc
+  // values and writes nown; the interior product reads the class matrices once
+  // and each box's nloc values and writes nown, four R x K products per box;
+  // the stencil reads and writes the three fields once.
   double kernel_time(int kernel, int level, int reps, hipStream_t s, double* bytes, double* flops) override {
     require(level >= 0 && level <= L_, "level out of range");
     require(reps >= 1 && reps <= 100000, "reps must lie in [1, 100000]");
@@ -1787,13 +1781,13 @@ class Solver final : public SolverBase {
         fl = 2.0 * lev.n_ib * g.nown * g.nloc;
       } else {
         require(n_int > 0, "the level has no interior boxes");
-        by = ((double)g.nown * g.nloc + (double)n_int * (g.nloc + g.nown)) * ts;
-        fl = 2.0 * n_int * g.nown * g.nloc;
+        by = ((double)lev.cls.n + (double)n_int * (g.nloc + g.nown)) * ts;
+        fl = 2.0 * n_int * 4.0 * lev.clsv.R * lev.clsv.K;
       }
       const int part = kernel == IBMG_KERNEL_RAS_IB ? 1 : 2;
       ms = time_launches([&] {
         ras_launch(lev, lev.r.p, lev.t.p, lev.inv.p, lev.d_ib.p, lev.n_ib, lev.d_int.p, n_int, s, part, false,
-                   lev.int_tb, part == 1 && lev.use_sym);
+                   part == 1 && lev.use_sym);
       }, reps, s);
     } else if (kernel == IBMG_KERNEL_STENCIL) {
       by = 2.0 * (double)n * ts;
@@ -1943,7 +1937,6 @@ class Solver final : public SolverBase {
   hipGraphExec_t gexec_ = nullptr;
   DBuf<double> vin_, vout_;
   DBuf<double> tpart_;   // slice sums of the IB-row values on coarse levels
-  std::vector<std::pair<int, int>> int_forms_;   // per level: interior boxes when timed, the form picked
   hipEvent_t est_ev_ = nullptr;   // the outer loop's estimate copy
   hipStream_t side_ = nullptr;    // the coarsest inversion beside the box inversions
   hipEvent_t ev_fork_ = nullptr, ev_join_ = nullptr;

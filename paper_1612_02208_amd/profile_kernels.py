@@ -15,11 +15,6 @@ With ``--step`` it runs ``--reps`` semi-implicit time steps of the annulus
 and prints each step's solve and rebuild times, the rebuild's phases going
 to stderr (IBMG_SETUP_TIMES).
 
-With ``--interior-forms`` it times the interior product in each of its
-forms at the finest level: 1 = pipelined 64-box tiles in XCD order, 16 and
-32 boxes per narrow tile, 64 = register-blocked tiles, 128 = gathered
-operand.
-
 With ``--large`` it times the grid and coupling kernels on a 4096^2 grid
 with 2^20 points instead (fields of 400 MB, beyond the caches): a
 suspension of 32 x 32 membranes in fibre order for the stencil, the
@@ -50,7 +45,6 @@ def main():
     p.add_argument("--solve", default="", choices=["", "membrane256"])
     p.add_argument("--kappa", type=float, default=1e4)
     p.add_argument("--smoother", default="sc", choices=["ras", "sc", "rms"])
-    p.add_argument("--interior-forms", action="store_true")
     p.add_argument("--step", action="store_true")
     a = p.parse_args()
     import numpy as np
@@ -118,22 +112,9 @@ def main():
         g.close()
         del os.environ["IBMG_SETUP_TIMES"]
         return
-    if a.interior_forms:
-        # each tile form of the interior product, forced through the set-up
-        # tuner's override, one handle per form
-        for form in (1, 16, 32, 64, 128):
-            os.environ["IBMG_INTERIOR_FORM"] = str(form)
-            g = StokesIB(wl, precision=a.precision)
-            t = g.kernel_time("ras_interior", -1, a.reps)
-            print(json.dumps(dict(kernel="k_ras_interior", form=form, precision=a.precision, N=a.N, reps=a.reps,
-                                  avg_ms=t["ms"], alg_flops=t["flops"], tflops=t["flops"] / t["ms"] / 1e9)),
-                  flush=True)
-            g.close()
-        del os.environ["IBMG_INTERIOR_FORM"]
-        return
     g = StokesIB(wl, precision=a.precision)
     suffix = "<double>" if a.precision == "fp64" else "<float>"
-    kinds = [("ras_ib", "k_ras_ib"), ("ras_interior", "k_ras_interior"), ("stencil", "k_apply"),
+    kinds = [("ras_ib", "k_ras_ib"), ("ras_interior", "k_ras_int"), ("stencil", "k_apply"),
              ("restrict", "k_restrict"), ("prolong", "k_prolong_add")]
     if a.precision == "fp64":
         kinds += [("spread", "k_spread"), ("interp", "k_interp_lanes")]
