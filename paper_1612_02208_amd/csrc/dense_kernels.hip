@@ -8,6 +8,7 @@
 // jj in [0, m]; cells 2m(m+1) + jj*m + ii.  Owned unknowns (b x b cells with
 // their left x-face and bottom y-face) are ordered x-faces, y-faces, cells,
 // each (oj, oi) row-major.
+#include <algorithm>
 #include <type_traits>
 
 #include "internal.hpp"
@@ -29,75 +30,81 @@ struct CsrView {
 
 // Add an IB entry of a box row: col indexes the level's [u | v] vector; the
 // entry lands on the box's x-face or y-face unknown when that face lies in
-// the enlarged box.
-__device__ __forceinline__ void add_ib_entry(double* Ar, int col, double v, int N, int x0, int y0, int m) {
+// the enlarged box (column c of the row goes to Ar[at(c)]).
+template <typename At>
+__device__ __forceinline__ void add_ib_entry(double* Ar, At at, int col, double v, int N, int x0, int y0, int m) {
   const int NN = N * N;
   const int comp = col >= NN ? 1 : 0;
   const int f = col - comp * NN;
   const int li = pmod(f % N - x0, N), lj = pmod(f / N - y0, N);
   if (comp == 0) {
-    if (li <= m && lj <= m - 1) Ar[lj * (m + 1) + li] += v;
+    if (li <= m && lj <= m - 1) Ar[at(lj * (m + 1) + li)] += v;
   } else {
-    if (li <= m - 1 && lj <= m) Ar[m * (m + 1) + lj * m + li] += v;
+    if (li <= m - 1 && lj <= m) Ar[at(m * (m + 1) + lj * m + li)] += v;
   }
 }
 
+// Box matrices, ld x ld each: local unknown k sits at row and column pos[k]
+// (pos = null: at k); diagonal entries [nn, nnp) that no unknown takes are 1.
 __global__ void __launch_bounds__(256) k_patch_assemble(const int* __restrict__ patch_ids, BoxGeom g,
                                                         StokesCoef<double> c, CsrView tu, CsrView tv,
+                                                        const int* __restrict__ pos, int ld, int nn, int nnp,
                                                         double* __restrict__ mats) {
   const int pid = patch_ids[blockIdx.x];
   const int N = g.N, m = g.m, n = g.nloc;
   const int x0 = (pid % g.npd) * g.b - g.o;
   const int y0 = (pid / g.npd) * g.b - g.o;
-  double* A = mats + (size_t)blockIdx.x * n * n;
-  for (size_t k = threadIdx.x; k < (size_t)n * n; k += blockDim.x) A[k] = 0.0;
+  double* A = mats + (size_t)blockIdx.x * ld * ld;
+  for (size_t k = threadIdx.x; k < (size_t)ld * ld; k += blockDim.x) A[k] = 0.0;
   __syncthreads();
+  auto at = [&](int k) { return pos ? pos[k] : k; };
+  for (int k = nn + threadIdx.x; k < nnp; k += blockDim.x) A[(size_t)k * ld + k] = 1.0;
   const int nu = m * (m + 1);
   const int p0 = 2 * nu;
   const double dg = c.alpha + 4.0 * c.beta;
   for (int row = threadIdx.x; row < n; row += blockDim.x) {
-    double* Ar = A + (size_t)row * n;
+    double* Ar = A + (size_t)at(row) * ld;
     if (row < nu) {  // x-face (ii, jj)
       const int ii = row % (m + 1), jj = row / (m + 1);
-      Ar[row] += dg;
-      if (ii >= 1) Ar[row - 1] -= c.beta;
-      if (ii <= m - 1) Ar[row + 1] -= c.beta;
-      if (jj >= 1) Ar[row - (m + 1)] -= c.beta;
-      if (jj <= m - 2) Ar[row + (m + 1)] -= c.beta;
-      if (ii <= m - 1) Ar[p0 + jj * m + ii] += c.gi;
-      if (ii >= 1) Ar[p0 + jj * m + ii - 1] -= c.gi;
+      Ar[at(row)] += dg;
+      if (ii >= 1) Ar[at(row - 1)] -= c.beta;
+      if (ii <= m - 1) Ar[at(row + 1)] -= c.beta;
+      if (jj >= 1) Ar[at(row - (m + 1))] -= c.beta;
+      if (jj <= m - 2) Ar[at(row + (m + 1))] -= c.beta;
+      if (ii <= m - 1) Ar[at(p0 + jj * m + ii)] += c.gi;
+      if (ii >= 1) Ar[at(p0 + jj * m + ii - 1)] -= c.gi;
       const int r = pmod(y0 + jj, N) * N + pmod(x0 + ii, N);
-      for (int k = tu.ptr[r]; k < tu.ptr[r + 1]; ++k) add_ib_entry(Ar, tu.col[k], tu.val[k], N, x0, y0, m);
+      for (int k = tu.ptr[r]; k < tu.ptr[r + 1]; ++k) add_ib_entry(Ar, at, tu.col[k], tu.val[k], N, x0, y0, m);
     } else if (row < p0) {  // y-face (ii, jj)
       const int q = row - nu;
       const int ii = q % m, jj = q / m;
-      Ar[row] += dg;
-      if (ii >= 1) Ar[row - 1] -= c.beta;
-      if (ii <= m - 2) Ar[row + 1] -= c.beta;
-      if (jj >= 1) Ar[row - m] -= c.beta;
-      if (jj <= m - 1) Ar[row + m] -= c.beta;
-      if (jj <= m - 1) Ar[p0 + jj * m + ii] += c.gi;
-      if (jj >= 1) Ar[p0 + (jj - 1) * m + ii] -= c.gi;
+      Ar[at(row)] += dg;
+      if (ii >= 1) Ar[at(row - 1)] -= c.beta;
+      if (ii <= m - 2) Ar[at(row + 1)] -= c.beta;
+      if (jj >= 1) Ar[at(row - m)] -= c.beta;
+      if (jj <= m - 1) Ar[at(row + m)] -= c.beta;
+      if (jj <= m - 1) Ar[at(p0 + jj * m + ii)] += c.gi;
+      if (jj >= 1) Ar[at(p0 + (jj - 1) * m + ii)] -= c.gi;
       const int r = pmod(y0 + jj, N) * N + pmod(x0 + ii, N);
-      for (int k = tv.ptr[r]; k < tv.ptr[r + 1]; ++k) add_ib_entry(Ar, tv.col[k], tv.val[k], N, x0, y0, m);
+      for (int k = tv.ptr[r]; k < tv.ptr[r + 1]; ++k) add_ib_entry(Ar, at, tv.col[k], tv.val[k], N, x0, y0, m);
     } else {  // cell (ii, jj): -(D u)
       const int q = row - p0;
       const int ii = q % m, jj = q / m;
-      Ar[jj * (m + 1) + ii + 1] -= c.gi;
-      Ar[jj * (m + 1) + ii] += c.gi;
-      Ar[nu + (jj + 1) * m + ii] -= c.gi;
-      Ar[nu + jj * m + ii] += c.gi;
+      Ar[at(jj * (m + 1) + ii + 1)] -= c.gi;
+      Ar[at(jj * (m + 1) + ii)] += c.gi;
+      Ar[at(nu + (jj + 1) * m + ii)] -= c.gi;
+      Ar[at(nu + jj * m + ii)] += c.gi;
     }
   }
 }
 
 void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoef<double> c,
                            const int* tptr_u, const int* tcol_u, const double* tval_u,
-                           const int* tptr_v, const int* tcol_v, const double* tval_v, double* mats,
-                           hipStream_t s) {
+                           const int* tptr_v, const int* tcol_v, const double* tval_v, const int* pos, BoxMat bm,
+                           double* mats, hipStream_t s) {
   if (!count) return;
   CsrView tu{tptr_u, tcol_u, tval_u}, tv{tptr_v, tcol_v, tval_v};
-  IBMG_KLAUNCH(k_patch_assemble, dim3(count), dim3(256), 0, s, patch_ids, g, c, tu, tv, mats);
+  IBMG_KLAUNCH(k_patch_assemble, dim3(count), dim3(256), 0, s, patch_ids, g, c, tu, tv, pos, bm.ld, bm.nn, bm.nnp, mats);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -138,7 +145,17 @@ struct Mfma<float> {
 // of a symmetric S with D = S_KK:
 //   S_IJ <- S_IJ - S_IK D^{-1} S_KJ   (I, J outside K),
 //   S_IK <- S_IK D^{-1},  S_KK <- -D^{-1};
-// after every block S = -A^{-1}.  Step K, five launches over every matrix:
+// after every block S = -A^{-1}.
+// The restricted boxes need less than the whole inverse: with the unknowns
+// ordered non-owned first (n), owned last (o), the solution on the owned ones is
+//   z_o = S_oo^{-1} (r_o - A_on A_nn^{-1} r_n),  S_oo = A_oo - A_on A_nn^{-1} A_no.
+// Sweeping the blocks of n leaves W = A_on A_nn^{-1} in the rows o; rows already
+// swept are not needed again, so those steps update the rows below their block
+// only (elimination, "partial" below), and the blocks of o are then swept
+// within o alone.  That is 59% of the whole inverse's arithmetic at 16 x 16/4.
+// Each half keeps the velocities before the pressures, so its pivot blocks stay
+// definite.
+// Step K, five launches over every matrix:
 //   diag       (a work-group per matrix): D^{-1} in LDS (128 x 128, the
 //              160 KB of gfx950), to dinv;
 //   panel read (64-row tiles): C = S_:K from the kept tiles (a tile above
@@ -161,7 +178,7 @@ static_assert(GJ_NB == 128, "the sweep kernels are written for 128-column blocks
 // pivot): the threads holding them publish them, and every thread updates
 // its sixteen entries from its column's row-k value and its rows' column-k
 // values (the latter the same for a whole wave, read as broadcasts).
-__global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mats, int n, int kb,
+__global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mats, int n, int kb, int w,
                                                   double* __restrict__ dinv_all) {
   __shared__ double rowk[2][GJ_NB];
   __shared__ double colk[2][GJ_NB];
@@ -169,7 +186,6 @@ __global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mat
   double* Di = dinv_all + (size_t)blockIdx.x * GJ_NB * GJ_NB;
   const int tid = threadIdx.x;
   const int b = tid & 127, a0 = tid >> 7;   // column, first row (rows a0 + 8 q)
-  const int w = n - kb < GJ_NB ? n - kb : GJ_NB;
   // the padding of a narrow last block is the identity, so the pivots stay
   // nonzero; the padded rows and columns never reach the matrix.  Above the
   // diagonal tiles only tile (K1, K0) is kept: D[a][b] with a in the first
@@ -282,14 +298,13 @@ __device__ __forceinline__ void gj_tile_product(GjTileSmem& sm, Mfma<double>::ac
 // tile I, one 64-column half h at a time (tile Kh = K0 + h): I >= Kh holds
 // S_I,Kh; above Kh, S_I,Kh = S_Kh,I^T is read from tile row Kh.  work holds
 // C, C^T and E per matrix.
-__global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict__ mats, int n, int kb,
+__global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict__ mats, int n, int kb, int w, int lo,
                                                        double* __restrict__ work) {
   __shared__ double Ts[64][65];   // [row of the tile][column of the half]
-  const int I0 = blockIdx.x * 64, I = blockIdx.x;
+  const int I = lo + blockIdx.x, I0 = I * 64;
   const double* A = mats + (size_t)blockIdx.y * n * n;
   double* C = work + (size_t)blockIdx.y * 3 * n * GJ_NB;
   double* Ct = C + (size_t)n * GJ_NB;
-  const int w = n - kb < GJ_NB ? n - kb : GJ_NB;
   const int tid = threadIdx.x;
   for (int h = 0; h < 2; ++h) {
     const int kbh = kb + 64 * h, Kh = kbh / 64;
@@ -322,11 +337,12 @@ __global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict_
   }
 }
 
-// E_I (columns 64 h .. 64 h + 63) = C_I D^{-1} for one 64-row tile I outside K
-__global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ dinv_all, int n, int kb,
+// E_I (columns 64 h .. 64 h + 63) = C_I D^{-1} for one 64-row tile I = lo +
+// blockIdx.x outside K (tiles K0 .. Ke - 1)
+__global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ dinv_all, int n, int kb, int Ke, int lo,
                                                   double* __restrict__ work) {
-  const int I0 = blockIdx.x * 64, I = blockIdx.x, K0 = kb / 64, h = blockIdx.z;
-  if (I == K0 || I == K0 + 1) return;   // E_K is not used
+  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, h = blockIdx.z;
+  if (I >= K0 && I < Ke) return;   // E_K is not used
   __shared__ GjTileSmem sm;
   const double* C = work + (size_t)blockIdx.y * 3 * n * GJ_NB;
   double* E = work + (size_t)blockIdx.y * 3 * n * GJ_NB + (size_t)2 * n * GJ_NB;
@@ -347,20 +363,21 @@ __global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ din
       }
 }
 
-// S_IJ <- S_IJ - E_I C_J^T over the kept tiles I >= J outside K (tiles K0
-// and K0 + 1); work-group p takes the p-th tile of the lower triangle in
-// row order.  Eight waves per tile, each a 32 x 16 block (two 16 x 16 MFMA
-// tiles), so four waves share each SIMD and hide one another's waits; the
-// reduction runs in chunks of 32 through LDS, the next chunk's values
-// loading into registers during the current chunk's MFMA steps.
-__global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, int n, int kb,
+// S_IJ <- S_IJ - E_I C_J^T over the kept tiles I >= J >= lo outside K (tiles K0
+// .. Ke - 1); work-group p takes the (p0 + p)-th tile of the lower triangle in
+// row order (p0 > 0: the rows below K only).  Eight waves per tile, each a 32 x
+// 16 block (two 16 x 16 MFMA tiles), so four waves share each SIMD and hide one
+// another's waits; the reduction runs in chunks of 32 through LDS, the next
+// chunk's values loading into registers during the current chunk's MFMA steps.
+__global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, int n, int kb, int Ke, int lo, int p0,
                                                    const double* __restrict__ work) {
-  const int p = blockIdx.x;
+  const int p = p0 + blockIdx.x;
   int I = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
   while (I * (I + 1) / 2 > p) --I;
   while ((I + 1) * (I + 2) / 2 <= p) ++I;
-  const int J = p - I * (I + 1) / 2, K0 = kb / 64;
-  if (I == K0 || I == K0 + 1 || J == K0 || J == K0 + 1) return;
+  const int J = lo + p - I * (I + 1) / 2, K0 = kb / 64;
+  I += lo;
+  if ((I >= K0 && I < Ke) || (J >= K0 && J < Ke)) return;
   __shared__ GjTileSmem sm;
   const int I0 = I * 64, J0 = J * 64;
   double* A = mats + (size_t)blockIdx.y * n * n;
@@ -423,20 +440,19 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
     }
 }
 
-// Row and column K of the swept matrix, one 64-row tile I per work-group:
-// the kept tiles of S_KK (K0,K0), (K1,K0), (K1,K1) <- -D^{-1}; below K,
-// S_I,Kh <- E_I's half h; above K, S_Kh,I <- that half transposed.
-__global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mats, int n, int kb,
+// Row and column K of the swept matrix, one 64-row tile I = lo + blockIdx.x per
+// work-group: the kept tiles of S_KK <- -D^{-1}; below K, S_I,Kh <- E_I's half
+// h; above K, S_Kh,I <- that half transposed.
+__global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mats, int n, int kb, int w, int lo,
                                                         const double* __restrict__ work,
                                                         const double* __restrict__ dinv_all) {
   __shared__ double Ts[64][65];
-  const int I0 = blockIdx.x * 64, K0 = kb / 64, I = blockIdx.x;
+  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
   double* A = mats + (size_t)blockIdx.y * n * n;
   const double* E = work + (size_t)blockIdx.y * 3 * n * GJ_NB + (size_t)2 * n * GJ_NB;
   const double* Di = dinv_all + (size_t)blockIdx.y * GJ_NB * GJ_NB;
-  const int w = n - kb < GJ_NB ? n - kb : GJ_NB;
   const int tid = threadIdx.x;
-  if (I == K0 || I == K0 + 1) {
+  if (I >= K0 && I < Ke) {
     // row tile I of D's kept lower part: columns 0 .. 64 (I - K0) + 63
     const int r0 = 64 * (I - K0);
     for (int h = 0; h <= I - K0; ++h) {
@@ -449,7 +465,7 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
     }
     return;
   }
-  if (I > K0 + 1) {    // S_IK <- E_I
+  if (I >= Ke) {    // S_IK <- E_I
 #pragma unroll 4
     for (int q = 0; q < 32; ++q) {
       const int t = tid + 256 * q, a = t >> 7, k = t & 127, i = I0 + a;
@@ -476,32 +492,109 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
   }
 }
 
-void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s) {
-  if (!count) return;
-  const int tiles = (n + 63) / 64;
-  const int pairs = tiles * (tiles + 1) / 2;
-  for (int kb = 0; kb < n; kb += GJ_NB) {
-    IBMG_KLAUNCH(k_gj_diag, dim3(count), dim3(1024), 0, s, mats, n, kb, dinv);
+// One step of the sweeps: block [kb, kb + w) (w <= 128, kb a multiple of 64, w
+// too unless the block ends the matrix) within the tiles from lo on; partial:
+// the rows below the block only.
+static void sweep_step(double* mats, int n, int kb, int w, int lo, bool partial, int count, double* work, double* dinv,
+                       hipStream_t s) {
+  const int T = (n + 63) / 64, Ke = (kb + w + 63) / 64;
+  IBMG_KLAUNCH(k_gj_diag, dim3(count), dim3(1024), 0, s, mats, n, kb, w, dinv);
+  IBMG_LAUNCH_CHECK();
+  IBMG_KLAUNCH(k_sw_panel_read, dim3(T - lo, count), dim3(256), 0, s, mats, n, kb, w, lo, work);
+  IBMG_LAUNCH_CHECK();
+  const int r0 = partial ? Ke : lo;   // first row tile of the scaling and of the panel
+  if (T - r0 > 0) {
+    IBMG_KLAUNCH(k_sw_scale, dim3(T - r0, count, 2), dim3(256), 0, s, dinv, n, kb, Ke, r0, work);
     IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_panel_read, dim3(tiles, count), dim3(256), 0, s, mats, n, kb, work);
+    const int t = T - lo, p0 = partial ? (Ke - lo) * (Ke - lo + 1) / 2 : 0;
+    IBMG_KLAUNCH(k_sw_update, dim3(t * (t + 1) / 2 - p0, count), dim3(512), 0, s, mats, n, kb, Ke, lo, p0, work);
     IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_scale, dim3(tiles, count, 2), dim3(256), 0, s, dinv, n, kb, work);
-    IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_update, dim3(pairs, count), dim3(512), 0, s, mats, n, kb, work);
-    IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_panel_write, dim3(tiles, count), dim3(256), 0, s, mats, n, kb, work, dinv);
+    IBMG_KLAUNCH(k_sw_panel_write, dim3(T - r0, count), dim3(256), 0, s, mats, n, kb, w, r0, work, dinv);
     IBMG_LAUNCH_CHECK();
   }
 }
 
-__device__ __forceinline__ int own_local(int r, const BoxGeom& g) {
-  const int bb = g.b * g.b;
-  const int comp = r / bb, q = r % bb;
-  const int oi = q % g.b + g.o, oj = q / g.b + g.o;
-  const int m = g.m;
-  if (comp == 0) return oj * (m + 1) + oi;
-  if (comp == 1) return m * (m + 1) + oj * m + oi;
-  return 2 * m * (m + 1) + oj * m + oi;
+void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s) {
+  if (!count) return;
+  for (int kb = 0; kb < n; kb += GJ_NB) sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, dinv, s);
+}
+
+void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s) {
+  if (!count) return;
+  if (bm.nnp % 64) throw Error(IBMG_ERR_ARG, "the owned unknowns start at a tile");
+  for (int kb = 0; kb < bm.nnp; kb += GJ_NB)
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, dinv, s);
+  for (int kb = bm.nnp; kb < bm.ld; kb += GJ_NB)
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.ld - kb), bm.nnp / 64, false, count, work, dinv, s);
+}
+
+// The inverse's owned rows at the non-owned columns, M_on = S_oo^{-1} (-W), for
+// the boxes that keep whole rows: after the elimination the kept tiles of o hold
+// -S_oo^{-1} and the rows o hold W, so M_on is their product.  One 64 x 64 tile
+// per work-group (four waves of 2 x 2 MFMA tiles, the reduction through LDS 32
+// indices at a time); the result goes, transposed, to the unused block right of
+// n: M_on[r][j] at (j, nnp + r).
+__global__ void __launch_bounds__(256) k_box_on(double* __restrict__ mats, BoxMat bm) {
+  __shared__ GjTileSmem sm;
+  double* A = mats + (size_t)blockIdx.z * bm.ld * bm.ld;
+  const int nown = bm.ld - bm.nnp, R0 = blockIdx.x * 64, J0 = blockIdx.y * 64, ld = bm.ld;
+  const double* O = A + (size_t)bm.nnp * ld + bm.nnp;   // the owned block
+  const double* W = A + (size_t)bm.nnp * ld;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;
+  Mfma<double>::acc_t acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = Mfma<double>::acc_t{0, 0, 0, 0};
+  for (int k0 = 0; k0 < nown; k0 += 32) {
+    const bool below = (k0 >> 6) <= (R0 >> 6);   // the tile (R0, k0) is a kept one
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int t = tid + 256 * q;
+      const int ra = below ? t >> 5 : t & 63, ka = below ? t & 31 : t >> 6;
+      const int r = R0 + ra, k = k0 + ka;
+      sm.Xs[ka][ra] = r < nown && k < nown ? (below ? O[(size_t)r * ld + k] : O[(size_t)k * ld + r]) : 0.0;
+      const int kb = k0 + (t >> 6), j = J0 + (t & 63);
+      sm.Ys[t >> 6][t & 63] = kb < nown && j < bm.nn ? W[(size_t)kb * ld + j] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const int kk = 4 * st + kq;
+      const double a0 = sm.Xs[kk][32 * wr + ln], a1 = sm.Xs[kk][32 * wr + 16 + ln];
+      const double b0 = sm.Ys[kk][32 * wc + ln], b1 = sm.Ys[kk][32 * wc + 16 + ln];
+      acc[0][0] = Mfma<double>::mma(a0, b0, acc[0][0]);
+      acc[0][1] = Mfma<double>::mma(a0, b1, acc[0][1]);
+      acc[1][0] = Mfma<double>::mma(a1, b0, acc[1][0]);
+      acc[1][1] = Mfma<double>::mma(a1, b1, acc[1][1]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int r = R0 + 32 * wr + 16 * a + Mfma<double>::row(kq, v), j = J0 + 32 * wc + 16 * b + ln;
+        if (r < nown && j < bm.nn) A[(size_t)j * ld + bm.nnp + r] = acc[a][b][v];
+      }
+}
+
+void launch_box_on(double* mats, BoxMat bm, int count, hipStream_t s) {
+  if (!count) return;
+  const int nown = bm.ld - bm.nnp;
+  IBMG_KLAUNCH(k_box_on, dim3((nown + 63) / 64, (bm.nn + 63) / 64, count), dim3(256), 0, s, mats, bm);
+  IBMG_LAUNCH_CHECK();
+}
+
+// entry (owned row r, local unknown at position q) of an eliminated box's
+// inverse (launch_box_on for q < nnp)
+__device__ __forceinline__ double box_inv_at(const double* A, const BoxMat& bm, int r, int q) {
+  if (q < bm.nnp) return A[(size_t)q * bm.ld + bm.nnp + r];
+  const int i = bm.nnp + r;
+  return -((i >> 6) >= (q >> 6) ? A[(size_t)i * bm.ld + q] : A[(size_t)q * bm.ld + i]);
 }
 
 // global index of local unknown k of box pid (periodic wrap)
@@ -537,13 +630,14 @@ __device__ __forceinline__ size_t own_glob(const BoxGeom& g, int pid, int r) {
   return (size_t)comp * g.N * g.N + (size_t)gj * g.N + gi;
 }
 
-// Owned rows of A^{-1}, stored per box as row chunks of 64: element (row, j)
+// Rows of A^{-1}, stored per box as row chunks of 64: element (row, j)
 // at (row / 64) * nloc * 64 + j * 64 + row % 64 (rows beyond nown are 0), so
 // a chunk's 64 rows of one column are contiguous and a chunk is one
-// contiguous stream of nloc * 64 values.
+// contiguous stream of nloc * 64 values.  pos = null: every row of a swept
+// matrix (the summed combination); else the owned rows of an eliminated one.
 template <typename T>
-__global__ void k_extract_owned(const double* __restrict__ mats, int count, BoxGeom g,
-                                T* __restrict__ out, bool full) {
+__global__ void k_extract_rows(const double* __restrict__ mats, int count, BoxGeom g, BoxMat bm,
+                               const int* __restrict__ pos, T* __restrict__ out) {
   const size_t per = (size_t)g.nch * g.nloc * 64;
   const size_t tot = per * count;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
@@ -553,81 +647,96 @@ __global__ void k_extract_owned(const double* __restrict__ mats, int count, BoxG
     rem %= (size_t)g.nloc * 64;
     const int j = (int)(rem / 64), rr = (int)(rem % 64);
     const int row = c * 64 + rr;
-    const double* A = mats + blk * g.nloc * g.nloc;
-    // the swept matrix holds -A^{-1} in the tiles on or below the diagonal
+    const double* A = mats + blk * bm.ld * bm.ld;
     T v = 0;
     if (row < g.nown) {
-      const int lr = full ? row : own_local(row, g);
-      v = (T)(-((lr >> 6) >= (j >> 6) ? A[(size_t)lr * g.nloc + j] : A[(size_t)j * g.nloc + lr]));
+      if (pos) v = (T)box_inv_at(A, bm, row, pos[j]);
+      else v = (T)(-((row >> 6) >= (j >> 6) ? A[(size_t)row * bm.ld + j] : A[(size_t)j * bm.ld + row]));
     }
     out[t] = v;
   }
 }
 
 template <typename T>
-void launch_extract_owned(const double* mats, int count, BoxGeom g, T* out, hipStream_t s, bool full) {
+void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, const int* pos, T* out, hipStream_t s) {
   if (!count) return;
   size_t tot = (size_t)g.nch * g.nloc * 64 * count;
   int grid = cdiv(tot, 256);
   if (grid > 16384) grid = 16384;
-  IBMG_KLAUNCH((k_extract_owned<T>), dim3(grid), dim3(256), 0, s, mats, count, g, out, full);
+  IBMG_KLAUNCH((k_extract_rows<T>), dim3(grid), dim3(256), 0, s, mats, count, g, bm, pos, out);
   IBMG_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------------------
-// Symmetric storage of the IB boxes' owned rows.  The owned-by-owned block
-// of L_k^{-1} is a principal submatrix of a symmetric inverse (L_IB is
-// symmetric), so only its tiles on and below the diagonal are kept: chunk c
-// (owned rows 64c .. 64c+63) holds ncol_c = 64 (c + 1) + (nloc - nown)
-// columns of 64 rows, in the permuted local order perm (the owned unknowns
-// first, in owned order, then the non-owned ones in increasing local index):
-// column q < 64 (c + 1) is owned column q, column q >= 64 (c + 1) is
-// non-owned column nown + q - 64 (c + 1) of that order.  The owned columns
-// of later tiles are the transposes of those tiles' entries: the chunks
-// holding them add them as column sums (the apply kernel below).  At
-// 16 x 16/4 boxes this streams 8.75 MB per box instead of 10.9 MB.
+// Eliminated storage of the IB boxes.  Instead of the owned rows of L_k^{-1} a
+// box keeps the two factors the elimination leaves (above):
+//   W rows: the owned rows coupled to a non-owned unknown (by the stencil along
+//           the box's edge or by the IB rows), nn columns each, row-major with
+//           a row stride of nn rounded up to even;
+//   Q:      S_oo^{-1}, symmetric: chunk c (owned rows 64c .. 64c+63) holds the
+//           columns 0 .. 64 (c + 1) - 1 of 64 rows each (the tiles on and below
+//           the diagonal; zero beyond nown); the others are the transposes of
+//           stored entries.
+// z_o = Q (r_o - W r_n): two passes instead of one product, but at 16 x 16/4
+// with 268 coupled rows of 768 (the mean of the 512^2 annulus's 172 boxes) 4.7
+// MB instead of 8.75 MB (symmetric owned block, whole non-owned columns) or
+// 10.9 MB (whole rows).
 // ---------------------------------------------------------------------------
-__host__ __device__ inline size_t sym_chunk_off(const BoxGeom& g, int c) {
-  const size_t ne = (size_t)(g.nloc - g.nown);
-  return 64 * (64 * (size_t)c * (size_t)(c + 1) / 2 + (size_t)c * ne);
-}
-__host__ __device__ inline size_t sym_stride(const BoxGeom& g) { return sym_chunk_off(g, g.nch); }
-size_t sym_box_stride(const BoxGeom& g) { return sym_stride(g); }
+__host__ __device__ inline size_t sym_chunk_off(int c) { return (size_t)4096 * ((size_t)c * (c + 1) / 2); }
+size_t sym_box_stride(const BoxGeom& g) { return sym_chunk_off(g.nch); }
 // partials per box, the chunks' columns cut into ks slices: chunk c's 64
 // row sums of each slice, then its 64 c column sums
 __host__ __device__ inline int sym_part_off(int c, int ks) { return 64 * ks * c + 32 * c * (c - 1); }
-int sym_part_len(const BoxGeom& g, int n_ib) { return sym_part_off(g.nch, ras_ib_ksplit(g, n_ib)); }
+// Column slices: enough work-groups to cover the device twice while a slice
+// keeps at least two tiles of the longest chunk.
+static int sym_ksplit(const BoxGeom& g, int n_ib) {
+  int ks = 1;
+  while (ks < 4 && n_ib * g.nch * ks < 512 && g.nch / (2 * ks) >= 2) ks *= 2;
+  return ks;
+}
+int sym_part_len(const BoxGeom& g) { return sym_part_off(g.nch, 4); }
 
 template <typename T>
-__global__ void k_extract_sym(const double* __restrict__ mats, int count, BoxGeom g, const int* __restrict__ perm,
-                              T* __restrict__ out) {
-  const size_t per = sym_stride(g);
+__global__ void k_extract_sym(const double* __restrict__ mats, int count, BoxGeom g, BoxMat bm, T* __restrict__ out) {
+  const size_t per = sym_chunk_off(g.nch);
   const size_t tot = per * count;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
     const size_t blk = t / per;
     size_t rem = t % per;
     int c = 0;
-    while (c + 1 < g.nch && sym_chunk_off(g, c + 1) <= rem) ++c;
-    rem -= sym_chunk_off(g, c);
-    const int q = (int)(rem / 64), rr = (int)(rem % 64);
-    const int row = c * 64 + rr;   // owned row (nown is a multiple of 64 here)
-    const int nq = 64 * (c + 1);
-    const int j = perm[q < nq ? q : g.nown + (q - nq)];
-    const int lr = own_local(row, g);
-    const double* A = mats + blk * g.nloc * g.nloc;
-    // the swept matrix holds -A^{-1} in the tiles on or below the diagonal
-    out[t] = (T)(-((lr >> 6) >= (j >> 6) ? A[(size_t)lr * g.nloc + j] : A[(size_t)j * g.nloc + lr]));
+    while (c + 1 < g.nch && sym_chunk_off(c + 1) <= rem) ++c;
+    rem -= sym_chunk_off(c);
+    const int q = (int)(rem / 64), row = c * 64 + (int)(rem % 64);
+    out[t] = row < g.nown && q < g.nown ? (T)box_inv_at(mats + blk * bm.ld * bm.ld, bm, row, bm.nnp + q) : T(0);
   }
 }
 
 template <typename T>
-void launch_extract_sym(const double* mats, int count, BoxGeom g, const int* perm, T* out, hipStream_t s) {
+void launch_extract_sym(const double* mats, int count, BoxGeom g, BoxMat bm, T* out, hipStream_t s) {
   if (!count) return;
-  if (g.nown % 64) throw Error(IBMG_ERR_ARG, "symmetric storage needs whole 64-row chunks");
-  const size_t tot = sym_stride(g) * count;
+  const size_t tot = sym_box_stride(g) * count;
   int grid = cdiv(tot, 256);
   if (grid > 16384) grid = 16384;
-  IBMG_KLAUNCH((k_extract_sym<T>), dim3(grid), dim3(256), 0, s, mats, count, g, perm, out);
+  IBMG_KLAUNCH((k_extract_sym<T>), dim3(grid), dim3(256), 0, s, mats, count, g, bm, out);
+  IBMG_LAUNCH_CHECK();
+}
+
+// the W rows of count boxes: rows wptr[i] .. wptr[i+1] of box i, owned row wrow
+template <typename T>
+__global__ void k_extract_w(const double* __restrict__ mats, BoxMat bm, const int* __restrict__ wptr,
+                            const int* __restrict__ wrow, int ws, T* __restrict__ out) {
+  const double* A = mats + (size_t)blockIdx.y * bm.ld * bm.ld;
+  for (int e = wptr[blockIdx.y] + blockIdx.x; e < wptr[blockIdx.y + 1]; e += gridDim.x) {
+    const double* Ar = A + (size_t)(bm.nnp + wrow[e]) * bm.ld;
+    for (int j = threadIdx.x; j < ws; j += blockDim.x) out[(size_t)e * ws + j] = j < bm.nn ? (T)Ar[j] : T(0);
+  }
+}
+
+template <typename T>
+void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr, const int* wrow, int ws, T* out,
+                      hipStream_t s) {
+  if (!count) return;
+  IBMG_KLAUNCH((k_extract_w<T>), dim3(32, count), dim3(256), 0, s, mats, bm, wptr, wrow, ws, out);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -760,21 +869,92 @@ __global__ void __launch_bounds__(256) k_ras_ib(const T* __restrict__ r, T* __re
                         blockIdx.y, x, part, acc, cb < ce ? cb : ce, ce, pout);
 }
 
-// IB boxes from the symmetric storage: work-group = (box, 64-row chunk c,
-// column slice).  R_k r is gathered into LDS in the permuted local order.
-// The chunk's stored columns are cut into gridDim.z slices of whole
-// 64-column tiles; a slice's columns stream in batches of UNR x VEC
-// (16-byte loads, eight in flight per lane), batches dealt to the four
-// waves in turn.  Every column adds
-// its entries times x_q to the rows (lane sums, as in k_ras_ib); a column
-// of an earlier owned tile (q < 64 c) also forms its transposed product,
-// the sum over the chunk's rows of M[row][q] x_row, reduced over the lanes
-// of its column phase, which belongs to owned row q of an earlier chunk.
-// The box's partials: the chunk's row sums per slice at sym_part_off(c,
-// ks), its column sums after them (each column in one slice).
+// First pass of the eliminated boxes: y = r_o - W r_n (owned order, y[box slot *
+// nown + row]).  Work-group = (box, RPG of its W rows): each lane keeps its
+// share of the box's non-owned residual in registers (CH pairs of columns) and
+// every wave streams its rows, two at a time, 16 bytes a lane and load, summing
+// a row over the wave by DPP.  The rows that couple to nothing outside take
+// y = r_o; the box's first work-group writes them.  Bound by HBM.  With the
+// second pass and the sum, the 172 boxes of the 512^2 annulus (16 x 16/4, 810
+// MB) take 153 us in FP64 and 81 us in FP32; the one-pass product of the owned
+// rows with symmetric owned tiles took 226 and 116 us (1.5 GB).
+template <typename T, int CH>
+__global__ void __launch_bounds__(256) k_ras_w(const T* __restrict__ r, BoxGeom g, const int* __restrict__ boxes,
+                                               WBoxView w, int rpg, T* __restrict__ y) {
+  using V = typename Vec16<T>::type;
+  constexpr int VEC = Vec16<T>::n;
+  const int slot = blockIdx.x, pid = boxes[slot], tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int e0 = w.wptr[slot], e1 = w.wptr[slot + 1];
+  const T* Wm = static_cast<const T*>(w.W);
+  T* yb = y + (size_t)slot * g.nown;
+  if (blockIdx.y == 0)
+    for (int k = tid; k < g.nown; k += 256)
+      if (!w.coupled[(size_t)slot * g.nown + k]) yb[k] = r[own_glob(g, pid, k)];
+  const int lo = e0 + blockIdx.y * rpg, hi = lo + rpg < e1 ? lo + rpg : e1;
+  if (lo >= hi) return;
+  extern __shared__ char smem_raw[];
+  T* xs = reinterpret_cast<T*>(smem_raw);
+  // the wave's first rows are issued before the residual gather
+  auto load = [&](V (&m)[CH], int e) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int j = (c * 64 + lane) * VEC;
+      if (j < w.ws) m[c] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Wm + (size_t)e * w.ws + j));
+      else m[c] = V{};
+    }
+  };
+  V m0[CH], m1[CH];
+  int e = lo + 2 * wave;
+  if (e < hi) load(m0, e);
+  if (e + 1 < hi) load(m1, e + 1);
+  for (int k = tid; k < w.ws; k += 256) xs[k] = k < w.nn ? r[box_glob(g, pid, w.nloc[k])] : T(0);
+  __syncthreads();
+  T x[CH * VEC];
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      const int j = (c * 64 + lane) * VEC + v;
+      x[c * VEC + v] = j < w.ws ? xs[j] : T(0);
+    }
+  auto row = [&](const V (&m)[CH], int q) {
+    T a = 0;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) a += m[c][v] * x[c * VEC + v];
+    a = wave_sum(a);
+    if (lane == 0) {
+      const int k = w.wrow[q];
+      yb[k] = r[own_glob(g, pid, k)] - a;
+    }
+  };
+  for (; e < hi; e += 8) {
+    V n0[CH], n1[CH];
+    if (e + 8 < hi) load(n0, e + 8);
+    if (e + 9 < hi) load(n1, e + 9);
+    row(m0, e);
+    if (e + 1 < hi) row(m1, e + 1);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      m0[c] = n0[c];
+      m1[c] = n1[c];
+    }
+  }
+}
+
+// Second pass, z_o = Q y: work-group = (box, 64-row chunk c, column slice),
+// longest chunks first.  The chunk's stored columns are cut into gridDim.z
+// slices of whole 64-column tiles; a slice's columns stream in batches of UNR x
+// VEC (16-byte loads, eight in flight per lane), batches dealt to the four waves
+// in turn.  Every column adds its entries times y_q to the rows (lane sums); a
+// column of an earlier tile (q < 64 c) also forms its transposed product, the
+// sum over the chunk's rows of Q[row][q] y_row, reduced over the lanes of its
+// column phase, which belongs to row q of an earlier chunk.  The box's partials:
+// the chunk's row sums per slice at sym_part_off(c, ks), its column sums after
+// them (each column in one slice).
 template <typename T>
-__global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, BoxGeom g, const T* __restrict__ inv,
-                                                    const int* __restrict__ boxes, const int* __restrict__ perm,
+__global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ y, BoxGeom g, const T* __restrict__ inv,
                                                     T* __restrict__ part) {
   using V = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
@@ -782,37 +962,43 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, Box
   constexpr int UNR = 8, B = UNR * VEC;
   extern __shared__ char smem_raw[];
   T* xs = reinterpret_cast<T*>(smem_raw);
-  T* red = xs + ((g.nloc + 3) & ~3);   // 4 waves x 64 row sums
-  T* tcol = red + 256;                 // the chunk's 64 c column sums
-  const int slot = blockIdx.x, c = blockIdx.y, sl = blockIdx.z, ks = gridDim.z, pid = boxes[slot];
+  T* red = xs + 64 * g.nch;       // 4 waves x 64 row sums
+  T* tcol = red + 256;            // the chunk's 64 c column sums
+  const int slot = blockIdx.x, c = g.nch - 1 - blockIdx.y, sl = blockIdx.z, ks = gridDim.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cph = lane / LPC, rl = (lane % LPC) * VEC;
-  const int nq = 64 * (c + 1), ntr = 64 * c, ncol = nq + (g.nloc - g.nown);
+  const int ntr = 64 * c, ncol = 64 * (c + 1);
   const int cs = ((ncol + ks - 1) / ks + 63) / 64 * 64;
   const int cb = sl * cs < ncol ? sl * cs : ncol, ce = cb + cs < ncol ? cb + cs : ncol;
-  const T* Mc = inv + (size_t)slot * sym_stride(g) + sym_chunk_off(g, c) + rl;
-  // the wave's first batch of the inverse is issued before the residual
-  // gather, so its trip from memory overlaps the gather
+  T* pb = part + (size_t)slot * sym_part_off(g.nch, ks) + sym_part_off(c, ks);
+  if (cb >= ce) {   // a short chunk's empty slice
+    if (tid < 64) pb[64 * sl + tid] = T(0);
+    return;
+  }
+  const T* Mc = inv + (size_t)slot * sym_chunk_off(g.nch) + sym_chunk_off(c) + rl;
+  // the wave's first batch is issued before the residual, so its trip from
+  // memory overlaps that one (columns come in whole batches: ce - cb is a
+  // multiple of 64)
   const int jb0 = cb + wave * B;
-  const bool pre = jb0 + B <= ce;
   V m0[UNR];
-  if (pre)
+  auto load = [&](V (&m)[UNR], int jb) {
 #pragma unroll
     for (int u = 0; u < UNR; ++u)
-      m0[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jb0 + cph + u * VEC) * 64));
-  for (int k = tid; k < g.nloc; k += 256) xs[k] = r[box_glob(g, pid, perm[k])];
+      m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jb + cph + u * VEC) * 64));
+  };
+  if (jb0 < ce) load(m0, jb0);
+  for (int k = tid; k < ncol; k += 256) xs[k] = k < g.nown ? y[(size_t)slot * g.nown + k] : T(0);
   __syncthreads();
-  T xr[VEC];   // this lane's rows' residual values (owned rows 64 c + rl + v)
+  T xr[VEC];   // this lane's rows' values (owned rows 64 c + rl + v)
 #pragma unroll
   for (int v = 0; v < VEC; ++v) xr[v] = xs[64 * c + rl + v];
   T acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0;
-  auto xcol = [&](int q) { return xs[q < nq ? q : g.nown + (q - nq)]; };
   // one column's contribution; tr: the column also needs its transposed sum
   auto column = [&](const V& m, int q, bool tr) {
     const T* a = reinterpret_cast<const T*>(&m);
-    const T x = xcol(q);
+    const T x = xs[q];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] += a[v] * x;
     if (tr) {
@@ -825,30 +1011,14 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, Box
       if (lane % LPC == 0) tcol[q] = p;
     }
   };
-  int jstart = jb0;
-  if (pre) {
-    const bool tr = jb0 + B <= ntr;
+  for (int jb = jb0; jb < ce; jb += 4 * B) {
+    V m[UNR];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) column(m0[u], jb0 + cph + u * VEC, tr);
-    jstart += 4 * B;
-  }
-  for (int jb = jstart; jb < ce; jb += 4 * B) {
-    if (jb + B <= ce) {
-      V m[UNR];
+    for (int u = 0; u < UNR; ++u) m[u] = m0[u];
+    if (jb + 4 * B < ce) load(m0, jb + 4 * B);
+    const bool tr = jb < ntr;   // batches never straddle ntr (multiples of 64)
 #pragma unroll
-      for (int u = 0; u < UNR; ++u)
-        m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jb + cph + u * VEC) * 64));
-      const bool tr = jb + B <= ntr;   // batches never straddle ntr (slices start at multiples of 64)
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) column(m[u], jb + cph + u * VEC, tr);
-    } else {
-      for (int u = 0; u < UNR; ++u) {
-        const int q = jb + cph + u * VEC;
-        if (q >= ce) break;
-        const V m0 = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)q * 64));
-        column(m0, q, false);   // a partial batch only ends the last slice, in the non-owned columns
-      }
-    }
+    for (int u = 0; u < UNR; ++u) column(m[u], jb + cph + u * VEC, tr);
   }
   // sum the VEC column phases, then the four waves
 #pragma unroll
@@ -859,7 +1029,6 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, Box
 #pragma unroll
     for (int v = 0; v < VEC; ++v) red[wave * 64 + rl + v] = acc[v];
   __syncthreads();
-  T* pb = part + (size_t)slot * sym_part_off(g.nch, ks) + sym_part_off(c, ks);
   if (tid < 64) pb[64 * sl + tid] = (red[tid] + red[64 + tid]) + (red[128 + tid] + red[192 + tid]);
   for (int q = cb + tid; q < (ce < ntr ? ce : ntr); q += 256) pb[64 * ks + q] = tcol[q];
 }
@@ -1069,11 +1238,11 @@ __global__ void __launch_bounds__(256 * KS) k_ras_int(const T* __restrict__ r, T
   }
 }
 
-// The class matrices of the swept interior box matrix (-A^{-1} in the tiles on
-// or below the diagonal); kl: the four images' local indices of every orbit,
-// rl: the local index of every row representative.
+// The class matrices of the eliminated interior box (launch_box_on done); kl:
+// the four images' positions of every orbit, rl: the owned row of every row
+// representative.
 template <typename T>
-__global__ void k_extract_classes(const double* __restrict__ mat, int nloc, IntClassView C, const int* __restrict__ kl,
+__global__ void k_extract_classes(const double* __restrict__ mat, BoxMat bm, IntClassView C, const int* __restrict__ kl,
                                   const int* __restrict__ rl, T* __restrict__ out) {
   const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
@@ -1085,9 +1254,7 @@ __global__ void k_extract_classes(const double* __restrict__ mat, int nloc, IntC
     if (row < C.R && k < C.K) {
       const int lr = rl[row], comp = C.kcode[k] >> 24;
       const int e = kl[4 * k], x = kl[4 * k + 1], y = kl[4 * k + 2], xy = kl[4 * k + 3];
-      auto at = [&](int j) {
-        return -((lr >> 6) >= (j >> 6) ? mat[(size_t)lr * nloc + j] : mat[(size_t)j * nloc + lr]);
-      };
+      auto at = [&](int j) { return box_inv_at(mat, bm, lr, j); };
       const double cx = (comp == 0 ? -1.0 : 1.0) * (cls & 1 ? -1.0 : 1.0), cy = (comp == 1 ? -1.0 : 1.0) * (cls & 2 ? -1.0 : 1.0);
       v = at(e);
       if (x != e) v += cx * at(x);
@@ -1100,16 +1267,16 @@ __global__ void k_extract_classes(const double* __restrict__ mat, int nloc, IntC
 }
 
 template <typename T>
-void launch_extract_classes(const double* mat, int nloc, IntClassView C, const int* kl, const int* rl, T* out,
+void launch_extract_classes(const double* mat, BoxMat bm, IntClassView C, const int* kl, const int* rl, T* out,
                             hipStream_t s) {
   const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
   int grid = cdiv(tot, 256);
   if (grid > 4096) grid = 4096;
-  IBMG_KLAUNCH((k_extract_classes<T>), dim3(grid), dim3(256), 0, s, mat, nloc, C, kl, rl, out);
+  IBMG_KLAUNCH((k_extract_classes<T>), dim3(grid), dim3(256), 0, s, mat, bm, C, kl, rl, out);
   IBMG_LAUNCH_CHECK();
 }
-template void launch_extract_classes<double>(const double*, int, IntClassView, const int*, const int*, double*, hipStream_t);
-template void launch_extract_classes<float>(const double*, int, IntClassView, const int*, const int*, float*, hipStream_t);
+template void launch_extract_classes<double>(const double*, BoxMat, IntClassView, const int*, const int*, double*, hipStream_t);
+template void launch_extract_classes<float>(const double*, BoxMat, IntClassView, const int*, const int*, float*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Interior tiles of the batched sweep (below): Z[64-row chunk, boxes] = M[chunk,
@@ -1452,13 +1619,25 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
   const bool do_ib = (parts & 1) && n_ib > 0, do_int = (parts & 2) && n_int > 0;
   const bool use_sym = do_ib && sym != nullptr;
   const int ks_ib = do_ib && !use_sym ? ras_ib_ksplit(g, n_ib) : 1;
-  const int ks_sym = use_sym ? ras_ib_ksplit(g, n_ib) : 1;
+  const int ks_sym = use_sym ? sym_ksplit(g, n_ib) : 1;
   T* spart = use_sym ? static_cast<T*>(sym->part) : nullptr;
   if (use_sym) {
-    if (g.nown % 64) throw Error(IBMG_ERR_ARG, "symmetric storage needs whole 64-row chunks");
-    const size_t lds = ((((size_t)g.nloc + 3) & ~(size_t)3) + 256 + 64 * (size_t)(g.nch - 1)) * sizeof(T);
-    IBMG_KLAUNCH((k_ras_ib_sym<T>), dim3(n_ib, g.nch, ks_sym), dim3(256), lds, s, r, g,
-                 static_cast<const T*>(sym->inv), ib_boxes, sym->perm, spart);
+    const WBoxView& w = sym->w;
+    T* y = static_cast<T*>(sym->y);
+    // rows per work-group: enough work-groups to cover the device
+    int rpg = 64;
+    while (rpg > 16 && (long long)n_ib * ((w.maxrows + rpg - 1) / rpg) < 768) rpg /= 2;
+    const dim3 grid(n_ib, std::max(1, (w.maxrows + rpg - 1) / rpg));
+    const size_t lds = (size_t)w.ws * sizeof(T);
+    const int ch = (w.ws + 64 * Vec16<T>::n - 1) / (64 * Vec16<T>::n);
+    if (ch <= 2) IBMG_KLAUNCH((k_ras_w<T, 2>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
+    else if (ch <= 4) IBMG_KLAUNCH((k_ras_w<T, 4>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
+    else if (ch <= 8) IBMG_KLAUNCH((k_ras_w<T, 8>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
+    else throw Error(IBMG_ERR_ARG, "eliminated boxes take at most 1024 non-owned unknowns");
+    IBMG_LAUNCH_CHECK();
+    const size_t lds2 = (64 * (size_t)g.nch + 256 + 64 * (size_t)(g.nch - 1)) * sizeof(T);
+    IBMG_KLAUNCH((k_ras_ib_sym<T>), dim3(n_ib, g.nch, ks_sym), dim3(256), lds2, s, y, g,
+                 static_cast<const T*>(sym->inv), spart);
     IBMG_LAUNCH_CHECK();
   } else if (do_ib) {
     const size_t lds = (((size_t)g.nloc + 3) & ~(size_t)3) * sizeof(T) + 256 * sizeof(T);
@@ -1862,8 +2041,10 @@ void launch_coarse_apply(const double* inv, int n0, const T* r, T* z, hipStream_
   launch_coarse_apply_batch<T>(inv, n0, r, z, 1, s);
 }
 
-template void launch_extract_owned<double>(const double*, int, BoxGeom, double*, hipStream_t, bool);
-template void launch_extract_owned<float>(const double*, int, BoxGeom, float*, hipStream_t, bool);
+template void launch_extract_rows<double>(const double*, int, BoxGeom, BoxMat, const int*, double*, hipStream_t);
+template void launch_extract_rows<float>(const double*, int, BoxGeom, BoxMat, const int*, float*, hipStream_t);
+template void launch_extract_w<double>(const double*, int, BoxMat, const int*, const int*, int, double*, hipStream_t);
+template void launch_extract_w<float>(const double*, int, BoxMat, const int*, const int*, int, float*, hipStream_t);
 template void launch_asm_apply<double>(const double*, double*, BoxGeom, const double*, const int*, double*,
                                        hipStream_t);
 template void launch_asm_apply<float>(const float*, float*, BoxGeom, const float*, const int*, float*, hipStream_t);
@@ -1873,8 +2054,8 @@ template void launch_ras_apply<double>(const double*, double*, BoxGeom, const do
 template void launch_ras_apply<float>(const float*, float*, BoxGeom, const float*, const int*, int,
                                       const IntClassView&, const int*, int, float*, hipStream_t, int, bool,
                                       const SymIB*);
-template void launch_extract_sym<double>(const double*, int, BoxGeom, const int*, double*, hipStream_t);
-template void launch_extract_sym<float>(const double*, int, BoxGeom, const int*, float*, hipStream_t);
+template void launch_extract_sym<double>(const double*, int, BoxGeom, BoxMat, double*, hipStream_t);
+template void launch_extract_sym<float>(const double*, int, BoxGeom, BoxMat, float*, hipStream_t);
 template void launch_coarse_apply<double>(const double*, int, const double*, double*, hipStream_t);
 template void launch_coarse_apply<float>(const double*, int, const float*, float*, hipStream_t);
 template void launch_coarse_apply_batch<double>(const double*, int, const double*, double*, int, hipStream_t);

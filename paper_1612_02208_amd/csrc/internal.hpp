@@ -514,19 +514,33 @@ constexpr int kStaticGradPoints = 1 << 18;
 double* static_grad_scratch();
 
 // dense boxes and coarsest solve
+// Layout of a box matrix, ld x ld: the restricted sweeps order the unknowns
+// non-owned first (nn, padded with ones on the diagonal to nnp, a multiple of
+// 64), then owned; the summed combination keeps the local order (nn = nnp = 0).
+struct BoxMat {
+  int ld, nn, nnp;
+};
 void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoef<double> c,
                            const int* tptr_u, const int* tcol_u, const double* tval_u,
-                           const int* tptr_v, const int* tcol_v, const double* tval_v,
+                           const int* tptr_v, const int* tcol_v, const double* tval_v, const int* pos, BoxMat bm,
                            double* mats, hipStream_t s);
 // In-place block sweeps of count symmetric n x n matrices: afterwards the
 // tiles on or below the diagonal (64 x 64, diagonal tiles in full) hold
-// -A^{-1}; launch_extract_owned reads them.  work: count x 3 x n x 64 and
-// dinv: count x 64 x 64 doubles of workspace.
+// -A^{-1}.  work: count x 3 x n x kGjNb and dinv: count x kGjNb^2 doubles of
+// workspace.
 void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s);
 constexpr int kGjNb = 128;  // block width of the batched inversion
-// full: every row of the inverse (g.nown = nloc, the summed combination)
+// The restricted boxes' elimination: afterwards the rows of the owned unknowns
+// hold W = A_on A_nn^{-1} at the non-owned columns and -S_oo^{-1} (tiles on or
+// below the diagonal) at the owned ones; launch_box_on adds the inverse's owned
+// rows at the non-owned columns.
+void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s);
+void launch_box_on(double* mats, BoxMat bm, int count, hipStream_t s);
+// rows of the inverse in 64-row chunks: the owned rows of eliminated matrices
+// (pos: the local unknowns' positions), or every row of swept ones (pos = null,
+// g.nown = nloc: the summed combination)
 template <typename T>
-void launch_extract_owned(const double* mats, int count, BoxGeom g, T* out, hipStream_t s, bool full = false);
+void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, const int* pos, T* out, hipStream_t s);
 // Summed additive Schwarz (IBMG_COMBINE_SUM): every box's whole local
 // solution L_k^{-1} R_k r into Y (box id-major, g.nch chunks of 64 rows; inv
 // holds full inverses, box_inv[box id] the inverse of each box), then every
@@ -534,21 +548,30 @@ void launch_extract_owned(const double* mats, int count, BoxGeom g, T* out, hipS
 // (boxes in a fixed order per unknown).
 template <typename T>
 void launch_asm_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* box_inv, T* Y, hipStream_t s);
-// Symmetric storage of the IB boxes' owned rows (restricted sweep): chunk c
-// keeps the owned columns of tiles 0..c and every non-owned column, in the
-// permuted local order perm (owned unknowns first, in owned order); the
-// owned columns of later tiles are added as the transposed column sums of
-// the chunks that hold them, through per-box partials.
+// Eliminated storage of the IB boxes (restricted additive sweep): box i's W rows
+// are rows wptr[i] .. wptr[i+1] of W (row stride ws), for the owned rows wrow;
+// coupled[i * nown + k] marks the owned rows that have one; nloc lists the nn
+// non-owned unknowns' local indices.
+struct WBoxView {
+  const void* W;
+  const int *wptr, *wrow, *nloc;
+  const unsigned char* coupled;
+  int nn, ws, maxrows;
+};
 struct SymIB {
-  const void* inv;   // T[n_ib * sym_box_stride(g)]
-  const int* perm;   // [nloc]
-  void* part;        // T[n_ib * sym_part_len(g, n_ib)]
+  const void* inv;   // Q: T[n_ib * sym_box_stride(g)]
+  void* part;        // T[n_ib * sym_part_len(g)]
+  WBoxView w;
+  void* y;           // T[n_ib * nown]: r_o - W r_n
 };
 size_t sym_box_stride(const BoxGeom& g);
-// partials per box (the column slices follow the IB-box kernel's split)
-int sym_part_len(const BoxGeom& g, int n_ib);
+int sym_part_len(const BoxGeom& g);
+constexpr int kElimMaxNn = 1024;   // most non-owned unknowns of an eliminated box
 template <typename T>
-void launch_extract_sym(const double* mats, int count, BoxGeom g, const int* perm, T* out, hipStream_t s);
+void launch_extract_sym(const double* mats, int count, BoxGeom g, BoxMat bm, T* out, hipStream_t s);
+template <typename T>
+void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr, const int* wrow, int ws, T* out,
+                      hipStream_t s);
 
 // The interior boxes' shared inverse in its four parity classes (k_ras_int):
 // M (T[4][nrt][Kp][16]), the orbits' representatives kcode[K] and the rows'
@@ -562,12 +585,12 @@ struct IntClassView {
 // the most orbits a box has (b + 2 o <= 32), padded to whole chunks
 constexpr int kIntMaxOrbits = 896;
 template <typename T>
-void launch_extract_classes(const double* mat, int nloc, IntClassView C, const int* kl, const int* rl, T* out,
+void launch_extract_classes(const double* mat, BoxMat bm, IntClassView C, const int* kl, const int* rl, T* out,
                             hipStream_t s);
 
 // One restricted Schwarz sweep (parts: bit 0 = IB boxes, bit 1 = interior
 // boxes); acc: add the local solutions to z on the owned sets instead of
-// storing them.  sym != null: the IB boxes run from the symmetric storage.
+// storing them.  sym != null: the IB boxes run from the eliminated storage.
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
                       const IntClassView& cls, const int* int_boxes, int n_int, T* part, hipStream_t s, int parts = 3,

@@ -34,6 +34,10 @@ constexpr int kScalY = 1;     // scal[1..16]: least-squares solution
 // us, 4.6 M (tangent springs) 36.3 against 24.2.  IBMG_NO_IB_ROWS in the
 // environment takes the other form on every level.
 constexpr size_t kIbRowsMaxEntries = 3500000;
+// The IB boxes are kept eliminated (two passes over W and the symmetric owned
+// factor) where their whole rows would take at least this much; see
+// prepare_boxes.
+constexpr size_t kElimMinBytes = (size_t)96 << 20;
 // lanes per explicit row: a wave where rows are long (crowded coarse levels)
 constexpr int kIbLongRow = 96;
 // partial-sum buffers: two of kPartStride doubles (blocks x vectors)
@@ -94,11 +98,20 @@ struct Level {
   DBuf<int> d_kcode, d_rcode, d_klocal, d_rlocal;
   DBuf<T> cls;
   IntClassView clsv{};
-  // symmetric storage of the IB boxes' owned rows (restricted additive
-  // sweep): the permuted local order, the storage, the per-box partials
+  // layout of the box matrices and the local unknowns' positions in it; the
+  // non-owned unknowns in that order
+  BoxMat bm{};
+  std::vector<int> pos, nonown;
+  DBuf<int> d_pos, d_nonown;
+  // eliminated storage of the IB boxes (restricted additive sweep): the W rows,
+  // the symmetric factor, the first pass's result and the per-box partials
   bool use_sym = false;
-  DBuf<int> d_perm;
-  DBuf<T> inv_sym, sym_part;
+  std::vector<int> wptr, wrow;
+  std::vector<unsigned char> coupled;
+  DBuf<int> d_wptr, d_wrow;
+  DBuf<unsigned char> d_coupled;
+  int w_max = 0, w_stride = 0;
+  DBuf<T> wmat, inv_sym, sym_y, sym_part;
   // restricted multiplicative Schwarz: box colours; ib_list and int_list
   // sorted by colour, colour c spanning [ib_off[c], ib_off[c+1]) and
   // [int_off[c], int_off[c+1])
@@ -248,6 +261,7 @@ class Solver final : public SolverBase {
       if (lev.inv.n) scan(lev.inv.p, lev.inv.n, ("the box inverses of level " + std::to_string(l)).c_str());
       if (lev.cls.n) scan(lev.cls.p, lev.cls.n, ("the interior box inverse of level " + std::to_string(l)).c_str());
       if (lev.inv_sym.n) scan(lev.inv_sym.p, lev.inv_sym.n, ("the IB box inverses of level " + std::to_string(l)).c_str());
+      if (lev.wmat.n) scan(lev.wmat.p, lev.wmat.n, ("the IB box factors of level " + std::to_string(l)).c_str());
       if (lev.sc)
         if (!(std::isfinite(lev.sc->lamA) && lev.sc->lamA > 0.0 && std::isfinite(lev.sc->lamM) && lev.sc->lamM > 0.0))
           throw Error(IBMG_ERR_BREAKDOWN, "Schur-complement Chebyshev bound of level " + std::to_string(l) +
@@ -553,15 +567,7 @@ class Solver final : public SolverBase {
     };
     // each worker keeps a stamp over the finest [u | v]: at most 1 GiB in all
     const size_t by_mem = std::max<size_t>(1, ((size_t)1 << 30) / (2 * nf_max * sizeof(int)));
-    const size_t hw = std::max(1u, std::thread::hardware_concurrency());
-    const size_t nth = std::min({(size_t)16, hw, by_mem, tasks.size()});
-    if (nth <= 1) {
-      worker();
-    } else {
-      std::vector<std::thread> th;
-      for (size_t t = 0; t < nth; ++t) th.emplace_back(worker);
-      for (auto& t : th) t.join();
-    }
+    run_workers(worker, std::min(by_mem, tasks.size()));
     for (int l = 0; l <= L_; ++l)
       for (int c = 0; c < 2; ++c) {
         CompFoot& f = levels_[l].f[c];
@@ -624,7 +630,102 @@ class Solver final : public SolverBase {
       lev.sum_mode = true;
       lev.g.nown = nloc;
       lev.g.nch = (nloc + 63) / 64;
+      lev.bm = BoxMat{nloc, 0, 0};
+      return;
     }
+    // matrix positions: the non-owned unknowns in local order (velocities
+    // before pressures), then the owned ones in owned order
+    lev.pos.assign(nloc, -1);
+    lev.nonown.clear();
+    const int bb = b * b, nown = lev.g.nown, nu = m * (m + 1);
+    std::vector<int> own(nown);
+    for (int r = 0; r < nown; ++r) {
+      const int comp = r / bb, oi = r % bb % b + o, oj = r % bb / b + o;
+      own[r] = comp == 0 ? oj * (m + 1) + oi : (comp == 1 ? nu + oj * m + oi : 2 * nu + oj * m + oi);
+      lev.pos[own[r]] = r;
+    }
+    for (int k = 0; k < nloc; ++k)
+      if (lev.pos[k] < 0) lev.nonown.push_back(k);
+    const int nn = (int)lev.nonown.size(), nnp = (nn + 63) / 64 * 64;
+    lev.bm = BoxMat{nnp + nown, nn, nnp};
+    for (int r = 0; r < nown; ++r) lev.pos[own[r]] = nnp + r;
+    for (int k = 0; k < nn; ++k) lev.pos[lev.nonown[k]] = k;
+  }
+
+  // The owned rows of every IB box that couple to a non-owned unknown of the
+  // box (the rows of W): rows whose stencil reaches one, and IB rows with a
+  // column on one.  The boxes are shared out over worker threads.
+  void coupled_rows(Level<T>& lev) {
+    const BoxGeom& g = lev.g;
+    const int N = g.N, NN = N * N, b = g.b, bb = b * b, nown = g.nown, m = g.m;
+    std::vector<unsigned char> edge(nown, 0);   // by the stencil
+    for (int r = 0; r < nown; ++r) {
+      const int comp = r / bb, i = r % bb % b, j = r % bb / b;
+      if (comp < 2) edge[r] = i == 0 || j == 0 || i == b - 1 || j == b - 1;
+      else edge[r] = i == b - 1 || j == b - 1;
+    }
+    if (g.o == 0)   // nothing lies beyond the low edges but the far faces do beyond the high ones
+      for (int r = 0; r < nown; ++r) {
+        const int i = r % bb % b, j = r % bb / b;
+        edge[r] = i == b - 1 || j == b - 1;
+      }
+    std::vector<short> fx(NN), fy(NN);
+    for (int q = 0; q < NN; ++q) {
+      fx[q] = (short)(q % N);
+      fy[q] = (short)(q / N);
+    }
+    lev.coupled.assign((size_t)lev.n_ib * nown, 0);
+    std::atomic<int> next{0};
+    auto worker = [&]() {
+      for (int s = next++; s < lev.n_ib; s = next++) {
+        const int pid = lev.ib_list[s], ox = pid % g.npd * b, oy = pid / g.npd * b;
+        unsigned char* cp = lev.coupled.data() + (size_t)s * nown;
+        for (int r = 0; r < nown; ++r) {
+          cp[r] = edge[r];
+          if (cp[r] || r >= 2 * bb) continue;
+          const CompFoot& f = lev.f[r / bb];
+          const int q = (oy + r % bb / b) * N + ox + r % bb % b;
+          for (int k = f.tptr[q]; k < f.tptr[q + 1]; ++k) {
+            const int comp = f.tcol[k] >= NN ? 1 : 0, c = f.tcol[k] - comp * NN;
+            int li = fx[c] - ox, lj = fy[c] - oy;   // from the owned corner
+            if (li >= 0 && li < b && lj >= 0 && lj < b) continue;   // owned
+            li += g.o;
+            lj += g.o;
+            li = li < 0 ? li + N : (li >= N ? li - N : li);
+            lj = lj < 0 ? lj + N : (lj >= N ? lj - N : lj);
+            if (comp == 0 ? (li <= m && lj < m) : (li < m && lj <= m)) {
+              cp[r] = 1;
+              break;
+            }
+          }
+        }
+      }
+    };
+    run_workers(worker, (size_t)lev.n_ib / 4 + 1);
+    lev.wptr.assign(1, 0);
+    lev.wrow.clear();
+    lev.w_max = 0;
+    for (int s = 0; s < lev.n_ib; ++s) {
+      for (int r = 0; r < nown; ++r)
+        if (lev.coupled[(size_t)s * nown + r]) lev.wrow.push_back(r);
+      lev.wptr.push_back((int)lev.wrow.size());
+      lev.w_max = std::max(lev.w_max, lev.wptr[s + 1] - lev.wptr[s]);
+    }
+    lev.w_stride = (lev.bm.nn + 3) / 4 * 4;
+  }
+
+  // fn on up to 16 host threads, at most `most` of them
+  template <typename F>
+  static void run_workers(F& fn, size_t most) {
+    const size_t hw = std::max(1u, std::thread::hardware_concurrency());
+    const size_t nth = std::min({(size_t)16, hw, most});
+    if (nth <= 1) {
+      fn();
+      return;
+    }
+    std::vector<std::thread> th;
+    for (size_t t = 0; t < nth; ++t) th.emplace_back([&fn] { fn(); });
+    for (auto& t : th) t.join();
   }
 
   size_t box_stride(const Level<T>& lev) const { return (size_t)lev.g.nch * lev.g.nloc * 64; }
@@ -636,17 +737,16 @@ class Solver final : public SolverBase {
     return ks > 1 ? (size_t)ks * cnt * g.nch * 64 : 0;
   }
 
-  // Every Schwarz launch goes through here: the slice buffer must hold the
-  // launch's column slices.
-  // sym: the IB boxes (the level's whole list) from the symmetric copy
-  void ras_launch(Level<T>& lev, const T* r, T* z, const T* inv, const int* ib, int n_ib, const int* in, int n_int,
-                  hipStream_t s, int parts, bool acc, bool sym = false) {
-    require(lev.ib_part.n >= ib_part_need(lev.g, (parts & 1) ? n_ib : 0), "Schwarz slice buffer too small");
-    require(!sym || (lev.use_sym && n_ib == lev.n_ib), "symmetric IB storage is for the whole IB list");
-    const SymIB sy = sym_of(lev);
-    require(sym || !lev.use_sym || !(parts & 1) || n_ib == 0, "the IB boxes of this level are in symmetric storage");
-    launch_ras_apply<T>(r, z, lev.g, inv, ib, n_ib, lev.clsv, in, n_int, lev.ib_part.p, s, parts, acc,
-                        sym ? &sy : nullptr);
+  // Every Schwarz launch goes through here: boxes [i0, i1) of the IB list and
+  // [k0, k1) of the interior list; the slice buffer must hold the launch's
+  // column slices.
+  void ras_launch(Level<T>& lev, const T* r, T* z, int i0, int i1, int k0, int k1, hipStream_t s, int parts, bool acc) {
+    require(lev.use_sym || lev.ib_part.n >= ib_part_need(lev.g, (parts & 1) ? i1 - i0 : 0),
+            "Schwarz slice buffer too small");
+    const SymIB sy = sym_of(lev, i0);
+    launch_ras_apply<T>(r, z, lev.g, lev.inv.p + (lev.use_sym ? 0 : (size_t)i0 * box_stride(lev)), lev.d_ib.p + i0,
+                        i1 - i0, lev.clsv, lev.d_int.p + k0, k1 - k0, lev.ib_part.p, s, parts, acc,
+                        lev.use_sym ? &sy : nullptr);
   }
 
   // blocks of the fused operator + dots kernel on a level
@@ -678,7 +778,7 @@ class Solver final : public SolverBase {
         for (int i = 0; 2 * i <= mx; ++i) {
           lev.kcode.push_back((c << 24) | (j << 12) | i);
           for (int l : {local(c, i, j), local(c, mx - i, j), local(c, i, my - j), local(c, mx - i, my - j)})
-            lev.klocal.push_back(l);
+            lev.klocal.push_back(lev.pos[l]);
           // an owned image e of the orbit, and which of its images are owned
           // (each unknown once)
           for (const auto& e : {std::pair<int, int>{i, j}, {mx - i, j}, {i, my - j}, {mx - i, my - j}}) {
@@ -689,7 +789,7 @@ class Solver final : public SolverBase {
             if (yb != b && owned(a, yb)) bits |= 4;
             if (xa != a && yb != b && owned(xa, yb)) bits |= 8;
             lev.rcode.push_back((bits << 26) | (c << 24) | (b << 12) | a);
-            lev.rlocal.push_back(local(c, a, b));
+            lev.rlocal.push_back(lev.pos[local(c, a, b)] - lev.bm.nnp);
             break;
           }
         }
@@ -1118,42 +1218,45 @@ class Solver final : public SolverBase {
       v.kcode = lev.d_kcode.p;
       v.rcode = lev.d_rcode.p;
     }
-    // The additive sweep of a single system streams the IB boxes' owned
-    // rows from a symmetric copy (lower owned tiles only; whole 64-row
-    // chunks) on levels with enough IB boxes: at least 256 (box, chunk)
-    // pairs, the IB-box kernel cut into at most four column slices in FP64,
-    // two in FP32 (measured: below that the symmetric form's uneven slices
-    // and longer sums cost more than its fewer bytes save).  The chunked
-    // copy (lev.inv) serves the other levels, the multiplicative sweep and
-    // the batched form.
-    lev.use_sym = d_.smoother == IBMG_RAS && !defer_coarse_ && lev.n_ib > 0 && g.nown % 64 == 0 &&
-                  lev.n_ib * g.nch >= 256 && ras_ib_ksplit(g, lev.n_ib) <= (sizeof(T) == 8 ? 4 : 2) &&
+    lev.d_pos.upload(lev.pos, s);
+    // A single system keeps the IB boxes eliminated (three short launches over
+    // fewer bytes) where the whole rows that one launch of the sweep reads (all
+    // boxes, or a colour's) take at least 96 MiB.  Kernel times, eliminated
+    // against whole rows, FP64 unless noted: 16 x 16/4 boxes at 125 MiB 22.7
+    // against 24.8 us, at 1790 MiB 153 against 287 us; 8 x 8/2 boxes at 166 MiB
+    // 27.4 against 28.9 us, at 86 MiB 19.1 against 16.7 us, at 21 MiB 15.7
+    // against 8.6 us; FP32 16 x 16/4 at 62 MiB 18.2 against 15.7 us, at 167 MiB
+    // 23.1 against 29.4 us.  The chunked rows (lev.inv) serve the smaller
+    // levels and the batched form.
+    const int per_launch = d_.smoother == IBMG_RMS ? lev.n_ib / std::max(1, lev.ncolour) : lev.n_ib;
+    lev.use_sym = !defer_coarse_ && lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
+                  (size_t)per_launch * box_stride(lev) * sizeof(T) >= kElimMinBytes &&
                   std::getenv("IBMG_NO_SYM") == nullptr;
     if (lev.use_sym) {
-      std::vector<int> perm;
-      perm.reserve(g.nloc);
-      std::vector<char> owned(g.nloc, 0);
-      const int bb = g.b * g.b, m = g.m;
-      for (int r = 0; r < g.nown; ++r) {
-        const int comp = r / bb, q = r % bb;
-        const int oi = q % g.b + g.o, oj = q / g.b + g.o;
-        const int k = comp == 0 ? oj * (m + 1) + oi : (comp == 1 ? m * (m + 1) + oj * m + oi : 2 * m * (m + 1) + oj * m + oi);
-        perm.push_back(k);
-        owned[k] = 1;
-      }
-      for (int k = 0; k < g.nloc; ++k)
-        if (!owned[k]) perm.push_back(k);
-      lev.d_perm.upload(perm, s);
+      coupled_rows(lev);
+      lev.d_nonown.upload(lev.nonown, s);
+      lev.d_wptr.upload(lev.wptr, s);
+      lev.d_wrow.upload(lev.wrow, s);
+      lev.d_coupled.upload(lev.coupled, s);
+      lev.wmat.alloc(lev.wrow.size() * (size_t)lev.w_stride);
       lev.inv_sym.alloc((size_t)lev.n_ib * sym_box_stride(g));
-      lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g, lev.n_ib));
+      lev.sym_y.alloc((size_t)lev.n_ib * g.nown);
+      lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
     }
     lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
   }
 
-  SymIB sym_of(Level<T>& lev) { return SymIB{lev.inv_sym.p, lev.d_perm.p, lev.sym_part.p}; }
+  // the eliminated storage from IB box i0 on
+  SymIB sym_of(Level<T>& lev, int i0) {
+    if (!lev.use_sym) return SymIB{};
+    return SymIB{lev.inv_sym.p + (size_t)i0 * sym_box_stride(lev.g), lev.sym_part.p,
+                 WBoxView{lev.wmat.p, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
+                          lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.bm.nn, lev.w_stride, lev.w_max},
+                 lev.sym_y.p};
+  }
 
   // The unique boxes [inv_base, inv_end) whose owned rows lev.inv holds in
-  // chunks: the IB boxes unless they are in symmetric storage, and the
+  // chunks: the IB boxes unless they are in eliminated storage, and the
   // interior boxes' shared inverse where no parity classes hold it.
   static int inv_base(const Level<T>& lev) { return lev.use_sym ? lev.n_ib : 0; }
   int inv_end(const Level<T>& lev) const { return has_classes(lev) ? lev.n_ib : lev.n_unique; }
@@ -1162,25 +1265,25 @@ class Solver final : public SolverBase {
   bool has_classes(const Level<T>& lev) const { return !lev.sum_mode && !defer_coarse_ && !lev.int_list.empty(); }
 
   // The unique box inverses of every Schwarz level: assembled per level,
-  // inverted in batches that mix levels whose boxes have the same number of
-  // unknowns (one run of block sweeps serves them all), owned rows extracted
-  // per level.  Batches hold at most 512 matrices and 8 GiB of them with
-  // their sweep workspace (a set-up temporary of the handle's workspace).
+  // eliminated (or, for the summed combination, inverted) in batches that mix
+  // levels whose boxes have the same number of unknowns (one run of sweeps
+  // serves them all), each level's storage extracted.  Batches hold at most
+  // 512 matrices and 10 GiB of them with their sweep workspace (a set-up
+  // temporary of the handle's workspace), split evenly.
   void build_boxes(hipStream_t s) {
-    std::map<int, std::vector<std::pair<int, int>>> groups;   // nloc -> (level, unique index)
+    std::map<std::pair<int, int>, std::vector<std::pair<int, int>>> groups;   // (size, nnp) -> (level, unique index)
     std::vector<DBuf<int>> ids(L_ + 1);
     for (int l = 1; l <= L_; ++l) {
       Level<T>& lev = levels_[l];
       prepare_boxes(lev, s);
       ids[l].upload(lev.uniq, s);
-      for (int u = 0; u < lev.n_unique; ++u) groups[lev.g.nloc].push_back({l, u});
+      for (int u = 0; u < lev.n_unique; ++u) groups[{lev.bm.ld, lev.bm.nnp}].push_back({l, u});
     }
-    // matrices of one size are inverted together, at most 10 GiB of them at
-    // a time, split into equal batches
     const size_t budget = (size_t)10 << 30;
     for (auto& grp : groups) {
-      const int n = grp.first;
+      const int n = grp.first.first;
       const auto& items = grp.second;
+      const BoxMat bm = levels_[items[0].first].bm;   // one box shape per group
       const size_t per = ((size_t)n * n + sweep_work(n, 1)) * sizeof(double);
       const size_t cap = std::min<size_t>(std::max<size_t>(1, budget / per), 512);
       const size_t nbatch = (items.size() + cap - 1) / cap;
@@ -1202,24 +1305,30 @@ class Solver final : public SolverBase {
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
           launch_patch_assemble(ids[l].p + u0, count, lev.g, lev.cd, lev.f[0].d_tptr.p, lev.f[0].d_tcol.p,
-                                lev.f[0].tval.p, lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p,
-                                mats.p + slot * n * n, s);
+                                lev.f[0].tval.p, lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p, lev.d_pos.p,
+                                bm, mats.p + slot * n * n, s);
         });
-        launch_gj_invert(mats.p, n, cnt, work.p, dinv.p, s);
+        if (bm.nnp) launch_box_eliminate(mats.p, bm, cnt, work.p, dinv.p, s);
+        else launch_gj_invert(mats.p, n, cnt, work.p, dinv.p, s);
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
+          double* m0 = mats.p + slot * n * n;
+          // unique indices below n_ib are the IB boxes; the eliminated ones
+          // come apart into their two factors, the others and the interior
+          // representative (the last) get whole rows
+          const int nsym = lev.use_sym ? std::min(count, std::max(0, lev.n_ib - u0)) : 0;
+          if (bm.nnp) launch_box_on(m0 + (size_t)nsym * n * n, bm, count - nsym, s);
           const int c0 = std::max(u0, inv_base(lev)), c1 = std::min(u0 + count, inv_end(lev));
           if (c1 > c0)
-            launch_extract_owned<T>(mats.p + (slot + (c0 - u0)) * n * n, c1 - c0, lev.g,
-                                    lev.inv.p + (size_t)(c0 - inv_base(lev)) * box_stride(lev), s, lev.sum_mode);
-          if (has_classes(lev) && u0 + count > lev.n_ib)   // the interior representative comes last
-            launch_extract_classes<T>(mats.p + (slot + (lev.n_ib - u0)) * n * n, n, lev.clsv, lev.d_klocal.p,
+            launch_extract_rows<T>(m0 + (size_t)(c0 - u0) * n * n, c1 - c0, lev.g, bm, lev.d_pos.p,
+                                   lev.inv.p + (size_t)(c0 - inv_base(lev)) * box_stride(lev), s);
+          if (has_classes(lev) && u0 + count > lev.n_ib)
+            launch_extract_classes<T>(m0 + (size_t)(lev.n_ib - u0) * n * n, bm, lev.clsv, lev.d_klocal.p,
                                       lev.d_rlocal.p, lev.cls.p, s);
-          // unique indices below n_ib are the IB boxes
-          const int nsym = lev.use_sym ? std::min(count, std::max(0, lev.n_ib - u0)) : 0;
-          if (nsym > 0)
-            launch_extract_sym<T>(mats.p + slot * n * n, nsym, lev.g, lev.d_perm.p,
-                                  lev.inv_sym.p + (size_t)u0 * sym_box_stride(lev.g), s);
+          if (nsym > 0) {
+            launch_extract_sym<T>(m0, nsym, lev.g, bm, lev.inv_sym.p + (size_t)u0 * sym_box_stride(lev.g), s);
+            launch_extract_w<T>(m0, nsym, bm, lev.d_wptr.p + u0, lev.d_wrow.p, lev.w_stride, lev.wmat.p, s);
+          }
         });
       }
       IBMG_HIP(hipStreamSynchronize(s));
@@ -1335,14 +1444,11 @@ class Solver final : public SolverBase {
           op<T>(l, z, lev.rr.p, v, false, lev.F.p, s);
           rc = lev.rr.p;
         }
-        const int i0 = lev.ib_off[c], k0 = lev.int_off[c];
-        ras_launch(lev, rc, z, lev.inv.p + (size_t)i0 * box_stride(lev), lev.d_ib.p + i0, lev.ib_off[c + 1] - i0,
-                   lev.d_int.p + k0, lev.int_off[c + 1] - k0, s, 3, true);
+        ras_launch(lev, rc, z, lev.ib_off[c], lev.ib_off[c + 1], lev.int_off[c], lev.int_off[c + 1], s, 3, true);
       }
       return;
     }
-    ras_launch(lev, v, z, lev.inv.p, lev.d_ib.p, lev.n_ib, lev.d_int.p, (int)lev.int_list.size(), s, 3, false,
-               lev.use_sym);
+    ras_launch(lev, v, z, 0, lev.n_ib, 0, (int)lev.int_list.size(), s, 3, false);
   }
 
   // w <- w + e, e = nu FGMRES iterations (classical Gram-Schmidt twice) on
@@ -1774,11 +1880,13 @@ class Solver final : public SolverBase {
       const int n_int = (int)lev.int_list.size();
       if (kernel == IBMG_KERNEL_RAS_IB) {
         require(lev.n_ib > 0, "the level has no IB boxes");
-        // the symmetric copy (as the additive sweep runs it, with the row
-        // sums' launch) streams only its stored rows
-        const double stored = lev.use_sym ? (double)sym_box_stride(g) : (double)g.nown * g.nloc;
-        by = (double)lev.n_ib * (stored + g.nloc + g.nown) * ts;
-        fl = 2.0 * lev.n_ib * g.nown * g.nloc;
+        // the eliminated boxes (as the additive sweep runs them, three
+        // launches) stream their two factors
+        const double stored = lev.use_sym ? (double)lev.n_ib * sym_box_stride(g) + (double)lev.wrow.size() * lev.bm.nn
+                                          : (double)lev.n_ib * g.nown * g.nloc;
+        by = (stored + (double)lev.n_ib * (g.nloc + g.nown)) * ts;
+        fl = lev.use_sym ? 2.0 * ((double)lev.n_ib * g.nown * g.nown + (double)lev.wrow.size() * lev.bm.nn)
+                         : 2.0 * lev.n_ib * g.nown * g.nloc;
       } else {
         require(n_int > 0, "the level has no interior boxes");
         by = ((double)lev.cls.n + (double)n_int * (g.nloc + g.nown)) * ts;
@@ -1786,8 +1894,7 @@ class Solver final : public SolverBase {
       }
       const int part = kernel == IBMG_KERNEL_RAS_IB ? 1 : 2;
       ms = time_launches([&] {
-        ras_launch(lev, lev.r.p, lev.t.p, lev.inv.p, lev.d_ib.p, lev.n_ib, lev.d_int.p, n_int, s, part, false,
-                   part == 1 && lev.use_sym);
+        ras_launch(lev, lev.r.p, lev.t.p, 0, lev.n_ib, 0, n_int, s, part, false);
       }, reps, s);
     } else if (kernel == IBMG_KERNEL_STENCIL) {
       by = 2.0 * (double)n * ts;
