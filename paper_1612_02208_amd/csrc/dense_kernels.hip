@@ -28,83 +28,110 @@ struct CsrView {
   const double* val;
 };
 
-// Add an IB entry of a box row: col indexes the level's [u | v] vector; the
-// entry lands on the box's x-face or y-face unknown when that face lies in
-// the enlarged box (column c of the row goes to Ar[at(c)]).
-template <typename At>
-__device__ __forceinline__ void add_ib_entry(double* Ar, At at, int col, double v, int N, int x0, int y0, int m) {
-  const int NN = N * N;
-  const int comp = col >= NN ? 1 : 0;
-  const int f = col - comp * NN;
-  const int li = pmod(f % N - x0, N), lj = pmod(f / N - y0, N);
-  if (comp == 0) {
-    if (li <= m && lj <= m - 1) Ar[at(lj * (m + 1) + li)] += v;
-  } else {
-    if (li <= m - 1 && lj <= m) Ar[at(m * (m + 1) + lj * m + li)] += v;
-  }
-}
-
-// Box matrices, ld x ld each: local unknown k sits at row and column pos[k]
-// (pos = null: at k); diagonal entries [nn, nnp) that no unknown takes are 1.
+// Box matrices, ld x ld each: row and column at(k) hold local unknown k (its
+// position; null maps: k itself).  One work-group per 64 rows: the kept tiles
+// (on or below the diagonal) are zeroed, a thread per row writes the stencil,
+// and a wave per row adds the IB entries, whose columns are distinct.  Bound by
+// the zeroing's writes; with one work-group per matrix it was bound by the rows'
+// serial entry loops and by the few work-groups (580 -> 200 us
+// on average over the levels of the 512^2 annulus).  Rows [nn, nnp) are the padding: 1 on the diagonal.
 __global__ void __launch_bounds__(256) k_patch_assemble(const int* __restrict__ patch_ids, BoxGeom g,
-                                                        StokesCoef<double> c, CsrView tu, CsrView tv,
-                                                        const int* __restrict__ pos, int ld, int nn, int nnp,
-                                                        double* __restrict__ mats) {
-  const int pid = patch_ids[blockIdx.x];
-  const int N = g.N, m = g.m, n = g.nloc;
+                                                        StokesCoef<double> c, CsrView tu, CsrView tv, BoxOrder bo,
+                                                        BoxMat bm, double* __restrict__ mats) {
+  const int mat = blockIdx.y, pid = patch_ids[mat], ld = bm.ld, nnp = bm.nnp;
+  const int N = g.N, NN = N * N, m = g.m, bb = g.b * g.b;
   const int x0 = (pid % g.npd) * g.b - g.o;
   const int y0 = (pid / g.npd) * g.b - g.o;
-  double* A = mats + (size_t)blockIdx.x * ld * ld;
-  for (size_t k = threadIdx.x; k < (size_t)ld * ld; k += blockDim.x) A[k] = 0.0;
+  double* A = mats + (size_t)mat * ld * ld;
+  const int R0 = blockIdx.x * 64, R1 = R0 + 64 < ld ? R0 + 64 : ld;
+  const unsigned short* ord = bo.ord ? bo.ord + (size_t)mat * g.nown : nullptr;
+  const unsigned short* own = bo.ord ? bo.own + (size_t)mat * g.nown : nullptr;
+  auto at = [&](int k) {
+    if (!bo.pos) return k;
+    const int p = bo.pos[k];
+    return p < nnp ? p : nnp + own[p - nnp];
+  };
+  const int nu = m * (m + 1), p0 = 2 * nu;
+  auto local = [&](int row) {   // -1: padding
+    if (!bo.pos) return row;
+    if (row < nnp) return row < bm.nn ? bo.nonown[row] : -1;
+    const int r = ord[row - nnp], comp = r / bb, oi = r % bb % g.b + g.o, oj = r % bb / g.b + g.o;
+    return comp == 0 ? oj * (m + 1) + oi : (comp == 1 ? nu + oj * m + oi : p0 + oj * m + oi);
+  };
+  for (int r = R0; r < R1; ++r)
+    for (int k = threadIdx.x; k < R1; k += 256) A[(size_t)r * ld + k] = 0.0;
   __syncthreads();
-  auto at = [&](int k) { return pos ? pos[k] : k; };
-  for (int k = nn + threadIdx.x; k < nnp; k += blockDim.x) A[(size_t)k * ld + k] = 1.0;
-  const int nu = m * (m + 1);
-  const int p0 = 2 * nu;
   const double dg = c.alpha + 4.0 * c.beta;
-  for (int row = threadIdx.x; row < n; row += blockDim.x) {
-    double* Ar = A + (size_t)at(row) * ld;
-    if (row < nu) {  // x-face (ii, jj)
-      const int ii = row % (m + 1), jj = row / (m + 1);
-      Ar[at(row)] += dg;
-      if (ii >= 1) Ar[at(row - 1)] -= c.beta;
-      if (ii <= m - 1) Ar[at(row + 1)] -= c.beta;
-      if (jj >= 1) Ar[at(row - (m + 1))] -= c.beta;
-      if (jj <= m - 2) Ar[at(row + (m + 1))] -= c.beta;
-      if (ii <= m - 1) Ar[at(p0 + jj * m + ii)] += c.gi;
-      if (ii >= 1) Ar[at(p0 + jj * m + ii - 1)] -= c.gi;
-      const int r = pmod(y0 + jj, N) * N + pmod(x0 + ii, N);
-      for (int k = tu.ptr[r]; k < tu.ptr[r + 1]; ++k) add_ib_entry(Ar, at, tu.col[k], tu.val[k], N, x0, y0, m);
-    } else if (row < p0) {  // y-face (ii, jj)
-      const int q = row - nu;
-      const int ii = q % m, jj = q / m;
-      Ar[at(row)] += dg;
-      if (ii >= 1) Ar[at(row - 1)] -= c.beta;
-      if (ii <= m - 2) Ar[at(row + 1)] -= c.beta;
-      if (jj >= 1) Ar[at(row - m)] -= c.beta;
-      if (jj <= m - 1) Ar[at(row + m)] -= c.beta;
-      if (jj <= m - 1) Ar[at(p0 + jj * m + ii)] += c.gi;
-      if (jj >= 1) Ar[at(p0 + (jj - 1) * m + ii)] -= c.gi;
-      const int r = pmod(y0 + jj, N) * N + pmod(x0 + ii, N);
-      for (int k = tv.ptr[r]; k < tv.ptr[r + 1]; ++k) add_ib_entry(Ar, at, tv.col[k], tv.val[k], N, x0, y0, m);
+  if (threadIdx.x < R1 - R0) {
+    const int row = R0 + threadIdx.x, k = local(row);
+    double* Ar = A + (size_t)row * ld;
+    auto put = [&](int kc, double v) {
+      const int q = at(kc);
+      if (q < R1) Ar[q] = v;
+    };
+    if (k < 0) {
+      Ar[row] = 1.0;
+    } else if (k < nu) {  // x-face (ii, jj)
+      const int ii = k % (m + 1), jj = k / (m + 1);
+      Ar[row] = dg;
+      if (ii >= 1) put(k - 1, -c.beta);
+      if (ii <= m - 1) put(k + 1, -c.beta);
+      if (jj >= 1) put(k - (m + 1), -c.beta);
+      if (jj <= m - 2) put(k + (m + 1), -c.beta);
+      if (ii <= m - 1) put(p0 + jj * m + ii, c.gi);
+      if (ii >= 1) put(p0 + jj * m + ii - 1, -c.gi);
+    } else if (k < p0) {  // y-face (ii, jj)
+      const int ii = (k - nu) % m, jj = (k - nu) / m;
+      Ar[row] = dg;
+      if (ii >= 1) put(k - 1, -c.beta);
+      if (ii <= m - 2) put(k + 1, -c.beta);
+      if (jj >= 1) put(k - m, -c.beta);
+      if (jj <= m - 1) put(k + m, -c.beta);
+      if (jj <= m - 1) put(p0 + jj * m + ii, c.gi);
+      if (jj >= 1) put(p0 + (jj - 1) * m + ii, -c.gi);
     } else {  // cell (ii, jj): -(D u)
-      const int q = row - p0;
-      const int ii = q % m, jj = q / m;
-      Ar[at(jj * (m + 1) + ii + 1)] -= c.gi;
-      Ar[at(jj * (m + 1) + ii)] += c.gi;
-      Ar[at(nu + (jj + 1) * m + ii)] -= c.gi;
-      Ar[at(nu + jj * m + ii)] += c.gi;
+      const int ii = (k - p0) % m, jj = (k - p0) / m;
+      put(jj * (m + 1) + ii + 1, -c.gi);
+      put(jj * (m + 1) + ii, c.gi);
+      put(nu + (jj + 1) * m + ii, -c.gi);
+      put(nu + jj * m + ii, c.gi);
+    }
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int row = R0 + wave; row < R1; row += 4) {
+    const int k = local(row);
+    if (k < 0 || k >= p0) continue;
+    const bool xf = k < nu;
+    const int ii = xf ? k % (m + 1) : (k - nu) % m, jj = xf ? k / (m + 1) : (k - nu) / m;
+    const int r = pmod(y0 + jj, N) * N + pmod(x0 + ii, N);
+    const CsrView& t = xf ? tu : tv;
+    double* Ar = A + (size_t)row * ld;
+    // col indexes the level's [u | v] vector; the entry counts when its face
+    // lies in the enlarged box
+    for (int e = t.ptr[r] + lane; e < t.ptr[r + 1]; e += 64) {
+      const int comp = t.col[e] >= NN ? 1 : 0, f = t.col[e] - comp * NN;
+      const int li = pmod(f % N - x0, N), lj = pmod(f / N - y0, N);
+      int kc = -1;
+      if (comp == 0) {
+        if (li <= m && lj <= m - 1) kc = lj * (m + 1) + li;
+      } else if (li <= m - 1 && lj <= m) {
+        kc = nu + lj * m + li;
+      }
+      if (kc < 0) continue;
+      const int q = at(kc);
+      if (q < R1) Ar[q] += t.val[e];
     }
   }
 }
 
 void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoef<double> c,
                            const int* tptr_u, const int* tcol_u, const double* tval_u,
-                           const int* tptr_v, const int* tcol_v, const double* tval_v, const int* pos, BoxMat bm,
+                           const int* tptr_v, const int* tcol_v, const double* tval_v, BoxOrder bo, BoxMat bm,
                            double* mats, hipStream_t s) {
   if (!count) return;
   CsrView tu{tptr_u, tcol_u, tval_u}, tv{tptr_v, tcol_v, tval_v};
-  IBMG_KLAUNCH(k_patch_assemble, dim3(count), dim3(256), 0, s, patch_ids, g, c, tu, tv, pos, bm.ld, bm.nn, bm.nnp, mats);
+  IBMG_KLAUNCH(k_patch_assemble, dim3((bm.ld + 63) / 64, count), dim3(256), 0, s, patch_ids, g, c, tu, tv, bo, bm, mats);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -152,89 +179,165 @@ struct Mfma<float> {
 // Sweeping the blocks of n leaves W = A_on A_nn^{-1} in the rows o; rows already
 // swept are not needed again, so those steps update the rows below their block
 // only (elimination, "partial" below), and the blocks of o are then swept
-// within o alone.  That is 59% of the whole inverse's arithmetic at 16 x 16/4.
-// Each half keeps the velocities before the pressures, so its pivot blocks stay
-// definite.
+// within o alone.
+// The box matrices are sparse, and a 64-row tile of column K that is zero takes
+// no part in step K: panel read flags the tiles that are not, and the other
+// launches skip the rest.  The order of the unknowns keeps many zero: n runs
+// around the ring, sector by sector (the faces before the cells), so a sector
+// meets its neighbours and the wrap only; o runs line by line (faces before
+// cells) through the rows that n does not reach and ends with those it does
+// (coupled velocities, then the cells beside one).  Every prefix of these orders
+// holds, with each of its cells, faces that lead out of the set of those cells,
+// so the pressure pivots stay definite as in the velocities-first order; the
+// result's error against refined solves is the same (FP64 on boxes of the 512^2
+// annulus and 256^2 membranes: 7e-16 to 7e-15 here, 1e-15 to 7e-15 there).  A 16
+// x 16/4 box takes 0.75 GFLOP (1.4 where the structure runs along its edge)
+// instead of 3.4, the whole inverse's 5.8.
 // Step K, five launches over every matrix:
 //   diag       (a work-group per matrix): D^{-1} in LDS (128 x 128, the
 //              160 KB of gfx950), to dinv;
-//   panel read (64-row tiles): C = S_:K from the kept tiles (a tile above
-//              K0 or K1 from that tile row's tile, transposed) and C^T;
+//   panel read (64-row tiles): which tiles of C = S_:K are not zero, and those
+//              above K, stored in K's tile rows, turned round;
 //   scale      (64-row tiles x two column halves): E = C D^{-1};
 //   update     (kept 64 x 64 tiles outside K): S_IJ <- S_IJ - E_I C_J^T;
 //   panel write: S_IK <- E_I below K, S_KI <- E_I^T above it, S_KK <- -D^{-1}.
 // The last block may be narrower (w < 128 columns): D is padded with the
 // identity, and the panel columns beyond w are zero, so they change nothing.
+// Loads run unconditionally from clamped indices and what lies outside is
+// selected away or never stored: a load under a lane condition makes the
+// compiler wait for each one in turn (that alone cost the update kernel 2.5x).
 // The scale and update products are 64 x 64 tiles with a 128-long reduction
 // on the FP64 matrix cores (16x16x4 MFMA, four waves of 2 x 2 tiles): twice
 // the flops per pass over the kept tiles of 64-column steps.
 constexpr int GJ_NB = kGjNb;   // 128
 static_assert(GJ_NB == 128, "the sweep kernels are written for 128-column blocks of two 64-wide tiles");
 
-// D^{-1} of the 128 x 128 pivot block by in-place Gauss-Jordan, one
-// work-group of 1024 threads per matrix.  Thread t holds column t mod 128 of
-// rows t / 128 + 8 q (q < 16) in registers; per pivot k only row k and
-// column k pass through LDS (two buffers by pivot parity, so one barrier per
-// pivot): the threads holding them publish them, and every thread updates
-// its sixteen entries from its column's row-k value and its rows' column-k
-// values (the latter the same for a whole wave, read as broadcasts).
+// In-place Gauss-Jordan step K of a 16 x 16 matrix in one wave's accumulator
+// layout (d[v]: row kq + 4 v, column ln).
+template <int K>
+__device__ __forceinline__ void gj16_step(Mfma<double>::acc_t& d, int kq, int ln) {
+  const double rk = __shfl(d[K >> 2], (K & 3) * 16 + ln, 64);   // row K at this lane's column
+  const double ip = 1.0 / dpp_move<0x150 + K>(rk);              // row_newbcast: lane K of the row of 16
+  const double rip = rk * ip;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double ck = dpp_move<0x150 + K>(d[v]);   // column K at this lane's row
+    const bool row = v == (K >> 2) && kq == (K & 3);
+    const double off = row ? rip : d[v] - ck * rip;
+    const double col = row ? ip : -ck * ip;
+    d[v] = ln == K ? col : off;
+  }
+}
+
+// D^{-1} of the 128 x 128 pivot block, one work-group of 1024 threads per matrix:
+// block sweeps of 16, wave w holding tiles (w / 2, 4 (w mod 2) + t), t < 4, of D
+// in MFMA accumulators.  Per step the wave with the diagonal tile inverts it in
+// registers (DPP and shuffles, no barrier), E = C T^{-1} and the update D -=
+// E C^T run on the matrix cores: 16 barriers in all.  Bound by the eight 16-step
+// chains of divisions.  One pivot per barrier, as scalar Gauss-Jordan through
+// LDS, took 188 us a block (295 us for 300 matrices); this 45 (69) us.
 __global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mats, int n, int kb, int w,
                                                   double* __restrict__ dinv_all) {
-  __shared__ double rowk[2][GJ_NB];
-  __shared__ double colk[2][GJ_NB];
+  constexpr int LD = 18;   // row stride in LDS: operand reads of 16 rows without bank conflicts
+  __shared__ double Cs[2][GJ_NB * LD];
+  __shared__ double Es[GJ_NB * LD];
+  __shared__ double Ts[2][16 * LD];
   const double* A = mats + (size_t)blockIdx.x * n * n;
   double* Di = dinv_all + (size_t)blockIdx.x * GJ_NB * GJ_NB;
-  const int tid = threadIdx.x;
-  const int b = tid & 127, a0 = tid >> 7;   // column, first row (rows a0 + 8 q)
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kq = lane >> 4, ln = lane & 15;
+  const int rt = wave >> 1, c0 = 4 * (wave & 1);
   // the padding of a narrow last block is the identity, so the pivots stay
   // nonzero; the padded rows and columns never reach the matrix.  Above the
   // diagonal tiles only tile (K1, K0) is kept: D[a][b] with a in the first
   // half and b in the second is read as D[b][a].
-  double v[16];
+  Mfma<double>::acc_t d[4];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int a = a0 + 8 * q;
-    double x = a == b ? 1.0 : 0.0;
-    if (a < w && b < w) {
-      const bool upper = (a >> 6) < (b >> 6);
-      x = upper ? A[(size_t)(kb + b) * n + kb + a] : A[(size_t)(kb + a) * n + kb + b];
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int a = 16 * rt + Mfma<double>::row(kq, v), b = 16 * (c0 + t) + ln;
+      const int ac = a < w ? a : w - 1, bc = b < w ? b : w - 1;
+      const bool upper = (ac >> 6) < (bc >> 6);
+      const double x = A[(size_t)(kb + (upper ? bc : ac)) * n + kb + (upper ? ac : bc)];
+      d[t][v] = a < w && b < w ? x : (a == b ? 1.0 : 0.0);
     }
-    v[q] = x;
-  }
-  for (int k = 0; k < GJ_NB; ++k) {
-    const int buf = k & 1;
-    // publish row k (the thread holding row k of column b) and column k
-    if ((k & 7) == a0) rowk[buf][b] = v[k >> 3];
-    if (b == k) {
+  for (int kk = 0; kk < GJ_NB / 16; ++kk) {
+    double* C = Cs[kk & 1];
+    double* T = Ts[kk & 1];
+    const bool mine = (kk >> 2) == (wave & 1);   // this wave holds tile (rt, kk)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) colk[buf][a0 + 8 * q] = v[q];
+    for (int t = 0; t < 4; ++t)
+      if (mine && t == (kk & 3)) {
+        if (rt == kk) {
+          Mfma<double>::acc_t x = d[t];
+          gj16_step<0>(x, kq, ln);
+          gj16_step<1>(x, kq, ln);
+          gj16_step<2>(x, kq, ln);
+          gj16_step<3>(x, kq, ln);
+          gj16_step<4>(x, kq, ln);
+          gj16_step<5>(x, kq, ln);
+          gj16_step<6>(x, kq, ln);
+          gj16_step<7>(x, kq, ln);
+          gj16_step<8>(x, kq, ln);
+          gj16_step<9>(x, kq, ln);
+          gj16_step<10>(x, kq, ln);
+          gj16_step<11>(x, kq, ln);
+          gj16_step<12>(x, kq, ln);
+          gj16_step<13>(x, kq, ln);
+          gj16_step<14>(x, kq, ln);
+          gj16_step<15>(x, kq, ln);
+          // the lower triangle, mirrored: the sweeps rely on T's symmetry, and
+          // its rounding errors off it would grow
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int i = Mfma<double>::row(kq, v);
+            if (ln <= i) {
+              T[i * LD + ln] = x[v];
+              T[ln * LD + i] = x[v];
+            }
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) C[(16 * rt + Mfma<double>::row(kq, v)) * LD + ln] = d[t][v];
+      }
+    __syncthreads();
+    if (wave < 8) {   // E for row tile `wave`
+      Mfma<double>::acc_t e = {0, 0, 0, 0};
+#pragma unroll
+      for (int st = 0; st < 4; ++st)
+        e = Mfma<double>::mma(C[(16 * wave + ln) * LD + 4 * st + kq], T[(4 * st + kq) * LD + ln], e);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Es[(16 * wave + Mfma<double>::row(kq, v)) * LD + ln] = e[v];
     }
     __syncthreads();
-    // every LDS read is issued before any arithmetic, so a pivot costs one
-    // round trip to LDS, not sixteen
-    const double pk = rowk[buf][k];
-    const double rk = rowk[buf][b];
-    double ck[16];
+    // C, E and T of this step are next written two barriers (E: one) later,
+    // after every wave has passed the reads below
+    double ea[4];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) ck[q] = colk[buf][a0 + 8 * q];
-    const double ip = 1.0 / pk;
-    const double rip = rk * ip;
-    // the pivot block's FP64 vector work bounds this kernel (one CU per
-    // matrix): the common entries take one FMA, and only row k (held at
-    // q = k / 8 by the threads with a0 = k mod 8) and column k (the threads
-    // of column k) are set apart
-    if (b != k) {
+    for (int st = 0; st < 4; ++st) ea[st] = -Es[(16 * rt + ln) * LD + 4 * st + kq];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) v[q] = v[q] - ck[q] * rip;
-      if ((k & 7) == a0) v[k >> 3] = rip;
-    } else {
+    for (int t = 0; t < 4; ++t) {
+      const int ct = c0 + t;
+      if (rt == kk) {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) v[q] = -ck[q] * ip;
-      if ((k & 7) == a0) v[k >> 3] = ip;
+        for (int v = 0; v < 4; ++v) {
+          const int i = Mfma<double>::row(kq, v);
+          d[t][v] = ct == kk ? -T[i * LD + ln] : Es[(16 * ct + ln) * LD + i];
+        }
+      } else if (ct == kk) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) d[t][v] = Es[(16 * rt + Mfma<double>::row(kq, v)) * LD + ln];
+      } else {
+#pragma unroll
+        for (int st = 0; st < 4; ++st) d[t] = Mfma<double>::mma(ea[st], C[(16 * ct + ln) * LD + 4 * st + kq], d[t]);
+      }
     }
   }
 #pragma unroll
-  for (int q = 0; q < 16; ++q) Di[(size_t)(a0 + 8 * q) * GJ_NB + b] = v[q];
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      Di[(size_t)(16 * rt + Mfma<double>::row(kq, v)) * GJ_NB + 16 * (c0 + t) + ln] = -d[t][v];
 }
 
 struct GjTileSmem {
@@ -242,16 +345,15 @@ struct GjTileSmem {
   double Ys[32][65];   // [reduction index of the chunk][column]
 };
 
-// acc = X Y for the wave's 32 x 32 quarter of a 64 x 64 tile: X is a
-// row-major block with GJ_NB columns (rows beyond xrows read as zero), Y the
-// rows 0 .. GJ_NB-1 of a row-major array with row stride ldy, columns
-// J0 .. J0+63 (zero for rows >= yrows or columns >= ycols); the reduction runs
-// in chunks of 32 through LDS, the next chunk's values loading into
-// registers during the current chunk's MFMA steps.
+// acc = X Y for the wave's 32 x 32 quarter of a 64 x 64 tile: X is a row-major
+// block of 64 rows with row stride ldx (rows from xrows on repeat the last:
+// their results are not used; columns from xcols on read as zero), Y the columns
+// J0 .. J0+63 of a GJ_NB x GJ_NB row-major array; the reduction runs in chunks of
+// 32 through LDS, the next chunk's values loading into registers during the
+// current chunk's MFMA steps.
 __device__ __forceinline__ void gj_tile_product(GjTileSmem& sm, Mfma<double>::acc_t acc[2][2],
-                                                const double* __restrict__ X, int xrows,
-                                                const double* __restrict__ Y, size_t ldy, int yrows, int ycols,
-                                                int J0) {
+                                                const double* __restrict__ X, size_t ldx, int xrows, int xcols,
+                                                const double* __restrict__ Y, int J0) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;
 #pragma unroll
@@ -263,14 +365,14 @@ __device__ __forceinline__ void gj_tile_product(GjTileSmem& sm, Mfma<double>::ac
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int t = tid + 256 * q;
-      const int row = t >> 5, k = t & 31;
-      xr[q] = row < xrows ? X[(size_t)row * GJ_NB + k0 + k] : 0.0;
-      const int ky = t >> 6, c = t & 63;
-      const int r = k0 + ky, j = J0 + c;
-      yr[q] = (r < yrows && j < ycols) ? Y[(size_t)r * ldy + j] : 0.0;
+      const int row = t >> 5, k = k0 + (t & 31);
+      xr[q] = X[(size_t)(row < xrows ? row : xrows - 1) * ldx + (k < xcols ? k : xcols - 1)];
+      xr[q] = k < xcols ? xr[q] : 0.0;
+      yr[q] = Y[(size_t)(k0 + (t >> 6)) * GJ_NB + J0 + (t & 63)];
     }
   };
   load(0);
+#pragma unroll
   for (int k0 = 0; k0 < GJ_NB; k0 += 32) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -294,62 +396,82 @@ __device__ __forceinline__ void gj_tile_product(GjTileSmem& sm, Mfma<double>::ac
   }
 }
 
-// C = S[:, K] and C^T (n x 128 and 128 x n, zero beyond w) for one 64-row
-// tile I, one 64-column half h at a time (tile Kh = K0 + h): I >= Kh holds
-// S_I,Kh; above Kh, S_I,Kh = S_Kh,I^T is read from tile row Kh.  work holds
-// C, C^T and E per matrix.
+// C_I = S_IK of a 64-row tile I outside K: below K the tiles themselves, above it
+// the copy that k_sw_panel_read makes (row stride 128).
+struct SwPanel {
+  const double* p;
+  size_t ld;
+};
+__device__ __forceinline__ SwPanel sw_panel(const double* A, const double* C, int n, int kb, int Ke, int I) {
+  return I >= Ke ? SwPanel{A + (size_t)I * 64 * n + kb, (size_t)n} : SwPanel{C + (size_t)I * 64 * GJ_NB, GJ_NB};
+}
+
+// flags[I]: whether tile I of S_:K outside K has a nonzero (a NaN counts); above K
+// (S_I,Kh = S_Kh,I^T from tile row Kh) the nonzero tiles are turned round into C,
+// n x 128, one 64-column half at a time.
 __global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict__ mats, int n, int kb, int w, int lo,
-                                                       double* __restrict__ work) {
+                                                       double* __restrict__ work, int* __restrict__ flags) {
   __shared__ double Ts[64][65];   // [row of the tile][column of the half]
-  const int I = lo + blockIdx.x, I0 = I * 64;
+  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
+  if (I >= K0 && I < Ke) return;
   const double* A = mats + (size_t)blockIdx.y * n * n;
-  double* C = work + (size_t)blockIdx.y * 3 * n * GJ_NB;
-  double* Ct = C + (size_t)n * GJ_NB;
+  double* C = work + (size_t)blockIdx.y * 2 * n * GJ_NB;
+  int* flag = flags + (size_t)blockIdx.y * ((n + 63) / 64) + I;
   const int tid = threadIdx.x;
-  for (int h = 0; h < 2; ++h) {
-    const int kbh = kb + 64 * h, Kh = kbh / 64;
-    const int wh = w - 64 * h;   // live columns of this half (<= 0: none)
-    if (I >= Kh) {
+  int any = 0;
+  if (I >= Ke) {
+    const int k = kb + ((tid & 127) < w ? tid & 127 : w - 1);
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int t = tid + 256 * q, a = t >> 6, k = t & 63, i = I0 + a;
-        Ts[a][k] = (i < n && k < wh) ? A[(size_t)i * n + kbh + k] : 0.0;
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int t = tid + 256 * q, k = t >> 6, c = t & 63, i = I0 + c;
-        Ts[c][k] = (k < wh && i < n) ? A[(size_t)(kbh + k) * n + i] : 0.0;
-      }
+    for (int q = 0; q < 32; ++q) {
+      const int i = I0 + (tid >> 7) + 2 * q;
+      any |= !(A[(size_t)(i < n ? i : n - 1) * n + k] == 0.0);
     }
+    any = __syncthreads_or(any);
+    if (tid == 0) *flag = any;
+    return;
+  }
+  double x[2][16];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int k = 64 * h + (tid >> 6) + 4 * q;
+      x[h][q] = A[(size_t)(kb + (k < w ? k : w - 1)) * n + I0 + (tid & 63)];
+      x[h][q] = k < w ? x[h][q] : 0.0;
+      any |= !(x[h][q] == 0.0);
+    }
+  any = __syncthreads_or(any);
+  if (tid == 0) *flag = any;
+  if (!any) return;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) Ts[tid & 63][(tid >> 6) + 4 * q] = x[h][q];
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int t = tid + 256 * q, a = t >> 6, k = t & 63, i = I0 + a;
-      if (i < n) C[(size_t)i * GJ_NB + 64 * h + k] = Ts[a][k];
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int t = tid + 256 * q, k = t >> 6, a = t & 63, i = I0 + a;
-      if (i < n) Ct[(size_t)(64 * h + k) * n + i] = Ts[a][k];
+      const int a = (tid >> 6) + 4 * q, k = tid & 63;
+      C[(size_t)(I0 + a) * GJ_NB + 64 * h + k] = Ts[a][k];
     }
     __syncthreads();
   }
 }
 
 // E_I (columns 64 h .. 64 h + 63) = C_I D^{-1} for one 64-row tile I = lo +
-// blockIdx.x outside K (tiles K0 .. Ke - 1)
-__global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ dinv_all, int n, int kb, int Ke, int lo,
-                                                  double* __restrict__ work) {
-  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, h = blockIdx.z;
-  if (I >= K0 && I < Ke) return;   // E_K is not used
+// blockIdx.x outside K (tiles K0 .. Ke - 1) that is not zero
+__global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ mats, const double* __restrict__ dinv_all,
+                                                  int n, int kb, int w, int lo, double* __restrict__ work,
+                                                  const int* __restrict__ flags) {
+  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64, h = blockIdx.z;
+  if ((I >= K0 && I < Ke) || !flags[(size_t)blockIdx.y * ((n + 63) / 64) + I]) return;   // E_K is not used
   __shared__ GjTileSmem sm;
-  const double* C = work + (size_t)blockIdx.y * 3 * n * GJ_NB;
-  double* E = work + (size_t)blockIdx.y * 3 * n * GJ_NB + (size_t)2 * n * GJ_NB;
+  const double* C = work + (size_t)blockIdx.y * 2 * n * GJ_NB;
+  double* E = work + (size_t)blockIdx.y * 2 * n * GJ_NB + (size_t)n * GJ_NB;
   const double* Di = dinv_all + (size_t)blockIdx.y * GJ_NB * GJ_NB;
   const int rows = n - I0 < 64 ? n - I0 : 64;
+  const SwPanel c = sw_panel(mats + (size_t)blockIdx.y * n * n, C, n, kb, Ke, I);
   Mfma<double>::acc_t acc[2][2];
-  gj_tile_product(sm, acc, C + (size_t)I0 * GJ_NB, rows, Di, GJ_NB, GJ_NB, GJ_NB, 64 * h);
+  gj_tile_product(sm, acc, c.p, c.ld, rows, w, Di, 64 * h);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;
 #pragma unroll
@@ -364,80 +486,128 @@ __global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ din
 }
 
 // S_IJ <- S_IJ - E_I C_J^T over the kept tiles I >= J >= lo outside K (tiles K0
-// .. Ke - 1); work-group p takes the (p0 + p)-th tile of the lower triangle in
-// row order (p0 > 0: the rows below K only).  Eight waves per tile, each a 32 x
-// 16 block (two 16 x 16 MFMA tiles), so four waves share each SIMD and hide one
-// another's waits; the reduction runs in chunks of 32 through LDS, the next
-// chunk's values loading into registers during the current chunk's MFMA steps.
-__global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, int n, int kb, int Ke, int lo, int p0,
-                                                   const double* __restrict__ work) {
-  const int p = p0 + blockIdx.x;
-  int I = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
-  while (I * (I + 1) / 2 > p) --I;
-  while ((I + 1) * (I + 2) / 2 <= p) ++I;
-  const int J = lo + p - I * (I + 1) / 2, K0 = kb / 64;
-  I += lo;
-  if ((I >= K0 && I < Ke) || (J >= K0 && J < Ke)) return;
-  __shared__ GjTileSmem sm;
-  const int I0 = I * 64, J0 = J * 64;
-  double* A = mats + (size_t)blockIdx.y * n * n;
-  const double* Ct = work + (size_t)blockIdx.y * 3 * n * GJ_NB + (size_t)n * GJ_NB;
-  const double* E = Ct + (size_t)n * GJ_NB + (size_t)I0 * GJ_NB;
-  const int xrows = n - I0 < 64 ? n - I0 : 64;
+// .. Ke - 1) whose panels are not zero, rows I >= r0 only.  gpm work-groups per
+// matrix share out the pairs of its active tiles in row order; a matrix's
+// work-groups run on one XCD (work-groups go to the eight in turn), whose L2
+// holds its panels.  Both 64 x 128 panels of a pair lie in LDS (133 of its 160
+// KB, E_I kept along a row, rows padded to 130 values so that operand reads meet
+// no bank conflicts), the next pair's panels and tile load into registers during
+// the MFMA steps, and the accumulators start from the old tile.  Bound by the
+// FP64 matrix cores and the turn between pairs: 300 boxes of 55 active pairs
+// take 490 us, 35 TFLOP/s (635 us with loads under lane conditions).
+constexpr int kSwMaxTiles = 1024;   // most 64-row tiles of a swept matrix
+__global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, int n, int kb, int w, int lo, int r0,
+                                                   int gpm, int count, const double* __restrict__ work,
+                                                   const int* __restrict__ flags) {
+  constexpr int LD = GJ_NB + 2;
+  __shared__ double Xs[64 * LD], Ys[64 * LD];
+  __shared__ unsigned short act[kSwMaxTiles];
+  __shared__ int nact, nskip;
+  const int slot = blockIdx.x >> 3, mat = (slot / gpm) * 8 + (blockIdx.x & 7), first = slot % gpm;
+  if (mat >= count) return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;   // rows 32 wr, columns 16 wc
-  // the tile's old values load first, so their trip from memory overlaps the
-  // product (no work-group of this launch writes another's tile, E or C^T)
-  double old[2][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = I0 + 32 * wr + 16 * a + Mfma<double>::row(kq, v);
-      const int j = J0 + 16 * wc + ln;
-      old[a][v] = (i < n && j < n) ? A[(size_t)i * n + j] : 0.0;
+  const int T = (n + 63) / 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
+  if (wave == 0) {   // the active tiles, in order; nskip of them lie above r0
+    int c = 0, sk = 0;
+    for (int i0 = lo; i0 < T; i0 += 64) {
+      const int I = i0 + lane;
+      const bool on = I < T && !(I >= K0 && I < Ke) && flags[(size_t)mat * T + I];
+      const unsigned long long m = __ballot(on);
+      if (on) act[c + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)I;
+      sk += __popcll(__ballot(on && I < r0));
+      c += __popcll(m);
     }
-  Mfma<double>::acc_t acc[2];
-  acc[0] = acc[1] = Mfma<double>::acc_t{0, 0, 0, 0};
-  double xr[4], yr[4];
-  auto load = [&](int k0) {
+    if (lane == 0) {
+      nact = c;
+      nskip = sk;
+    }
+  }
+  __syncthreads();
+  const int pa = nskip * (nskip + 1) / 2, pairs = nact * (nact + 1) / 2 - pa;
+  const int per = (pairs + gpm - 1) / gpm;
+  int p = pa + first * per;
+  const int p1 = p + per < pa + pairs ? p + per : pa + pairs;
+  if (p >= p1) return;
+  double* A = mats + (size_t)mat * n * n;
+  const double* C = work + (size_t)mat * 2 * n * GJ_NB;
+  const double* Ew = C + (size_t)n * GJ_NB;
+  const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;   // rows 32 wr, columns 16 wc
+  const int lr = tid >> 7, lk = tid & 127;   // panel loads: rows lr + 4 q, column lk
+  double xr[16], yr[16], old[2][4];
+  auto load_e = [&](int I) {
+    const double* E = Ew + (size_t)I * 64 * GJ_NB;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int t = tid + 512 * q;
-      const int row = t >> 5, k = t & 31;
-      xr[q] = row < xrows ? E[(size_t)row * GJ_NB + k0 + k] : 0.0;
-      const int ky = t >> 6, c = t & 63, j = J0 + c;
-      yr[q] = j < n ? Ct[(size_t)(k0 + ky) * n + j] : 0.0;
+    for (int q = 0; q < 16; ++q) {
+      const int a = lr + 4 * q;
+      xr[q] = E[(size_t)(I * 64 + a < n ? a : n - 1 - I * 64) * GJ_NB + lk];
     }
   };
-  load(0);
-  for (int k0 = 0; k0 < GJ_NB; k0 += 32) {
+  auto load_c = [&](int J) {
+    // (columns from w on meet the zeros of E)
+    const SwPanel c = sw_panel(A, C, n, kb, Ke, J);
+    const int k = lk < w ? lk : w - 1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int t = tid + 512 * q;
-      sm.Xs[t & 31][t >> 5] = xr[q];
-      sm.Ys[t >> 6][t & 63] = yr[q];
+    for (int q = 0; q < 16; ++q) {
+      const int a = lr + 4 * q;
+      yr[q] = c.p[(size_t)(J * 64 + a < n ? a : n - 1 - J * 64) * c.ld + k];
     }
-    __syncthreads();
-    if (k0 + 32 < GJ_NB) load(k0 + 32);
+  };
+  auto load_old = [&](int I, int J) {
 #pragma unroll
-    for (int st = 0; st < 8; ++st) {
-      const int kk = 4 * st + kq;
-      const double a0 = sm.Xs[kk][32 * wr + ln], a1 = sm.Xs[kk][32 * wr + 16 + ln];
-      const double b0 = sm.Ys[kk][16 * wc + ln];
-      acc[0] = Mfma<double>::mma(a0, b0, acc[0]);
-      acc[1] = Mfma<double>::mma(a1, b0, acc[1]);
-    }
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = 64 * I + 32 * wr + 16 * a + Mfma<double>::row(kq, v), j = 64 * J + 16 * wc + ln;
+        old[a][v] = A[(size_t)(i < n ? i : n - 1) * n + (j < n ? j : n - 1)];
+      }
+  };
+  int ri = (int)((sqrtf(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);   // row and column of pair p among the active
+  while (ri * (ri + 1) / 2 > p) --ri;
+  while ((ri + 1) * (ri + 2) / 2 <= p) ++ri;
+  int rj = p - ri * (ri + 1) / 2;
+  bool fresh = true;   // E of the current row is in registers, not yet in LDS
+  load_e(act[ri]);
+  load_c(act[rj]);
+  load_old(act[ri], act[rj]);
+  for (; p < p1; ++p) {
+    const int I0 = act[ri] * 64, J0 = act[rj] * 64;
+    __syncthreads();   // the last pair's operand reads are done
+    if (fresh)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) Xs[(lr + 4 * q) * LD + lk] = -xr[q];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) Ys[(lr + 4 * q) * LD + lk] = yr[q];
+    Mfma<double>::acc_t acc[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[a][v] = old[a][v];
     __syncthreads();
+    fresh = rj == ri;
+    ri += fresh ? 1 : 0;
+    rj = fresh ? 0 : rj + 1;
+    if (p + 1 < p1) {   // no work-group of this launch writes another's tile, E or C
+      if (fresh) load_e(act[ri]);
+      load_c(act[rj]);
+      load_old(act[ri], act[rj]);
+    }
+    const double* xa = Xs + (32 * wr + ln) * LD + kq;
+    const double* xb = xa + 16 * LD;
+    const double* yb = Ys + (16 * wc + ln) * LD + kq;
+#pragma unroll 8
+    for (int st = 0; st < GJ_NB / 4; ++st) {
+      const double b0 = yb[4 * st];
+      acc[0] = Mfma<double>::mma(xa[4 * st], b0, acc[0]);
+      acc[1] = Mfma<double>::mma(xb[4 * st], b0, acc[1]);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = I0 + 32 * wr + 16 * a + Mfma<double>::row(kq, v), j = J0 + 16 * wc + ln;
+        if (i < n && j < n) A[(size_t)i * n + j] = acc[a][v];
+      }
   }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = I0 + 32 * wr + 16 * a + Mfma<double>::row(kq, v);
-      const int j = J0 + 16 * wc + ln;
-      if (i < n && j < n) A[(size_t)i * n + j] = old[a][v] - acc[a][v];
-    }
 }
 
 // Row and column K of the swept matrix, one 64-row tile I = lo + blockIdx.x per
@@ -445,11 +615,13 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
 // h; above K, S_Kh,I <- that half transposed.
 __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mats, int n, int kb, int w, int lo,
                                                         const double* __restrict__ work,
-                                                        const double* __restrict__ dinv_all) {
+                                                        const double* __restrict__ dinv_all,
+                                                        const int* __restrict__ flags) {
   __shared__ double Ts[64][65];
   const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
+  if (!(I >= K0 && I < Ke) && !flags[(size_t)blockIdx.y * ((n + 63) / 64) + I]) return;   // stays zero
   double* A = mats + (size_t)blockIdx.y * n * n;
-  const double* E = work + (size_t)blockIdx.y * 3 * n * GJ_NB + (size_t)2 * n * GJ_NB;
+  const double* E = work + (size_t)blockIdx.y * 2 * n * GJ_NB + (size_t)n * GJ_NB;
   const double* Di = dinv_all + (size_t)blockIdx.y * GJ_NB * GJ_NB;
   const int tid = threadIdx.x;
   if (I >= K0 && I < Ke) {
@@ -460,16 +632,23 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
       for (int q = 0; q < 16; ++q) {
         const int t = tid + 256 * q, a = t >> 6, b = t & 63;
         const int ra = r0 + a, cb = 64 * h + b;
-        if (ra < w && cb < w) A[(size_t)(kb + ra) * n + kb + cb] = -Di[(size_t)ra * GJ_NB + cb];
+        const double x = -Di[(size_t)ra * GJ_NB + cb];
+        if (ra < w && cb < w) A[(size_t)(kb + ra) * n + kb + cb] = x;
       }
     }
     return;
   }
   if (I >= Ke) {    // S_IK <- E_I
-#pragma unroll 4
+    double x[32];
+#pragma unroll
     for (int q = 0; q < 32; ++q) {
-      const int t = tid + 256 * q, a = t >> 7, k = t & 127, i = I0 + a;
-      if (i < n && k < w) A[(size_t)i * n + kb + k] = E[(size_t)i * GJ_NB + k];
+      const int i = I0 + (tid >> 7) + 2 * q;
+      x[q] = E[(size_t)(i < n ? i : n - 1) * GJ_NB + (tid & 127)];
+    }
+#pragma unroll
+    for (int q = 0; q < 32; ++q) {
+      const int i = I0 + (tid >> 7) + 2 * q;
+      if (i < n && (tid & 127) < w) A[(size_t)i * n + kb + (tid & 127)] = x[q];
     }
     return;
   }
@@ -479,14 +658,14 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
     if (wh <= 0) break;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int t = tid + 256 * q, a = t >> 6, k = t & 63, i = I0 + a;
-      Ts[a][k] = i < n ? E[(size_t)i * GJ_NB + 64 * h + k] : 0.0;
+      const int t = tid + 256 * q, a = t >> 6, k = t & 63;
+      Ts[a][k] = E[(size_t)(I0 + a) * GJ_NB + 64 * h + k];   // above K: whole tiles
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int t = tid + 256 * q, k = t >> 6, c = t & 63, i = I0 + c;
-      if (k < wh && i < n) A[(size_t)(kb + 64 * h + k) * n + i] = Ts[c][k];
+      if (k < wh) A[(size_t)(kb + 64 * h + k) * n + i] = Ts[c][k];
     }
     __syncthreads();
   }
@@ -496,36 +675,48 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
 // too unless the block ends the matrix) within the tiles from lo on; partial:
 // the rows below the block only.
 static void sweep_step(double* mats, int n, int kb, int w, int lo, bool partial, int count, double* work, double* dinv,
-                       hipStream_t s) {
+                       int* flags, hipStream_t s) {
   const int T = (n + 63) / 64, Ke = (kb + w + 63) / 64;
   IBMG_KLAUNCH(k_gj_diag, dim3(count), dim3(1024), 0, s, mats, n, kb, w, dinv);
   IBMG_LAUNCH_CHECK();
-  IBMG_KLAUNCH(k_sw_panel_read, dim3(T - lo, count), dim3(256), 0, s, mats, n, kb, w, lo, work);
+  IBMG_KLAUNCH(k_sw_panel_read, dim3(T - lo, count), dim3(256), 0, s, mats, n, kb, w, lo, work, flags);
   IBMG_LAUNCH_CHECK();
   const int r0 = partial ? Ke : lo;   // first row tile of the scaling and of the panel
   if (T - r0 > 0) {
-    IBMG_KLAUNCH(k_sw_scale, dim3(T - r0, count, 2), dim3(256), 0, s, dinv, n, kb, Ke, r0, work);
+    IBMG_KLAUNCH(k_sw_scale, dim3(T - r0, count, 2), dim3(256), 0, s, mats, dinv, n, kb, w, r0, work, flags);
     IBMG_LAUNCH_CHECK();
-    const int t = T - lo, p0 = partial ? (Ke - lo) * (Ke - lo + 1) / 2 : 0;
-    IBMG_KLAUNCH(k_sw_update, dim3(t * (t + 1) / 2 - p0, count), dim3(512), 0, s, mats, n, kb, Ke, lo, p0, work);
+    // work-groups per matrix (one fits a CU): a pair each for a few matrices,
+    // else enough for six rounds of the device, so that matrices with more
+    // active pairs even out
+    const int t = T - lo, pairs = t * (t + 1) / 2, gpm = std::min(pairs, std::max(4, 1536 / count));
+    IBMG_KLAUNCH(k_sw_update, dim3(gpm * ((count + 7) / 8 * 8)), dim3(512), 0, s, mats, n, kb, w, lo, r0, gpm, count,
+                 work, flags);
     IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_panel_write, dim3(T - r0, count), dim3(256), 0, s, mats, n, kb, w, r0, work, dinv);
+    IBMG_KLAUNCH(k_sw_panel_write, dim3(T - r0, count), dim3(256), 0, s, mats, n, kb, w, r0, work, dinv, flags);
     IBMG_LAUNCH_CHECK();
   }
 }
 
+static int* sweep_flags(double* dinv, int count) {
+  return reinterpret_cast<int*>(dinv + (size_t)count * GJ_NB * GJ_NB);
+}
+
 void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s) {
   if (!count) return;
-  for (int kb = 0; kb < n; kb += GJ_NB) sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, dinv, s);
+  if (n > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
+  for (int kb = 0; kb < n; kb += GJ_NB)
+    sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, dinv, sweep_flags(dinv, count), s);
 }
 
 void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s) {
   if (!count) return;
   if (bm.nnp % 64) throw Error(IBMG_ERR_ARG, "the owned unknowns start at a tile");
+  if (bm.ld > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
+  int* flags = sweep_flags(dinv, count);
   for (int kb = 0; kb < bm.nnp; kb += GJ_NB)
-    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, dinv, s);
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, dinv, flags, s);
   for (int kb = bm.nnp; kb < bm.ld; kb += GJ_NB)
-    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.ld - kb), bm.nnp / 64, false, count, work, dinv, s);
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.ld - kb), bm.nnp / 64, false, count, work, dinv, flags, s);
 }
 
 // The inverse's owned rows at the non-owned columns, M_on = S_oo^{-1} (-W), for
@@ -547,18 +738,32 @@ __global__ void __launch_bounds__(256) k_box_on(double* __restrict__ mats, BoxMa
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = Mfma<double>::acc_t{0, 0, 0, 0};
-  for (int k0 = 0; k0 < nown; k0 += 32) {
+  double xr[8], yr[8];
+  auto load = [&](int k0) {
     const bool below = (k0 >> 6) <= (R0 >> 6);   // the tile (R0, k0) is a kept one
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int t = tid + 256 * q;
-      const int ra = below ? t >> 5 : t & 63, ka = below ? t & 31 : t >> 6;
-      const int r = R0 + ra, k = k0 + ka;
-      sm.Xs[ka][ra] = r < nown && k < nown ? (below ? O[(size_t)r * ld + k] : O[(size_t)k * ld + r]) : 0.0;
+      const int r = R0 + (below ? t >> 5 : t & 63), k = k0 + (below ? t & 31 : t >> 6);
+      const int rc = r < nown ? r : nown - 1, kc = k < nown ? k : nown - 1;
+      xr[q] = O[(size_t)(below ? rc : kc) * ld + (below ? kc : rc)];
+      xr[q] = k < nown ? xr[q] : 0.0;
       const int kb = k0 + (t >> 6), j = J0 + (t & 63);
-      sm.Ys[t >> 6][t & 63] = kb < nown && j < bm.nn ? W[(size_t)kb * ld + j] : 0.0;
+      yr[q] = W[(size_t)(kb < nown ? kb : nown - 1) * ld + (j < bm.nn ? j : bm.nn - 1)];
+    }
+  };
+  load(0);
+#pragma unroll 1
+  for (int k0 = 0; k0 < nown; k0 += 32) {
+    const bool below = (k0 >> 6) <= (R0 >> 6);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int t = tid + 256 * q;
+      sm.Xs[below ? t & 31 : t >> 6][below ? t >> 5 : t & 63] = xr[q];
+      sm.Ys[t >> 6][t & 63] = yr[q];
     }
     __syncthreads();
+    if (k0 + 32 < nown) load(k0 + 32);
 #pragma unroll
     for (int st = 0; st < 8; ++st) {
       const int kk = 4 * st + kq;
@@ -589,12 +794,16 @@ void launch_box_on(double* mats, BoxMat bm, int count, hipStream_t s) {
   IBMG_LAUNCH_CHECK();
 }
 
-// entry (owned row r, local unknown at position q) of an eliminated box's
-// inverse (launch_box_on for q < nnp)
-__device__ __forceinline__ double box_inv_at(const double* A, const BoxMat& bm, int r, int q) {
-  if (q < bm.nnp) return A[(size_t)q * bm.ld + bm.nnp + r];
-  const int i = bm.nnp + r;
-  return -((i >> 6) >= (q >> 6) ? A[(size_t)i * bm.ld + q] : A[(size_t)q * bm.ld + i]);
+// entry (owned position r, owned position q) of an eliminated box's inverse
+__device__ __forceinline__ double box_oo(const double* A, const BoxMat& bm, int r, int q) {
+  const int i = bm.nnp + r, j = bm.nnp + q;
+  return -((i >> 6) >= (j >> 6) ? A[(size_t)i * bm.ld + j] : A[(size_t)j * bm.ld + i]);
+}
+// entry (owned unknown r, local unknown p: non-owned position or nnp + owned
+// unknown) of an eliminated box's inverse (launch_box_on for p < nnp); own: the
+// owned unknowns' positions
+__device__ __forceinline__ double box_inv_at(const double* A, const BoxMat& bm, const unsigned short* own, int r, int p) {
+  return p < bm.nnp ? A[(size_t)p * bm.ld + bm.nnp + own[r]] : box_oo(A, bm, own[r], own[p - bm.nnp]);
 }
 
 // global index of local unknown k of box pid (periodic wrap)
@@ -633,11 +842,11 @@ __device__ __forceinline__ size_t own_glob(const BoxGeom& g, int pid, int r) {
 // Rows of A^{-1}, stored per box as row chunks of 64: element (row, j)
 // at (row / 64) * nloc * 64 + j * 64 + row % 64 (rows beyond nown are 0), so
 // a chunk's 64 rows of one column are contiguous and a chunk is one
-// contiguous stream of nloc * 64 values.  pos = null: every row of a swept
+// contiguous stream of nloc * 64 values.  bo.pos = null: every row of a swept
 // matrix (the summed combination); else the owned rows of an eliminated one.
 template <typename T>
-__global__ void k_extract_rows(const double* __restrict__ mats, int count, BoxGeom g, BoxMat bm,
-                               const int* __restrict__ pos, T* __restrict__ out) {
+__global__ void k_extract_rows(const double* __restrict__ mats, int count, BoxGeom g, BoxMat bm, BoxOrder bo,
+                               T* __restrict__ out) {
   const size_t per = (size_t)g.nch * g.nloc * 64;
   const size_t tot = per * count;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
@@ -650,7 +859,7 @@ __global__ void k_extract_rows(const double* __restrict__ mats, int count, BoxGe
     const double* A = mats + blk * bm.ld * bm.ld;
     T v = 0;
     if (row < g.nown) {
-      if (pos) v = (T)box_inv_at(A, bm, row, pos[j]);
+      if (bo.pos) v = (T)box_inv_at(A, bm, bo.own + blk * g.nown, row, bo.pos[j]);
       else v = (T)(-((row >> 6) >= (j >> 6) ? A[(size_t)row * bm.ld + j] : A[(size_t)j * bm.ld + row]));
     }
     out[t] = v;
@@ -658,12 +867,12 @@ __global__ void k_extract_rows(const double* __restrict__ mats, int count, BoxGe
 }
 
 template <typename T>
-void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, const int* pos, T* out, hipStream_t s) {
+void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, BoxOrder bo, T* out, hipStream_t s) {
   if (!count) return;
   size_t tot = (size_t)g.nch * g.nloc * 64 * count;
   int grid = cdiv(tot, 256);
   if (grid > 16384) grid = 16384;
-  IBMG_KLAUNCH((k_extract_rows<T>), dim3(grid), dim3(256), 0, s, mats, count, g, bm, pos, out);
+  IBMG_KLAUNCH((k_extract_rows<T>), dim3(grid), dim3(256), 0, s, mats, count, g, bm, bo, out);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -707,7 +916,7 @@ __global__ void k_extract_sym(const double* __restrict__ mats, int count, BoxGeo
     while (c + 1 < g.nch && sym_chunk_off(c + 1) <= rem) ++c;
     rem -= sym_chunk_off(c);
     const int q = (int)(rem / 64), row = c * 64 + (int)(rem % 64);
-    out[t] = row < g.nown && q < g.nown ? (T)box_inv_at(mats + blk * bm.ld * bm.ld, bm, row, bm.nnp + q) : T(0);
+    out[t] = row < g.nown && q < g.nown ? (T)box_oo(mats + blk * bm.ld * bm.ld, bm, row, q) : T(0);
   }
 }
 
@@ -721,7 +930,8 @@ void launch_extract_sym(const double* mats, int count, BoxGeom g, BoxMat bm, T* 
   IBMG_LAUNCH_CHECK();
 }
 
-// the W rows of count boxes: rows wptr[i] .. wptr[i+1] of box i, owned row wrow
+// the W rows of count boxes: rows wptr[i] .. wptr[i+1] of box i, owned position
+// wrow
 template <typename T>
 __global__ void k_extract_w(const double* __restrict__ mats, BoxMat bm, const int* __restrict__ wptr,
                             const int* __restrict__ wrow, int ws, T* __restrict__ out) {
@@ -869,8 +1079,8 @@ __global__ void __launch_bounds__(256) k_ras_ib(const T* __restrict__ r, T* __re
                         blockIdx.y, x, part, acc, cb < ce ? cb : ce, ce, pout);
 }
 
-// First pass of the eliminated boxes: y = r_o - W r_n (owned order, y[box slot *
-// nown + row]).  Work-group = (box, RPG of its W rows): each lane keeps its
+// First pass of the eliminated boxes: y = r_o - W r_n (in positions, y[box slot *
+// nown + position]).  Work-group = (box, RPG of its W rows): each lane keeps its
 // share of the box's non-owned residual in registers (CH pairs of columns) and
 // every wave streams its rows, two at a time, 16 bytes a lane and load, summing
 // a row over the wave by DPP.  The rows that couple to nothing outside take
@@ -887,9 +1097,10 @@ __global__ void __launch_bounds__(256) k_ras_w(const T* __restrict__ r, BoxGeom 
   const int e0 = w.wptr[slot], e1 = w.wptr[slot + 1];
   const T* Wm = static_cast<const T*>(w.W);
   T* yb = y + (size_t)slot * g.nown;
+  const unsigned short* ord = w.ord + (size_t)slot * g.nown;
   if (blockIdx.y == 0)
     for (int k = tid; k < g.nown; k += 256)
-      if (!w.coupled[(size_t)slot * g.nown + k]) yb[k] = r[own_glob(g, pid, k)];
+      if (!w.coupled[(size_t)slot * g.nown + k]) yb[k] = r[own_glob(g, pid, ord[k])];
   const int lo = e0 + blockIdx.y * rpg, hi = lo + rpg < e1 ? lo + rpg : e1;
   if (lo >= hi) return;
   extern __shared__ char smem_raw[];
@@ -926,7 +1137,7 @@ __global__ void __launch_bounds__(256) k_ras_w(const T* __restrict__ r, BoxGeom 
     a = wave_sum(a);
     if (lane == 0) {
       const int k = w.wrow[q];
-      yb[k] = r[own_glob(g, pid, k)] - a;
+      yb[k] = r[own_glob(g, pid, ord[k])] - a;
     }
   };
   for (; e < hi; e += 8) {
@@ -1041,7 +1252,8 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ y, Box
 // column sums at r of every later chunk, added in chunk order.
 template <typename T>
 __global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ boxes, int na, int ks,
-                          const T* __restrict__ ps, int ns, int kss, T* __restrict__ z, BoxGeom g, bool acc) {
+                          const T* __restrict__ ps, int ns, int kss, const unsigned short* __restrict__ ord,
+                          T* __restrict__ z, BoxGeom g, bool acc) {
   const int nown_pad = g.nch * 64;
   const size_t tot = (size_t)(ns > 0 ? ns : na) * g.nown;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
@@ -1074,7 +1286,7 @@ __global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ boxe
           if (s0 + j < ks) a += v[j];
       }
     }
-    const size_t o = own_glob(g, boxes[b], row);
+    const size_t o = own_glob(g, boxes[b], ord ? ord[t] : row);
     z[o] = acc ? z[o] + a : a;
   }
 }
@@ -1242,8 +1454,9 @@ __global__ void __launch_bounds__(256 * KS) k_ras_int(const T* __restrict__ r, T
 // the four images' positions of every orbit, rl: the owned row of every row
 // representative.
 template <typename T>
-__global__ void k_extract_classes(const double* __restrict__ mat, BoxMat bm, IntClassView C, const int* __restrict__ kl,
-                                  const int* __restrict__ rl, T* __restrict__ out) {
+__global__ void k_extract_classes(const double* __restrict__ mat, BoxMat bm, const unsigned short* __restrict__ own,
+                                  IntClassView C, const int* __restrict__ kl, const int* __restrict__ rl,
+                                  T* __restrict__ out) {
   const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
     const int rr = (int)(t % 16);
@@ -1254,7 +1467,7 @@ __global__ void k_extract_classes(const double* __restrict__ mat, BoxMat bm, Int
     if (row < C.R && k < C.K) {
       const int lr = rl[row], comp = C.kcode[k] >> 24;
       const int e = kl[4 * k], x = kl[4 * k + 1], y = kl[4 * k + 2], xy = kl[4 * k + 3];
-      auto at = [&](int j) { return box_inv_at(mat, bm, lr, j); };
+      auto at = [&](int j) { return box_inv_at(mat, bm, own, lr, j); };
       const double cx = (comp == 0 ? -1.0 : 1.0) * (cls & 1 ? -1.0 : 1.0), cy = (comp == 1 ? -1.0 : 1.0) * (cls & 2 ? -1.0 : 1.0);
       v = at(e);
       if (x != e) v += cx * at(x);
@@ -1267,16 +1480,18 @@ __global__ void k_extract_classes(const double* __restrict__ mat, BoxMat bm, Int
 }
 
 template <typename T>
-void launch_extract_classes(const double* mat, BoxMat bm, IntClassView C, const int* kl, const int* rl, T* out,
-                            hipStream_t s) {
+void launch_extract_classes(const double* mat, BoxMat bm, const unsigned short* own, IntClassView C, const int* kl,
+                            const int* rl, T* out, hipStream_t s) {
   const size_t tot = (size_t)4 * C.nrt * C.Kp * 16;
   int grid = cdiv(tot, 256);
   if (grid > 4096) grid = 4096;
-  IBMG_KLAUNCH((k_extract_classes<T>), dim3(grid), dim3(256), 0, s, mat, bm, C, kl, rl, out);
+  IBMG_KLAUNCH((k_extract_classes<T>), dim3(grid), dim3(256), 0, s, mat, bm, own, C, kl, rl, out);
   IBMG_LAUNCH_CHECK();
 }
-template void launch_extract_classes<double>(const double*, BoxMat, IntClassView, const int*, const int*, double*, hipStream_t);
-template void launch_extract_classes<float>(const double*, BoxMat, IntClassView, const int*, const int*, float*, hipStream_t);
+template void launch_extract_classes<double>(const double*, BoxMat, const unsigned short*, IntClassView, const int*,
+                                            const int*, double*, hipStream_t);
+template void launch_extract_classes<float>(const double*, BoxMat, const unsigned short*, IntClassView, const int*,
+                                            const int*, float*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Interior tiles of the batched sweep (below): Z[64-row chunk, boxes] = M[chunk,
@@ -1653,7 +1868,8 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
   if (na + ns > 0) {
     int grid = cdiv((size_t)(na + ns) * g.nown, 256);
     if (grid > 4096) grid = 4096;
-    IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, part, ib_boxes, na, ks_ib, spart, ns, ks_sym, z, g, acc);
+    IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, part, ib_boxes, na, ks_ib, spart, ns, ks_sym,
+                 use_sym ? sym->w.ord : nullptr, z, g, acc);
     IBMG_LAUNCH_CHECK();
   }
 }
@@ -2041,8 +2257,8 @@ void launch_coarse_apply(const double* inv, int n0, const T* r, T* z, hipStream_
   launch_coarse_apply_batch<T>(inv, n0, r, z, 1, s);
 }
 
-template void launch_extract_rows<double>(const double*, int, BoxGeom, BoxMat, const int*, double*, hipStream_t);
-template void launch_extract_rows<float>(const double*, int, BoxGeom, BoxMat, const int*, float*, hipStream_t);
+template void launch_extract_rows<double>(const double*, int, BoxGeom, BoxMat, BoxOrder, double*, hipStream_t);
+template void launch_extract_rows<float>(const double*, int, BoxGeom, BoxMat, BoxOrder, float*, hipStream_t);
 template void launch_extract_w<double>(const double*, int, BoxMat, const int*, const int*, int, double*, hipStream_t);
 template void launch_extract_w<float>(const double*, int, BoxMat, const int*, const int*, int, float*, hipStream_t);
 template void launch_asm_apply<double>(const double*, double*, BoxGeom, const double*, const int*, double*,

@@ -520,14 +520,22 @@ double* static_grad_scratch();
 struct BoxMat {
   int ld, nn, nnp;
 };
+// Their order: local unknown k is at position pos[k] < nnp when not owned
+// (nonown lists those), and owned unknown pos[k] - nnp otherwise, which box i
+// puts at nnp + own[i * nown + .] (ord: the inverse, position to owned unknown).
+// pos = null: the local order.
+struct BoxOrder {
+  const int *pos, *nonown;
+  const unsigned short *ord, *own;
+};
 void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoef<double> c,
                            const int* tptr_u, const int* tcol_u, const double* tval_u,
-                           const int* tptr_v, const int* tcol_v, const double* tval_v, const int* pos, BoxMat bm,
+                           const int* tptr_v, const int* tcol_v, const double* tval_v, BoxOrder bo, BoxMat bm,
                            double* mats, hipStream_t s);
 // In-place block sweeps of count symmetric n x n matrices: afterwards the
 // tiles on or below the diagonal (64 x 64, diagonal tiles in full) hold
-// -A^{-1}.  work: count x 3 x n x kGjNb and dinv: count x kGjNb^2 doubles of
-// workspace.
+// -A^{-1}.  work: count x 2 x n x kGjNb doubles of workspace; dinv: count x
+// kGjNb^2 doubles, then an int per matrix and 64 rows.
 void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s);
 constexpr int kGjNb = 128;  // block width of the batched inversion
 // The restricted boxes' elimination: afterwards the rows of the owned unknowns
@@ -537,10 +545,10 @@ constexpr int kGjNb = 128;  // block width of the batched inversion
 void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s);
 void launch_box_on(double* mats, BoxMat bm, int count, hipStream_t s);
 // rows of the inverse in 64-row chunks: the owned rows of eliminated matrices
-// (pos: the local unknowns' positions), or every row of swept ones (pos = null,
-// g.nown = nloc: the summed combination)
+// or every row of swept ones (bo.pos = null, g.nown = nloc: the summed
+// combination)
 template <typename T>
-void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, const int* pos, T* out, hipStream_t s);
+void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, BoxOrder bo, T* out, hipStream_t s);
 // Summed additive Schwarz (IBMG_COMBINE_SUM): every box's whole local
 // solution L_k^{-1} R_k r into Y (box id-major, g.nch chunks of 64 rows; inv
 // holds full inverses, box_inv[box id] the inverse of each box), then every
@@ -549,13 +557,14 @@ void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, co
 template <typename T>
 void launch_asm_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* box_inv, T* Y, hipStream_t s);
 // Eliminated storage of the IB boxes (restricted additive sweep): box i's W rows
-// are rows wptr[i] .. wptr[i+1] of W (row stride ws), for the owned rows wrow;
-// coupled[i * nown + k] marks the owned rows that have one; nloc lists the nn
-// non-owned unknowns' local indices.
+// are rows wptr[i] .. wptr[i+1] of W (row stride ws), for the owned positions
+// wrow; coupled[i * nown + k] marks the positions that have one; ord: the owned
+// unknowns in position order; nloc lists the nn non-owned unknowns' local indices.
 struct WBoxView {
   const void* W;
   const int *wptr, *wrow, *nloc;
   const unsigned char* coupled;
+  const unsigned short* ord;
   int nn, ws, maxrows;
 };
 struct SymIB {
@@ -585,8 +594,8 @@ struct IntClassView {
 // the most orbits a box has (b + 2 o <= 32), padded to whole chunks
 constexpr int kIntMaxOrbits = 896;
 template <typename T>
-void launch_extract_classes(const double* mat, BoxMat bm, IntClassView C, const int* kl, const int* rl, T* out,
-                            hipStream_t s);
+void launch_extract_classes(const double* mat, BoxMat bm, const unsigned short* own, IntClassView C, const int* kl,
+                            const int* rl, T* out, hipStream_t s);
 
 // One restricted Schwarz sweep (parts: bit 0 = IB boxes, bit 1 = interior
 // boxes); acc: add the local solutions to z on the owned sets instead of

@@ -103,6 +103,9 @@ struct Level {
   BoxMat bm{};
   std::vector<int> pos, nonown;
   DBuf<int> d_pos, d_nonown;
+  // per unique box: the owned unknowns by position and back
+  std::vector<unsigned short> ord, own;
+  DBuf<unsigned short> d_ord, d_own;
   // eliminated storage of the IB boxes (restricted additive sweep): the W rows,
   // the symmetric factor, the first pass's result and the per-box partials
   bool use_sym = false;
@@ -633,8 +636,8 @@ class Solver final : public SolverBase {
       lev.bm = BoxMat{nloc, 0, 0};
       return;
     }
-    // matrix positions: the non-owned unknowns in local order (velocities
-    // before pressures), then the owned ones in owned order
+    // matrix positions: the non-owned unknowns around the ring, then the owned
+    // ones (each box orders them, order_boxes)
     lev.pos.assign(nloc, -1);
     lev.nonown.clear();
     const int bb = b * b, nown = lev.g.nown, nu = m * (m + 1);
@@ -646,62 +649,110 @@ class Solver final : public SolverBase {
     }
     for (int k = 0; k < nloc; ++k)
       if (lev.pos[k] < 0) lev.nonown.push_back(k);
+    // the ring's sectors (lines of o cells across it): bottom, right, top, left
+    // strip, each with the corner it ends in; a face belongs to the first
+    // sector of its non-owned cells, faces before cells within a sector
+    auto sector = [&](int i, int j) {
+      if (i < 0 || j < 0 || i >= m || j >= m) return INT_MAX;
+      if (j < o && i < m - o) return i;
+      if (i >= m - o && j < m - o) return m - o + j;
+      if (j >= m - o && i >= o) return 2 * (m - o) + m - 1 - i;
+      if (i < o && j >= o) return 3 * (m - o) + m - 1 - j;
+      return INT_MAX;   // owned
+    };
+    auto key = [&](int k) {
+      if (k < nu) {
+        const int i = k % (m + 1), j = k / (m + 1);
+        return std::array<int, 3>{std::min(sector(i - 1, j), sector(i, j)), 0, k};
+      }
+      if (k < 2 * nu) {
+        const int i = (k - nu) % m, j = (k - nu) / m;
+        return std::array<int, 3>{std::min(sector(i, j - 1), sector(i, j)), 0, k};
+      }
+      return std::array<int, 3>{sector((k - 2 * nu) % m, (k - 2 * nu) / m), 1, k};
+    };
+    std::sort(lev.nonown.begin(), lev.nonown.end(), [&](int p, int q) { return key(p) < key(q); });
     const int nn = (int)lev.nonown.size(), nnp = (nn + 63) / 64 * 64;
     lev.bm = BoxMat{nnp + nown, nn, nnp};
     for (int r = 0; r < nown; ++r) lev.pos[own[r]] = nnp + r;
     for (int k = 0; k < nn; ++k) lev.pos[lev.nonown[k]] = k;
   }
 
-  // The owned rows of every IB box that couple to a non-owned unknown of the
-  // box (the rows of W): rows whose stencil reaches one, and IB rows with a
-  // column on one.  The boxes are shared out over worker threads.
-  void coupled_rows(Level<T>& lev) {
+  // The order of every unique box's owned unknowns in its matrix, and the owned
+  // rows that couple to a non-owned unknown of the box (the rows of W): rows
+  // whose stencil reaches one, and IB rows with a column on one.  Line by line
+  // (x-faces, y-faces, cells) through the uncoupled faces and the cells with
+  // four uncoupled faces, then the coupled faces, then the other cells.  The
+  // boxes are shared out over worker threads.
+  void order_boxes(Level<T>& lev) {
     const BoxGeom& g = lev.g;
     const int N = g.N, NN = N * N, b = g.b, bb = b * b, nown = g.nown, m = g.m;
-    std::vector<unsigned char> edge(nown, 0);   // by the stencil
+    std::vector<unsigned char> edge(nown, 0);   // coupled by the stencil
     for (int r = 0; r < nown; ++r) {
       const int comp = r / bb, i = r % bb % b, j = r % bb / b;
-      if (comp < 2) edge[r] = i == 0 || j == 0 || i == b - 1 || j == b - 1;
-      else edge[r] = i == b - 1 || j == b - 1;
+      edge[r] = i == b - 1 || j == b - 1 || (comp < 2 && g.o > 0 && (i == 0 || j == 0));
     }
-    if (g.o == 0)   // nothing lies beyond the low edges but the far faces do beyond the high ones
-      for (int r = 0; r < nown; ++r) {
-        const int i = r % bb % b, j = r % bb / b;
-        edge[r] = i == b - 1 || j == b - 1;
-      }
-    std::vector<short> fx(NN), fy(NN);
-    for (int q = 0; q < NN; ++q) {
-      fx[q] = (short)(q % N);
-      fy[q] = (short)(q / N);
-    }
-    lev.coupled.assign((size_t)lev.n_ib * nown, 0);
+    lev.coupled.assign((size_t)lev.n_unique * nown, 0);
+    lev.ord.resize((size_t)lev.n_unique * nown);
+    lev.own.resize((size_t)lev.n_unique * nown);
     std::atomic<int> next{0};
     auto worker = [&]() {
-      for (int s = next++; s < lev.n_ib; s = next++) {
-        const int pid = lev.ib_list[s], ox = pid % g.npd * b, oy = pid / g.npd * b;
-        unsigned char* cp = lev.coupled.data() + (size_t)s * nown;
-        for (int r = 0; r < nown; ++r) {
-          cp[r] = edge[r];
-          if (cp[r] || r >= 2 * bb) continue;
-          const CompFoot& f = lev.f[r / bb];
-          const int q = (oy + r % bb / b) * N + ox + r % bb % b;
-          for (int k = f.tptr[q]; k < f.tptr[q + 1]; ++k) {
-            const int comp = f.tcol[k] >= NN ? 1 : 0, c = f.tcol[k] - comp * NN;
-            int li = fx[c] - ox, lj = fy[c] - oy;   // from the owned corner
-            if (li >= 0 && li < b && lj >= 0 && lj < b) continue;   // owned
-            li += g.o;
-            lj += g.o;
-            li = li < 0 ? li + N : (li >= N ? li - N : li);
-            lj = lj < 0 ? lj + N : (lj >= N ? lj - N : lj);
-            if (comp == 0 ? (li <= m && lj < m) : (li < m && lj <= m)) {
-              cp[r] = 1;
-              break;
+      std::vector<unsigned char> cp(nown), late(nown);
+      for (int s = next++; s < lev.n_unique; s = next++) {
+        cp = edge;
+        if (s < lev.n_ib) {   // the last unique box may be the interior one: no IB rows
+          const int pid = lev.ib_list[s], ox = pid % g.npd * b, oy = pid / g.npd * b;
+          for (int r = 0; r < 2 * bb; ++r) {
+            if (cp[r]) continue;
+            const CompFoot& f = lev.f[r / bb];
+            const int q = (oy + r % bb / b) * N + ox + r % bb % b;
+            for (int k = f.tptr[q]; k < f.tptr[q + 1]; ++k) {
+              const int comp = f.tcol[k] >= NN ? 1 : 0, c = f.tcol[k] - comp * NN;
+              int lj = c / N, li = c - lj * N - ox;   // from the owned corner
+              lj -= oy;
+              if (li >= 0 && li < b && lj >= 0 && lj < b) continue;   // owned
+              li += g.o;
+              lj += g.o;
+              li = li < 0 ? li + N : (li >= N ? li - N : li);
+              lj = lj < 0 ? lj + N : (lj >= N ? lj - N : lj);
+              if (comp == 0 ? (li <= m && lj < m) : (li < m && lj <= m)) {
+                cp[r] = 1;
+                break;
+              }
             }
           }
         }
+        late = cp;
+        for (int j = 0; j < b; ++j)
+          for (int i = 0; i < b; ++i) {
+            const int q = j * b + i;
+            late[2 * bb + q] = i == b - 1 || j == b - 1 || cp[q] || cp[q + 1] || cp[bb + q] || cp[bb + q + b];
+          }
+        unsigned short *ord = lev.ord.data() + (size_t)s * nown, *own = lev.own.data() + (size_t)s * nown;
+        unsigned char* cpos = lev.coupled.data() + (size_t)s * nown;
+        int p = 0;
+        auto take = [&](int comp0, int comp1, int which) {
+          for (int j = 0; j < b; ++j)
+            for (int comp = comp0; comp < comp1; ++comp)
+              for (int i = 0; i < b; ++i) {
+                const int r = comp * bb + j * b + i;
+                if (late[r] != which) continue;
+                ord[p] = (unsigned short)r;
+                own[r] = (unsigned short)p;
+                cpos[p++] = cp[r];
+              }
+        };
+        take(0, 3, 0);
+        take(0, 2, 1);
+        take(2, 3, 1);
       }
     };
-    run_workers(worker, (size_t)lev.n_ib / 4 + 1);
+    run_workers(worker, (size_t)lev.n_unique * nown / 16384 + 1);
+  }
+
+  // The rows of W of a level's IB boxes (order_boxes done).
+  void list_w_rows(Level<T>& lev) {
+    const int nown = lev.g.nown;
     lev.wptr.assign(1, 0);
     lev.wrow.clear();
     lev.w_max = 0;
@@ -1097,7 +1148,8 @@ class Solver final : public SolverBase {
   }
 
   // doubles of the sweeps' workspace for cnt matrices of n unknowns
-  static size_t sweep_work(size_t n, size_t cnt) { return cnt * (3 * n * kGjNb + (size_t)kGjNb * kGjNb); }
+  static size_t sweep_work(size_t n, size_t cnt) { return cnt * 2 * n * kGjNb + sweep_dinv(n, cnt); }
+  static size_t sweep_dinv(size_t n, size_t cnt) { return cnt * ((size_t)kGjNb * kGjNb + (n + 127) / 128); }
 
   // Springs shorter than their rest length (tangent model): the velocity
   // blocks may be indefinite, so the coarsest elimination pivots.
@@ -1157,7 +1209,7 @@ class Solver final : public SolverBase {
       launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
     } else {
       double* work = aug.p + mat;
-      launch_gj_invert(aug.p, n0_, 1, work, work + 3 * (size_t)n0_ * kGjNb, side_);
+      launch_gj_invert(aug.p, n0_, 1, work, work + 2 * (size_t)n0_ * kGjNb, side_);
       launch_coarse_extract_sym(aug.p, N, sh, inv0_.p, side_);
     }
     IBMG_HIP(hipEventRecord(ev_join_, side_));
@@ -1218,7 +1270,11 @@ class Solver final : public SolverBase {
       v.kcode = lev.d_kcode.p;
       v.rcode = lev.d_rcode.p;
     }
+    order_boxes(lev);
     lev.d_pos.upload(lev.pos, s);
+    lev.d_nonown.upload(lev.nonown, s);
+    lev.d_ord.upload(lev.ord, s);
+    lev.d_own.upload(lev.own, s);
     // A single system keeps the IB boxes eliminated (three short launches over
     // fewer bytes) where the whole rows that one launch of the sweep reads (all
     // boxes, or a colour's) take at least 96 MiB.  Kernel times, eliminated
@@ -1233,8 +1289,7 @@ class Solver final : public SolverBase {
                   (size_t)per_launch * box_stride(lev) * sizeof(T) >= kElimMinBytes &&
                   std::getenv("IBMG_NO_SYM") == nullptr;
     if (lev.use_sym) {
-      coupled_rows(lev);
-      lev.d_nonown.upload(lev.nonown, s);
+      list_w_rows(lev);
       lev.d_wptr.upload(lev.wptr, s);
       lev.d_wrow.upload(lev.wrow, s);
       lev.d_coupled.upload(lev.coupled, s);
@@ -1246,12 +1301,20 @@ class Solver final : public SolverBase {
     lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
   }
 
+  // the box matrices' order from unique box u0 on
+  BoxOrder order_of(Level<T>& lev, int u0) {
+    if (lev.sum_mode) return BoxOrder{};
+    return BoxOrder{lev.d_pos.p, lev.d_nonown.p, lev.d_ord.p + (size_t)u0 * lev.g.nown,
+                    lev.d_own.p + (size_t)u0 * lev.g.nown};
+  }
+
   // the eliminated storage from IB box i0 on
   SymIB sym_of(Level<T>& lev, int i0) {
     if (!lev.use_sym) return SymIB{};
     return SymIB{lev.inv_sym.p + (size_t)i0 * sym_box_stride(lev.g), lev.sym_part.p,
                  WBoxView{lev.wmat.p, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
-                          lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.bm.nn, lev.w_stride, lev.w_max},
+                          lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.d_ord.p + (size_t)i0 * lev.g.nown, lev.bm.nn,
+                          lev.w_stride, lev.w_max},
                  lev.sym_y.p};
   }
 
@@ -1288,8 +1351,8 @@ class Solver final : public SolverBase {
       const size_t cap = std::min<size_t>(std::max<size_t>(1, budget / per), 512);
       const size_t nbatch = (items.size() + cap - 1) / cap;
       const int batch = (int)((items.size() + nbatch - 1) / nbatch);
-      DBuf<double> mats((size_t)batch * n * n), work(3 * (size_t)batch * n * kGjNb),
-          dinv((size_t)batch * kGjNb * kGjNb);
+      DBuf<double> mats((size_t)batch * n * n), work(2 * (size_t)batch * n * kGjNb),
+          dinv(sweep_dinv(n, batch));
       for (size_t b0 = 0; b0 < items.size(); b0 += batch) {
         const int cnt = (int)std::min<size_t>(batch, items.size() - b0);
         // runs of one level with consecutive unique indices
@@ -1305,8 +1368,8 @@ class Solver final : public SolverBase {
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
           launch_patch_assemble(ids[l].p + u0, count, lev.g, lev.cd, lev.f[0].d_tptr.p, lev.f[0].d_tcol.p,
-                                lev.f[0].tval.p, lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p, lev.d_pos.p,
-                                bm, mats.p + slot * n * n, s);
+                                lev.f[0].tval.p, lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p,
+                                order_of(lev, u0), bm, mats.p + slot * n * n, s);
         });
         if (bm.nnp) launch_box_eliminate(mats.p, bm, cnt, work.p, dinv.p, s);
         else launch_gj_invert(mats.p, n, cnt, work.p, dinv.p, s);
@@ -1320,10 +1383,11 @@ class Solver final : public SolverBase {
           if (bm.nnp) launch_box_on(m0 + (size_t)nsym * n * n, bm, count - nsym, s);
           const int c0 = std::max(u0, inv_base(lev)), c1 = std::min(u0 + count, inv_end(lev));
           if (c1 > c0)
-            launch_extract_rows<T>(m0 + (size_t)(c0 - u0) * n * n, c1 - c0, lev.g, bm, lev.d_pos.p,
+            launch_extract_rows<T>(m0 + (size_t)(c0 - u0) * n * n, c1 - c0, lev.g, bm, order_of(lev, c0),
                                    lev.inv.p + (size_t)(c0 - inv_base(lev)) * box_stride(lev), s);
           if (has_classes(lev) && u0 + count > lev.n_ib)
-            launch_extract_classes<T>(m0 + (size_t)(lev.n_ib - u0) * n * n, bm, lev.clsv, lev.d_klocal.p,
+            launch_extract_classes<T>(m0 + (size_t)(lev.n_ib - u0) * n * n, bm,
+                                      lev.d_own.p + (size_t)lev.n_ib * lev.g.nown, lev.clsv, lev.d_klocal.p,
                                       lev.d_rlocal.p, lev.cls.p, s);
           if (nsym > 0) {
             launch_extract_sym<T>(m0, nsym, lev.g, bm, lev.inv_sym.p + (size_t)u0 * sym_box_stride(lev.g), s);
