@@ -315,11 +315,11 @@ ibmg_status ibmg_sc_info(const ibmg_handle* h, int32_t level, double* lam, int32
  * *avg_ms with the kernel's algorithmic bytes and flops per launch (nullable
  * outputs).  Kernels:
  *   IBMG_KERNEL_RAS_IB        Schwarz boxes with their own matrix: whole rows
- *                             (k_ras_ib), n_ib (nown nloc + nloc + nown) values, 2
+ *                             (k_ras_rows), n_ib (nown nloc + nloc + nown) values, 2
  *                             n_ib nown nloc flops; or, on levels with many, the
  *                             elimination's two factors (k_ras_w, k_ras_ib_sym and
  *                             the sums), their stored values
- *   IBMG_KERNEL_RAS_INTERIOR  interior boxes on the matrix cores (k_ras_int,
+ *   IBMG_KERNEL_RAS_INTERIOR  interior boxes on the matrix cores (k_ras_rows,
  *                             the shared inverse split by the box's two
  *                             reflections): the four class matrices once plus
  *                             n_int (nloc + nown) values, 2 n_int 4 R K flops (R

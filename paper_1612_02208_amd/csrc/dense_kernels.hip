@@ -1062,99 +1062,120 @@ __device__ __forceinline__ void ras_ib_chunk(const T* __restrict__ r, T* __restr
   }
 }
 
-// grid (boxes, row chunks, column slices); with more than one slice the
-// slices' row sums go to spart[((slice * n_ib + box) * nch + chunk) * 64 + row]
-template <typename T>
-__global__ void __launch_bounds__(256) k_ras_ib(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                const T* __restrict__ inv, const int* __restrict__ boxes, bool acc,
-                                                T* __restrict__ spart) {
-  extern __shared__ char smem_raw[];
-  T* x = reinterpret_cast<T*>(smem_raw);
-  T* part = x + ((g.nloc + 3) & ~3);
-  const int slot = blockIdx.x, ks = gridDim.z;
-  const int cs = ((g.nloc + ks - 1) / ks + 63) / 64 * 64;
-  const int cb = blockIdx.z * cs, ce = cb + cs < g.nloc ? cb + cs : g.nloc;
-  T* pout = ks > 1 ? spart + (((size_t)blockIdx.z * gridDim.x + slot) * g.nch + blockIdx.y) * 64 : nullptr;
-  ras_ib_chunk<T, true>(r, z, g, inv + ((size_t)slot * g.nch + blockIdx.y) * g.nloc * 64, boxes[slot],
-                        blockIdx.y, x, part, acc, cb < ce ? cb : ce, ce, pout);
+// Rows rsub R .. (R = 64 / RS) of one (box, 64-row chunk) item, whole columns, by
+// NW waves: a wave streams batches of eight 16-byte loads a lane (CP columns of R
+// rows side by side per load), the next batch loading during the current one's
+// sums and the first before the residual gather.  RS > 1 spreads few boxes over
+// the device: a chunk's rows split between work-groups need no partial sums.
+constexpr int kRowsPad = 128;   // zeros behind the gathered residual: batches run past nloc
+template <typename T, int NW, int RS>
+__device__ __forceinline__ void ras_rows_block(const T* __restrict__ r, T* __restrict__ z, const BoxGeom& g,
+                                               const T* __restrict__ Mc, int pid, int chunk, int rsub, T* x, T* part,
+                                               bool acc_mode) {
+  using V = typename Vec16<T>::type;
+  constexpr int VEC = Vec16<T>::n, R = 64 / RS, LPC = R / VEC, CP = 64 / LPC, UNR = 8, B = UNR * CP;
+  static_assert(B <= kRowsPad, "a batch reads at most the padding");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cph = lane / LPC, rl = (lane % LPC) * VEC, n = g.nloc;
+  Mc += rsub * R + rl;
+  V m0[UNR];
+  auto load = [&](int jb) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int j = jb + cph + u * CP;
+      m0[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(j < n ? j : n - 1) * 64));
+    }
+  };
+  int jb = wave * B;
+  if (jb < n) load(jb);
+  for (int k = tid; k < n + kRowsPad; k += 64 * NW) x[k] = k < n ? r[box_glob(g, pid, k)] : T(0);
+  __syncthreads();
+  T acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0;
+  for (; jb < n; jb += NW * B) {
+    V m[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) m[u] = m0[u];
+    if (jb + NW * B < n) load(jb + NW * B);
+    T xv[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) xv[u] = x[jb + cph + u * CP];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      T t[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) t[u] = m[u][v] * xv[u];
+      acc[v] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    }
+  }
+  // the column phases, then the waves
+#pragma unroll
+  for (int off = 32; off >= LPC; off >>= 1)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] += __shfl_down(acc[v], off, 64);
+  if (lane < LPC)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) part[wave * R + rl + v] = acc[v];
+  __syncthreads();
+  const int row = chunk * 64 + rsub * R + tid;
+  if (tid < R && row < g.nown) {
+    T a = 0;
+#pragma unroll
+    for (int q = 0; q < NW; q += 2) a += part[q * R + tid] + part[(q + 1) * R + tid];
+    const size_t o = own_glob(g, pid, row);
+    z[o] = acc_mode ? z[o] + a : a;
+  }
 }
 
-// First pass of the eliminated boxes: y = r_o - W r_n (in positions, y[box slot *
-// nown + position]).  Work-group = (box, RPG of its W rows): each lane keeps its
-// share of the box's non-owned residual in registers (CH pairs of columns) and
-// every wave streams its rows, two at a time, 16 bytes a lane and load, summing
-// a row over the wave by DPP.  The rows that couple to nothing outside take
-// y = r_o; the box's first work-group writes them.  Bound by HBM.  With the
-// second pass and the sum, the 172 boxes of the 512^2 annulus (16 x 16/4, 810
-// MB) take 153 us in FP64 and 81 us in FP32; the one-pass product of the owned
-// rows with symmetric owned tiles took 226 and 116 us (1.5 GB).
-template <typename T, int CH>
-__global__ void __launch_bounds__(256) k_ras_w(const T* __restrict__ r, BoxGeom g, const int* __restrict__ boxes,
-                                               WBoxView w, int rpg, T* __restrict__ y) {
+// First pass of the eliminated boxes: t = W r_n for the rows [lo, hi) of W (box
+// slot's rows; t by position).  Each lane keeps its share of the box's non-owned
+// residual in registers (CH 16-byte groups of columns) and every wave streams its
+// rows, 16 bytes a lane and load, the next row loading during the current one's
+// sum over the wave.
+template <typename T, int CH, int NW>
+__device__ __forceinline__ void ras_w_block(const T* __restrict__ r, const BoxGeom& g, int pid, const WBoxView& w,
+                                            int lo, int hi, T* __restrict__ t, T* xs) {
   using V = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
-  const int slot = blockIdx.x, pid = boxes[slot], tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int e0 = w.wptr[slot], e1 = w.wptr[slot + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const T* Wm = static_cast<const T*>(w.W);
-  T* yb = y + (size_t)slot * g.nown;
-  const unsigned short* ord = w.ord + (size_t)slot * g.nown;
-  if (blockIdx.y == 0)
-    for (int k = tid; k < g.nown; k += 256)
-      if (!w.coupled[(size_t)slot * g.nown + k]) yb[k] = r[own_glob(g, pid, ord[k])];
-  const int lo = e0 + blockIdx.y * rpg, hi = lo + rpg < e1 ? lo + rpg : e1;
-  if (lo >= hi) return;
-  extern __shared__ char smem_raw[];
-  T* xs = reinterpret_cast<T*>(smem_raw);
-  // the wave's first rows are issued before the residual gather
-  auto load = [&](V (&m)[CH], int e) {
+  V m[CH], nx[CH];
+  int pos = 0, npos = 0;
+  auto load = [&](int e) {
+    npos = w.wrow[e];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int j = (c * 64 + lane) * VEC;
-      if (j < w.ws) m[c] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Wm + (size_t)e * w.ws + j));
-      else m[c] = V{};
+      nx[c] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Wm + (size_t)e * w.ws + (j < w.ws ? j : 0)));
     }
   };
-  V m0[CH], m1[CH];
-  int e = lo + 2 * wave;
-  if (e < hi) load(m0, e);
-  if (e + 1 < hi) load(m1, e + 1);
-  for (int k = tid; k < w.ws; k += 256) xs[k] = k < w.nn ? r[box_glob(g, pid, w.nloc[k])] : T(0);
+  int e = lo + wave;
+  if (e < hi) load(e);
+  for (int k = tid; k < CH * 64 * VEC; k += 64 * NW) xs[k] = k < w.nn ? r[box_glob(g, pid, w.nloc[k])] : T(0);
   __syncthreads();
-  T x[CH * VEC];
+  V x[CH];   // zero where a lane's columns end: its repeated loads count nothing
 #pragma unroll
   for (int c = 0; c < CH; ++c)
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      const int j = (c * 64 + lane) * VEC + v;
-      x[c * VEC + v] = j < w.ws ? xs[j] : T(0);
-    }
-  auto row = [&](const V (&m)[CH], int q) {
+    for (int v = 0; v < VEC; ++v) x[c][v] = xs[(c * 64 + lane) * VEC + v];
+  for (; e < hi; e += NW) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) m[c] = nx[c];
+    pos = npos;
+    if (e + NW < hi) load(e + NW);
     T a = 0;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) a += m[c][v] * x[c * VEC + v];
+      for (int v = 0; v < VEC; ++v) a += m[c][v] * x[c][v];
     a = wave_sum(a);
-    if (lane == 0) {
-      const int k = w.wrow[q];
-      yb[k] = r[own_glob(g, pid, ord[k])] - a;
-    }
-  };
-  for (; e < hi; e += 8) {
-    V n0[CH], n1[CH];
-    if (e + 8 < hi) load(n0, e + 8);
-    if (e + 9 < hi) load(n1, e + 9);
-    row(m0, e);
-    if (e + 1 < hi) row(m1, e + 1);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      m0[c] = n0[c];
-      m1[c] = n1[c];
-    }
+    if (lane == 0) t[pos] = a;
   }
 }
 
-// Second pass, z_o = Q y: work-group = (box, 64-row chunk c, column slice),
+// Second pass, z_o = Q y with y = r_o - t on the coupled rows and r_o on the
+// others: work-group = (box, 64-row chunk c, column slice),
 // longest chunks first.  The chunk's stored columns are cut into gridDim.z
 // slices of whole 64-column tiles; a slice's columns stream in batches of UNR x
 // VEC (16-byte loads, eight in flight per lane), batches dealt to the four waves
@@ -1165,8 +1186,9 @@ __global__ void __launch_bounds__(256) k_ras_w(const T* __restrict__ r, BoxGeom 
 // the chunk's row sums per slice at sym_part_off(c, ks), its column sums after
 // them (each column in one slice).
 template <typename T>
-__global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ y, BoxGeom g, const T* __restrict__ inv,
-                                                    T* __restrict__ part) {
+__global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, const T* __restrict__ t, BoxGeom g,
+                                                    const int* __restrict__ boxes, WBoxView w,
+                                                    const T* __restrict__ inv, T* __restrict__ part) {
   using V = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
   constexpr int LPC = 64 / VEC;   // lanes per column
@@ -1198,7 +1220,12 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ y, Box
       m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jb + cph + u * VEC) * 64));
   };
   if (jb0 < ce) load(m0, jb0);
-  for (int k = tid; k < ncol; k += 256) xs[k] = k < g.nown ? y[(size_t)slot * g.nown + k] : T(0);
+  const int pid = boxes[slot];
+  for (int k = tid; k < ncol; k += 256) {
+    const size_t at = (size_t)slot * g.nown + (k < g.nown ? k : 0);
+    const T ro = r[own_glob(g, pid, w.ord[at])], tk = t[at];
+    xs[k] = k < g.nown ? (w.coupled[at] ? ro - tk : ro) : T(0);
+  }
   __syncthreads();
   T xr[VEC];   // this lane's rows' values (owned rows 64 c + rl + v)
 #pragma unroll
@@ -1244,60 +1271,38 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ y, Box
   for (int q = cb + tid; q < (ce < ntr ? ce : ntr); q += 256) pb[64 * ks + q] = tcol[q];
 }
 
-// z[owned rows] (=, or += with acc) from the partial sums of one sweep's IB
-// launch.  Split chunked form (na boxes in ks slices): slice sl of box b holds
-// row `row` at pa[(sl * na + b) * nch * 64 + row], added in slice order.
-// Symmetric form (ps: partials of ns boxes, kss column slices): owned row
-// r = 64 c + i is chunk c's row sums i of its slices, in slice order, plus the
-// column sums at r of every later chunk, added in chunk order.
+// z[owned rows] (=, or += with acc) from the partials of ns eliminated boxes, ks
+// column slices: the owned unknown at position r = 64 c + i is chunk c's row sums
+// i of its slices, in slice order, plus the column sums at r of every later
+// chunk, added in chunk order.
 template <typename T>
-__global__ void k_ras_sum(const T* __restrict__ pa, const int* __restrict__ boxes, int na, int ks,
-                          const T* __restrict__ ps, int ns, int kss, const unsigned short* __restrict__ ord,
-                          T* __restrict__ z, BoxGeom g, bool acc) {
-  const int nown_pad = g.nch * 64;
-  const size_t tot = (size_t)(ns > 0 ? ns : na) * g.nown;
+__global__ void k_ras_sum(const T* __restrict__ ps, const int* __restrict__ boxes, int ns, int ks,
+                          const unsigned short* __restrict__ ord, T* __restrict__ z, BoxGeom g, bool acc) {
+  const size_t tot = (size_t)ns * g.nown;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
     const int b = (int)(t / g.nown), row = (int)(t % g.nown);
-    T a = 0;
-    if (ns > 0) {
-      const int cr = row >> 6;
-      const T* pp = ps + (size_t)b * sym_part_off(g.nch, kss);
-      const T* pr = pp + sym_part_off(cr, kss) + (row & 63);
-      // the row's kss slice sums, then the later chunks' column sums: read
-      // eight at a time, added one by one in that order
-      const int m = kss + (g.nch - cr - 1);
-      auto val = [&](int i) { return i < kss ? pr[64 * i] : pp[sym_part_off(cr + 1 + i - kss, kss) + 64 * kss + row]; };
-      a = pr[0];
-      for (int i0 = 1; i0 < m; i0 += 8) {
-        T v[8];
+    const size_t o = own_glob(g, boxes[b], ord[t]);
+    const int cr = row >> 6;
+    const T* pp = ps + (size_t)b * sym_part_off(g.nch, ks);
+    const T* pr = pp + sym_part_off(cr, ks) + (row & 63);
+    // the row's ks slice sums, then the later chunks' column sums: read eight
+    // at a time (past the end the first again), added one by one in that order
+    const int m = ks + (g.nch - cr - 1);
+    auto val = [&](int i) {
+      const T* p = i < ks ? pr + 64 * i : pp + sym_part_off(cr + 1 + i - ks, ks) + 64 * ks + row;
+      return *(i < m ? p : pr);
+    };
+    T a = pr[0];
+    for (int i0 = 1; i0 < m; i0 += 8) {
+      T v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = i0 + j < m ? val(i0 + j) : T(0);
+      for (int j = 0; j < 8; ++j) v[j] = val(i0 + j);
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (i0 + j < m) a += v[j];
-      }
-    } else {
-      for (int s0 = 0; s0 < ks; s0 += 8) {
-        T v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = s0 + j < ks ? pa[((size_t)(s0 + j) * na + b) * nown_pad + row] : T(0);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (s0 + j < ks) a += v[j];
-      }
+      for (int j = 0; j < 8; ++j)
+        if (i0 + j < m) a += v[j];
     }
-    const size_t o = own_glob(g, boxes[b], ord ? ord[t] : row);
     z[o] = acc ? z[o] + a : a;
   }
-}
-
-// Column slices of the IB-box kernel: enough work-groups to cover the
-// device (>= 1024) while every slice keeps at least 128 columns.
-int ras_ib_ksplit(const BoxGeom& g, int n_ib) {
-  if (n_ib <= 0) return 1;
-  int ks = 1;
-  while (ks < 16 && n_ib * g.nch * ks < 1024 && g.nloc / (2 * ks) >= 128) ks *= 2;
-  return ks;
 }
 
 // ---------------------------------------------------------------------------
@@ -1329,17 +1334,23 @@ int ras_ib_ksplit(const BoxGeom& g, int n_ib) {
 // sum launch; 188 boxes 16.5 against 31; 896 boxes of 8 x 8/2 6.7 against 22.
 // ---------------------------------------------------------------------------
 template <typename T, int KS>
-__global__ void __launch_bounds__(256 * KS) k_ras_int(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                      IntClassView C, const int* __restrict__ boxes, int nlist,
-                                                      bool acc_mode) {
+struct RasIntSmem {
+  T Xs[4][64 * KS][17];   // [class][orbit of the chunk][box]
+  int bid[16];
+  int kcode[kIntMaxOrbits];
+};
+template <typename T, int KS>
+__device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __restrict__ r, T* __restrict__ z,
+                                              const BoxGeom& g, const IntClassView& C, const int* __restrict__ boxes,
+                                              int nlist, int bt, int rt, bool acc_mode) {
   constexpr int KC = 64 * KS, NT = 256 * KS, GPT = 4, AS = 16;
   using acc_t = typename Mfma<T>::acc_t;
-  __shared__ T Xs[4][KC][17];   // [class][orbit of the chunk][box]
-  __shared__ int bid[16];
-  __shared__ int kcode[kIntMaxOrbits];
+  auto& Xs = sm.Xs;
+  int *bid = sm.bid, *kcode = sm.kcode;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kq = lane >> 4, bl = lane & 15;
   const int cls = wave & 3, kp = (wave >> 2) * 64;   // the wave's class and part of the chunk
-  const int bt = blockIdx.x * 16, rt = blockIdx.y, N = g.N, m = g.m, nn = N * N;
+  const int N = g.N, m = g.m, nn = N * N;
+  bt *= 16;
   if (tid < 16) bid[tid] = bt + tid < nlist ? boxes[bt + tid] : -1;
   for (int k = tid; k < C.Kp; k += NT) kcode[k] = k < C.K ? C.kcode[k] : -1;
   // a thread's orbit within a chunk and its four boxes are fixed, the boxes
@@ -1449,6 +1460,53 @@ __global__ void __launch_bounds__(256 * KS) k_ras_int(const T* __restrict__ r, T
     if (own & 8) put(mi, mj, sx * sy * (d - e));
   }
 }
+
+// One launch of the sweep: the first nib work-groups take the IB boxes (whole
+// rows: box, chunk and row part; or the eliminated boxes' W pass: box and rpg rows
+// of W), the others the interior ones (box tile and row tile).  The two kinds
+// share nothing but r, and one launch lets the interior work-groups' gathers and
+// MFMAs run under the IB boxes' streaming; splitting a chunk's rows instead of its
+// columns needs no sum.  A coarse level's application is bound by its chain of
+// latencies: 28 + 36 boxes of 8 x 8/2 9 us as one launch against 20 as three
+// (rows, interior, sum); V-cycle at 64^2 274 -> 225 us.
+template <typename T, int KS, int RS>
+__global__ void __launch_bounds__(256 * KS) k_ras_rows(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
+                                                       const T* __restrict__ inv, const int* __restrict__ ib_boxes,
+                                                       int nib, IntClassView C, const int* __restrict__ int_boxes,
+                                                       int n_int, bool acc) {
+  __shared__ RasIntSmem<T, KS> sm;
+  const int p = blockIdx.x;
+  if (p < nib) {
+    const int item = p / RS, slot = item / g.nch, chunk = item % g.nch;
+    T* x = &sm.Xs[0][0][0];
+    ras_rows_block<T, 4 * KS, RS>(r, z, g, inv + (size_t)item * g.nloc * 64, ib_boxes[slot], chunk, p % RS, x,
+                                  x + g.nloc + kRowsPad, acc);
+  } else {
+    const int q = p - nib, nt = (n_int + 15) / 16;
+    ras_int_block<T, KS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
+  }
+}
+// the rows' residual, its padding and the waves' sums fit in Xs
+static_assert(4 * 64 * 17 >= kMaxNloc + kRowsPad + 4 * 64 && 4 * 128 * 17 >= kMaxNloc + kRowsPad + 8 * 64, "");
+
+template <typename T, int KS, int CH>
+__global__ void __launch_bounds__(256 * KS) k_ras_w(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
+                                                    WBoxView w, const int* __restrict__ ib_boxes, int n_ib, int nib,
+                                                    int rpg, T* __restrict__ t, IntClassView C,
+                                                    const int* __restrict__ int_boxes, int n_int, bool acc) {
+  __shared__ RasIntSmem<T, KS> sm;
+  const int p = blockIdx.x;
+  if (p < nib) {
+    const int slot = p % n_ib, e1 = w.wptr[slot + 1], lo = w.wptr[slot] + p / n_ib * rpg;
+    const int hi = lo + rpg < e1 ? lo + rpg : e1;
+    if (lo < hi)
+      ras_w_block<T, CH, 4 * KS>(r, g, ib_boxes[slot], w, lo, hi, t + (size_t)slot * g.nown, &sm.Xs[0][0][0]);
+  } else {
+    const int q = p - nib, nt = (n_int + 15) / 16;
+    ras_int_block<T, KS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
+  }
+}
+static_assert(4 * 64 * 17 >= kElimMaxNn, "");
 
 // The class matrices of the eliminated interior box (launch_box_on done); kl:
 // the four images' positions of every orbit, rl: the owned row of every row
@@ -1808,70 +1866,73 @@ __device__ __forceinline__ void ras_int_gemm(const T* __restrict__ r, T* __restr
       }
 }
 
-template <typename T>
-static void launch_interior(const T* r, T* z, BoxGeom g, const IntClassView& C, const int* boxes, int n, bool acc,
-                            hipStream_t s) {
-  if (C.Kp > kIntMaxOrbits || C.Kp % 128) throw Error(IBMG_ERR_ARG, "class matrices padded to whole chunks");
-  const dim3 grid((n + 15) / 16, C.nrt);
-  // two parts shorten a work-group's chain of chunks (188 boxes of 16 x 16/4,
-  // 156 work-groups: 16.5 us against 22.2 FP64, 11.2 against 16.7 FP32); once
-  // the work-groups fill the device their size costs more (852 boxes, 702
-  // work-groups: 46.6 against 38.5 FP64, 22.1 against 24.7 FP32; 3584 boxes of
-  // 8 x 8/2, 896 work-groups: 20.6 against 16.9, 13.1 against 12.3)
-  if ((int)(grid.x * grid.y) >= (sizeof(T) == 8 ? 512 : 768))
-    IBMG_KLAUNCH((k_ras_int<T, 1>), grid, dim3(256), 0, s, r, z, g, C, boxes, n, acc);
-  else
-    IBMG_KLAUNCH((k_ras_int<T, 2>), grid, dim3(512), 0, s, r, z, g, C, boxes, n, acc);
+template <typename T, int KS>
+static void launch_ras(const T* r, T* z, const BoxGeom& g, const T* inv, const int* ib_boxes, int n_ib,
+                       const IntClassView& C, const int* int_boxes, int n_int, hipStream_t s, bool acc,
+                       const SymIB* sym) {
+  const int nint = (n_int + 15) / 16 * (n_int ? C.nrt : 0);
+  const dim3 block(256 * KS);
+  if (n_ib && sym) {
+    const WBoxView& w = sym->w;
+    T* t = static_cast<T*>(sym->t);
+    // rows per work-group: enough work-groups to cover the device
+    int rpg = 64;
+    while (rpg > 16 && (long long)n_ib * ((w.maxrows + rpg - 1) / rpg) < 768 / KS) rpg /= 2;
+    const int nib = n_ib * std::max(1, (w.maxrows + rpg - 1) / rpg);
+    const int ch = (w.ws + 64 * Vec16<T>::n - 1) / (64 * Vec16<T>::n);
+    if (ch > 8 || w.nn > kElimMaxNn) throw Error(IBMG_ERR_ARG, "eliminated boxes take at most 1024 non-owned unknowns");
+    const dim3 grid(nib + nint);
+    if (ch <= 2) IBMG_KLAUNCH((k_ras_w<T, KS, 2>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    else if (ch <= 4) IBMG_KLAUNCH((k_ras_w<T, KS, 4>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    else IBMG_KLAUNCH((k_ras_w<T, KS, 8>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    IBMG_LAUNCH_CHECK();
+    return;
+  }
+  // row parts of a chunk: more work-groups where there are few (one fits a CU;
+  // each gathers the whole residual).  Solves with the line at 64, 128, 256 and
+  // 512 work-groups: 256^2 8 x 8/2 3.68, 3.63, 3.79 and 3.91 ms; multiplicative
+  // 256^2 16 x 16/4 19.7, 18.4, 19.5 and 19.5 ms
+  const int items = n_ib * g.nch;
+  int rs = 1;
+  while (rs < 4 && items * rs < 128) rs *= 2;
+  const dim3 grid(items * rs + nint);
+  if (rs == 1) IBMG_KLAUNCH((k_ras_rows<T, KS, 1>), grid, block, 0, s, r, z, g, inv, ib_boxes, items, C, int_boxes, n_int, acc);
+  else if (rs == 2) IBMG_KLAUNCH((k_ras_rows<T, KS, 2>), grid, block, 0, s, r, z, g, inv, ib_boxes, 2 * items, C, int_boxes, n_int, acc);
+  else IBMG_KLAUNCH((k_ras_rows<T, KS, 4>), grid, block, 0, s, r, z, g, inv, ib_boxes, 4 * items, C, int_boxes, n_int, acc);
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
-                      const IntClassView& cls, const int* int_boxes, int n_int,
-                      T* part, hipStream_t s, int parts, bool acc, const SymIB* sym) {
-  // slices of a split IB launch go to part; one sum launch adds them (or the
-  // symmetric IB partials)
-  const bool do_ib = (parts & 1) && n_ib > 0, do_int = (parts & 2) && n_int > 0;
-  const bool use_sym = do_ib && sym != nullptr;
-  const int ks_ib = do_ib && !use_sym ? ras_ib_ksplit(g, n_ib) : 1;
-  const int ks_sym = use_sym ? sym_ksplit(g, n_ib) : 1;
-  T* spart = use_sym ? static_cast<T*>(sym->part) : nullptr;
-  if (use_sym) {
-    const WBoxView& w = sym->w;
-    T* y = static_cast<T*>(sym->y);
-    // rows per work-group: enough work-groups to cover the device
-    int rpg = 64;
-    while (rpg > 16 && (long long)n_ib * ((w.maxrows + rpg - 1) / rpg) < 768) rpg /= 2;
-    const dim3 grid(n_ib, std::max(1, (w.maxrows + rpg - 1) / rpg));
-    const size_t lds = (size_t)w.ws * sizeof(T);
-    const int ch = (w.ws + 64 * Vec16<T>::n - 1) / (64 * Vec16<T>::n);
-    if (ch <= 2) IBMG_KLAUNCH((k_ras_w<T, 2>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
-    else if (ch <= 4) IBMG_KLAUNCH((k_ras_w<T, 4>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
-    else if (ch <= 8) IBMG_KLAUNCH((k_ras_w<T, 8>), grid, dim3(256), lds, s, r, g, ib_boxes, w, rpg, y);
-    else throw Error(IBMG_ERR_ARG, "eliminated boxes take at most 1024 non-owned unknowns");
-    IBMG_LAUNCH_CHECK();
-    const size_t lds2 = (64 * (size_t)g.nch + 256 + 64 * (size_t)(g.nch - 1)) * sizeof(T);
-    IBMG_KLAUNCH((k_ras_ib_sym<T>), dim3(n_ib, g.nch, ks_sym), dim3(256), lds2, s, y, g,
-                 static_cast<const T*>(sym->inv), spart);
-    IBMG_LAUNCH_CHECK();
-  } else if (do_ib) {
-    const size_t lds = (((size_t)g.nloc + 3) & ~(size_t)3) * sizeof(T) + 256 * sizeof(T);
-    IBMG_KLAUNCH((k_ras_ib<T>), dim3(n_ib, g.nch, ks_ib), dim3(256), lds, s, r, z, g, inv, ib_boxes, acc,
-                       part);
-    IBMG_LAUNCH_CHECK();
+                      const IntClassView& C, const int* int_boxes, int n_int, hipStream_t s, int parts, bool acc,
+                      const SymIB* sym) {
+  if (!(parts & 1)) n_ib = 0;
+  if (!(parts & 2)) n_int = 0;
+  if (n_ib + n_int == 0) return;
+  if (g.nloc > kMaxNloc) throw Error(IBMG_ERR_ARG, "box too large");
+  if (n_int) {
+    if (!C.M || g.nown != 3 * g.b * g.b) throw Error(IBMG_ERR_ARG, "interior boxes without class matrices");
+    if (C.Kp > kIntMaxOrbits || C.Kp % 128) throw Error(IBMG_ERR_ARG, "class matrices padded to whole chunks");
   }
-  if (do_int) {
-    if (!cls.M || g.nown != 3 * g.b * g.b) throw Error(IBMG_ERR_ARG, "interior boxes without class matrices");
-    launch_interior<T>(r, z, g, cls, int_boxes, n_int, acc, s);
-  }
-  const int na = ks_ib > 1 ? n_ib : 0, ns = use_sym ? n_ib : 0;
-  if (na + ns > 0) {
-    int grid = cdiv((size_t)(na + ns) * g.nown, 256);
-    if (grid > 4096) grid = 4096;
-    IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, part, ib_boxes, na, ks_ib, spart, ns, ks_sym,
-                 use_sym ? sym->w.ord : nullptr, z, g, acc);
-    IBMG_LAUNCH_CHECK();
-  }
+  // interior parts: two shorten a work-group's chain of chunks (188 boxes of 16 x
+  // 16/4, 156 work-groups: 16.5 us against 22.2 FP64, 11.2 against 16.7 FP32);
+  // once the work-groups fill the device their size costs more (852 boxes, 702
+  // work-groups: 46.6 against 38.5 FP64, 22.1 against 24.7 FP32; 3584 boxes of
+  // 8 x 8/2, 896 work-groups: 20.6 against 16.9, 13.1 against 12.3)
+  if ((n_int + 15) / 16 * (n_int ? C.nrt : 0) >= (sizeof(T) == 8 ? 512 : 768))
+    launch_ras<T, 1>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
+  else
+    launch_ras<T, 2>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
+  if (!n_ib || !sym) return;
+  const int ks = sym_ksplit(g, n_ib);
+  const size_t lds = (64 * (size_t)g.nch + 256 + 64 * (size_t)(g.nch - 1)) * sizeof(T);
+  IBMG_KLAUNCH((k_ras_ib_sym<T>), dim3(n_ib, g.nch, ks), dim3(256), lds, s, r, static_cast<const T*>(sym->t), g,
+               ib_boxes, sym->w, static_cast<const T*>(sym->inv), static_cast<T*>(sym->part));
+  IBMG_LAUNCH_CHECK();
+  const int grid = std::min(4096, cdiv((size_t)n_ib * g.nown, 256));
+  IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, static_cast<const T*>(sym->part), ib_boxes, n_ib, ks,
+               sym->w.ord, z, g, acc);
+  IBMG_LAUNCH_CHECK();
 }
 
 // ---------------------------------------------------------------------------
@@ -2265,11 +2326,9 @@ template void launch_asm_apply<double>(const double*, double*, BoxGeom, const do
                                        hipStream_t);
 template void launch_asm_apply<float>(const float*, float*, BoxGeom, const float*, const int*, float*, hipStream_t);
 template void launch_ras_apply<double>(const double*, double*, BoxGeom, const double*, const int*, int,
-                                       const IntClassView&, const int*, int, double*, hipStream_t, int, bool,
-                                       const SymIB*);
+                                       const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*);
 template void launch_ras_apply<float>(const float*, float*, BoxGeom, const float*, const int*, int,
-                                      const IntClassView&, const int*, int, float*, hipStream_t, int, bool,
-                                      const SymIB*);
+                                      const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*);
 template void launch_extract_sym<double>(const double*, int, BoxGeom, BoxMat, double*, hipStream_t);
 template void launch_extract_sym<float>(const double*, int, BoxGeom, BoxMat, float*, hipStream_t);
 template void launch_coarse_apply<double>(const double*, int, const double*, double*, hipStream_t);

@@ -571,7 +571,7 @@ struct SymIB {
   const void* inv;   // Q: T[n_ib * sym_box_stride(g)]
   void* part;        // T[n_ib * sym_part_len(g)]
   WBoxView w;
-  void* y;           // T[n_ib * nown]: r_o - W r_n
+  void* t;           // T[n_ib * nown]: W r_n at the coupled positions
 };
 size_t sym_box_stride(const BoxGeom& g);
 int sym_part_len(const BoxGeom& g);
@@ -582,7 +582,7 @@ template <typename T>
 void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr, const int* wrow, int ws, T* out,
                       hipStream_t s);
 
-// The interior boxes' shared inverse in its four parity classes (k_ras_int):
+// The interior boxes' shared inverse in its four parity classes (ras_int_block):
 // M (T[4][nrt][Kp][16]), the orbits' representatives kcode[K] and the rows'
 // rcode[R] (comp << 24 | jj << 12 | ii; rcode with the owned images' bits 1 e,
 // 2 X, 4 Y, 8 XY above at 26), nrt = 16-row tiles, Kp = K rounded up to 128.
@@ -602,10 +602,8 @@ void launch_extract_classes(const double* mat, BoxMat bm, const unsigned short* 
 // storing them.  sym != null: the IB boxes run from the eliminated storage.
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
-                      const IntClassView& cls, const int* int_boxes, int n_int, T* part, hipStream_t s, int parts = 3,
+                      const IntClassView& cls, const int* int_boxes, int n_int, hipStream_t s, int parts = 3,
                       bool acc = false, const SymIB* sym = nullptr);
-// column slices of the IB-box kernel (part holds ksplit * n_ib * nch * 64)
-int ras_ib_ksplit(const BoxGeom& g, int n_ib);
 void launch_coarse_assemble(int N, StokesCoef<double> c, const int* tptr_u, const int* tcol_u,
                             const double* tval_u, const int* tptr_v, const int* tcol_v,
                             const double* tval_v, int nb, double* aug, hipStream_t s);

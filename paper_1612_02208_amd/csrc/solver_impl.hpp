@@ -37,7 +37,7 @@ constexpr size_t kIbRowsMaxEntries = 3500000;
 // The IB boxes are kept eliminated (two passes over W and the symmetric owned
 // factor) where their whole rows would take at least this much; see
 // prepare_boxes.
-constexpr size_t kElimMinBytes = (size_t)96 << 20;
+constexpr size_t kElimMinBytes = (size_t)192 << 20;
 // lanes per explicit row: a wave where rows are long (crowded coarse levels)
 constexpr int kIbLongRow = 96;
 // partial-sum buffers: two of kPartStride doubles (blocks x vectors)
@@ -92,8 +92,7 @@ struct Level {
   std::vector<int> loc_tab;  // local unknown -> (comp << 24) | (jj << 12) | ii, then -> comp N^2 + jj N + ii
   DBuf<int> d_ib, d_int;
   DBuf<T> inv;            // [n_unique][nch][nloc][64]
-  DBuf<T> ib_part;        // column slices of the IB boxes' product
-  // the interior boxes' shared inverse in its four parity classes (k_ras_int)
+  // the interior boxes' shared inverse in its four parity classes (ras_int_block)
   std::vector<int> kcode, rcode, klocal, rlocal;
   DBuf<int> d_kcode, d_rcode, d_klocal, d_rlocal;
   DBuf<T> cls;
@@ -106,15 +105,15 @@ struct Level {
   // per unique box: the owned unknowns by position and back
   std::vector<unsigned short> ord, own;
   DBuf<unsigned short> d_ord, d_own;
-  // eliminated storage of the IB boxes (restricted additive sweep): the W rows,
-  // the symmetric factor, the first pass's result and the per-box partials
+  // eliminated storage of the IB boxes: the W rows, the symmetric factor, the
+  // first pass's result and the per-box partials
   bool use_sym = false;
   std::vector<int> wptr, wrow;
   std::vector<unsigned char> coupled;
   DBuf<int> d_wptr, d_wrow;
   DBuf<unsigned char> d_coupled;
   int w_max = 0, w_stride = 0;
-  DBuf<T> wmat, inv_sym, sym_y, sym_part;
+  DBuf<T> wmat, inv_sym, w_res, sym_part;
   // restricted multiplicative Schwarz: box colours; ib_list and int_list
   // sorted by colour, colour c spanning [ib_off[c], ib_off[c+1]) and
   // [int_off[c], int_off[c+1])
@@ -781,23 +780,12 @@ class Solver final : public SolverBase {
 
   size_t box_stride(const Level<T>& lev) const { return (size_t)lev.g.nch * lev.g.nloc * 64; }
 
-  // elements of the IB-box kernel's slice buffer for cnt boxes
-  static size_t ib_part_need(const BoxGeom& g, int cnt) {
-    if (cnt <= 0) return 0;
-    const int ks = ras_ib_ksplit(g, cnt);
-    return ks > 1 ? (size_t)ks * cnt * g.nch * 64 : 0;
-  }
-
   // Every Schwarz launch goes through here: boxes [i0, i1) of the IB list and
-  // [k0, k1) of the interior list; the slice buffer must hold the launch's
-  // column slices.
+  // [k0, k1) of the interior list.
   void ras_launch(Level<T>& lev, const T* r, T* z, int i0, int i1, int k0, int k1, hipStream_t s, int parts, bool acc) {
-    require(lev.use_sym || lev.ib_part.n >= ib_part_need(lev.g, (parts & 1) ? i1 - i0 : 0),
-            "Schwarz slice buffer too small");
     const SymIB sy = sym_of(lev, i0);
     launch_ras_apply<T>(r, z, lev.g, lev.inv.p + (lev.use_sym ? 0 : (size_t)i0 * box_stride(lev)), lev.d_ib.p + i0,
-                        i1 - i0, lev.clsv, lev.d_int.p + k0, k1 - k0, lev.ib_part.p, s, parts, acc,
-                        lev.use_sym ? &sy : nullptr);
+                        i1 - i0, lev.clsv, lev.d_int.p + k0, k1 - k0, s, parts, acc, lev.use_sym ? &sy : nullptr);
   }
 
   // blocks of the fused operator + dots kernel on a level
@@ -811,7 +799,7 @@ class Solver final : public SolverBase {
     return (size_t)std::max({dot_blocks(lev), gs_blocks(3 * (size_t)lev.N * lev.N), 1024}) * (kMaxNu + 1);
   }
 
-  // Orbits of a box's local unknowns under its two reflections (k_ras_int):
+  // Orbits of a box's local unknowns under its two reflections (ras_int_block):
   // one representative per orbit for the columns, and for the rows every orbit
   // that holds an owned unknown, represented by an owned one.
   void class_tables(Level<T>& lev) {
@@ -1246,14 +1234,6 @@ class Solver final : public SolverBase {
       lev.Y.alloc((size_t)g.npd * g.npd * g.nch * 64);
       return;
     }
-    {
-      // column slices of the IB boxes: the whole list (additive sweep,
-      // single-kernel timing) and each colour's ranges (multiplicative sweep)
-      size_t need = ib_part_need(g, lev.n_ib);
-      if (d_.smoother == IBMG_RMS)
-        for (int c = 0; c < lev.ncolour; ++c) need = std::max(need, ib_part_need(g, lev.ib_off[c + 1] - lev.ib_off[c]));
-      if (lev.ib_part.n < need) lev.ib_part.alloc(need);
-    }
     if (has_classes(lev)) {
       class_tables(lev);
       lev.d_kcode.upload(lev.kcode, s);
@@ -1275,15 +1255,17 @@ class Solver final : public SolverBase {
     lev.d_nonown.upload(lev.nonown, s);
     lev.d_ord.upload(lev.ord, s);
     lev.d_own.upload(lev.own, s);
-    // A single system keeps the IB boxes eliminated (three short launches over
-    // fewer bytes) where the whole rows that one launch of the sweep reads (all
-    // boxes, or a colour's) take at least 96 MiB.  Kernel times, eliminated
-    // against whole rows, FP64 unless noted: 16 x 16/4 boxes at 125 MiB 22.7
-    // against 24.8 us, at 1790 MiB 153 against 287 us; 8 x 8/2 boxes at 166 MiB
-    // 27.4 against 28.9 us, at 86 MiB 19.1 against 16.7 us, at 21 MiB 15.7
-    // against 8.6 us; FP32 16 x 16/4 at 62 MiB 18.2 against 15.7 us, at 167 MiB
-    // 23.1 against 29.4 us.  The chunked rows (lev.inv) serve the smaller
-    // levels and the batched form.
+    // A single system keeps the IB boxes eliminated (three launches over fewer
+    // bytes) where the whole rows that one launch of the sweep reads (all boxes,
+    // or a colour's) take at least 192 MiB.  Alone, the eliminated form breaks
+    // even near 100 MiB (FP64 16 x 16/4: 42 MiB 18.3 against 10.7 us for whole
+    // rows, 125 MiB 21.2 against 24.3, 1790 MiB 146 against 286; 8 x 8/2: 75 MiB
+    // 20.7 against 15.9, 166 MiB 30.0 against 27.6; FP32 16 x 16/4: 62 MiB 15.9
+    // against 13.9, 166 MiB 21.5 against 28.2), but its launches wait for one
+    // another where the whole rows' one also covers the interior boxes: a
+    // multiplicative 256^2 solve took 18.4 ms with the line at 96 MiB, 17.6 at
+    // 192 and 17.7 at 320 (additive 512^2 67.4 ms at all three).  The chunked
+    // rows (lev.inv) serve the smaller levels and the batched form.
     const int per_launch = d_.smoother == IBMG_RMS ? lev.n_ib / std::max(1, lev.ncolour) : lev.n_ib;
     lev.use_sym = !defer_coarse_ && lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
                   (size_t)per_launch * box_stride(lev) * sizeof(T) >= kElimMinBytes &&
@@ -1295,7 +1277,7 @@ class Solver final : public SolverBase {
       lev.d_coupled.upload(lev.coupled, s);
       lev.wmat.alloc(lev.wrow.size() * (size_t)lev.w_stride);
       lev.inv_sym.alloc((size_t)lev.n_ib * sym_box_stride(g));
-      lev.sym_y.alloc((size_t)lev.n_ib * g.nown);
+      lev.w_res.alloc((size_t)lev.n_ib * g.nown);
       lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
     }
     lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
@@ -1315,7 +1297,7 @@ class Solver final : public SolverBase {
                  WBoxView{lev.wmat.p, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
                           lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.d_ord.p + (size_t)i0 * lev.g.nown, lev.bm.nn,
                           lev.w_stride, lev.w_max},
-                 lev.sym_y.p};
+                 lev.w_res.p};
   }
 
   // The unique boxes [inv_base, inv_end) whose owned rows lev.inv holds in
@@ -1922,8 +1904,8 @@ class Solver final : public SolverBase {
   }
 
   // One kernel of level `level`, launched alone on the level's work vectors
-  // (filled with ones): IB-box Schwarz (k_ras_ib), interior-box Schwarz
-  // (k_ras_int) or the stencil k_apply.  Algorithmic work per launch: every IB
+  // (filled with ones): IB-box Schwarz (k_ras_rows, or k_ras_w and its
+  // followers), interior-box Schwarz (k_ras_rows) or the stencil k_apply.  Algorithmic work per launch: every IB
   // box streams its owned rows of the inverse (nown x nloc), gathers nloc
   // values and writes nown; the interior product reads the class matrices once
   // and each box's nloc values and writes nown, four R x K products per box;

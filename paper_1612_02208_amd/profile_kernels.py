@@ -114,7 +114,7 @@ def main():
         return
     g = StokesIB(wl, precision=a.precision)
     suffix = "<double>" if a.precision == "fp64" else "<float>"
-    kinds = [("ras_ib", "k_ras_ib"), ("ras_interior", "k_ras_int"), ("stencil", "k_apply"),
+    kinds = [("ras_ib", "IB boxes"), ("ras_interior", "interior boxes"), ("stencil", "k_apply"),
              ("restrict", "k_restrict"), ("prolong", "k_prolong_add")]
     if a.precision == "fp64":
         kinds += [("spread", "k_spread"), ("interp", "k_interp_lanes")]
