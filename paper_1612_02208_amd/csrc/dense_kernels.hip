@@ -697,22 +697,26 @@ static void sweep_step(double* mats, int n, int kb, int w, int lo, bool partial,
   }
 }
 
-static int* sweep_flags(double* dinv, int count) {
-  return reinterpret_cast<int*>(dinv + (size_t)count * GJ_NB * GJ_NB);
+// the parts of a sweep's workspace (sweep_work)
+static double* sweep_dinv(double* work, int n, int count) { return work + (size_t)count * 2 * n * GJ_NB; }
+static int* sweep_flags(double* work, int n, int count) {
+  return reinterpret_cast<int*>(sweep_dinv(work, n, count) + (size_t)count * GJ_NB * GJ_NB);
 }
 
-void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s) {
+void launch_gj_invert(double* mats, int n, int count, double* work, hipStream_t s) {
   if (!count) return;
   if (n > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
   for (int kb = 0; kb < n; kb += GJ_NB)
-    sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, dinv, sweep_flags(dinv, count), s);
+    sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, sweep_dinv(work, n, count),
+               sweep_flags(work, n, count), s);
 }
 
-void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s) {
+void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, hipStream_t s) {
   if (!count) return;
   if (bm.nnp % 64) throw Error(IBMG_ERR_ARG, "the owned unknowns start at a tile");
   if (bm.ld > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
-  int* flags = sweep_flags(dinv, count);
+  double* dinv = sweep_dinv(work, bm.ld, count);
+  int* flags = sweep_flags(work, bm.ld, count);
   for (int kb = 0; kb < bm.nnp; kb += GJ_NB)
     sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, dinv, flags, s);
   for (int kb = bm.nnp; kb < bm.ld; kb += GJ_NB)

@@ -534,15 +534,18 @@ void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoe
                            double* mats, hipStream_t s);
 // In-place block sweeps of count symmetric n x n matrices: afterwards the
 // tiles on or below the diagonal (64 x 64, diagonal tiles in full) hold
-// -A^{-1}.  work: count x 2 x n x kGjNb doubles of workspace; dinv: count x
-// kGjNb^2 doubles, then an int per matrix and 64 rows.
-void launch_gj_invert(double* mats, int n, int count, double* work, double* dinv, hipStream_t s);
-constexpr int kGjNb = 128;  // block width of the batched inversion
+// -A^{-1}.  work: sweep_work(n, count) doubles.
+constexpr int kGjNb = 128;  // block width of the sweeps
+inline size_t sweep_work(size_t n, size_t count) {
+  // per matrix: the panels C and E, the pivot block's inverse, a flag per 64 rows
+  return count * (2 * n * kGjNb + (size_t)kGjNb * kGjNb + (n + 127) / 128);
+}
+void launch_gj_invert(double* mats, int n, int count, double* work, hipStream_t s);
 // The restricted boxes' elimination: afterwards the rows of the owned unknowns
 // hold W = A_on A_nn^{-1} at the non-owned columns and -S_oo^{-1} (tiles on or
 // below the diagonal) at the owned ones; launch_box_on adds the inverse's owned
 // rows at the non-owned columns.
-void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, double* dinv, hipStream_t s);
+void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, hipStream_t s);
 void launch_box_on(double* mats, BoxMat bm, int count, hipStream_t s);
 // rows of the inverse in 64-row chunks: the owned rows of eliminated matrices
 // or every row of swept ones (bo.pos = null, g.nown = nloc: the summed

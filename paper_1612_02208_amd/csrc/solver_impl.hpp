@@ -1135,10 +1135,6 @@ class Solver final : public SolverBase {
     IBMG_HIP(hipStreamSynchronize(s));
   }
 
-  // doubles of the sweeps' workspace for cnt matrices of n unknowns
-  static size_t sweep_work(size_t n, size_t cnt) { return cnt * 2 * n * kGjNb + sweep_dinv(n, cnt); }
-  static size_t sweep_dinv(size_t n, size_t cnt) { return cnt * ((size_t)kGjNb * kGjNb + (n + 127) / 128); }
-
   // Springs shorter than their rest length (tangent model): the velocity
   // blocks may be indefinite, so the coarsest elimination pivots.
   bool compressed() const {
@@ -1196,8 +1192,7 @@ class Solver final : public SolverBase {
       launch_coarse_invert(aug.p, nn, 1, 0, side_);
       launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
     } else {
-      double* work = aug.p + mat;
-      launch_gj_invert(aug.p, n0_, 1, work, work + 2 * (size_t)n0_ * kGjNb, side_);
+      launch_gj_invert(aug.p, n0_, 1, aug.p + mat, side_);
       launch_coarse_extract_sym(aug.p, N, sh, inv0_.p, side_);
     }
     IBMG_HIP(hipEventRecord(ev_join_, side_));
@@ -1333,8 +1328,7 @@ class Solver final : public SolverBase {
       const size_t cap = std::min<size_t>(std::max<size_t>(1, budget / per), 512);
       const size_t nbatch = (items.size() + cap - 1) / cap;
       const int batch = (int)((items.size() + nbatch - 1) / nbatch);
-      DBuf<double> mats((size_t)batch * n * n), work(2 * (size_t)batch * n * kGjNb),
-          dinv(sweep_dinv(n, batch));
+      DBuf<double> mats((size_t)batch * n * n), work(sweep_work(n, batch));
       for (size_t b0 = 0; b0 < items.size(); b0 += batch) {
         const int cnt = (int)std::min<size_t>(batch, items.size() - b0);
         // runs of one level with consecutive unique indices
@@ -1353,8 +1347,8 @@ class Solver final : public SolverBase {
                                 lev.f[0].tval.p, lev.f[1].d_tptr.p, lev.f[1].d_tcol.p, lev.f[1].tval.p,
                                 order_of(lev, u0), bm, mats.p + slot * n * n, s);
         });
-        if (bm.nnp) launch_box_eliminate(mats.p, bm, cnt, work.p, dinv.p, s);
-        else launch_gj_invert(mats.p, n, cnt, work.p, dinv.p, s);
+        if (bm.nnp) launch_box_eliminate(mats.p, bm, cnt, work.p, s);
+        else launch_gj_invert(mats.p, n, cnt, work.p, s);
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
           double* m0 = mats.p + slot * n * n;
