@@ -7,9 +7,9 @@
 // largest first, make level l's active systems a prefix [0, nact_l) and a
 // level's batch vectors are nact_l level vectors back to back.  A system
 // whose finest level is l joins the descent there and leaves the ascent
-// there.  Per level and sweep: one stencil launch and one IB-row launch for
-// L_IB, one persistent RAS launch over every (system, box) item, and the
-// Gram-Schmidt kernels over all systems at once.  The outer FGMRES(m) runs
+// there.  Per level and sweep: one launch for L_IB with its IB rows and dots,
+// one persistent RAS launch over every (system, box) item, and the
+// Gram-Schmidt update over all systems at once.  The outer FGMRES(m) runs
 // per system in lockstep with one host read of all residual estimates per
 // iteration; converged systems drop out through device-side active flags.
 #include <numeric>
@@ -20,7 +20,6 @@ namespace ibmg {
 
 namespace {
 
-constexpr size_t kScalStride = 64;  // per-system smoother scalars (beta, y)
 
 }  // namespace
 
@@ -120,10 +119,10 @@ class BatchSolver final : public BatchBase {
     size_t n = 0, pst = 0;
     StokesCoef<T> c{};
     DBuf<T> w, b, r, V, Z;
-    DBuf<double> H, scal, pa, pb;
-    // explicit IB rows of the level's systems, indices into the batch vector
-    DBuf<int> rows, ptr, col;
-    DBuf<T> val;
+    DBuf<double> scal, part;
+    // the systems' explicit IB rows, and the most of one system
+    DBuf<IbRows<T>> ib_tab;
+    IbRows<T> rows{};
     int nrows = 0;
     // Schwarz boxes
     BoxGeom g{};
@@ -202,15 +201,27 @@ class BatchSolver final : public BatchBase {
       L.Z.alloc((size_t)nv * bn);
       launch_fill<T>(L.V.p, T(0), L.V.n, s);
       launch_fill<T>(L.Z.p, T(0), L.Z.n, s);
-      L.nblk = dots_blocks(L.n, 1024);
-      L.pst = (size_t)L.nblk * (kMaxNu + 1);
-      L.pa.alloc((size_t)L.nact * L.pst);
-      L.pb.alloc((size_t)L.nact * L.pst);
-      L.H.alloc((size_t)L.nact * (kMaxNu + 1) * kMaxNu);
-      L.scal.alloc((size_t)L.nact * kScalStride);
-      std::vector<size_t> base(L.nact);
-      for (int p = 0; p < L.nact; ++p) base[p] = (size_t)p * L.n;
-      gather_rows<T>(l, L.nact, base, L.rows, L.ptr, L.col, L.val, &L.nrows, s);
+      std::vector<IbRows<T>> tab;
+      L.rows = IbRows<T>{nullptr, nullptr, {}, {}, 0, 16};
+      int blocks = 0;
+      for (int p = 0; p < L.nact; ++p) {
+        Level<T>& lev = sys_[p]->levels_[l];
+        tab.push_back(IbRows<T>{lev.d_ib_rows.p, lev.d_ib_flag.p, sys_[p]->template csr<T>(lev.f[0]),
+                                sys_[p]->template csr<T>(lev.f[1]), (int)lev.ib_rows.size(), lev.ib_lanes});
+        L.nrows += tab[p].n;
+        if (apply_blocks(L.N, tab[p].n, tab[p].lanes) > blocks) {   // the largest grid of one system
+          blocks = apply_blocks(L.N, tab[p].n, tab[p].lanes);
+          L.rows.n = tab[p].n;
+          L.rows.lanes = tab[p].lanes;
+        }
+      }
+      L.ib_tab.upload(tab, s);
+      L.rows.each = L.ib_tab.p;
+      // blocks per system: the device four times over, shared by the systems
+      L.nblk = std::max(8, (4096 + L.nact - 1) / L.nact);
+      L.pst = (size_t)std::max(apply_blocks(L.N, L.rows.n, L.rows.lanes, L.nblk), gs_blocks(L.n)) * (kMaxNu + 1);
+      L.part.alloc(3 * (size_t)L.nact * L.pst);
+      L.scal.alloc((size_t)L.nact * kGsScal);
       // Schwarz items: (system, box) entries, own inverses for IB boxes, the
       // first available interior inverse for every interior box (equal
       // fluid coefficients and box geometry give one interior matrix)
@@ -312,49 +323,45 @@ class BatchSolver final : public BatchBase {
                         L.n_ib, L.loc.p, d_act_.p, pl, s);
   }
 
-  // y = L_IB x on level l for every active system (b != null: y = b - L_IB x)
-  void op(int l, const T* x, T* y, const T* b, hipStream_t s) {
-    BLevel& L = lv_[l];
-    launch_apply_batch<T>(x, y, b, L.N, L.c, L.nact, L.n, s);
-    launch_ib_rows<T>(x, y, L.rows.p, L.ptr.p, L.col.p, L.val.p, L.nrows, b ? T(-1) : T(1), s);
+  Many many(const BLevel& L) const {
+    Many m;
+    m.nsys = L.nact;
+    m.bs = L.n;
+    m.ps = L.pst;
+    m.nblk = L.nblk;
+    m.act = d_act_.p;
+    return m;
   }
 
-  // Sec. 3.3 smoothing on every system of level l: w <- w + e, e from nu
-  // FGMRES iterations (classical Gram-Schmidt twice) on L e = b - L w.
-  void smooth(int l, T* w, const T* b, int nu, bool w_zero, hipStream_t s) {
+  // Sec. 3.3 smoothing on every active system of level l: w <- w + e, e from
+  // nu FGMRES iterations on L e = b - L w, on the unnormalised basis of the
+  // single-system form and with its launches; crs: also the restriction of the
+  // new residual to the next coarser level (from w = 0).
+  void smooth(int l, T* w, const T* b, int nu, T* crs, hipStream_t s) {
     BLevel& L = lv_[l];
-    const int ns = L.nact;
-    const size_t n = L.n, bn = (size_t)ns * n;
-    const BSeg sg{nullptr, n, d_act_.p};
-    const int ldh = kMaxNu + 1;
-    const size_t hst = (size_t)(kMaxNu + 1) * kMaxNu;
-    const T* r0;
-    if (w_zero) {
-      launch_fill<T>(w, T(0), bn, s);
-      r0 = b;
-    } else {
-      op(l, w, L.r.p, b, s);
-      r0 = L.r.p;
+    const size_t n = L.n, bn = (size_t)L.nact * n, pn = (size_t)L.nact * L.pst;
+    const Many m = many(L);
+    const FootView<T> none{};
+    T* V = L.V.p;
+    const T* u0 = b;
+    if (!crs) {
+      launch_apply<T>(w, V, b, nullptr, L.rows, none, none, L.N, 0, L.c, false, s, m);
+      u0 = V;
     }
-    launch_dots_b<T>(r0, 1, bn, r0, sg, ns, L.pa.p, L.pst, L.nblk, s);
-    launch_scale_red_b<T>(r0, L.V.p, sg, ns, n, L.pa.p, L.nblk, L.pst, L.scal.p, kScalStride, s);
+    double* pd = L.part.p;
+    double* pu[2] = {L.part.p + pn, L.part.p + 2 * pn};
+    const int nd = apply_blocks(L.N, L.rows.n, L.rows.lanes, L.nblk);
     for (int k = 0; k < nu; ++k) {
-      T* vk = L.V.p + (size_t)k * bn;
+      const T* uk = k == 0 ? u0 : V + (size_t)k * bn;
       T* zk = L.Z.p + (size_t)k * bn;
-      T* t = L.V.p + (size_t)(k + 1) * bn;
-      ras(l, vk, zk, L.plan, s);
-      op(l, zk, t, nullptr, s);
-      double* hcol = L.H.p + (size_t)k * ldh;
-      launch_dots_b<T>(L.V.p, k + 1, bn, t, sg, ns, L.pa.p, L.pst, L.nblk, s);
-      // the second pass with |t|^2 beside its dots; one more sweep updates
-      // and normalises (the norm from those sums), none for the last basis
-      // vector, whose coefficients and norm go straight to the least squares
-      launch_upd_dots_b<T>(t, L.V.p, k + 1, bn, sg, ns, L.pa.p, L.nblk, L.pst, hcol, hst, L.pb.p, s, 0, true);
-      if (k + 1 < nu)
-        launch_scale_upd_b<T>(t, L.V.p, k + 1, bn, sg, ns, n, L.pb.p, L.nblk, L.pst, hcol, hst, s);
+      T* t = V + (size_t)(k + 1) * bn;
+      ras(l, uk, zk, L.plan, s);
+      launch_apply_dots<T>(zk, t, nullptr, L.rows, none, none, L.N, 0, L.c, u0, V, k + 1, bn, pd, s, m);
+      launch_gs_update<T>(t, u0, V, k + 1, bn, n, pd, nd, pu[(k + 1) & 1], L.scal.p, pu[k & 1], s, m);
     }
-    launch_combine_ls_b<T>(w, L.Z.p, nu, bn, sg, ns, n, L.H.p, ldh, hst, L.scal.p, L.scal.p + kScalY,
-                           kScalStride, s, false, L.pb.p, L.nblk, L.pst, true);
+    const double* pl = pu[(nu - 1) & 1];
+    if (crs) launch_gs_combine_restrict<T>(w, L.Z.p, u0, V, nu, bn, L.N / 2, pl, L.scal.p, crs, s, m);
+    else launch_gs_combine<T>(w, L.Z.p, nu, bn, n, pl, L.scal.p, false, s, m);
   }
 
   // Alg. 1 on every system: r and z are ragged batch vectors (FP64).
@@ -363,16 +370,14 @@ class BatchSolver final : public BatchBase {
       BLevel& L = lv_[l];
       const int p0 = nact_[l + 1], p1 = nact_[l];
       if (p1 > p0) launch_cast<double, T>(r + off_[p0], L.b.p + (size_t)p0 * L.n, (size_t)(p1 - p0) * L.n, s);
-      smooth(l, L.w.p, L.b.p, nu1_, true, s);
-      op(l, L.w.p, L.r.p, L.b.p, s);
-      launch_restrict_batch<T>(L.r.p, lv_[l - 1].b.p, lv_[l - 1].N, p1, s);
+      smooth(l, L.w.p, L.b.p, nu1_, lv_[l - 1].b.p, s);
     }
     launch_coarse_apply_batch<T>(inv0_.p, n0_, lv_[0].b.p, lv_[0].w.p, nact_[0], s);
     for (int l = 1; l <= Lmax_; ++l) {
       BLevel& L = lv_[l];
       const int p0 = nact_[l + 1], p1 = nact_[l];
-      launch_prolong_add_batch<T>(lv_[l - 1].w.p, L.w.p, lv_[l - 1].N, p1, s);
-      smooth(l, L.w.p, L.b.p, nu2_, false, s);
+      launch_prolong_add_batch<T>(lv_[l - 1].w.p, L.w.p, lv_[l - 1].N, p1, d_act_.p, s);
+      smooth(l, L.w.p, L.b.p, nu2_, nullptr, s);
       if (p1 > p0) launch_cast<T, double>(L.w.p + (size_t)p0 * L.n, z + off_[p0], (size_t)(p1 - p0) * L.n, s);
     }
   }

@@ -1,6 +1,8 @@
 // Grid kernels: the MAC Stokes-IB operator (Eq. matrix-impib, App. A.1), its
 // transpose, the inter-level transfers (Sec. 3.2) and the BLAS-1 / small
 // dense pieces of the Krylov iterations (Sec. 3.3 smoothing, outer FGMRES).
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace ibmg {
@@ -166,21 +168,26 @@ static inline int strip_blocks(int N) {
   const int rows = (int)blk.y * rj;
   return ((N + (int)blk.x - 1) / (int)blk.x) * ((N + rows - 1) / rows);
 }
-static inline int ib_row_blocks(int nrows, int lanes) {
+static inline int ib_row_blocks(int nrows, int lanes, int cap) {
   if (nrows <= 0) return 0;
   const int g = cdiv((size_t)nrows * lanes, 256);
-  return g < 1024 ? g : 1024;
+  return std::min(g, cap > 0 ? cap : 1024);
 }
-int apply_blocks(int N, int nrows, int lanes) { return strip_blocks(N) + ib_row_blocks(nrows, lanes); }
+int apply_blocks(int N, int nrows, int lanes, int cap) { return strip_blocks(N) + ib_row_blocks(nrows, lanes, cap); }
 
 // grid: strip_blocks(N) work-groups of the stencil, then the IB rows' (x);
-// systems (z; batched launches, which take no IB rows here)
+// systems (z)
 template <typename T, bool TRANS, bool RESID, int IBM, int RJ>
 __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __restrict__ y,
                                                const T* __restrict__ b, const T* __restrict__ F,
                                                IbRows<T> R, FootView<T> fx,
                                                FootView<T> fy, int N, int M, StokesCoef<T> c,
-                                               size_t bs, int nsb) {
+                                               Many m, int nsb) {
+  if (m.act && !m.act[blockIdx.z]) return;
+  if (IBM == 2 && R.each) R = R.each[blockIdx.z];
+  w += blockIdx.z * m.bs;
+  y += blockIdx.z * m.bs;
+  if (RESID) b += blockIdx.z * m.bs;
   if (IBM == 2 && (int)blockIdx.x >= nsb) {
     const int tid = threadIdx.y * blockDim.x + threadIdx.x, blk = blockIdx.x - nsb, nrb = gridDim.x - nsb;
     auto emit = [&](int r, T v) { y[r] = v; };
@@ -192,10 +199,6 @@ __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __res
   const int i = ((int)blockIdx.x % gx) * blockDim.x + threadIdx.x;
   const int j0 = (((int)blockIdx.x / gx) * blockDim.y + threadIdx.y) * RJ;
   if (i >= N || j0 >= N) return;
-  // batched launches: system blockIdx.z, systems bs apart
-  w += blockIdx.z * bs;
-  y += blockIdx.z * bs;
-  if (RESID) b += blockIdx.z * bs;
   const size_t n = (size_t)N * N;
   apply_strip<T, TRANS, RESID, IBM, RJ>(w, b, F, R.flag, fx, fy, N, M, c, i, j0,
                                         [&](size_t c0, int flag, T yu, T yv, T yp) {
@@ -215,8 +218,15 @@ __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* 
                                                     const T* __restrict__ F, IbRows<T> R, FootView<T> fx,
                                                     FootView<T> fy, int N, int M, StokesCoef<T> c,
                                                     const T* __restrict__ u0, const T* __restrict__ V,
-                                                    size_t vstride, double* __restrict__ partial, int nsb) {
+                                                    size_t vstride, double* __restrict__ partial, Many m, int nsb) {
   constexpr int NS = NV == 1 ? 2 : NV;   // sums per block
+  if (m.act && !m.act[blockIdx.z]) return;
+  if (IBM == 2 && R.each) R = R.each[blockIdx.z];
+  w += blockIdx.z * m.bs;
+  y += blockIdx.z * m.bs;
+  u0 += blockIdx.z * m.bs;
+  if (NV > 1) V += blockIdx.z * m.bs;
+  partial += blockIdx.z * m.ps;
   __shared__ double red[NS * 4];
   const size_t n = (size_t)N * N;
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
@@ -267,20 +277,20 @@ __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* 
 template <typename T, int IBM, int RJ>
 static void launch_apply_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                            FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose,
-                           hipStream_t s, int nsys, size_t bs) {
+                           hipStream_t s, Many m) {
   const dim3 blk = apply_block(RJ);
   const int nsb = strip_blocks(N);
-  const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0), 1, nsys);
+  const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes, m.nblk) : 0), 1, m.nsys);
   if (b) {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
+      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
+      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
   } else {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
+      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, bs, nsb);
+      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
   }
   IBMG_LAUNCH_CHECK();
 }
@@ -288,9 +298,9 @@ static void launch_apply_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R
 template <typename T, int IBM>
 static void launch_apply_m(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                            FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose,
-                           hipStream_t s, int nsys = 1, size_t bs = 0) {
-  if (apply_rows(N) == 4) launch_apply_r<T, IBM, 4>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, nsys, bs);
-  else launch_apply_r<T, IBM, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, nsys, bs);
+                           hipStream_t s, Many m) {
+  if (apply_rows(N) == 4) launch_apply_r<T, IBM, 4>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, m);
+  else launch_apply_r<T, IBM, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, m);
 }
 
 template <typename T>
@@ -300,31 +310,32 @@ static void check_ib_rows(const IbRows<T>& R) {
 
 template <typename T>
 void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
-                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s) {
+                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s, Many m) {
   check_ib_rows(R);
+  if (m.nsys <= 0) return;
   if (R.n > 0)
-    launch_apply_m<T, 2>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
+    launch_apply_m<T, 2>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, m);
   else if (F)
-    launch_apply_m<T, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
+    launch_apply_m<T, 1>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, m);
   else
-    launch_apply_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, transpose, s);
+    launch_apply_m<T, 0>(w, y, b, F, R, fx, fy, N, M, c, transpose, s, m);
 }
 
 template <typename T, int IBM, int RJ, int NV>
 static void launch_apply_dots_n(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
                                 StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
-                                hipStream_t s) {
+                                hipStream_t s, Many m) {
   if constexpr (NV > 8) {
     throw Error(IBMG_ERR_ARG, "fused dots take 1..8 vectors");
   } else {
     if (nvec != NV) {
-      launch_apply_dots_n<T, IBM, RJ, NV + 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+      launch_apply_dots_n<T, IBM, RJ, NV + 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
       return;
     }
     const int nsb = strip_blocks(N);
-    const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes) : 0));
+    const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes, m.nblk) : 0), 1, m.nsys);
     IBMG_KLAUNCH((k_apply_dots<T, IBM, RJ, NV>), grd, apply_block(RJ), 0, s, w, y, F, R, fx, fy, N, M, c, u0, V, vstride,
-                 partial, nsb);
+                 partial, m, nsb);
     IBMG_LAUNCH_CHECK();
   }
 }
@@ -332,25 +343,26 @@ static void launch_apply_dots_n(const T* w, T* y, const T* F, IbRows<T> R, FootV
 template <typename T, int IBM>
 static void launch_apply_dots_m(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
                                 StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
-                                hipStream_t s) {
+                                hipStream_t s, Many m) {
   if (apply_rows(N) == 4)
-    launch_apply_dots_n<T, IBM, 4, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+    launch_apply_dots_n<T, IBM, 4, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
   else
-    launch_apply_dots_n<T, IBM, 1, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+    launch_apply_dots_n<T, IBM, 1, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
 }
 
 template <typename T>
 void launch_apply_dots(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
                        StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
-                       hipStream_t s) {
+                       hipStream_t s, Many m) {
+  if (m.nsys <= 0) return;
   if (nvec < 1 || nvec > 8) throw Error(IBMG_ERR_ARG, "fused dots take 1..8 vectors");
   check_ib_rows(R);
   if (R.n > 0)
-    launch_apply_dots_m<T, 2>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 2>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
   else if (F)
-    launch_apply_dots_m<T, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 1>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
   else
-    launch_apply_dots_m<T, 0>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s);
+    launch_apply_dots_m<T, 0>(w, y, F, R, fx, fy, N, M, c, u0, V, nvec, vstride, partial, s, m);
 }
 
 // Stencil part of L_IB (or the residual) for nsys systems of one grid size,
@@ -359,8 +371,11 @@ template <typename T>
 void launch_apply_batch(const T* w, T* y, const T* b, int N, StokesCoef<T> c, int nsys, size_t bs,
                         hipStream_t s) {
   if (nsys <= 0) return;
-  FootView<T> none{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  launch_apply_m<T, 0>(w, y, b, nullptr, IbRows<T>{}, none, none, N, 0, c, false, s, nsys, bs);
+  FootView<T> none{};
+  Many m;
+  m.nsys = nsys;
+  m.bs = bs;
+  launch_apply_m<T, 0>(w, y, b, nullptr, IbRows<T>{}, none, none, N, 0, c, false, s, m);
 }
 
 // Explicit IB rows: one wave per listed row, lanes over its entries, the
@@ -396,24 +411,17 @@ __global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc) 
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y * blockDim.y + threadIdx.y;
   if (i >= Nc || j >= Nc) return;
-  const size_t nf = (size_t)4 * Nc * Nc, nc = (size_t)Nc * Nc;
-  f += blockIdx.z * 3 * nf;
-  restrict_point<T>(cz + blockIdx.z * 3 * nc, Nc, i, j,
+  const size_t nf = (size_t)4 * Nc * Nc;
+  restrict_point<T>(cz, Nc, i, j,
                     [&](int comp, int I, int J) -> T { return f[comp * nf + (size_t)J * 2 * Nc + I]; });
 }
 
 template <typename T>
-void launch_restrict_batch(const T* fine, T* coarse, int Nc, int nsys, hipStream_t s) {
-  if (nsys <= 0) return;
+void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s) {
   dim3 blk(64, 4);
-  dim3 grd((Nc + 63) / 64, (Nc + 3) / 4, nsys);
+  dim3 grd((Nc + 63) / 64, (Nc + 3) / 4);
   IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc);
   IBMG_LAUNCH_CHECK();
-}
-
-template <typename T>
-void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s) {
-  launch_restrict_batch<T>(fine, coarse, Nc, 1, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -422,7 +430,8 @@ void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s) {
 // it), bilinear cell-centred interpolation for pressure.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_prolong_add(const T* __restrict__ cz, T* __restrict__ f, int Nc) {
+__global__ void k_prolong_add(const T* __restrict__ cz, T* __restrict__ f, int Nc, const int* __restrict__ act) {
+  if (act && !act[blockIdx.z]) return;
   const int I = blockIdx.x * blockDim.x + threadIdx.x;
   const int J = blockIdx.y * blockDim.y + threadIdx.y;
   const int Nf = 2 * Nc;
@@ -448,18 +457,18 @@ __global__ void k_prolong_add(const T* __restrict__ cz, T* __restrict__ f, int N
 }
 
 template <typename T>
-void launch_prolong_add_batch(const T* coarse, T* fine, int Nc, int nsys, hipStream_t s) {
+void launch_prolong_add_batch(const T* coarse, T* fine, int Nc, int nsys, const int* act, hipStream_t s) {
   if (nsys <= 0) return;
   const int Nf = 2 * Nc;
   dim3 blk(64, 4);
   dim3 grd((Nf + 63) / 64, (Nf + 3) / 4, nsys);
-  IBMG_KLAUNCH((k_prolong_add<T>), grd, blk, 0, s, coarse, fine, Nc);
+  IBMG_KLAUNCH((k_prolong_add<T>), grd, blk, 0, s, coarse, fine, Nc, act);
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_prolong_add(const T* coarse, T* fine, int Nc, hipStream_t s) {
-  launch_prolong_add_batch<T>(coarse, fine, Nc, 1, s);
+  launch_prolong_add_batch<T>(coarse, fine, Nc, 1, nullptr, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -876,7 +885,7 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
 // ---------------------------------------------------------------------------
 #define IBMG_INST_GRID(T)                                                                         \
   template void launch_apply<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,         \
-                                FootView<T>, int, int, StokesCoef<T>, bool, hipStream_t);         \
+                                FootView<T>, int, int, StokesCoef<T>, bool, hipStream_t, Many);         \
   template void launch_restrict<T>(const T*, T*, int, hipStream_t);                               \
   template void launch_prolong_add<T>(const T*, T*, int, hipStream_t);                            \
   template void launch_fill<T>(T*, T, size_t, hipStream_t);                                       \
@@ -891,13 +900,12 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
   template void launch_subtract_means<T>(T*, int, const double*, int, hipStream_t);               \
   template void launch_apply_dots<T>(const T*, T*, const T*, IbRows<T>, FootView<T>, FootView<T>, \
                                      int, int, StokesCoef<T>, const T*, const T*, int, size_t,     \
-                                     double*, hipStream_t);                                        \
+                                     double*, hipStream_t, Many);                                        \
   template void launch_apply_batch<T>(const T*, T*, const T*, int, StokesCoef<T>, int, size_t,    \
                                       hipStream_t);                                               \
   template void launch_ib_rows<T>(const T*, T*, const int*, const int*, const int*, const T*, int, \
                                   T, hipStream_t);                                                \
-  template void launch_restrict_batch<T>(const T*, T*, int, int, hipStream_t);                    \
-  template void launch_prolong_add_batch<T>(const T*, T*, int, int, hipStream_t);                 \
+  template void launch_prolong_add_batch<T>(const T*, T*, int, int, const int*, hipStream_t);     \
   template void launch_dots_b<T>(const T*, int, size_t, const T*, BSeg, int, double*, size_t, int, \
                                  hipStream_t);                                                    \
   template void launch_scale_b<T>(const T*, T*, const double*, size_t, BSeg, int, size_t,         \

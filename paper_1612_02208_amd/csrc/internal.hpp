@@ -372,23 +372,36 @@ struct IbRows {
   CsrT<T> tu, tv;
   int n;
   int lanes;                  // lanes per row: 16 or 64
+  // batched launches: every system's rows, [nsys] (n and lanes above then the
+  // largest of them)
+  const IbRows<T>* each = nullptr;
+};
+// A launch over many systems of one level: bs elements between the systems'
+// vectors, ps doubles between their partial sums, nblk blocks per system for
+// the IB rows and for the Gram-Schmidt kernels (0: as for one system); systems
+// whose act is 0 do nothing.
+struct Many {
+  int nsys = 1;
+  size_t bs = 0, ps = 0;
+  int nblk = 0;
+  const int* act = nullptr;
 };
 // y = L_IB w or b - L_IB w (b != null), or the transposed product.  The IB
 // term comes from the explicit rows (R.n > 0), else from the nodal forces F
 // (F != null), else there is none.
 template <typename T>
 void launch_apply(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
-                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s);
+                  FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose, hipStream_t s, Many m = {});
 // y = L_IB w with the first Gram-Schmidt pass fused: the dots u_q . y of
 // nvec <= 8 basis vectors (u_0 = u0, u_q = V + q vstride), nvec per block,
 // over apply_blocks blocks; with nvec = 1 a second sum, u_0 . u_0, follows
 template <typename T>
 void launch_apply_dots(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx, FootView<T> fy, int N, int M,
                        StokesCoef<T> c, const T* u0, const T* V, int nvec, size_t vstride, double* partial,
-                       hipStream_t s);
+                       hipStream_t s, Many m = {});
 // blocks of launch_apply_dots on an N x N level with nrows explicit IB rows
-// of `lanes` lanes each (0: none)
-int apply_blocks(int N, int nrows, int lanes);
+// of `lanes` lanes each (0: none), at most cap of them for the rows (0: 1024)
+int apply_blocks(int N, int nrows, int lanes, int cap = 0);
 template <typename T>
 void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s);
 template <typename T>
@@ -459,17 +472,17 @@ int gs_blocks(size_t n);
 // block, gs_blocks(n) blocks).  pu: the previous call's pout (k > 1).
 template <typename T>
 void launch_gs_update(T* t, const T* u0, const T* V, int k, size_t stride, size_t n, const double* pd, int nd,
-                      const double* pu, double* S, double* pout, hipStream_t s);
+                      const double* pu, double* S, double* pout, hipStream_t s, Many m = {});
 // the least squares, then x += sum_q y_q Z_q (assign: x = ...)
 template <typename T>
 void launch_gs_combine(T* x, const T* Z, int k, size_t stride, size_t n, const double* pu, double* S, bool assign,
-                       hipStream_t s);
+                       hipStream_t s, Many m = {});
 // the same with x assigned on a grid of 2 Nc x 2 Nc points, and the
 // restriction of the residual r = u_0 - sum_q y_q L z_q to the coarse grid;
 // r comes from the Arnoldi relation (a combination of u_0 .. u_k)
 template <typename T>
 void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k, size_t stride, int Nc,
-                                const double* pu, double* S, T* coarse, hipStream_t s);
+                                const double* pu, double* S, T* coarse, hipStream_t s, Many m = {});
 
 // immersed boundary
 void launch_fp_fine(const double* X, int M, int N, int comp, const int* base, const int* mask,
@@ -639,9 +652,7 @@ template <typename T>
 void launch_ib_rows(const T* x, T* y, const int* rows, const int* ptr, const int* col, const T* val,
                     int nrows, T sign, hipStream_t s);
 template <typename T>
-void launch_restrict_batch(const T* fine, T* coarse, int Nc, int nsys, hipStream_t s);
-template <typename T>
-void launch_prolong_add_batch(const T* coarse, T* fine, int Nc, int nsys, hipStream_t s);
+void launch_prolong_add_batch(const T* coarse, T* fine, int Nc, int nsys, const int* act, hipStream_t s);
 template <typename T>
 void launch_dots_b(const T* V, int nvec, size_t stride, const T* t, BSeg sg, int nsys, double* partial,
                    size_t pstride, int nblk, hipStream_t s);

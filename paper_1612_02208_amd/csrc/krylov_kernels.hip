@@ -391,7 +391,16 @@ __global__ void __launch_bounds__(kThreads) k_gs_update(T* __restrict__ t, const
                                                         const T* __restrict__ V, size_t stride, size_t n,
                                                         const double* __restrict__ pd, int nd,
                                                         const double* __restrict__ pu, int npu,
-                                                        double* __restrict__ S, double* __restrict__ pout) {
+                                                        double* __restrict__ S, double* __restrict__ pout,
+                                                        Many m) {
+  if (m.act && !m.act[blockIdx.y]) return;
+  t += blockIdx.y * m.bs;
+  u0 += blockIdx.y * m.bs;
+  if (K > 1) V += blockIdx.y * m.bs;
+  pd += blockIdx.y * m.ps;
+  if (K > 1) pu += blockIdx.y * m.ps;
+  pout += blockIdx.y * m.ps;
+  S += blockIdx.y * kGsScal;
   constexpr int NA = K == 1 ? 2 : K, NB = K == 1 ? 0 : K;
   __shared__ double red[(NA + NB) * 4];
   __shared__ double red2[(K + 1) * 4];
@@ -551,7 +560,12 @@ __device__ __forceinline__ void gs_solve(const double* __restrict__ pu, int npu,
 template <typename T, int K>
 __global__ void __launch_bounds__(kThreads) k_gs_combine(T* __restrict__ x, const T* __restrict__ Z, size_t stride,
                                                          size_t n, const double* __restrict__ pu, int npu,
-                                                         const double* __restrict__ S, bool assign) {
+                                                         const double* __restrict__ S, bool assign, Many m) {
+  if (m.act && !m.act[blockIdx.y]) return;
+  x += blockIdx.y * m.bs;
+  Z += blockIdx.y * m.bs;
+  pu += blockIdx.y * m.ps;
+  S += blockIdx.y * kGsScal;
   __shared__ double red[(K + 1) * 4];
   double y[K], rho[K + 1];
   gs_solve<K, false>(pu, npu, S, red, threadIdx.x, y, rho);
@@ -572,7 +586,15 @@ __global__ void __launch_bounds__(kThreads) k_gs_combine_restrict(T* __restrict_
                                                                   const T* __restrict__ u0, const T* __restrict__ V,
                                                                   size_t stride, int Nc, const double* __restrict__ pu,
                                                                   int npu, const double* __restrict__ S,
-                                                                  T* __restrict__ coarse) {
+                                                                  T* __restrict__ coarse, Many m) {
+  if (m.act && !m.act[blockIdx.y]) return;
+  x += blockIdx.y * m.bs;
+  Z += blockIdx.y * m.bs;
+  u0 += blockIdx.y * m.bs;
+  V += blockIdx.y * m.bs;
+  pu += blockIdx.y * m.ps;
+  S += blockIdx.y * kGsScal;
+  coarse += blockIdx.y * (m.bs / 4);
   __shared__ double red[(K + 1) * 4];
   double y[K], rho[K + 1];
   gs_solve<K, true>(pu, npu, S, red, threadIdx.x, y, rho);
@@ -691,6 +713,10 @@ int gs_blocks(size_t n) {
   const size_t g = (n + kThreads - 1) / kThreads;
   return (int)(g < 1 ? 1 : (g > 768 ? 768 : g));
 }
+static int gs_blocks(size_t n, const Many& m) {
+  const int g = gs_blocks(n);
+  return m.nblk > 0 && m.nblk < g ? m.nblk : g;
+}
 
 // f(std::integral_constant<int, k>) for 1 <= k <= 8
 template <typename F>
@@ -710,44 +736,49 @@ static void gs_dispatch(int k, F f) {
 
 template <typename T>
 void launch_gs_update(T* t, const T* u0, const T* V, int k, size_t stride, size_t n, const double* pd, int nd,
-                      const double* pu, double* S, double* pout, hipStream_t s) {
+                      const double* pu, double* S, double* pout, hipStream_t s, Many m) {
   if (k > 1 && pu == pout) throw Error(IBMG_ERR_ARG, "the update's partial sums need a buffer of their own");
+  if (m.nsys <= 0) return;
+  const int nb = gs_blocks(n, m);
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_update<T, decltype(kc)::value>), dim3(gs_blocks(n)), dim3(kThreads), 0, s, t, u0, V, stride, n, pd,
-                 nd, pu, gs_blocks(n), S, pout);
+    IBMG_KLAUNCH((k_gs_update<T, decltype(kc)::value>), dim3(nb, m.nsys), dim3(kThreads), 0, s, t, u0, V, stride, n, pd,
+                 nd, pu, nb, S, pout, m);
   });
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_gs_combine(T* x, const T* Z, int k, size_t stride, size_t n, const double* pu, double* S, bool assign,
-                       hipStream_t s) {
+                       hipStream_t s, Many m) {
+  if (m.nsys <= 0) return;
+  const int nb = gs_blocks(n, m);
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_combine<T, decltype(kc)::value>), dim3(stream_blocks(n)), dim3(kThreads), 0, s, x, Z, stride, n, pu,
-                 gs_blocks(n), S, assign);
+    IBMG_KLAUNCH((k_gs_combine<T, decltype(kc)::value>), dim3(m.nblk > 0 ? nb : stream_blocks(n), m.nsys), dim3(kThreads),
+                 0, s, x, Z, stride, n, pu, nb, S, assign, m);
   });
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k, size_t stride, int Nc,
-                                const double* pu, double* S, T* coarse, hipStream_t s) {
+                                const double* pu, double* S, T* coarse, hipStream_t s, Many m) {
+  if (m.nsys <= 0) return;
   const int nb = ((Nc + 63) / 64) * ((Nc + 3) / 4);
   const size_t n = (size_t)12 * Nc * Nc;
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_combine_restrict<T, decltype(kc)::value>), dim3(nb), dim3(kThreads), 0, s, x, Z, u0, V, stride, Nc,
-                 pu, gs_blocks(n), S, coarse);
+    IBMG_KLAUNCH((k_gs_combine_restrict<T, decltype(kc)::value>), dim3(nb, m.nsys), dim3(kThreads), 0, s, x, Z, u0, V,
+                 stride, Nc, pu, gs_blocks(n, m), S, coarse, m);
   });
   IBMG_LAUNCH_CHECK();
 }
 
 #define IBMG_INST_KRY(T)                                                                               \
   template void launch_gs_update<T>(T*, const T*, const T*, int, size_t, size_t, const double*, int,   \
-                                    const double*, double*, double*, hipStream_t);                     \
+                                    const double*, double*, double*, hipStream_t, Many);               \
   template void launch_gs_combine<T>(T*, const T*, int, size_t, size_t, const double*, double*, bool,  \
-                                     hipStream_t);                                                     \
+                                     hipStream_t, Many);                                               \
   template void launch_gs_combine_restrict<T>(T*, const T*, const T*, const T*, int, size_t, int,      \
-                                              const double*, double*, T*, hipStream_t);                \
+                                              const double*, double*, T*, hipStream_t, Many);          \
   template void launch_upd_dots<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,     \
                                    double*, hipStream_t, int);                                         \
   template void launch_upd_norm<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,     \

@@ -387,11 +387,11 @@ class Solver final : public SolverBase {
     const size_t nnz = lev.f[0].tcol.size() + lev.f[1].tcol.size();
     lev.ib_rows.clear();
     lev.ib_lanes = 0;
-    // (a member of a batch applies its operator through the batch's own rows)
-    if (defer_coarse_ || nnz == 0 || nnz > kIbRowsMaxEntries || std::getenv("IBMG_NO_IB_ROWS")) return;
+    // (a batch runs every member's rows in one launch, whatever their number)
+    if (!defer_coarse_ && (nnz == 0 || nnz > kIbRowsMaxEntries || std::getenv("IBMG_NO_IB_ROWS"))) return;
     std::vector<unsigned char> flag(nn, 0);
     for (int c = 0; c < 2; ++c)
-      for (int q = 0; q < nn; ++q)
+      for (int q = 0; q < nn && !lev.f[c].tcol.empty(); ++q)
         if (lev.f[c].tptr[q + 1] > lev.f[c].tptr[q]) {
           lev.ib_rows.push_back(c * nn + q);
           flag[q] |= (unsigned char)(1 << c);
