@@ -220,7 +220,7 @@ def large_bench(reps=20):
 def batch_bench(dev, reps=3):
     """The batched form: 64 independent systems (N in {64, 128, 256}, kappa
     log-uniform in [1e1, 1e5], membranes of 4N points), FP32 smoother, each
-    solved to 1e-8; set-up (with the tile autotuner) timed separately."""
+    solved to 1e-8; set-up timed separately."""
     import torch
     import workloads as W
     from paper_1612_02208_amd import StokesIBBatch
@@ -248,9 +248,10 @@ def batch_bench(dev, reps=3):
            "converged": info["converged"], "solve_ms": 1e3 * t, "systems_per_s": 64 / t,
            "vcycles_per_s": sum(its) / t, "iters_min": min(its), "iters_max": max(its),
            "max_rel_res_true": max(si["rel_res_true"] for si in info["systems"]), "setup_s": setup,
-           "tuned_plans": [dict(N=lv["N"], systems=lv["systems"], tile=lv["tile"], grid=lv["grid"],
-                                sweep_us=lv["sweep_us"]) for lv in st["levels"][1:]],
-           "ras_batch_finest": {"kernel": "k_ras_batch<float>", "N": top["N"], "systems": top["systems"],
+           "sweeps": [dict(N=lv["N"], systems=lv["systems"], tile=lv["tile"], grid=lv["grid"],
+                           sweep_us=lv["sweep_us"]) for lv in st["levels"][1:]],
+           "ras_batch_finest": {"kernel": "k_ras_rows<float> / k_ras_w<float> and its followers, all systems",
+                                "N": top["N"], "systems": top["systems"],
                                 "avg_ms": kt["ms"], "alg_bytes": kt["bytes"],
                                 "achieved_gbs": kt["bytes"] / kt["ms"] / 1e6,
                                 "frac_hbm": kt["bytes"] / kt["ms"] / 1e6 / HBM_PEAK_GBS}}

@@ -326,8 +326,8 @@ ibmg_status ibmg_sc_info(const ibmg_handle* h, int32_t level, double* lam, int32
  *                             row and K column orbits)
  *   IBMG_KERNEL_STENCIL       the Stokes stencil k_apply (no IB term): 6 N^2
  *                             values
- *   IBMG_KERNEL_RAS_BATCH     (batch handles) the persistent batched Schwarz
- *                             launch of a level with its tuned plan
+ *   IBMG_KERNEL_RAS_BATCH     (batch handles) the Schwarz sweep of a level over
+ *                             every system's boxes
  *   IBMG_KERNEL_RESTRICT      restriction from `level` (>= 1) to the next
  *                             coarser level: 3 n_f^2 + 3 n_c^2 values
  *   IBMG_KERNEL_PROLONG       prolongation from the next coarser level added
@@ -381,9 +381,8 @@ ibmg_status ibmg_kernel_time(ibmg_handle* h, int32_t kernel, int32_t level, int3
  * systems must share coarse_N, rho, mu, dt, box, overlap, nu1, nu2 and
  * precision, and use the Schwarz smoother (IBMG_ERR_ARG otherwise).  The
  * V-cycle (Alg. 1) runs on every system in lockstep by level: each smoother
- * sweep is one persistent launch over all (system, box) items, tuned at
- * creation by timing the candidate tile widths and grid sizes; the V-cycle
- * is replayed from a HIP graph.  Vectors are passed as host arrays of nsys
+ * sweep runs over every system's boxes at once; the V-cycle is replayed from
+ * a HIP graph.  Vectors are passed as host arrays of nsys
  * device pointers in the order of descs, system i's vector holding 3 N_i^2
  * doubles in the single-system layout.  Single-system calls on a batch
  * handle (and batch calls on a single handle) return IBMG_ERR_STATE.
@@ -411,8 +410,9 @@ ibmg_status ibmg_batch_fgmres_solve(ibmg_handle* h, const double* const* b, doub
                                     ibmg_stream stream);
 
 /* Batch statistics: [nsys, levels, then per level: n, systems on the level,
- * interior boxes, IB boxes, explicit IB rows, chosen tile width, chosen
- * persistent grid, tuned sweep time in ns]; count in *written. */
+ * interior boxes, IB boxes, explicit IB rows, boxes of an interior tile,
+ * items of a sweep (interior tiles and IB row chunks), time of a sweep in ns
+ * measured at creation]; count in *written. */
 ibmg_status ibmg_batch_stats(const ibmg_handle* h, int64_t* out, int32_t cap, int32_t* written);
 
 #ifdef __cplusplus

@@ -8,7 +8,7 @@
 // level's batch vectors are nact_l level vectors back to back.  A system
 // whose finest level is l joins the descent there and leaves the ascent
 // there.  Per level and sweep: one launch for L_IB with its IB rows and dots,
-// one persistent RAS launch over every (system, box) item, and the
+// the Schwarz launches over every system's boxes, and the
 // Gram-Schmidt update over all systems at once.  The outer FGMRES(m) runs
 // per system in lockstep with one host read of all residual estimates per
 // iteration; converged systems drop out through device-side active flags.
@@ -57,7 +57,16 @@ class BatchSolver final : public BatchBase {
     order_.resize(nsys);
     std::iota(order_.begin(), order_.end(), 0);
     std::stable_sort(order_.begin(), order_.end(), [&](int a, int b) { return d[a].N > d[b].N; });
-    for (int p = 0; p < nsys; ++p) sys_.emplace_back(new Solver<T>(d[order_[p]], s, true));
+    // systems per level (coarse_N 2^l has the same size in every system)
+    std::vector<int> members;
+    for (int p = 0; p < nsys; ++p) {
+      int l = 0;
+      for (int n = d[order_[p]].N; ; n /= 2, ++l)
+        if (n <= d0.coarse_N) break;
+      if ((int)members.size() <= l) members.resize(l + 1, 0);
+      for (int k = 0; k <= l; ++k) members[k]++;
+    }
+    for (int p = 0; p < nsys; ++p) sys_.emplace_back(new Solver<T>(d[order_[p]], s, true, members));
     {
       // every system's coarsest matrix has the same size (shared coarse_N):
       // they are swept a group at a time, one run of sweeps per group of up
@@ -99,7 +108,7 @@ class BatchSolver final : public BatchBase {
     build_outer_rows(s);
     build_coarse(s);
     alloc_outer(max_restart_);
-    tune(s);
+    time_sweeps(s);
     IBMG_HIP(hipStreamSynchronize(s));
     setup_ms_ = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_begin).count();
   }
@@ -124,14 +133,21 @@ class BatchSolver final : public BatchBase {
     DBuf<IbRows<T>> ib_tab;
     IbRows<T> rows{};
     int nrows = 0;
-    // Schwarz boxes
+    // Schwarz boxes: (system, box) entries; IB boxes with whole rows and their
+    // inverses, eliminated ones and their factors, interior boxes and the class
+    // matrices of the first member that has one
     BoxGeom g{};
-    int nbox = 0, n_int = 0, n_ib = 0;
-    DBuf<int> int_ents, ib_ents, loc;
-    DBuf<const T*> ib_inv;
-    const T* shared_inv = nullptr;
-    RasBatchPlan plan;
-    double tuned_us = 0;
+    int nbox = 0, n_int = 0, n_rows = 0, n_elim = 0;
+    double w_vals = 0;   // values of W over all eliminated boxes
+    DBuf<int> int_ents, row_ents, elim_ents, wptr, wrow;
+    DBuf<const T*> row_inv;
+    DBuf<const void*> wtab, qtab;
+    DBuf<unsigned short> ord;
+    DBuf<unsigned char> coupled;
+    DBuf<T> w_res, sym_part;
+    SymIB sym{};
+    IntClassView cls{};
+    double sweep_us = 0;
   };
 
   // ---------------------------------------------------------------- set-up
@@ -222,30 +238,66 @@ class BatchSolver final : public BatchBase {
       L.pst = (size_t)std::max(apply_blocks(L.N, L.rows.n, L.rows.lanes, L.nblk), gs_blocks(L.n)) * (kMaxNu + 1);
       L.part.alloc(3 * (size_t)L.nact * L.pst);
       L.scal.alloc((size_t)L.nact * kGsScal);
-      // Schwarz items: (system, box) entries, own inverses for IB boxes, the
-      // first available interior inverse for every interior box (equal
-      // fluid coefficients and box geometry give one interior matrix)
+      // (equal fluid coefficients and box geometry give one interior matrix)
       L.g = l0.g;
       L.nbox = L.g.npd * L.g.npd;
       require((size_t)L.nact * L.nbox < ((size_t)1 << 31), "too many boxes");
-      std::vector<int> ie, be;
-      std::vector<const T*> bi;
+      L.g.nbs = L.nbox;
+      L.g.sysn = L.n;
+      L.g.act = d_act_.p;
       const size_t stride = sys_[0]->box_stride(l0);
+      std::vector<int> ie, re, ee, wptr(1, 0), wrow;
+      std::vector<const T*> ri;
+      std::vector<const void*> wt, qt;
+      std::vector<unsigned short> ord;
+      std::vector<unsigned char> cpl;
+      int wmax = 0;
       for (int p = 0; p < L.nact; ++p) {
         Level<T>& lev = sys_[p]->levels_[l];
         for (int i = 0; i < lev.n_ib; ++i) {
-          be.push_back(p * L.nbox + lev.ib_list[i]);
-          bi.push_back(lev.inv.p + (size_t)i * stride);
+          const int ent = p * L.nbox + lev.ib_list[i];
+          if (!lev.use_sym) {
+            re.push_back(ent);
+            ri.push_back(lev.inv.p + (size_t)i * stride);
+            continue;
+          }
+          ee.push_back(ent);
+          wt.push_back(lev.wmat.p + (size_t)lev.wptr[i] * lev.w_stride);
+          qt.push_back(lev.inv_sym.p + (size_t)i * sym_box_stride(lev.g));
+          wrow.insert(wrow.end(), lev.wrow.begin() + lev.wptr[i], lev.wrow.begin() + lev.wptr[i + 1]);
+          wptr.push_back((int)wrow.size());
+          ord.insert(ord.end(), lev.ord.begin() + (size_t)i * lev.g.nown, lev.ord.begin() + (size_t)(i + 1) * lev.g.nown);
+          cpl.insert(cpl.end(), lev.coupled.begin() + (size_t)i * lev.g.nown,
+                     lev.coupled.begin() + (size_t)(i + 1) * lev.g.nown);
+          wmax = std::max(wmax, lev.wptr[i + 1] - lev.wptr[i]);
         }
         for (int q : lev.int_list) ie.push_back(p * L.nbox + q);
-        if (!L.shared_inv && !lev.int_list.empty()) L.shared_inv = lev.inv.p + (size_t)lev.n_ib * stride;
+        if (!L.cls.M && !lev.int_list.empty()) L.cls = lev.clsv;
       }
       L.n_int = (int)ie.size();
-      L.n_ib = (int)be.size();
+      L.n_rows = (int)re.size();
+      L.n_elim = (int)ee.size();
       L.int_ents.upload(ie, s);
-      L.ib_ents.upload(be, s);
-      L.ib_inv.upload(bi, s);
-      L.loc.upload(l0.loc_tab, s);
+      L.row_ents.upload(re, s);
+      L.row_inv.upload(ri, s);
+      if (L.n_elim) {
+        L.w_vals = (double)wrow.size() * l0.bm.nn;
+        L.elim_ents.upload(ee, s);
+        L.wtab.upload(wt, s);
+        L.qtab.upload(qt, s);
+        L.wptr.upload(wptr, s);
+        L.wrow.upload(wrow, s);
+        L.ord.upload(ord, s);
+        L.coupled.upload(cpl, s);
+        L.w_res.alloc((size_t)L.n_elim * L.g.nown);
+        L.sym_part.alloc((size_t)L.n_elim * sym_part_len(L.g));
+        L.sym = SymIB{nullptr, L.qtab.p, L.sym_part.p,
+                      WBoxView{nullptr, L.wtab.p, L.wptr.p, L.wrow.p, l0.d_nonown.p, L.coupled.p, L.ord.p, l0.bm.nn,
+                               (l0.bm.nn + 3) / 4 * 4, wmax},
+                      L.w_res.p};
+      }
+      // (the sources of asynchronous copies end with this level's scope)
+      IBMG_HIP(hipStreamSynchronize(s));
     }
     n0_ = sys_[0]->n0_;
   }
@@ -265,62 +317,31 @@ class BatchSolver final : public BatchBase {
                               hipMemcpyDeviceToDevice, s));
   }
 
-  // Autotuner: time every (tile width, persistent grid) candidate of each
-  // level's Schwarz launch with HIP events and keep the fastest.  All
-  // candidates compute the same sums in the same order, so the choice
-  // changes the time only.
-  void tune(hipStream_t s) {
+  // Time of each level's Schwarz sweep (reported by stats).
+  void time_sweeps(hipStream_t s) {
     if (dry_run()) return;
-    hipEvent_t e0, e1;
-    IBMG_HIP(hipEventCreate(&e0));
-    IBMG_HIP(hipEventCreate(&e1));
-    try {
-      for (int l = 1; l <= Lmax_; ++l) {
-        BLevel& L = lv_[l];
-        launch_fill<T>(L.r.p, T(1), (size_t)L.nact * L.n, s);
-        double best = 1e300;
-        for (int tb : {16, 32, 64}) {
-          const int items = ras_batch_items(L.g, L.n_int, L.n_ib, tb);
-          if (items <= 0) continue;
-          std::vector<int> grids;
-          for (int gsz : {256, 512, 1024, 2048, 4096})
-            if (gsz < items) grids.push_back(gsz);
-          grids.push_back(items);
-          for (int gsz : grids) {
-            RasBatchPlan pl{tb, gsz};
-            ras(l, L.r.p, L.w.p, pl, s);
-            IBMG_HIP(hipEventRecord(e0, s));
-            constexpr int reps = 5;
-            for (int k = 0; k < reps; ++k) ras(l, L.r.p, L.w.p, pl, s);
-            IBMG_HIP(hipEventRecord(e1, s));
-            IBMG_HIP(hipEventSynchronize(e1));
-            float ms = 0;
-            IBMG_HIP(hipEventElapsedTime(&ms, e0, e1));
-            const double us = 1e3 * ms / reps;
-            if (us < best) {
-              best = us;
-              L.plan = pl;
-            }
-          }
-        }
-        L.tuned_us = best < 1e300 ? best : 0.0;
-        launch_fill<T>(L.r.p, T(0), (size_t)L.nact * L.n, s);
-        launch_fill<T>(L.w.p, T(0), (size_t)L.nact * L.n, s);
-      }
-    } catch (...) {
-      (void)hipEventDestroy(e0);
-      (void)hipEventDestroy(e1);
-      throw;
+    for (int l = 1; l <= Lmax_; ++l) {
+      BLevel& L = lv_[l];
+      launch_fill<T>(L.r.p, T(1), (size_t)L.nact * L.n, s);
+      L.sweep_us = 1e3 * time_launches([&] { ras(l, L.r.p, L.w.p, s); }, 5, s);
+      launch_fill<T>(L.r.p, T(0), (size_t)L.nact * L.n, s);
+      launch_fill<T>(L.w.p, T(0), (size_t)L.nact * L.n, s);
     }
-    IBMG_HIP(hipEventDestroy(e0));
-    IBMG_HIP(hipEventDestroy(e1));
   }
 
   // --------------------------------------------------------- level pieces
-  void ras(int l, const T* r, T* z, RasBatchPlan pl, hipStream_t s) {
+  // One sweep over every active system's boxes: the boxes with whole rows and
+  // the interior ones in one launch, then the eliminated boxes' three (the first
+  // with the interior boxes where no box has whole rows).
+  void ras(int l, const T* r, T* z, hipStream_t s) {
     BLevel& L = lv_[l];
-    launch_ras_batch<T>(r, z, L.g, L.n, L.nbox, L.shared_inv, L.int_ents.p, L.n_int, L.ib_ents.p, L.ib_inv.p,
-                        L.n_ib, L.loc.p, d_act_.p, pl, s);
+    const bool rows = L.n_rows > 0 || !L.n_elim;
+    if (rows)
+      launch_ras_apply<T>(r, z, L.g, nullptr, L.row_ents.p, L.n_rows, L.cls, L.int_ents.p, L.n_int, s, 3, false,
+                          nullptr, L.row_inv.p);
+    if (L.n_elim)
+      launch_ras_apply<T>(r, z, L.g, nullptr, L.elim_ents.p, L.n_elim, L.cls, L.int_ents.p, rows ? 0 : L.n_int, s, 3,
+                          false, &L.sym);
   }
 
   Many many(const BLevel& L) const {
@@ -355,7 +376,7 @@ class BatchSolver final : public BatchBase {
       const T* uk = k == 0 ? u0 : V + (size_t)k * bn;
       T* zk = L.Z.p + (size_t)k * bn;
       T* t = V + (size_t)(k + 1) * bn;
-      ras(l, uk, zk, L.plan, s);
+      ras(l, uk, zk, s);
       launch_apply_dots<T>(zk, t, nullptr, L.rows, none, none, L.N, 0, L.c, u0, V, k + 1, bn, pd, s, m);
       launch_gs_update<T>(t, u0, V, k + 1, bn, n, pd, nd, pu[(k + 1) & 1], L.scal.p, pu[k & 1], s, m);
     }
@@ -673,10 +694,10 @@ class BatchSolver final : public BatchBase {
     return all ? IBMG_OK : IBMG_NOT_CONVERGED;
   }
 
-  // The persistent Schwarz launch of a batch level alone, on the level's
-  // work vectors (filled with ones), with the tuned plan.  Algorithmic work:
-  // each IB box streams its owned inverse rows, the interior product reads
-  // the shared inverse once; every box gathers nloc values and writes nown.
+  // The Schwarz sweep of a batch level alone, on the level's work vectors
+  // (filled with ones).  Algorithmic work: each IB box streams its whole rows or
+  // its two factors, the interior product reads the class matrices once; every
+  // box gathers nloc values and writes nown.
   double kernel_time(int kernel, int level, int reps, hipStream_t s, double* bytes, double* flops) override {
     require(kernel == IBMG_KERNEL_RAS_BATCH, "batch handles time the batched Schwarz launch only");
     require(level >= 1 && level <= Lmax_, "level out of range");
@@ -686,17 +707,20 @@ class BatchSolver final : public BatchBase {
     launch_fill<T>(L.r.p, T(1), (size_t)L.nact * L.n, s);
     const double ts = sizeof(T);
     const BoxGeom& g = L.g;
-    double by = (double)L.n_ib * ((double)g.nown * g.nloc + g.nloc + g.nown) * ts +
-                (double)L.n_int * (g.nloc + g.nown) * ts;
-    if (L.n_int > 0) by += (double)g.nown * g.nloc * ts;
-    const double ms = time_launches([&] { ras(level, L.r.p, L.w.p, L.plan, s); }, reps, s);
+    const double n_ib = L.n_rows + L.n_elim, q = (double)L.n_elim * sym_box_stride(g);
+    double by = ((double)L.n_rows * g.nown * g.nloc + L.w_vals + q + (n_ib + L.n_int) * (g.nloc + g.nown)) * ts;
+    if (L.n_int > 0) by += 4.0 * L.cls.nrt * L.cls.Kp * 16 * ts;
+    const double ms = time_launches([&] { ras(level, L.r.p, L.w.p, s); }, reps, s);
     if (bytes) *bytes = by;
-    if (flops) *flops = 2.0 * (double)(L.n_ib + L.n_int) * g.nown * g.nloc;
+    if (flops)
+      *flops = 2.0 * ((double)L.n_rows * g.nown * g.nloc + L.w_vals + (double)L.n_elim * g.nown * g.nown +
+                      4.0 * L.n_int * L.cls.R * L.cls.K);
     return ms;
   }
 
-  // [nsys, levels, then per level: N, systems, interior boxes, IB boxes,
-  //  IB rows, tile width, persistent grid, tuned sweep time (ns)]
+  // [nsys, levels, then per level: N, systems, interior boxes, IB boxes, IB
+  //  rows, boxes of an interior tile, items of a sweep (interior tiles and IB
+  //  row chunks), sweep time (ns)]
   std::vector<int64_t> stats() const override {
     std::vector<int64_t> v{ns_, Lmax_ + 1};
     for (int l = 0; l <= Lmax_; ++l) {
@@ -704,11 +728,11 @@ class BatchSolver final : public BatchBase {
       v.push_back(L.N);
       v.push_back(L.nact);
       v.push_back(L.n_int);
-      v.push_back(L.n_ib);
+      v.push_back(L.n_rows + L.n_elim);
       v.push_back(L.nrows);
-      v.push_back(L.plan.tb);
-      v.push_back(L.plan.grid);
-      v.push_back((int64_t)(L.tuned_us * 1e3));
+      v.push_back(l ? 16 : 0);
+      v.push_back((L.n_int + 15) / 16 * L.cls.nrt + (L.n_rows + L.n_elim) * L.g.nch);
+      v.push_back((int64_t)(L.sweep_us * 1e3));
     }
     return v;
   }

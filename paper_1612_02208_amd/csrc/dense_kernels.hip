@@ -843,6 +843,19 @@ __device__ __forceinline__ size_t own_glob(const BoxGeom& g, int pid, int r) {
   return (size_t)comp * g.N * g.N + (size_t)gj * g.N + gi;
 }
 
+// box and vector offset of an entry (SYS: of many systems); false: its system is
+// not active
+template <bool SYS>
+__device__ __forceinline__ bool box_entry(const BoxGeom& g, int ent, int& pid, size_t& base) {
+  pid = ent;
+  base = 0;
+  if (!SYS) return true;
+  const int sys = ent / g.nbs;
+  pid = ent - sys * g.nbs;
+  base = sys * g.sysn;
+  return !g.act || g.act[sys];
+}
+
 // Rows of A^{-1}, stored per box as row chunks of 64: element (row, j)
 // at (row / 64) * nloc * 64 + j * 64 + row % 64 (rows beyond nown are 0), so
 // a chunk's 64 rows of one column are contiguous and a chunk is one
@@ -959,12 +972,6 @@ void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr,
 //   z[G~_k] = (L_k^{-1} R_k r)[G~_k]  for every box k.
 // The owned sets partition the unknowns, so every z entry is written by
 // exactly one work-group and no atomics are needed.
-//
-// Boxes with their own inverse (IB boxes): work-group = (box, 64-row chunk).
-// R_k r is gathered into LDS; each wave streams a quarter of the chunk's
-// columns with 16-byte loads (a wave reads 1 KB of contiguous inverse per
-// load: VEC rows per lane, VEC columns side by side), lane groups are summed
-// by shuffles and the four quarters in a fixed order.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Vec16;
@@ -978,93 +985,6 @@ struct Vec16<float> {
   typedef float type __attribute__((ext_vector_type(4)));
   static constexpr int n = 4;
 };
-
-// One (box, 64-row chunk) item over columns [cb, ce) of the chunk: Mc is the
-// chunk of the box's owned-row inverse, r and z the box's system vectors; x
-// holds nloc values (LDS, indexed by column), part 256.  With pout the 64
-// row sums of this column slice go to pout instead of z.  PRE issues the
-// first loads of the inverse before the gather (it holds their registers
-// across it, which the batched kernel cannot spare).
-template <typename T, bool PRE>
-__device__ __forceinline__ void ras_ib_chunk(const T* __restrict__ r, T* __restrict__ z, const BoxGeom& g,
-                                             const T* __restrict__ Mc, int pid, int chunk, T* x, T* part,
-                                             bool acc_mode, int cb, int ce, T* __restrict__ pout) {
-  using V = typename Vec16<T>::type;
-  constexpr int VEC = Vec16<T>::n;
-  constexpr int LPC = 64 / VEC;  // lanes per column
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int cph = lane / LPC;           // column phase 0..VEC-1
-  const int rl = (lane % LPC) * VEC;    // first of this lane's VEC rows
-  const int per = ((ce - cb + 4 * VEC - 1) / (4 * VEC)) * VEC;
-  const int j0 = cb + q * per, j1 = j0 + per < ce ? j0 + per : ce;
-  Mc += rl;
-  int j = j0 + cph;
-  // eight 16-byte loads in flight per lane, summed in a fixed tree; the
-  // inverse streams through once per sweep, so its loads are non-temporal
-  // and leave the caches to the level's vectors.  With PRE the first eight
-  // are issued before the residual gather, so that they overlap it.
-  constexpr int UNR = 8;
-  auto load8 = [&](V* m, int jj) {
-#pragma unroll
-    for (int u = 0; u < UNR; ++u)
-      m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jj + u * VEC) * 64));
-  };
-  T acc[VEC];
-#pragma unroll
-  for (int v = 0; v < VEC; ++v) acc[v] = 0;
-  auto fma8 = [&](const V* m, int jj) {
-    T xv[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) xv[u] = x[jj + u * VEC];
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      T t[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) t[u] = reinterpret_cast<const T*>(&m[u])[v] * xv[u];
-      acc[v] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-    }
-  };
-  const bool first = PRE && j + (UNR - 1) * VEC < j1;
-  V m0[UNR];
-  if (first) load8(m0, j);
-  for (int k = cb + threadIdx.x; k < ce; k += blockDim.x) x[k] = r[box_glob(g, pid, k)];
-  __syncthreads();
-  if (first) {
-    fma8(m0, j);
-    j += UNR * VEC;
-  }
-  for (; j + (UNR - 1) * VEC < j1; j += UNR * VEC) {
-    V m[UNR];
-    load8(m, j);
-    fma8(m, j);
-  }
-  for (; j < j1; j += VEC) {
-    const V m0 = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)j * 64));
-    const T* a0 = reinterpret_cast<const T*>(&m0);
-    const T x0 = x[j];
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[v] += a0[v] * x0;
-  }
-  // sum the VEC column phases (lanes l, l + LPC, ...)
-#pragma unroll
-  for (int off = 32; off >= LPC; off >>= 1)
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[v] += __shfl_down(acc[v], off, 64);
-  if (lane < LPC)
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) part[q * 64 + rl + v] = acc[v];
-  __syncthreads();
-  if (q == 0) {
-    const int row = chunk * 64 + lane;
-    const T v = (part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]);
-    if (pout) {
-      pout[lane] = v;
-    } else if (row < g.nown) {
-      const size_t o = own_glob(g, pid, row);
-      z[o] = acc_mode ? z[o] + v : v;
-    }
-  }
-}
 
 // Rows rsub R .. (R = 64 / RS) of one (box, 64-row chunk) item, whole columns, by
 // NW waves: a wave streams batches of eight 16-byte loads a lane (CP columns of R
@@ -1132,18 +1052,17 @@ __device__ __forceinline__ void ras_rows_block(const T* __restrict__ r, T* __res
   }
 }
 
-// First pass of the eliminated boxes: t = W r_n for the rows [lo, hi) of W (box
-// slot's rows; t by position).  Each lane keeps its share of the box's non-owned
+// First pass of the eliminated boxes: t = W r_n for the rows [lo, hi) of W (row e
+// at Wm + e ws; t by position).  Each lane keeps its share of the box's non-owned
 // residual in registers (CH 16-byte groups of columns) and every wave streams its
 // rows, 16 bytes a lane and load, the next row loading during the current one's
 // sum over the wave.
 template <typename T, int CH, int NW>
 __device__ __forceinline__ void ras_w_block(const T* __restrict__ r, const BoxGeom& g, int pid, const WBoxView& w,
-                                            int lo, int hi, T* __restrict__ t, T* xs) {
+                                            const T* __restrict__ Wm, int lo, int hi, T* __restrict__ t, T* xs) {
   using V = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const T* Wm = static_cast<const T*>(w.W);
   V m[CH], nx[CH];
   int pos = 0, npos = 0;
   auto load = [&](int e) {
@@ -1189,10 +1108,11 @@ __device__ __forceinline__ void ras_w_block(const T* __restrict__ r, const BoxGe
 // column phase, which belongs to row q of an earlier chunk.  The box's partials:
 // the chunk's row sums per slice at sym_part_off(c, ks), its column sums after
 // them (each column in one slice).
-template <typename T>
+template <typename T, bool SYS>
 __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, const T* __restrict__ t, BoxGeom g,
                                                     const int* __restrict__ boxes, WBoxView w,
-                                                    const T* __restrict__ inv, T* __restrict__ part) {
+                                                    const T* __restrict__ inv, const void* const* __restrict__ qtab,
+                                                    T* __restrict__ part) {
   using V = typename Vec16<T>::type;
   constexpr int VEC = Vec16<T>::n;
   constexpr int LPC = 64 / VEC;   // lanes per column
@@ -1212,7 +1132,12 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, con
     if (tid < 64) pb[64 * sl + tid] = T(0);
     return;
   }
-  const T* Mc = inv + (size_t)slot * sym_chunk_off(g.nch) + sym_chunk_off(c) + rl;
+  int pid;
+  size_t base;
+  if (!box_entry<SYS>(g, boxes[slot], pid, base)) return;
+  r += base;
+  const T* Q = SYS ? static_cast<const T*>(qtab[slot]) : inv + (size_t)slot * sym_chunk_off(g.nch);
+  const T* Mc = Q + sym_chunk_off(c) + rl;
   // the wave's first batch is issued before the residual, so its trip from
   // memory overlaps that one (columns come in whole batches: ce - cb is a
   // multiple of 64)
@@ -1224,7 +1149,6 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, con
       m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jb + cph + u * VEC) * 64));
   };
   if (jb0 < ce) load(m0, jb0);
-  const int pid = boxes[slot];
   for (int k = tid; k < ncol; k += 256) {
     const size_t at = (size_t)slot * g.nown + (k < g.nown ? k : 0);
     const T ro = r[own_glob(g, pid, w.ord[at])], tk = t[at];
@@ -1279,13 +1203,16 @@ __global__ void __launch_bounds__(256) k_ras_ib_sym(const T* __restrict__ r, con
 // column slices: the owned unknown at position r = 64 c + i is chunk c's row sums
 // i of its slices, in slice order, plus the column sums at r of every later
 // chunk, added in chunk order.
-template <typename T>
+template <typename T, bool SYS>
 __global__ void k_ras_sum(const T* __restrict__ ps, const int* __restrict__ boxes, int ns, int ks,
                           const unsigned short* __restrict__ ord, T* __restrict__ z, BoxGeom g, bool acc) {
   const size_t tot = (size_t)ns * g.nown;
   for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < tot; t += (size_t)gridDim.x * blockDim.x) {
     const int b = (int)(t / g.nown), row = (int)(t % g.nown);
-    const size_t o = own_glob(g, boxes[b], ord[t]);
+    int pid;
+    size_t base;
+    if (!box_entry<SYS>(g, boxes[b], pid, base)) continue;
+    const size_t o = base + own_glob(g, pid, ord[t]);
     const int cr = row >> 6;
     const T* pp = ps + (size_t)b * sym_part_off(g.nch, ks);
     const T* pr = pp + sym_part_off(cr, ks) + (row & 63);
@@ -1340,10 +1267,11 @@ __global__ void k_ras_sum(const T* __restrict__ ps, const int* __restrict__ boxe
 template <typename T, int KS>
 struct RasIntSmem {
   T Xs[4][64 * KS][17];   // [class][orbit of the chunk][box]
-  int bid[16];
+  int bid[16];    // a box tile's boxes (-1: none) and their vectors' offsets
+  int base[16];
   int kcode[kIntMaxOrbits];
 };
-template <typename T, int KS>
+template <typename T, int KS, bool SYS>
 __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __restrict__ r, T* __restrict__ z,
                                               const BoxGeom& g, const IntClassView& C, const int* __restrict__ boxes,
                                               int nlist, int bt, int rt, bool acc_mode) {
@@ -1355,15 +1283,27 @@ __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __
   const int cls = wave & 3, kp = (wave >> 2) * 64;   // the wave's class and part of the chunk
   const int N = g.N, m = g.m, nn = N * N;
   bt *= 16;
-  if (tid < 16) bid[tid] = bt + tid < nlist ? boxes[bt + tid] : -1;
+  bool on = false;
+  if (tid < 16) {
+    int pid = -1;
+    size_t base = 0;
+    on = bt + tid < nlist && box_entry<SYS>(g, boxes[bt + tid], pid, base);
+    bid[tid] = on ? pid : -1;
+    if (SYS) sm.base[tid] = (int)base;   // (a batch's vectors have fewer than 2^31 entries)
+  }
   for (int k = tid; k < C.Kp; k += NT) kcode[k] = k < C.K ? C.kcode[k] : -1;
   // a thread's orbit within a chunk and its four boxes are fixed, the boxes
   // the same for its whole wave
-  int xb[GPT], yb[GPT];
-  __syncthreads();
+  int xb[GPT], yb[GPT], ob[GPT];
+  if (SYS) {
+    if (!__syncthreads_or(on)) return;
+  } else {
+    __syncthreads();
+  }
 #pragma unroll
   for (int u = 0; u < GPT; ++u) {
     const int pid = __builtin_amdgcn_readfirstlane(bid[(tid + u * NT) / KC]);
+    ob[u] = SYS ? __builtin_amdgcn_readfirstlane(sm.base[(tid + u * NT) / KC]) : 0;
     xb[u] = pid >= 0 ? (pid % g.npd) * g.b - g.o : -N;   // -N: no box
     yb[u] = pid >= 0 ? (pid / g.npd) * g.b - g.o : 0;
   }
@@ -1383,7 +1323,7 @@ __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __
 #pragma unroll
       for (int q = 0; q < 4; ++q) gx[u][q] = T(0);
       if (x0 >= 0 && y0 >= 0 && x0 + m < N && y0 + m < N) {   // clear of the periodic edges
-        const int at = y0 * N + x0;
+        const int at = ob[u] + y0 * N + x0;
         if (code >= 0) {
           gx[u][0] = rc[at + oe];
           gx[u][1] = rc[at + ox];
@@ -1391,7 +1331,7 @@ __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __
           gx[u][3] = rc[at + oxy];
         }
       } else if (x0 > -N && code >= 0) {
-        const int xe = wrap(x0 + ii), xm = wrap(x0 + mi), ye = wrap(y0 + jj) * N, ym = wrap(y0 + mj) * N;
+        const int xe = wrap(x0 + ii), xm = wrap(x0 + mi), ye = ob[u] + wrap(y0 + jj) * N, ym = ob[u] + wrap(y0 + mj) * N;
         gx[u][0] = rc[ye + xe];
         gx[u][1] = rc[ye + xm];
         gx[u][2] = rc[ym + xe];
@@ -1455,7 +1395,7 @@ __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __
     }
     const T p = zc[0] + zc[2], q = zc[1] + zc[3], d = zc[0] - zc[2], e = zc[1] - zc[3];
     auto put = [&](int i, int j, T v) {   // an owned image: inside the grid, no wrap
-      T* zp = z + (size_t)comp * nn + (size_t)(y0 + j) * N + x0 + i;
+      T* zp = z + (SYS ? sm.base[b] : 0) + (size_t)comp * nn + (size_t)(y0 + j) * N + x0 + i;
       *zp = acc_mode ? *zp + v : v;
     };
     if (own & 1) put(ii, jj, p + q);
@@ -1473,27 +1413,31 @@ __device__ __forceinline__ void ras_int_block(RasIntSmem<T, KS>& sm, const T* __
 // columns needs no sum.  A coarse level's application is bound by its chain of
 // latencies: 28 + 36 boxes of 8 x 8/2 9 us as one launch against 20 as three
 // (rows, interior, sum); V-cycle at 64^2 274 -> 225 us.
-template <typename T, int KS, int RS>
+template <typename T, int KS, int RS, bool SYS>
 __global__ void __launch_bounds__(256 * KS) k_ras_rows(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                       const T* __restrict__ inv, const int* __restrict__ ib_boxes,
-                                                       int nib, IntClassView C, const int* __restrict__ int_boxes,
-                                                       int n_int, bool acc) {
+                                                       const T* __restrict__ inv, const T* const* __restrict__ inv_tab,
+                                                       const int* __restrict__ ib_boxes, int nib, IntClassView C,
+                                                       const int* __restrict__ int_boxes, int n_int, bool acc) {
   __shared__ RasIntSmem<T, KS> sm;
   const int p = blockIdx.x;
   if (p < nib) {
     const int item = p / RS, slot = item / g.nch, chunk = item % g.nch;
     T* x = &sm.Xs[0][0][0];
-    ras_rows_block<T, 4 * KS, RS>(r, z, g, inv + (size_t)item * g.nloc * 64, ib_boxes[slot], chunk, p % RS, x,
+    int pid;
+    size_t base;
+    if (!box_entry<SYS>(g, ib_boxes[slot], pid, base)) return;
+    const T* M = SYS ? inv_tab[slot] : inv + (size_t)slot * g.nch * g.nloc * 64;
+    ras_rows_block<T, 4 * KS, RS>(r + base, z + base, g, M + (size_t)chunk * g.nloc * 64, pid, chunk, p % RS, x,
                                   x + g.nloc + kRowsPad, acc);
   } else {
     const int q = p - nib, nt = (n_int + 15) / 16;
-    ras_int_block<T, KS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
+    ras_int_block<T, KS, SYS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
   }
 }
 // the rows' residual, its padding and the waves' sums fit in Xs
 static_assert(4 * 64 * 17 >= kMaxNloc + kRowsPad + 4 * 64 && 4 * 128 * 17 >= kMaxNloc + kRowsPad + 8 * 64, "");
 
-template <typename T, int KS, int CH>
+template <typename T, int KS, int CH, bool SYS>
 __global__ void __launch_bounds__(256 * KS) k_ras_w(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
                                                     WBoxView w, const int* __restrict__ ib_boxes, int n_ib, int nib,
                                                     int rpg, T* __restrict__ t, IntClassView C,
@@ -1503,11 +1447,14 @@ __global__ void __launch_bounds__(256 * KS) k_ras_w(const T* __restrict__ r, T* 
   if (p < nib) {
     const int slot = p % n_ib, e1 = w.wptr[slot + 1], lo = w.wptr[slot] + p / n_ib * rpg;
     const int hi = lo + rpg < e1 ? lo + rpg : e1;
-    if (lo < hi)
-      ras_w_block<T, CH, 4 * KS>(r, g, ib_boxes[slot], w, lo, hi, t + (size_t)slot * g.nown, &sm.Xs[0][0][0]);
+    int pid;
+    size_t base;
+    if (lo >= hi || !box_entry<SYS>(g, ib_boxes[slot], pid, base)) return;
+    const T* Wm = SYS ? static_cast<const T*>(w.wtab[slot]) - (size_t)w.wptr[slot] * w.ws : static_cast<const T*>(w.W);
+    ras_w_block<T, CH, 4 * KS>(r + base, g, pid, w, Wm, lo, hi, t + (size_t)slot * g.nown, &sm.Xs[0][0][0]);
   } else {
     const int q = p - nib, nt = (n_int + 15) / 16;
-    ras_int_block<T, KS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
+    ras_int_block<T, KS, SYS>(sm, r, z, g, C, int_boxes, n_int, q % nt, q / nt, acc);
   }
 }
 static_assert(4 * 64 * 17 >= kElimMaxNn, "");
@@ -1555,323 +1502,8 @@ template void launch_extract_classes<double>(const double*, BoxMat, const unsign
 template void launch_extract_classes<float>(const double*, BoxMat, const unsigned short*, IntClassView, const int*,
                                             const int*, float*, hipStream_t);
 
-// ---------------------------------------------------------------------------
-// Interior tiles of the batched sweep (below): Z[64-row chunk, boxes] = M[chunk,
-// :] X[:, boxes] on the matrix cores, M in 64-row chunks.
-// ---------------------------------------------------------------------------
-// Gathers of a box's local residual.  The level's local-unknown table holds
-// nloc codes (comp << 24 | jj << 12 | ii) followed by nloc linear offsets
-// comp N^2 + jj N + ii.  A box whose enlarged region (corner x0, y0, faces up
-// to x0 + m, y0 + m) lies clear of the periodic edges reads unknown k at
-// base + y0 N + x0 + offset[k] (box_lin returns that start, or -1 where the
-// region wraps and each coordinate is reduced instead).
-__device__ __forceinline__ long long box_lin(const BoxGeom& g, size_t base, int x0, int y0) {
-  const bool clear = x0 >= 0 && y0 >= 0 && x0 + g.m < g.N && y0 + g.m < g.N;
-  return clear ? (long long)base + (long long)y0 * g.N + x0 : -1;
-}
-
-template <typename T>
-__device__ __forceinline__ T box_value(const T* __restrict__ r, const BoxGeom& g, const int* __restrict__ loc_tab,
-                                       int k, size_t base, long long lin, int x0, int y0) {
-  if (lin >= 0) return r[lin + loc_tab[g.nloc + k]];
-  const int N = g.N;
-  const int code = loc_tab[k];
-  int ii = (code & 0xfff) + x0, jj = ((code >> 12) & 0xfff) + y0;
-  ii = ii < 0 ? ii + N : (ii >= N ? ii - N : ii);
-  jj = jj < 0 ? jj + N : (jj >= N ? jj - N : jj);
-  return r[base + (size_t)(code >> 24) * N * N + (size_t)jj * N + ii];
-}
-
-// Shared memory of one interior tile: the gathered residual columns and the
-// tile's box table.
-constexpr int kIntLinTab = 2048;   // linear offsets of one item's reduction range kept in LDS
-
-template <typename T, int TB>
-struct IntTileSmem {
-  T Xs[64][TB + 1];
-  size_t base[TB];   // system offset of each box's vectors
-  long long lin[TB];  // see box_lin
-  int bid[TB], bx0[TB], by0[TB];
-  int ltab[kIntLinTab];
-};
-
-// One interior tile (boxes ents[tile * TB ..], 64-row chunk, reduction slice
-// kslice of ksplit): box entry e = s * nbox + box id, system s at r + s
-// sys_n; boxes of inactive systems are left out.
-template <typename T, int TB, bool REGPLAN = true>
-__device__ __forceinline__ void ras_int_tile(const T* __restrict__ r, T* __restrict__ z, const BoxGeom& g,
-                                             size_t sys_n, int nbox, const T* __restrict__ M,
-                                             const int* __restrict__ ents, int nlist, int tile, int chunk,
-                                             int kslice, int ksplit, const int* __restrict__ loc_tab,
-                                             const int* __restrict__ active, T* __restrict__ part,
-                                             IntTileSmem<T, TB>& sm, bool acc_mode) {
-  constexpr int KC = 64, GPT = KC * TB / 256, AS = KC / 4;
-  using acc_t = typename Mfma<T>::acc_t;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int bt = tile * TB;
-  if (tid < TB) {
-    const int b = bt + tid;
-    int pid = -1, sy = 0;
-    if (b < nlist) {
-      const int e = ents[b];
-      sy = e / nbox;
-      pid = e - sy * nbox;
-      if (active && !active[sy]) pid = -1;
-    }
-    sm.bid[tid] = pid;
-    sm.base[tid] = (size_t)sy * sys_n;
-    sm.bx0[tid] = pid >= 0 ? (pid % g.npd) * g.b - g.o : 0;
-    sm.by0[tid] = pid >= 0 ? (pid / g.npd) * g.b - g.o : 0;
-    sm.lin[tid] = box_lin(g, sm.base[tid], sm.bx0[tid], sm.by0[tid]);
-  }
-  // this item's slice of the reduction index: chunks [c0, c1) of KC columns
-  const int nchunk = (g.nloc + KC - 1) / KC;
-  const int per = (nchunk + ksplit - 1) / ksplit;
-  const int c0 = kslice * per;
-  const int c1 = c0 + per < nchunk ? c0 + per : nchunk;
-  // the slice's linear offsets in LDS (when they fit), so a gather waits on
-  // one trip to memory, not two
-  const int kb0 = c0 * KC, kspan = (c1 - c0) * KC;
-  const bool ltab_lds = kspan <= kIntLinTab;
-  if (ltab_lds)
-    for (int k = tid; k < kspan; k += 256) sm.ltab[k] = kb0 + k < g.nloc ? loc_tab[g.nloc + kb0 + k] : 0;
-  __syncthreads();
-  const T* Mrow = M + (size_t)chunk * g.nloc * 64 + 16 * wave + (lane & 15);
-  const int kq = lane >> 4, bl = lane & 15;
-  constexpr int NT = TB / 16;  // 16 x 16 output tiles per wave
-  acc_t acc[NT];
-#pragma unroll
-  for (int q = 0; q < NT; ++q) acc[q] = acc_t{0, 0, 0, 0};
-  T ga[AS];
-  // the gather runs along the reduction index (a wave reads 64 consecutive
-  // local unknowns of one box, mostly contiguous rows of the grid) and is
-  // transposed into Xs[k][box].  A thread's reduction index within a chunk
-  // (tid mod KC) and its boxes (one per u) are fixed, so the boxes' linear
-  // starts stay in registers and a chunk costs one offset read per thread;
-  // boxes that wrap the periodic edges (or an offset table not in LDS) take
-  // the general path.
-  // (REGPLAN = false, the batched launch: the boxes' starts are re-read from
-  // LDS per value, which keeps that kernel's register count down)
-  long long glin[GPT];
-  bool gslow = false;
-#pragma unroll
-  for (int u = 0; u < GPT; ++u) {
-    const int b = (tid + u * 256) / KC;
-    glin[u] = sm.bid[b] >= 0 ? sm.lin[b] : -2;
-    gslow |= sm.bid[b] >= 0 && (!ltab_lds || sm.lin[b] < 0);
-  }
-  auto gather = [&](int c, T* gxo) {
-    if constexpr (!REGPLAN) {
-      const int j0 = c * KC;
-#pragma unroll
-      for (int u = 0; u < GPT; ++u) {
-        const int t = tid + u * 256;
-        const int k = t % KC, b = t / KC;
-        const int jk = j0 + k;
-        T val = 0;
-        if (jk < g.nloc && sm.bid[b] >= 0) {
-          if (ltab_lds && sm.lin[b] >= 0) val = r[sm.lin[b] + sm.ltab[jk - kb0]];
-          else val = box_value<T>(r, g, loc_tab, jk, sm.base[b], sm.lin[b], sm.bx0[b], sm.by0[b]);
-        }
-        gxo[u] = val;
-      }
-      return;
-    }
-    const int jk = c * KC + tid % KC;
-    const bool in = jk < g.nloc;
-    const int off = in && ltab_lds ? sm.ltab[jk - kb0] : 0;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      T val = 0;
-      if (in && glin[u] >= 0 && ltab_lds) {
-        val = r[glin[u] + off];
-      } else if (in && gslow && glin[u] != -2) {
-        const int b = (tid + u * 256) / KC;
-        val = box_value<T>(r, g, loc_tab, jk, sm.base[b], sm.lin[b], sm.bx0[b], sm.by0[b]);
-      }
-      gxo[u] = val;
-    }
-  };
-  auto load_a = [&](int c, T* gao) {
-    const int j0 = c * KC;
-    if (j0 + KC <= g.nloc) {   // a full chunk: no bounds to test
-      const T* Mj = Mrow + (size_t)(j0 + kq) * 64;
-#pragma unroll
-      for (int s = 0; s < AS; ++s) gao[s] = Mj[(size_t)s * 256];
-    } else {
-#pragma unroll
-      for (int s = 0; s < AS; ++s) {
-        const int jk = j0 + 4 * s + kq;
-        gao[s] = jk < g.nloc ? Mrow[(size_t)jk * 64] : (T)0;
-      }
-    }
-  };
-  // the next chunk's gather and inverse rows load during the MFMAs
-  T gx[GPT];
-  if (c0 < c1) {
-    gather(c0, gx);
-    load_a(c0, ga);
-  }
-  for (int c = c0; c < c1; ++c) {
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-      const int t = tid + u * 256;
-      sm.Xs[t % KC][t / KC] = gx[u];
-    }
-    __syncthreads();
-    T a[AS];
-#pragma unroll
-    for (int s = 0; s < AS; ++s) a[s] = ga[s];
-    if (c + 1 < c1) {
-      gather(c + 1, gx);
-      load_a(c + 1, ga);
-    }
-#pragma unroll
-    for (int s = 0; s < AS; ++s) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q) acc[q] = Mfma<T>::mma(a[s], sm.Xs[4 * s + kq][16 * q + bl], acc[q]);
-    }
-    __syncthreads();
-  }
-  const int nown_pad = g.nch * 64;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int row = chunk * 64 + 16 * wave + Mfma<T>::row(kq, v);
-    if (row >= g.nown) continue;
-    if (ksplit == 1) {
-#pragma unroll
-      for (int q = 0; q < NT; ++q) {
-        const int bb = 16 * q + bl;
-        if (sm.bid[bb] >= 0) {
-          const size_t o = sm.base[bb] + own_glob(g, sm.bid[bb], row);
-          z[o] = acc_mode ? z[o] + acc[q][v] : acc[q][v];
-        }
-      }
-    } else {
-      T* pp = part + (size_t)kslice * nlist * nown_pad;
-#pragma unroll
-      for (int q = 0; q < NT; ++q)
-        if (bt + 16 * q + bl < nlist) pp[(size_t)(bt + 16 * q + bl) * nown_pad + row] = acc[q][v];
-    }
-  }
-}
-
-// Register-blocked form of the interior product: a work-group owns a
-// 64-row chunk and 64 boxes, its four waves 2 x 2 blocks of 32 rows x 32
-// boxes (four 16 x 16 MFMA tiles each).  Each 32-wide reduction step stages
-// the chunk's A block (32 x 64, contiguous rows) and the boxes' gathered
-// residuals (32 x 64) in LDS, the next step's values loading into registers
-// during the MFMAs.  The reduction runs over the same 64-column chunks and
-// slices, in the same order, as the narrow tiles, so the sums agree.
-template <typename T>
-struct GemmSmem {
-  T As[32][64];        // [reduction index][row of the chunk]
-  T Bs[32][65];        // [reduction index][box]
-  size_t base[64];
-  long long lin[64];
-  int bid[64], bx0[64], by0[64];
-};
-
-template <typename T>
-__device__ __forceinline__ void ras_int_gemm(const T* __restrict__ r, T* __restrict__ z, const BoxGeom& g,
-                                             size_t sys_n, int nbox, const T* __restrict__ M,
-                                             const int* __restrict__ ents, int nlist, int tile, int chunk,
-                                             int kslice, int ksplit, const int* __restrict__ loc_tab,
-                                             const int* __restrict__ active, T* __restrict__ part,
-                                             GemmSmem<T>& sm, bool acc_mode) {
-  constexpr int TBX = 64, KC = 32, GP = KC * TBX / 256;
-  using acc_t = typename Mfma<T>::acc_t;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wr = wave & 1, wb = wave >> 1;
-  const int bt = tile * TBX;
-  if (tid < TBX) {
-    const int b = bt + tid;
-    int pid = -1, sy = 0;
-    if (b < nlist) {
-      const int e = ents[b];
-      sy = e / nbox;
-      pid = e - sy * nbox;
-      if (active && !active[sy]) pid = -1;
-    }
-    sm.bid[tid] = pid;
-    sm.base[tid] = (size_t)sy * sys_n;
-    sm.bx0[tid] = pid >= 0 ? (pid % g.npd) * g.b - g.o : 0;
-    sm.by0[tid] = pid >= 0 ? (pid / g.npd) * g.b - g.o : 0;
-    sm.lin[tid] = box_lin(g, sm.base[tid], sm.bx0[tid], sm.by0[tid]);
-  }
-  __syncthreads();
-  const int nchunk = (g.nloc + 63) / 64;
-  const int per = (nchunk + ksplit - 1) / ksplit;
-  const int c0 = kslice * per, c1 = c0 + per < nchunk ? c0 + per : nchunk;
-  const int kb = c0 * 64, ke = c1 * 64;     // reduction indices beyond nloc read as zero
-  const T* Mc = M + (size_t)chunk * g.nloc * 64;
-  const int kq = lane >> 4, ln = lane & 15;
-  acc_t acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
-  T ga[GP], gb[GP];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < GP; ++u) {
-      const int t = tid + u * 256;
-      const int ka = t / 64, row = t % 64;   // A: 64 consecutive rows per index
-      const int ja = k0 + ka;
-      ga[u] = ja < g.nloc ? Mc[(size_t)ja * 64 + row] : (T)0;
-      const int kx = t % KC, b = t / KC;     // X: consecutive indices of one box
-      const int jx = k0 + kx;
-      T val = 0;
-      if (jx < g.nloc && sm.bid[b] >= 0)
-        val = box_value<T>(r, g, loc_tab, jx, sm.base[b], sm.lin[b], sm.bx0[b], sm.by0[b]);
-      gb[u] = val;
-    }
-  };
-  if (kb < ke) load(kb);
-  for (int k0 = kb; k0 < ke; k0 += KC) {
-#pragma unroll
-    for (int u = 0; u < GP; ++u) {
-      const int t = tid + u * 256;
-      sm.As[t / 64][t % 64] = ga[u];
-      sm.Bs[t % KC][t / KC] = gb[u];
-    }
-    __syncthreads();
-    if (k0 + KC < ke) load(k0 + KC);   // in flight during the MFMAs below
-#pragma unroll
-    for (int st = 0; st < KC / 4; ++st) {
-      const int kk = 4 * st + kq;
-      const T a0 = sm.As[kk][32 * wr + ln], a1 = sm.As[kk][32 * wr + 16 + ln];
-      const T b0 = sm.Bs[kk][32 * wb + ln], b1 = sm.Bs[kk][32 * wb + 16 + ln];
-      acc[0][0] = Mfma<T>::mma(a0, b0, acc[0][0]);
-      acc[0][1] = Mfma<T>::mma(a0, b1, acc[0][1]);
-      acc[1][0] = Mfma<T>::mma(a1, b0, acc[1][0]);
-      acc[1][1] = Mfma<T>::mma(a1, b1, acc[1][1]);
-    }
-    __syncthreads();
-  }
-  const int nown_pad = g.nch * 64;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = chunk * 64 + 32 * wr + 16 * a + Mfma<T>::row(kq, v);
-        const int bb = 32 * wb + 16 * b + ln;
-        if (row >= g.nown) continue;
-        if (ksplit == 1) {
-          if (sm.bid[bb] >= 0) {
-            const size_t o = sm.base[bb] + own_glob(g, sm.bid[bb], row);
-            z[o] = acc_mode ? z[o] + acc[a][b][v] : acc[a][b][v];
-          }
-        } else if (bt + bb < nlist) {
-          part[((size_t)kslice * nlist + bt + bb) * nown_pad + row] = acc[a][b][v];
-        }
-      }
-}
-
-template <typename T, int KS>
-static void launch_ras(const T* r, T* z, const BoxGeom& g, const T* inv, const int* ib_boxes, int n_ib,
+template <typename T, int KS, bool SYS>
+static void launch_ras(const T* r, T* z, const BoxGeom& g, const T* inv, const T* const* inv_tab, const int* ib_boxes, int n_ib,
                        const IntClassView& C, const int* int_boxes, int n_int, hipStream_t s, bool acc,
                        const SymIB* sym) {
   const int nint = (n_int + 15) / 16 * (n_int ? C.nrt : 0);
@@ -1886,9 +1518,9 @@ static void launch_ras(const T* r, T* z, const BoxGeom& g, const T* inv, const i
     const int ch = (w.ws + 64 * Vec16<T>::n - 1) / (64 * Vec16<T>::n);
     if (ch > 8 || w.nn > kElimMaxNn) throw Error(IBMG_ERR_ARG, "eliminated boxes take at most 1024 non-owned unknowns");
     const dim3 grid(nib + nint);
-    if (ch <= 2) IBMG_KLAUNCH((k_ras_w<T, KS, 2>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
-    else if (ch <= 4) IBMG_KLAUNCH((k_ras_w<T, KS, 4>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
-    else IBMG_KLAUNCH((k_ras_w<T, KS, 8>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    if (ch <= 2) IBMG_KLAUNCH((k_ras_w<T, KS, 2, SYS>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    else if (ch <= 4) IBMG_KLAUNCH((k_ras_w<T, KS, 4, SYS>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
+    else IBMG_KLAUNCH((k_ras_w<T, KS, 8, SYS>), grid, block, 0, s, r, z, g, w, ib_boxes, n_ib, nib, rpg, t, C, int_boxes, n_int, acc);
     IBMG_LAUNCH_CHECK();
     return;
   }
@@ -1900,16 +1532,16 @@ static void launch_ras(const T* r, T* z, const BoxGeom& g, const T* inv, const i
   int rs = 1;
   while (rs < 4 && items * rs < 128) rs *= 2;
   const dim3 grid(items * rs + nint);
-  if (rs == 1) IBMG_KLAUNCH((k_ras_rows<T, KS, 1>), grid, block, 0, s, r, z, g, inv, ib_boxes, items, C, int_boxes, n_int, acc);
-  else if (rs == 2) IBMG_KLAUNCH((k_ras_rows<T, KS, 2>), grid, block, 0, s, r, z, g, inv, ib_boxes, 2 * items, C, int_boxes, n_int, acc);
-  else IBMG_KLAUNCH((k_ras_rows<T, KS, 4>), grid, block, 0, s, r, z, g, inv, ib_boxes, 4 * items, C, int_boxes, n_int, acc);
+  if (rs == 1) IBMG_KLAUNCH((k_ras_rows<T, KS, 1, SYS>), grid, block, 0, s, r, z, g, inv, inv_tab, ib_boxes, items, C, int_boxes, n_int, acc);
+  else if (rs == 2) IBMG_KLAUNCH((k_ras_rows<T, KS, 2, SYS>), grid, block, 0, s, r, z, g, inv, inv_tab, ib_boxes, 2 * items, C, int_boxes, n_int, acc);
+  else IBMG_KLAUNCH((k_ras_rows<T, KS, 4, SYS>), grid, block, 0, s, r, z, g, inv, inv_tab, ib_boxes, 4 * items, C, int_boxes, n_int, acc);
   IBMG_LAUNCH_CHECK();
 }
 
-template <typename T>
-void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
+template <typename T, bool SYS>
+static void launch_ras_sweep(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
                       const IntClassView& C, const int* int_boxes, int n_int, hipStream_t s, int parts, bool acc,
-                      const SymIB* sym) {
+                      const SymIB* sym, const T* const* inv_tab) {
   if (!(parts & 1)) n_ib = 0;
   if (!(parts & 2)) n_int = 0;
   if (n_ib + n_int == 0) return;
@@ -1924,19 +1556,27 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
   // work-groups: 46.6 against 38.5 FP64, 22.1 against 24.7 FP32; 3584 boxes of
   // 8 x 8/2, 896 work-groups: 20.6 against 16.9, 13.1 against 12.3)
   if ((n_int + 15) / 16 * (n_int ? C.nrt : 0) >= (sizeof(T) == 8 ? 512 : 768))
-    launch_ras<T, 1>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
+    launch_ras<T, 1, SYS>(r, z, g, inv, inv_tab, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
   else
-    launch_ras<T, 2>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
+    launch_ras<T, 2, SYS>(r, z, g, inv, inv_tab, ib_boxes, n_ib, C, int_boxes, n_int, s, acc, sym);
   if (!n_ib || !sym) return;
   const int ks = sym_ksplit(g, n_ib);
   const size_t lds = (64 * (size_t)g.nch + 256 + 64 * (size_t)(g.nch - 1)) * sizeof(T);
-  IBMG_KLAUNCH((k_ras_ib_sym<T>), dim3(n_ib, g.nch, ks), dim3(256), lds, s, r, static_cast<const T*>(sym->t), g,
-               ib_boxes, sym->w, static_cast<const T*>(sym->inv), static_cast<T*>(sym->part));
+  IBMG_KLAUNCH((k_ras_ib_sym<T, SYS>), dim3(n_ib, g.nch, ks), dim3(256), lds, s, r, static_cast<const T*>(sym->t), g,
+               ib_boxes, sym->w, static_cast<const T*>(sym->inv), sym->qtab, static_cast<T*>(sym->part));
   IBMG_LAUNCH_CHECK();
   const int grid = std::min(4096, cdiv((size_t)n_ib * g.nown, 256));
-  IBMG_KLAUNCH((k_ras_sum<T>), dim3(grid), dim3(256), 0, s, static_cast<const T*>(sym->part), ib_boxes, n_ib, ks,
+  IBMG_KLAUNCH((k_ras_sum<T, SYS>), dim3(grid), dim3(256), 0, s, static_cast<const T*>(sym->part), ib_boxes, n_ib, ks,
                sym->w.ord, z, g, acc);
   IBMG_LAUNCH_CHECK();
+}
+
+template <typename T>
+void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
+                      const IntClassView& C, const int* int_boxes, int n_int, hipStream_t s, int parts, bool acc,
+                      const SymIB* sym, const T* const* inv_tab) {
+  if (g.nbs) launch_ras_sweep<T, true>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, parts, acc, sym, inv_tab);
+  else launch_ras_sweep<T, false>(r, z, g, inv, ib_boxes, n_ib, C, int_boxes, n_int, s, parts, acc, sym, inv_tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -1948,6 +1588,79 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
 // from the boxes whose index set holds it: no two work-groups write one
 // unknown, and no atomics are needed.
 // ---------------------------------------------------------------------------
+// One (box, 64-row chunk) item: Mc is the chunk of the box's inverse; x holds nloc
+// values (LDS), part 256; the 64 row sums go to out.  The first loads of the
+// inverse are issued before the gather.
+template <typename T>
+__device__ __forceinline__ void asm_chunk(const T* __restrict__ r, const BoxGeom& g, const T* __restrict__ Mc, int pid,
+                                          T* x, T* part, T* __restrict__ out) {
+  using V = typename Vec16<T>::type;
+  constexpr int VEC = Vec16<T>::n;
+  constexpr int LPC = 64 / VEC;  // lanes per column
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int cph = lane / LPC;           // column phase 0..VEC-1
+  const int rl = (lane % LPC) * VEC;    // first of this lane's VEC rows
+  const int per = ((g.nloc + 4 * VEC - 1) / (4 * VEC)) * VEC;
+  const int j0 = q * per, j1 = j0 + per < g.nloc ? j0 + per : g.nloc;
+  Mc += rl;
+  int j = j0 + cph;
+  // eight 16-byte loads in flight per lane, summed in a fixed tree; the
+  // inverse streams through once per sweep, so its loads are non-temporal
+  // and leave the caches to the level's vectors
+  constexpr int UNR = 8;
+  auto load8 = [&](V* m, int jj) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u)
+      m[u] = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)(jj + u * VEC) * 64));
+  };
+  T acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0;
+  auto fma8 = [&](const V* m, int jj) {
+    T xv[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) xv[u] = x[jj + u * VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      T t[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) t[u] = reinterpret_cast<const T*>(&m[u])[v] * xv[u];
+      acc[v] += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    }
+  };
+  const bool first = j + (UNR - 1) * VEC < j1;
+  V m0[UNR];
+  if (first) load8(m0, j);
+  for (int k = threadIdx.x; k < g.nloc; k += blockDim.x) x[k] = r[box_glob(g, pid, k)];
+  __syncthreads();
+  if (first) {
+    fma8(m0, j);
+    j += UNR * VEC;
+  }
+  for (; j + (UNR - 1) * VEC < j1; j += UNR * VEC) {
+    V m[UNR];
+    load8(m, j);
+    fma8(m, j);
+  }
+  for (; j < j1; j += VEC) {
+    const V m0 = __builtin_nontemporal_load(reinterpret_cast<const V*>(Mc + (size_t)j * 64));
+    const T* a0 = reinterpret_cast<const T*>(&m0);
+    const T x0 = x[j];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] += a0[v] * x0;
+  }
+  // sum the VEC column phases (lanes l, l + LPC, ...)
+#pragma unroll
+  for (int off = 32; off >= LPC; off >>= 1)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] += __shfl_down(acc[v], off, 64);
+  if (lane < LPC)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) part[q * 64 + rl + v] = acc[v];
+  __syncthreads();
+  if (q == 0) out[lane] = (part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]);
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_asm_local(const T* __restrict__ r, BoxGeom g, const T* __restrict__ inv,
                                                    const int* __restrict__ box_inv, T* __restrict__ Y) {
@@ -1956,8 +1669,7 @@ __global__ void __launch_bounds__(256) k_asm_local(const T* __restrict__ r, BoxG
   T* part = x + ((g.nloc + 3) & ~3);
   const int pid = blockIdx.x, chunk = blockIdx.y;
   const T* Mc = inv + ((size_t)box_inv[pid] * g.nch + chunk) * g.nloc * 64;
-  ras_ib_chunk<T, true>(r, nullptr, g, Mc, pid, chunk, x, part, false, 0, g.nloc,
-                        Y + ((size_t)pid * g.nch + chunk) * 64);
+  asm_chunk<T>(r, g, Mc, pid, x, part, Y + ((size_t)pid * g.nch + chunk) * 64);
 }
 
 // z[d] = sum of unknown d's entries over the boxes that hold it.  Along each
@@ -2005,82 +1717,6 @@ void launch_asm_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* box_
   int grid = cdiv(tot, 256);
   if (grid > 8192) grid = 8192;
   IBMG_KLAUNCH((k_asm_gather<T>), dim3(grid), dim3(256), 0, s, Y, z, g);
-  IBMG_LAUNCH_CHECK();
-}
-
-// ---------------------------------------------------------------------------
-// Batched RAS sweep: one persistent launch per sweep.  Items are interior
-// tiles x row chunks (matrix cores, shared inverse) and (IB box, row chunk)
-// pairs (streamed own inverses), interleaved evenly: item t is an IB item
-// when floor((t + 1) B / total) > floor(t B / total), B = IB items, so every
-// CU holds both kinds and the inverse streaming overlaps the products.
-// Work-group w takes items w, w + grid, ...  Every item writes disjoint
-// owned rows, so the result does not depend on the order.
-// ---------------------------------------------------------------------------
-template <typename T, int TB>
-__global__ void __launch_bounds__(256) k_ras_batch(const T* __restrict__ r, T* __restrict__ z, BoxGeom g,
-                                                   size_t sys_n, int nbox, const T* __restrict__ M,
-                                                   const int* __restrict__ int_ents, int n_int,
-                                                   const int* __restrict__ ib_ents, const T* const* __restrict__ ib_inv,
-                                                   int n_ib, const int* __restrict__ loc_tab,
-                                                   const int* __restrict__ active) {
-  extern __shared__ char smem_raw[];
-  const int n_tiles = (n_int + TB - 1) / TB;
-  const long long int_items = (long long)n_tiles * g.nch;
-  const long long ib_items = (long long)n_ib * g.nch;
-  const long long total = int_items + ib_items;
-  for (long long it = blockIdx.x; it < total; it += gridDim.x) {
-    const long long before = it * ib_items / total;           // IB items among [0, it)
-    const bool is_ib = (it + 1) * ib_items / total > before;
-    if (!is_ib) {
-      const int ti = (int)(it - before);
-      if constexpr (TB == 64)
-        ras_int_gemm<T>(r, z, g, sys_n, nbox, M, int_ents, n_int, ti / g.nch, ti % g.nch, 0, 1, loc_tab, active,
-                        nullptr, *reinterpret_cast<GemmSmem<T>*>(smem_raw), false);
-      else
-        ras_int_tile<T, TB, false>(r, z, g, sys_n, nbox, M, int_ents, n_int, ti / g.nch, ti % g.nch, 0, 1,
-                                   loc_tab, active, nullptr, *reinterpret_cast<IntTileSmem<T, TB>*>(smem_raw),
-                                   false);
-    } else {
-      const int q = (int)before, e = q / g.nch, c = q % g.nch;
-      const int ent = ib_ents[e], sy = ent / nbox;
-      if (active && !active[sy]) continue;
-      T* x = reinterpret_cast<T*>(smem_raw);
-      ras_ib_chunk<T, false>(r + (size_t)sy * sys_n, z + (size_t)sy * sys_n, g,
-                             ib_inv[e] + (size_t)c * g.nloc * 64, ent - sy * nbox, c, x,
-                             x + ((g.nloc + 3) & ~3), false, 0, g.nloc, nullptr);
-    }
-    __syncthreads();
-  }
-}
-
-int ras_batch_items(const BoxGeom& g, int n_int, int n_ib, int tb) {
-  return ((n_int + tb - 1) / tb) * g.nch + n_ib * g.nch;
-}
-
-template <typename T>
-void launch_ras_batch(const T* r, T* z, BoxGeom g, size_t sys_n, int nbox, const T* shared_inv,
-                      const int* int_ents, int n_int, const int* ib_ents, const T* const* ib_inv, int n_ib,
-                      const int* loc_tab, const int* active, RasBatchPlan plan, hipStream_t s) {
-  const int tb = plan.tb == 16 ? 16 : (plan.tb == 64 ? 64 : 32);
-  const int items = ras_batch_items(g, n_int, n_ib, tb);
-  if (items <= 0) return;
-  if (n_int > 0 && !shared_inv) throw Error(IBMG_ERR_ARG, "interior boxes without a shared inverse");
-  int grid = plan.grid > 0 ? plan.grid : items;
-  if (grid > items) grid = items;
-  size_t lds = ((((size_t)g.nloc + 3) & ~(size_t)3) + 256) * sizeof(T);
-  const size_t tile = tb == 16 ? sizeof(IntTileSmem<T, 16>)
-                                : (tb == 64 ? sizeof(GemmSmem<T>) : sizeof(IntTileSmem<T, 32>));
-  if (tile > lds) lds = tile;
-  if (tb == 16)
-    IBMG_KLAUNCH((k_ras_batch<T, 16>), dim3(grid), dim3(256), lds, s, r, z, g, sys_n, nbox, shared_inv,
-                       int_ents, n_int, ib_ents, ib_inv, n_ib, loc_tab, active);
-  else if (tb == 64)
-    IBMG_KLAUNCH((k_ras_batch<T, 64>), dim3(grid), dim3(256), lds, s, r, z, g, sys_n, nbox, shared_inv,
-                       int_ents, n_int, ib_ents, ib_inv, n_ib, loc_tab, active);
-  else
-    IBMG_KLAUNCH((k_ras_batch<T, 32>), dim3(grid), dim3(256), lds, s, r, z, g, sys_n, nbox, shared_inv,
-                       int_ents, n_int, ib_ents, ib_inv, n_ib, loc_tab, active);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -2330,20 +1966,16 @@ template void launch_asm_apply<double>(const double*, double*, BoxGeom, const do
                                        hipStream_t);
 template void launch_asm_apply<float>(const float*, float*, BoxGeom, const float*, const int*, float*, hipStream_t);
 template void launch_ras_apply<double>(const double*, double*, BoxGeom, const double*, const int*, int,
-                                       const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*);
+                                       const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*,
+                                       const double* const*);
 template void launch_ras_apply<float>(const float*, float*, BoxGeom, const float*, const int*, int,
-                                      const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*);
+                                      const IntClassView&, const int*, int, hipStream_t, int, bool, const SymIB*,
+                                       const float* const*);
 template void launch_extract_sym<double>(const double*, int, BoxGeom, BoxMat, double*, hipStream_t);
 template void launch_extract_sym<float>(const double*, int, BoxGeom, BoxMat, float*, hipStream_t);
 template void launch_coarse_apply<double>(const double*, int, const double*, double*, hipStream_t);
 template void launch_coarse_apply<float>(const double*, int, const float*, float*, hipStream_t);
 template void launch_coarse_apply_batch<double>(const double*, int, const double*, double*, int, hipStream_t);
 template void launch_coarse_apply_batch<float>(const double*, int, const float*, float*, int, hipStream_t);
-template void launch_ras_batch<double>(const double*, double*, BoxGeom, size_t, int, const double*, const int*,
-                                       int, const int*, const double* const*, int, const int*, const int*,
-                                       RasBatchPlan, hipStream_t);
-template void launch_ras_batch<float>(const float*, float*, BoxGeom, size_t, int, const float*, const int*, int,
-                                      const int*, const float* const*, int, const int*, const int*, RasBatchPlan,
-                                      hipStream_t);
 
 }  // namespace ibmg

@@ -177,17 +177,19 @@ int apply_blocks(int N, int nrows, int lanes, int cap) { return strip_blocks(N) 
 
 // grid: strip_blocks(N) work-groups of the stencil, then the IB rows' (x);
 // systems (z)
-template <typename T, bool TRANS, bool RESID, int IBM, int RJ>
+template <typename T, bool TRANS, bool RESID, int IBM, int RJ, bool SYS>
 __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __restrict__ y,
                                                const T* __restrict__ b, const T* __restrict__ F,
                                                IbRows<T> R, FootView<T> fx,
                                                FootView<T> fy, int N, int M, StokesCoef<T> c,
                                                Many m, int nsb) {
-  if (m.act && !m.act[blockIdx.z]) return;
-  if (IBM == 2 && R.each) R = R.each[blockIdx.z];
-  w += blockIdx.z * m.bs;
-  y += blockIdx.z * m.bs;
-  if (RESID) b += blockIdx.z * m.bs;
+  if (SYS) {
+    if (m.act && !m.act[blockIdx.z]) return;
+    if (IBM == 2) R = R.each[blockIdx.z];
+    w += blockIdx.z * m.bs;
+    y += blockIdx.z * m.bs;
+    if (RESID) b += blockIdx.z * m.bs;
+  }
   if (IBM == 2 && (int)blockIdx.x >= nsb) {
     const int tid = threadIdx.y * blockDim.x + threadIdx.x, blk = blockIdx.x - nsb, nrb = gridDim.x - nsb;
     auto emit = [&](int r, T v) { y[r] = v; };
@@ -213,20 +215,22 @@ __global__ void __launch_bounds__(256) k_apply(const T* __restrict__ w, T* __res
 // u0, u_q = V + q vstride; NV = nvec), with NV = 1 also u_0 . u_0 (two sums per
 // block); each thread's points summed in row order, then over the block in a
 // fixed order; blk = the block's linear index.
-template <typename T, int IBM, int RJ, int NV>
+template <typename T, int IBM, int RJ, int NV, bool SYS>
 __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* __restrict__ y,
                                                     const T* __restrict__ F, IbRows<T> R, FootView<T> fx,
                                                     FootView<T> fy, int N, int M, StokesCoef<T> c,
                                                     const T* __restrict__ u0, const T* __restrict__ V,
                                                     size_t vstride, double* __restrict__ partial, Many m, int nsb) {
   constexpr int NS = NV == 1 ? 2 : NV;   // sums per block
-  if (m.act && !m.act[blockIdx.z]) return;
-  if (IBM == 2 && R.each) R = R.each[blockIdx.z];
-  w += blockIdx.z * m.bs;
-  y += blockIdx.z * m.bs;
-  u0 += blockIdx.z * m.bs;
-  if (NV > 1) V += blockIdx.z * m.bs;
-  partial += blockIdx.z * m.ps;
+  if (SYS) {
+    if (m.act && !m.act[blockIdx.z]) return;
+    if (IBM == 2) R = R.each[blockIdx.z];
+    w += blockIdx.z * m.bs;
+    y += blockIdx.z * m.bs;
+    u0 += blockIdx.z * m.bs;
+    if (NV > 1) V += blockIdx.z * m.bs;
+    partial += blockIdx.z * m.ps;
+  }
   __shared__ double red[NS * 4];
   const size_t n = (size_t)N * N;
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
@@ -274,6 +278,7 @@ __global__ void __launch_bounds__(256) k_apply_dots(const T* __restrict__ w, T* 
     for (int q = 0; q < NS; ++q) partial[(size_t)blockIdx.x * NS + q] = d[q];
 }
 
+// (many systems take no transposed products)
 template <typename T, int IBM, int RJ>
 static void launch_apply_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R, FootView<T> fx,
                            FootView<T> fy, int N, int M, StokesCoef<T> c, bool transpose,
@@ -281,16 +286,22 @@ static void launch_apply_r(const T* w, T* y, const T* b, const T* F, IbRows<T> R
   const dim3 blk = apply_block(RJ);
   const int nsb = strip_blocks(N);
   const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes, m.nblk) : 0), 1, m.nsys);
-  if (b) {
+  if (m.bs) {
+    if (transpose || IBM == 1) throw Error(IBMG_ERR_ARG, "no such product over many systems");
+    if constexpr (IBM != 1) {
+      if (b) IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ, true>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+      else IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ, true>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+    }
+  } else if (b) {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+      IBMG_KLAUNCH((k_apply<T, true, true, IBM, RJ, false>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+      IBMG_KLAUNCH((k_apply<T, false, true, IBM, RJ, false>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
   } else {
     if (transpose)
-      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+      IBMG_KLAUNCH((k_apply<T, true, false, IBM, RJ, false>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
     else
-      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
+      IBMG_KLAUNCH((k_apply<T, false, false, IBM, RJ, false>), grd, blk, 0, s, w, y, b, F, R, fx, fy, N, M, c, m, nsb);
   }
   IBMG_LAUNCH_CHECK();
 }
@@ -334,8 +345,15 @@ static void launch_apply_dots_n(const T* w, T* y, const T* F, IbRows<T> R, FootV
     }
     const int nsb = strip_blocks(N);
     const dim3 grd(nsb + (IBM == 2 ? ib_row_blocks(R.n, R.lanes, m.nblk) : 0), 1, m.nsys);
-    IBMG_KLAUNCH((k_apply_dots<T, IBM, RJ, NV>), grd, apply_block(RJ), 0, s, w, y, F, R, fx, fy, N, M, c, u0, V, vstride,
-                 partial, m, nsb);
+    if (m.bs) {
+      if (IBM == 1) throw Error(IBMG_ERR_ARG, "no such product over many systems");
+      if constexpr (IBM != 1)
+        IBMG_KLAUNCH((k_apply_dots<T, IBM, RJ, NV, true>), grd, apply_block(RJ), 0, s, w, y, F, R, fx, fy, N, M, c, u0, V,
+                     vstride, partial, m, nsb);
+    } else {
+      IBMG_KLAUNCH((k_apply_dots<T, IBM, RJ, NV, false>), grd, apply_block(RJ), 0, s, w, y, F, R, fx, fy, N, M, c, u0, V,
+                   vstride, partial, m, nsb);
+    }
     IBMG_LAUNCH_CHECK();
   }
 }

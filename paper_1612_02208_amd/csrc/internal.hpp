@@ -239,6 +239,12 @@ struct StokesCoef {     // A = alpha I - mu Lap: alpha, beta = mu/h^2, gi = 1/h,
 
 struct BoxGeom {        // RAS boxes on one level
   int N, b, o, m, npd, nloc, nown, nch;  // nch = ceil(nown / 64) row chunks
+  // batched sweeps: a box entry is s * nbs + box (nbs boxes a system), system
+  // s's vectors start at s * sysn, and its boxes run while act[s] is set (null:
+  // always).  nbs = 0: one system, entries are boxes.
+  int nbs = 0;
+  size_t sysn = 0;
+  const int* act = nullptr;
 };
 
 // Segments of a batch vector: system s owns entries [begin(s), begin(s) +
@@ -372,11 +378,13 @@ struct IbRows {
   CsrT<T> tu, tv;
   int n;
   int lanes;                  // lanes per row: 16 or 64
-  // batched launches: every system's rows, [nsys] (n and lanes above then the
-  // largest of them)
+  // launches over many systems: every system's rows, [nsys] (n and lanes above
+  // then the largest of them)
   const IbRows<T>* each = nullptr;
 };
-// A launch over many systems of one level: bs elements between the systems'
+// A launch over many systems of one level (bs > 0; kernels of their own, as the
+// system's offsets and flag cost a single system's short launches a few per
+// cent): bs elements between the systems'
 // vectors, ps doubles between their partial sums, nblk blocks per system for
 // the IB rows and for the Gram-Schmidt kernels (0: as for one system); systems
 // whose act is 0 do nothing.
@@ -576,8 +584,10 @@ void launch_asm_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* box_
 // are rows wptr[i] .. wptr[i+1] of W (row stride ws), for the owned positions
 // wrow; coupled[i * nown + k] marks the positions that have one; ord: the owned
 // unknowns in position order; nloc lists the nn non-owned unknowns' local indices.
+// Batched sweeps: wtab (SymIB: qtab) holds every box's own W (Q) instead.
 struct WBoxView {
   const void* W;
+  const void* const* wtab;
   const int *wptr, *wrow, *nloc;
   const unsigned char* coupled;
   const unsigned short* ord;
@@ -585,6 +595,7 @@ struct WBoxView {
 };
 struct SymIB {
   const void* inv;   // Q: T[n_ib * sym_box_stride(g)]
+  const void* const* qtab;
   void* part;        // T[n_ib * sym_part_len(g)]
   WBoxView w;
   void* t;           // T[n_ib * nown]: W r_n at the coupled positions
@@ -615,11 +626,12 @@ void launch_extract_classes(const double* mat, BoxMat bm, const unsigned short* 
 
 // One restricted Schwarz sweep (parts: bit 0 = IB boxes, bit 1 = interior
 // boxes); acc: add the local solutions to z on the owned sets instead of
-// storing them.  sym != null: the IB boxes run from the eliminated storage.
+// storing them.  sym != null: the IB boxes run from the eliminated storage; else
+// from whole rows, box i's at inv + i boxes or, where inv_tab is given, inv_tab[i].
 template <typename T>
 void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_boxes, int n_ib,
                       const IntClassView& cls, const int* int_boxes, int n_int, hipStream_t s, int parts = 3,
-                      bool acc = false, const SymIB* sym = nullptr);
+                      bool acc = false, const SymIB* sym = nullptr, const T* const* inv_tab = nullptr);
 void launch_coarse_assemble(int N, StokesCoef<double> c, const int* tptr_u, const int* tcol_u,
                             const double* tval_u, const int* tptr_v, const int* tcol_v,
                             const double* tval_v, int nb, double* aug, hipStream_t s);
@@ -698,19 +710,5 @@ void launch_combine_ls_b(T* x, const T* Z, int k, size_t stride, BSeg sg, int ns
                          int nnblk = 0, size_t pstride = 0, bool pass2 = false);
 template <typename T>
 void launch_coarse_apply_batch(const double* inv, int n0, const T* r, T* z, int nsys, hipStream_t s);
-
-// One persistent launch per smoother sweep over every (system, box) of a
-// batch level: interior tiles of TB boxes on the matrix cores against the
-// shared interior inverse, then (IB box, row chunk) items against each box's
-// own inverse.  Box entries are s * nbox + box id; systems are sys_n apart.
-struct RasBatchPlan {
-  int tb = 32;      // interior tile width (16, 32, or 64: register-blocked)
-  int grid = 0;     // work-groups of the persistent launch
-};
-template <typename T>
-void launch_ras_batch(const T* r, T* z, BoxGeom g, size_t sys_n, int nbox, const T* shared_inv,
-                      const int* int_ents, int n_int, const int* ib_ents, const T* const* ib_inv, int n_ib,
-                      const int* loc_tab, const int* active, RasBatchPlan plan, hipStream_t s);
-int ras_batch_items(const BoxGeom& g, int n_int, int n_ib, int tb);
 
 }  // namespace ibmg

@@ -386,21 +386,23 @@ __device__ __forceinline__ double gs_second(double (&e)[K], double uu, const dou
   return d <= 0.0 ? 0.0 : d;
 }
 
-template <typename T, int K>
+template <typename T, int K, bool SYS>
 __global__ void __launch_bounds__(kThreads) k_gs_update(T* __restrict__ t, const T* __restrict__ u0,
                                                         const T* __restrict__ V, size_t stride, size_t n,
                                                         const double* __restrict__ pd, int nd,
                                                         const double* __restrict__ pu, int npu,
                                                         double* __restrict__ S, double* __restrict__ pout,
                                                         Many m) {
-  if (m.act && !m.act[blockIdx.y]) return;
-  t += blockIdx.y * m.bs;
-  u0 += blockIdx.y * m.bs;
-  if (K > 1) V += blockIdx.y * m.bs;
-  pd += blockIdx.y * m.ps;
-  if (K > 1) pu += blockIdx.y * m.ps;
-  pout += blockIdx.y * m.ps;
-  S += blockIdx.y * kGsScal;
+  if (SYS) {
+    if (m.act && !m.act[blockIdx.y]) return;
+    t += blockIdx.y * m.bs;
+    u0 += blockIdx.y * m.bs;
+    if (K > 1) V += blockIdx.y * m.bs;
+    pd += blockIdx.y * m.ps;
+    if (K > 1) pu += blockIdx.y * m.ps;
+    pout += blockIdx.y * m.ps;
+    S += blockIdx.y * kGsScal;
+  }
   constexpr int NA = K == 1 ? 2 : K, NB = K == 1 ? 0 : K;
   __shared__ double red[(NA + NB) * 4];
   __shared__ double red2[(K + 1) * 4];
@@ -557,15 +559,17 @@ __device__ __forceinline__ void gs_solve(const double* __restrict__ pu, int npu,
   }
 }
 
-template <typename T, int K>
+template <typename T, int K, bool SYS>
 __global__ void __launch_bounds__(kThreads) k_gs_combine(T* __restrict__ x, const T* __restrict__ Z, size_t stride,
                                                          size_t n, const double* __restrict__ pu, int npu,
                                                          const double* __restrict__ S, bool assign, Many m) {
-  if (m.act && !m.act[blockIdx.y]) return;
-  x += blockIdx.y * m.bs;
-  Z += blockIdx.y * m.bs;
-  pu += blockIdx.y * m.ps;
-  S += blockIdx.y * kGsScal;
+  if (SYS) {
+    if (m.act && !m.act[blockIdx.y]) return;
+    x += blockIdx.y * m.bs;
+    Z += blockIdx.y * m.bs;
+    pu += blockIdx.y * m.ps;
+    S += blockIdx.y * kGsScal;
+  }
   __shared__ double red[(K + 1) * 4];
   double y[K], rho[K + 1];
   gs_solve<K, false>(pu, npu, S, red, threadIdx.x, y, rho);
@@ -581,20 +585,22 @@ __global__ void __launch_bounds__(kThreads) k_gs_combine(T* __restrict__ x, cons
 // the restriction of r = sum_q rho_q u_q (neighbouring threads share the fine
 // values of r through the caches), in place of an operator application, a
 // residual and a restriction.
-template <typename T, int K>
+template <typename T, int K, bool SYS>
 __global__ void __launch_bounds__(kThreads) k_gs_combine_restrict(T* __restrict__ x, const T* __restrict__ Z,
                                                                   const T* __restrict__ u0, const T* __restrict__ V,
                                                                   size_t stride, int Nc, const double* __restrict__ pu,
                                                                   int npu, const double* __restrict__ S,
                                                                   T* __restrict__ coarse, Many m) {
-  if (m.act && !m.act[blockIdx.y]) return;
-  x += blockIdx.y * m.bs;
-  Z += blockIdx.y * m.bs;
-  u0 += blockIdx.y * m.bs;
-  V += blockIdx.y * m.bs;
-  pu += blockIdx.y * m.ps;
-  S += blockIdx.y * kGsScal;
-  coarse += blockIdx.y * (m.bs / 4);
+  if (SYS) {
+    if (m.act && !m.act[blockIdx.y]) return;
+    x += blockIdx.y * m.bs;
+    Z += blockIdx.y * m.bs;
+    u0 += blockIdx.y * m.bs;
+    V += blockIdx.y * m.bs;
+    pu += blockIdx.y * m.ps;
+    S += blockIdx.y * kGsScal;
+    coarse += blockIdx.y * (m.bs / 4);
+  }
   __shared__ double red[(K + 1) * 4];
   double y[K], rho[K + 1];
   gs_solve<K, true>(pu, npu, S, red, threadIdx.x, y, rho);
@@ -741,8 +747,10 @@ void launch_gs_update(T* t, const T* u0, const T* V, int k, size_t stride, size_
   if (m.nsys <= 0) return;
   const int nb = gs_blocks(n, m);
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_update<T, decltype(kc)::value>), dim3(nb, m.nsys), dim3(kThreads), 0, s, t, u0, V, stride, n, pd,
-                 nd, pu, nb, S, pout, m);
+    constexpr int K = decltype(kc)::value;
+    const dim3 grid(nb, m.nsys);
+    if (m.bs) IBMG_KLAUNCH((k_gs_update<T, K, true>), grid, dim3(kThreads), 0, s, t, u0, V, stride, n, pd, nd, pu, nb, S, pout, m);
+    else IBMG_KLAUNCH((k_gs_update<T, K, false>), grid, dim3(kThreads), 0, s, t, u0, V, stride, n, pd, nd, pu, nb, S, pout, m);
   });
   IBMG_LAUNCH_CHECK();
 }
@@ -753,8 +761,9 @@ void launch_gs_combine(T* x, const T* Z, int k, size_t stride, size_t n, const d
   if (m.nsys <= 0) return;
   const int nb = gs_blocks(n, m);
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_combine<T, decltype(kc)::value>), dim3(m.nblk > 0 ? nb : stream_blocks(n), m.nsys), dim3(kThreads),
-                 0, s, x, Z, stride, n, pu, nb, S, assign, m);
+    constexpr int K = decltype(kc)::value;
+    if (m.bs) IBMG_KLAUNCH((k_gs_combine<T, K, true>), dim3(nb, m.nsys), dim3(kThreads), 0, s, x, Z, stride, n, pu, nb, S, assign, m);
+    else IBMG_KLAUNCH((k_gs_combine<T, K, false>), dim3(stream_blocks(n)), dim3(kThreads), 0, s, x, Z, stride, n, pu, nb, S, assign, m);
   });
   IBMG_LAUNCH_CHECK();
 }
@@ -763,11 +772,12 @@ template <typename T>
 void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k, size_t stride, int Nc,
                                 const double* pu, double* S, T* coarse, hipStream_t s, Many m) {
   if (m.nsys <= 0) return;
-  const int nb = ((Nc + 63) / 64) * ((Nc + 3) / 4);
-  const size_t n = (size_t)12 * Nc * Nc;
+  const dim3 grid(((Nc + 63) / 64) * ((Nc + 3) / 4), m.nsys);
+  const int nb = gs_blocks((size_t)12 * Nc * Nc, m);
   gs_dispatch(k, [&](auto kc) {
-    IBMG_KLAUNCH((k_gs_combine_restrict<T, decltype(kc)::value>), dim3(nb, m.nsys), dim3(kThreads), 0, s, x, Z, u0, V,
-                 stride, Nc, pu, gs_blocks(n, m), S, coarse, m);
+    constexpr int K = decltype(kc)::value;
+    if (m.bs) IBMG_KLAUNCH((k_gs_combine_restrict<T, K, true>), grid, dim3(kThreads), 0, s, x, Z, u0, V, stride, Nc, pu, nb, S, coarse, m);
+    else IBMG_KLAUNCH((k_gs_combine_restrict<T, K, false>), grid, dim3(kThreads), 0, s, x, Z, u0, V, stride, Nc, pu, nb, S, coarse, m);
   });
   IBMG_LAUNCH_CHECK();
 }

@@ -89,7 +89,6 @@ struct Level {
   int n_unique = 0, n_ib = 0;
   std::vector<int> uniq;  // unique box ids (IB boxes, then one interior representative)
   std::vector<int> ib_list, int_list;
-  std::vector<int> loc_tab;  // local unknown -> (comp << 24) | (jj << 12) | ii, then -> comp N^2 + jj N + ii
   DBuf<int> d_ib, d_int;
   DBuf<T> inv;            // [n_unique][nch][nloc][64]
   // the interior boxes' shared inverse in its four parity classes (ras_int_block)
@@ -144,7 +143,9 @@ class Solver final : public SolverBase {
   // defer_coarse: assemble the coarsest system but leave its inversion to
   // the caller (the batched form inverts every system's in one launch and
   // hands each back through finish_coarse)
-  Solver(const ibmg_desc& d, hipStream_t s, bool defer_coarse = false) : d_(d), defer_coarse_(defer_coarse) {
+  // members: per level, the systems of the batch that have it (a batch member)
+  Solver(const ibmg_desc& d, hipStream_t s, bool defer_coarse = false, std::vector<int> members = {})
+      : d_(d), defer_coarse_(defer_coarse), members_(std::move(members)) {
     M_ = d.M;
     E_ = d.n_springs;
     X_.assign(d.X, d.X + 2 * (size_t)M_);
@@ -611,18 +612,7 @@ class Solver final : public SolverBase {
       if (ib) lev.ib_list.push_back(p);
       else lev.int_list.push_back(p);
     }
-    // codes, then linear offsets from the box's corner (the gathers' table)
     const int nloc = lev.g.nloc;
-    lev.loc_tab.assign(2 * (size_t)nloc, 0);
-    for (int k = 0; k < nloc; ++k) {
-      const int nu = m * (m + 1);
-      int comp, ii, jj;
-      if (k < nu) { comp = 0; ii = k % (m + 1); jj = k / (m + 1); }
-      else if (k < 2 * nu) { comp = 1; ii = (k - nu) % m; jj = (k - nu) / m; }
-      else { comp = 2; ii = (k - 2 * nu) % m; jj = (k - 2 * nu) / m; }
-      lev.loc_tab[k] = (comp << 24) | (jj << 12) | ii;
-      lev.loc_tab[nloc + k] = (int)((int64_t)comp * N * N + (int64_t)jj * N + ii);
-    }
     lev.n_ib = (int)lev.ib_list.size();
     lev.uniq = lev.ib_list;
     if (!lev.int_list.empty()) lev.uniq.push_back(lev.int_list.front());
@@ -1250,7 +1240,7 @@ class Solver final : public SolverBase {
     lev.d_nonown.upload(lev.nonown, s);
     lev.d_ord.upload(lev.ord, s);
     lev.d_own.upload(lev.own, s);
-    // A single system keeps the IB boxes eliminated (three launches over fewer
+    // The IB boxes are kept eliminated (three launches over fewer
     // bytes) where the whole rows that one launch of the sweep reads (all boxes,
     // or a colour's) take at least 192 MiB.  Alone, the eliminated form breaks
     // even near 100 MiB (FP64 16 x 16/4: 42 MiB 18.3 against 10.7 us for whole
@@ -1259,10 +1249,12 @@ class Solver final : public SolverBase {
     // against 13.9, 166 MiB 21.5 against 28.2), but its launches wait for one
     // another where the whole rows' one also covers the interior boxes: a
     // multiplicative 256^2 solve took 18.4 ms with the line at 96 MiB, 17.6 at
-    // 192 and 17.7 at 320 (additive 512^2 67.4 ms at all three).  The chunked
-    // rows (lev.inv) serve the smaller levels and the batched form.
-    const int per_launch = d_.smoother == IBMG_RMS ? lev.n_ib / std::max(1, lev.ncolour) : lev.n_ib;
-    lev.use_sym = !defer_coarse_ && lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
+    // 192 and 17.7 at 320 (additive 512^2 67.4 ms at all three).  A batch's
+    // launches read every member's boxes (taken as the same number each).
+    const size_t l = &lev - levels_.data();
+    const int per_launch = d_.smoother == IBMG_RMS ? lev.n_ib / std::max(1, lev.ncolour)
+                                                   : lev.n_ib * (l < members_.size() ? members_[l] : 1);
+    lev.use_sym = lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
                   (size_t)per_launch * box_stride(lev) * sizeof(T) >= kElimMinBytes &&
                   std::getenv("IBMG_NO_SYM") == nullptr;
     if (lev.use_sym) {
@@ -1272,8 +1264,10 @@ class Solver final : public SolverBase {
       lev.d_coupled.upload(lev.coupled, s);
       lev.wmat.alloc(lev.wrow.size() * (size_t)lev.w_stride);
       lev.inv_sym.alloc((size_t)lev.n_ib * sym_box_stride(g));
-      lev.w_res.alloc((size_t)lev.n_ib * g.nown);
-      lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
+      if (!defer_coarse_) {   // (a batch has its own for all members)
+        lev.w_res.alloc((size_t)lev.n_ib * g.nown);
+        lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
+      }
     }
     lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
   }
@@ -1288,8 +1282,8 @@ class Solver final : public SolverBase {
   // the eliminated storage from IB box i0 on
   SymIB sym_of(Level<T>& lev, int i0) {
     if (!lev.use_sym) return SymIB{};
-    return SymIB{lev.inv_sym.p + (size_t)i0 * sym_box_stride(lev.g), lev.sym_part.p,
-                 WBoxView{lev.wmat.p, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
+    return SymIB{lev.inv_sym.p + (size_t)i0 * sym_box_stride(lev.g), nullptr, lev.sym_part.p,
+                 WBoxView{lev.wmat.p, nullptr, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
                           lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.d_ord.p + (size_t)i0 * lev.g.nown, lev.bm.nn,
                           lev.w_stride, lev.w_max},
                  lev.w_res.p};
@@ -1302,7 +1296,7 @@ class Solver final : public SolverBase {
   int inv_end(const Level<T>& lev) const { return has_classes(lev) ? lev.n_ib : lev.n_unique; }
   // the single-system restricted sweeps take the interior boxes in parity
   // classes; the summed combination and the batched form read whole rows
-  bool has_classes(const Level<T>& lev) const { return !lev.sum_mode && !defer_coarse_ && !lev.int_list.empty(); }
+  bool has_classes(const Level<T>& lev) const { return !lev.sum_mode && !lev.int_list.empty(); }
 
   // The unique box inverses of every Schwarz level: assembled per level,
   // eliminated (or, for the summed combination, inverted) in batches that mix
@@ -2089,6 +2083,7 @@ class Solver final : public SolverBase {
   hipEvent_t ev_fork_ = nullptr, ev_join_ = nullptr;
   DBuf<double> coarse_aug_;       // its work matrix until the join
   bool defer_coarse_ = false;   // a member of a batch: the batch inverts the coarsest system
+  std::vector<int> members_;    // and has this many systems on each level
   bool valid_ = true;
   double setup_ms_ = 0.0;   // wall time of the latest build_all (device work included)
   DBuf<double> aug0_;    // the assembled coarsest matrix while its inversion is deferred

@@ -336,8 +336,8 @@ class StokesIB:
 
 
 class StokesIBBatch:
-    """Many independent periodic Stokes-IB systems solved together (one
-    persistent launch per smoother sweep across all of them).  ``systems`` is
+    """Many independent periodic Stokes-IB systems solved together (every
+    launch of the V-cycle runs across all of them).  ``systems`` is
     a list of system descriptions as for ``StokesIB``; they may differ in N,
     structure and stiffness but must share the fluid and box parameters."""
 
