@@ -317,10 +317,15 @@ template <> struct Pair<float> { using type = float2; };
 // multiple of S with empty ones.  Colours are run-relative: f0..f1
 // ascending, then g0..g1 descending.  The sums run in the order of the
 // row's entries per lane, then over lanes 2 apart and neighbours.
+// Bound by the issue and L1 rate of one CU per work-group, so each component's
+// rows have a CU where the springs leave them apart (3297 rows of 24 colours at
+// 256^2, two work-groups of 512 threads: 97 -> 49 us a sweep with 32-bit offsets,
+// no sums in waves without rows and the reciprocal for the division).
 template <typename T, int KP, int S>
-__global__ void __launch_bounds__(1024) k_gs_band_lds(T* x, const T* __restrict__ b, BandView<T> v, int f0, int f1,
+__global__ void __launch_bounds__(1024) k_gs_band_lds(T* x, const T* __restrict__ b, BandViews<T> vs, int f0, int f1,
                                                       int g0, int g1) {
   using T2 = typename Pair<T>::type;
+  const BandView<T>& v = vs.v[blockIdx.x];
   extern __shared__ char smem_raw[];
   T* xl = reinterpret_cast<T*>(smem_raw);
   T* cb = xl + v.nb;
@@ -381,25 +386,31 @@ __global__ void __launch_bounds__(1024) k_gs_band_lds(T* x, const T* __restrict_
   lds_barrier();
   const int ns = span_steps(f0, f1, g0, g1);
   if (ns > 0) {
+    // 32-bit offsets throughout (a run has fewer than 2^16 / sizeof(T) slots)
     const unsigned* __restrict__ went = v.bent;
     const T2* __restrict__ wval = reinterpret_cast<const T2*>(v.bval);
+    const T2* __restrict__ wdiag = reinterpret_cast<const T2*>(v.bdiag);
+    const unsigned half = v.stride / 2;
+    const int wgrp = __builtin_amdgcn_readfirstlane(tid >> 6) * (64 / kBandG);   // the wave's first row of a colour
     unsigned w[S][KP];
-    T2 val[S][KP];
-    T dg[S];
+    T2 val[S][KP], dg[S];
     int s0[S], n[S];
     auto fetch = [&](int st, int k) {
       const int col = span_colour(k < ns ? k : ns - 1, f0, f1, g0);
-      const int c0 = cp[col], cn = cp[col + 1] - c0;
-      s0[st] = k < ns ? c0 : 0;
+      const int c0 = __builtin_amdgcn_readfirstlane(cp[col]);
+      const int cn = __builtin_amdgcn_readfirstlane(cp[col + 1]) - c0;
+      s0[st] = c0;
       n[st] = k < ns ? cn : 0;
-      const int li = grp < cn ? grp : cn - 1;
-      dg[st] = v.bdiag[c0 + li];
-      const size_t at = (size_t)c0 * (v.stride / 2) + (size_t)li * kBandG + sub;
-      const size_t step = (size_t)cn * kBandG;
+      const int cc = cn > 0 ? c0 : 0, cm = cn > 0 ? cn : 1;   // (a colour without rows here: slot 0)
+      const int li = grp < cm ? grp : cm - 1;
+      dg[st] = wdiag[cc + li];
+      unsigned at = cc * half + li * kBandG + sub;
+      const unsigned step = cn > 0 ? cm * kBandG : kBandG;
 #pragma unroll
       for (int q = 0; q < KP; ++q) {
-        w[st][q] = went[at + q * step];
-        val[st][q] = wval[at + q * step];
+        w[st][q] = went[at];
+        val[st][q] = wval[at];
+        at += step;
       }
     };
 
@@ -412,15 +423,22 @@ __global__ void __launch_bounds__(1024) k_gs_band_lds(T* x, const T* __restrict_
     for (int k0 = 0; k0 < ns; k0 += S) {
 #pragma unroll
       for (int st = 0; st < S; ++st) {
-        T a = 0;
+        if (wgrp < n[st]) {   // a wave without rows of this colour skips its sums
+          T a = 0;
 #pragma unroll
-        for (int q = 0; q < KP; ++q) {
-          a += val[st][q].x * *reinterpret_cast<const T*>(xlb + (w[st][q] & 0xffffu));
-          a += val[st][q].y * *reinterpret_cast<const T*>(xlb + (w[st][q] >> 16));
+          for (int q = 0; q < KP; ++q) {
+            a += val[st][q].x * *reinterpret_cast<const T*>(xlb + (w[st][q] & 0xffffu));
+            a += val[st][q].y * *reinterpret_cast<const T*>(xlb + (w[st][q] >> 16));
+          }
+          a = quad_sum(a);
+          if (grp < n[st] && sub == 0) {
+            // (cb - a) / diagonal: the product with the reciprocal, corrected by
+            // its remainder, off the chain of a division
+            const int myrow = s0[st] + grp;
+            const T r = cb[myrow] - a, q0 = r * dg[st].y;
+            xl[myrow] += fma(fma(-q0, dg[st].x, r), dg[st].y, q0);
+          }
         }
-        a = quad_sum(a);
-        const int myrow = grp < n[st] ? s0[st] + grp : -1;
-        if (myrow >= 0 && sub == 0) xl[myrow] += (cb[myrow] - a) / dg[st];
         fetch(st, k0 + st + S);
         lds_barrier();
       }
@@ -450,7 +468,11 @@ __global__ void k_band_values(const int* __restrict__ bcode, T* __restrict__ bva
        e += (size_t)gridDim.x * blockDim.x) {
     if (e < nbe) bval[e] = band_value(bcode[e], c, tu, tv, nnz_u);
     else if (e < nbe + noe) oval[e - nbe] = band_value(ocode[e - nbe], c, tu, tv, nnz_u);
-    else bdiag[e - nbe - noe] = diag[brow[e - nbe - noe]];
+    else {
+      const T d = diag[brow[e - nbe - noe]];
+      bdiag[2 * (e - nbe - noe)] = d;
+      bdiag[2 * (e - nbe - noe) + 1] = T(1) / d;
+    }
   }
 }
 
@@ -549,24 +571,33 @@ void launch_gs_sweep(T* x, const T* b, const GsSweep<T>& g, hipStream_t s) {
       g0 = seq[std::max(a, turn + 1)];
       g1 = seq[z];
     }
+    BandViews<T> vs{};
     const BandRun<T>* run = nullptr;
+    int parts = 0, most = 0;
+    size_t lds = 0;
     if (g.runs)
       for (const BandRun<T>& rr : *g.runs)
-        if (rr.cf <= seq[a] && seq[a] <= rr.cl) run = &rr;
-    if (run && run->lds) {
-      const int nc = run->cl - run->cf + 1;
-      const BandView<T> v{run->nb,   nc,          run->stride, run->cptr.p, run->brow.p, run->optr.p,
-                          run->ocol.p, run->bent.p, run->bval.p, run->oval.p, run->bdiag.p};
+        if (rr.cf <= seq[a] && seq[a] <= rr.cl && rr.lds) {
+          const int nc = rr.cl - rr.cf + 1;
+          if (parts == 2) throw Error(IBMG_ERR_STATE, "a run of colours has at most two parts");
+          run = &rr;
+          most = std::max(most, rr.most);
+          lds = std::max(lds, 2 * (size_t)rr.nb * sizeof(T) + (nc + 1) * sizeof(int));
+          vs.v[parts++] = BandView<T>{rr.nb,     nc,        rr.stride, rr.cptr.p, rr.brow.p, rr.optr.p,
+                                      rr.ocol.p, rr.bent.p, rr.bval.p, rr.oval.p, rr.bdiag.p};
+        }
+    if (run) {
       const int o = run->cf;
-      const size_t lds = 2 * (size_t)run->nb * sizeof(T) + (nc + 1) * sizeof(int);
       const int a0 = f0 - o, a1 = f1 - o, b0 = g0 - o, b1 = g1 - o;
+      // a colour in one pass of the work-group
+      const dim3 grid(parts), block(most * kBandG <= 512 ? 512 : 1024);
       switch (run->kp) {
-        case 1: IBMG_KLAUNCH((k_gs_band_lds<T, 1, 4>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
-        case 2: IBMG_KLAUNCH((k_gs_band_lds<T, 2, 4>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
-        case 3: IBMG_KLAUNCH((k_gs_band_lds<T, 3, 4>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
-        case 4: IBMG_KLAUNCH((k_gs_band_lds<T, 4, 3>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
-        case 6: IBMG_KLAUNCH((k_gs_band_lds<T, 6, 3>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
-        default: IBMG_KLAUNCH((k_gs_band_lds<T, 8, 2>), dim3(1), dim3(1024), lds, s, x, b, v, a0, a1, b0, b1); break;
+        case 1: IBMG_KLAUNCH((k_gs_band_lds<T, 1, 4>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
+        case 2: IBMG_KLAUNCH((k_gs_band_lds<T, 2, 4>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
+        case 3: IBMG_KLAUNCH((k_gs_band_lds<T, 3, 4>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
+        case 4: IBMG_KLAUNCH((k_gs_band_lds<T, 4, 3>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
+        case 6: IBMG_KLAUNCH((k_gs_band_lds<T, 6, 3>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
+        default: IBMG_KLAUNCH((k_gs_band_lds<T, 8, 2>), grid, block, lds, s, x, b, vs, a0, a1, b0, b1); break;
       }
     } else if (g.mhat) {
       IBMG_KLAUNCH((k_gs_band_p<T>), dim3(1), dim3(1024), 0, s, x, b, cl.d_ptr.p, cl.d_rows.p, f0, f1, g0, g1, g.N,

@@ -37,9 +37,10 @@ constexpr int kGsLongRow = 8;
 constexpr size_t kGsBandLds = 64 << 10;
 
 // A run of consecutive small colours of the velocity sweep, swept by one
-// work-group with the run's rows resident in LDS.  Slots 0..nb-1 are the
-// run's rows in colour order (colour cf + k holds slots [cptr[k],
-// cptr[k+1])).  Each slot's row of A_IB (stencil and IB entries merged by
+// work-group with the run's rows resident in LDS; where the springs do not
+// couple the components, one run (and work-group) for each component's rows.
+// Slots 0..nb-1 are the run's rows in colour order (colour cf + k holds slots
+// [cptr[k], cptr[k+1]), none if the component has no row of it).  Each slot's row of A_IB (stencil and IB entries merged by
 // column) is split into band entries (columns that are slots of the run)
 // and outer entries (every other column, constant while the run is swept).
 // A row's band entries go to kBandG lanes, entry e to lane e % kBandG as
@@ -57,7 +58,7 @@ constexpr size_t kGsBandLds = 64 << 10;
 // level's coefficients and Galerkin rows.
 template <typename T>
 struct BandRun {
-  int cf = 0, cl = 0, nb = 0, stride = 0, kp = 0, nnz_u = 0;
+  int cf = 0, cl = 0, nb = 0, stride = 0, kp = 0, nnz_u = 0, most = 0;   // most: rows of a colour
   bool lds = false;
   std::vector<int> hcptr, hbrow, hbcode, hoptr, hocol, hocode;
   std::vector<unsigned> hbent;
@@ -71,7 +72,12 @@ struct BandView {
   int nb, ncol, stride;
   const int *cptr, *brow, *optr, *ocol;
   const unsigned* bent;
-  const T *bval, *oval, *bdiag;
+  const T *bval, *oval, *bdiag;   // bdiag: every slot's diagonal and its reciprocal
+};
+// the runs of one launch, a work-group each
+template <typename T>
+struct BandViews {
+  BandView<T> v[2];
 };
 
 // band kernel shape: lanes per row, and the most padded entries a lane holds
@@ -208,6 +214,9 @@ void build_band_runs(const ColourLists& cl, const std::vector<int>& tptr_u, cons
   const std::vector<int>* tcol[2] = {&tcol_u, &tcol_v};
   runs.clear();
   const int NN = N * N;
+  bool coupled = false;   // a u row with a v column or the reverse (tangent blocks)
+  for (int c : tcol_u) coupled = coupled || c >= NN;
+  for (int c : tcol_v) coupled = coupled || c < NN;
   std::vector<int> slot(2 * (size_t)NN, -1);
   for (int c0 = 0; c0 < cl.ncol;) {
     if (cl.big(c0)) {
@@ -216,87 +225,100 @@ void build_band_runs(const ColourLists& cl, const std::vector<int>& tptr_u, cons
     }
     int c1 = c0;
     while (c1 + 1 < cl.ncol && !cl.big(c1 + 1)) ++c1;
-    runs.emplace_back();
-    BandRun<T>& run = runs.back();
-    run.cf = c0;
-    run.cl = c1;
-    const int s0 = cl.ptr[c0], s1 = cl.ptr[c1 + 1];
-    run.nb = s1 - s0;
-    run.hbrow.assign(cl.rows.begin() + s0, cl.rows.begin() + s1);
-    for (int i = 0; i < run.nb; ++i) slot[run.hbrow[i]] = i;
-    run.hcptr.clear();
-    for (int c = c0; c <= c1 + 1; ++c) run.hcptr.push_back(cl.ptr[c] - s0);
-    run.hoptr.assign(1, 0);
-    run.hocol.clear();
-    run.hocode.clear();
-    std::vector<std::vector<std::pair<int, int>>> band(run.nb);   // per slot: (slot, code)
-    std::vector<std::pair<int, int>> ents;   // (column, code)
-    for (int i = 0; i < run.nb; ++i) {
-      const int r = run.hbrow[i], comp = r >= NN ? 1 : 0, q = r - comp * NN, o = comp * NN;
-      const int ii = q % N, jj = q / N;
-      ents.clear();
-      ents.push_back({r, 1});
-      ents.push_back({o + jj * N + (ii + 1) % N, 2});
-      ents.push_back({o + jj * N + (ii + N - 1) % N, 2});
-      ents.push_back({o + ((jj + 1) % N) * N + ii, 2});
-      ents.push_back({o + ((jj + N - 1) % N) * N + ii, 2});
-      const int ib0 = comp ? (int)tcol_u.size() : 0;
-      for (int k = (*tptr[comp])[q]; k < (*tptr[comp])[q + 1]; ++k)
-        ents.push_back({(*tcol[comp])[k], (ib0 + k + 1) * 4});
-      std::sort(ents.begin(), ents.end());
-      for (size_t a = 0; a < ents.size();) {
-        const int col = ents[a].first;
-        int code = 0;
-        for (; a < ents.size() && ents[a].first == col; ++a) code += ents[a].second;
-        if (slot[col] >= 0) {
-          band[i].push_back({slot[col], code});
-        } else {
-          run.hocol.push_back(col);
-          run.hocode.push_back(code);
-        }
-      }
-      run.hoptr.push_back((int)run.hocol.size());
-    }
-    for (int i = 0; i < run.nb; ++i) slot[run.hbrow[i]] = -1;
+    const size_t first = runs.size();
     size_t longest = 1;
-    for (const auto& bi : band) longest = std::max(longest, bi.size());
-    const int pairs = (int)((longest + 2 * kBandG - 1) / (2 * kBandG));
-    run.kp = 0;
-    for (int kp : kBandPairs)
-      if (!run.kp && kp >= pairs) run.kp = kp;
-    bool nonempty = true;
-    for (int k = 0; k + 1 < (int)run.hcptr.size(); ++k) nonempty = nonempty && run.hcptr[k + 1] > run.hcptr[k];
-    run.lds = run.kp > 0 && nonempty && (size_t)run.nb * sizeof(T) < 65536 &&
-              2 * (size_t)run.nb * sizeof(T) + (run.hcptr.size() + 1) * sizeof(int) <= kGsBandLds;
-    if (!run.kp) run.kp = kBandK / 2;
-    run.stride = 2 * kBandG * run.kp;
-    run.nnz_u = (int)tcol_u.size();
-    run.hbent.assign(run.lds ? (size_t)run.nb * run.stride / 2 : 0, 0u);
-    run.hbcode.assign(run.lds ? (size_t)run.nb * run.stride : 0, 0);
-    if (run.lds)
-      for (int k = 0; k + 1 < (int)run.hcptr.size(); ++k) {
-        const int a0 = run.hcptr[k], n = run.hcptr[k + 1] - a0;
-        for (int li = 0; li < n; ++li) {
-          const auto& bi = band[a0 + li];
-          for (size_t e = 0; e < bi.size(); ++e) {
-            const size_t q = e / kBandG, g = e % kBandG, pr = q / 2, h = q % 2;
-            const size_t w = (size_t)a0 * run.stride / 2 + (pr * n + li) * kBandG + g;
-            run.hbent[w] |= (unsigned)(bi[e].first * sizeof(T)) << (16 * h);
-            run.hbcode[2 * w + h] = bi[e].second;
+    bool lds = true;
+    std::vector<std::vector<std::vector<std::pair<int, int>>>> bands;   // per part and slot: (slot, code)
+    for (int part = 0; part < (coupled ? 1 : 2); ++part) {
+      BandRun<T> run;
+      run.cf = c0;
+      run.cl = c1;
+      run.hcptr.assign(1, 0);
+      for (int c = c0; c <= c1; ++c) {
+        for (int k = cl.ptr[c]; k < cl.ptr[c + 1]; ++k)
+          if (coupled || (cl.rows[k] >= NN) == (part == 1)) run.hbrow.push_back(cl.rows[k]);
+        run.hcptr.push_back((int)run.hbrow.size());
+        run.most = std::max(run.most, run.hcptr.end()[-1] - run.hcptr.end()[-2]);
+      }
+      run.nb = (int)run.hbrow.size();
+      if (!run.nb) continue;
+      for (int i = 0; i < run.nb; ++i) slot[run.hbrow[i]] = i;
+      run.hoptr.assign(1, 0);
+      std::vector<std::vector<std::pair<int, int>>> band(run.nb);
+      std::vector<std::pair<int, int>> ents;   // (column, code)
+      for (int i = 0; i < run.nb; ++i) {
+        const int r = run.hbrow[i], comp = r >= NN ? 1 : 0, q = r - comp * NN, o = comp * NN;
+        const int ii = q % N, jj = q / N;
+        ents.clear();
+        ents.push_back({r, 1});
+        ents.push_back({o + jj * N + (ii + 1) % N, 2});
+        ents.push_back({o + jj * N + (ii + N - 1) % N, 2});
+        ents.push_back({o + ((jj + 1) % N) * N + ii, 2});
+        ents.push_back({o + ((jj + N - 1) % N) * N + ii, 2});
+        const int ib0 = comp ? (int)tcol_u.size() : 0;
+        for (int k = (*tptr[comp])[q]; k < (*tptr[comp])[q + 1]; ++k)
+          ents.push_back({(*tcol[comp])[k], (ib0 + k + 1) * 4});
+        std::sort(ents.begin(), ents.end());
+        for (size_t a = 0; a < ents.size();) {
+          const int col = ents[a].first;
+          int code = 0;
+          for (; a < ents.size() && ents[a].first == col; ++a) code += ents[a].second;
+          if (slot[col] >= 0) {
+            band[i].push_back({slot[col], code});
+          } else {
+            run.hocol.push_back(col);
+            run.hocode.push_back(code);
           }
         }
+        run.hoptr.push_back((int)run.hocol.size());
+        longest = std::max(longest, band[i].size());
       }
-    run.cptr.upload(run.hcptr, s);
-    run.brow.upload(run.hbrow, s);
-    run.bent.upload(run.hbent, s);
-    run.bcode.upload(run.hbcode, s);
-    run.optr.upload(run.hoptr, s);
-    run.ocol.upload(run.hocol, s);
-    if (!run.ocol.p) run.ocol.alloc(1);   // the band kernel's prologue reads index 0 of an empty list
-    run.ocode.upload(run.hocode, s);
-    run.bval.alloc(std::max<size_t>(run.hbcode.size(), 1));
-    run.oval.alloc(std::max<size_t>(run.hocol.size(), 1));
-    run.bdiag.alloc(std::max(run.nb, 1));
+      for (int i = 0; i < run.nb; ++i) slot[run.hbrow[i]] = -1;
+      lds = lds && (size_t)run.nb * sizeof(T) < 65536 &&
+            2 * (size_t)run.nb * sizeof(T) + (run.hcptr.size() + 1) * sizeof(int) <= kGsBandLds;
+      run.nnz_u = (int)tcol_u.size();
+      bands.push_back(std::move(band));
+      runs.push_back(std::move(run));
+    }
+    const int pairs = (int)((longest + 2 * kBandG - 1) / (2 * kBandG));
+    int kp = 0;
+    for (int k : kBandPairs)
+      if (!kp && k >= pairs) kp = k;
+    lds = lds && kp > 0;
+    if (!kp) kp = kBandK / 2;
+    for (size_t p = first; p < runs.size(); ++p) {
+      BandRun<T>& run = runs[p];
+      const auto& band = bands[p - first];
+      run.lds = lds;
+      run.kp = kp;
+      run.stride = 2 * kBandG * kp;
+      run.hbent.assign(lds ? (size_t)run.nb * run.stride / 2 : 0, 0u);
+      run.hbcode.assign(lds ? (size_t)run.nb * run.stride : 0, 0);
+      if (lds)
+        for (int k = 0; k + 1 < (int)run.hcptr.size(); ++k) {
+          const int a0 = run.hcptr[k], n = run.hcptr[k + 1] - a0;
+          for (int li = 0; li < n; ++li) {
+            const auto& bi = band[a0 + li];
+            for (size_t e = 0; e < bi.size(); ++e) {
+              const size_t q = e / kBandG, g = e % kBandG, pr = q / 2, h = q % 2;
+              const size_t w = (size_t)a0 * run.stride / 2 + (pr * n + li) * kBandG + g;
+              run.hbent[w] |= (unsigned)(bi[e].first * sizeof(T)) << (16 * h);
+              run.hbcode[2 * w + h] = bi[e].second;
+            }
+          }
+        }
+      run.cptr.upload(run.hcptr, s);
+      run.brow.upload(run.hbrow, s);
+      run.bent.upload(run.hbent, s);
+      run.bcode.upload(run.hbcode, s);
+      run.optr.upload(run.hoptr, s);
+      run.ocol.upload(run.hocol, s);
+      if (!run.ocol.p) run.ocol.alloc(1);   // the band kernel's prologue reads index 0 of an empty list
+      run.ocode.upload(run.hocode, s);
+      run.bval.alloc(std::max<size_t>(run.hbcode.size(), 1));
+      run.oval.alloc(std::max<size_t>(run.hocol.size(), 1));
+      run.bdiag.alloc(2 * (size_t)run.nb);
+    }
     c0 = c1 + 1;
   }
 }
