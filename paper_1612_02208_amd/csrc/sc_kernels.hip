@@ -682,17 +682,45 @@ __global__ void k_aib_sub(const T* __restrict__ x, T* __restrict__ y, int N, Sto
 }
 
 // Chebyshev start with the first residual update: d = theta_inv s, x = d,
-// rc = r - A_IB d, the neighbours' d formed from s as the start forms it
+// rc = r - A_IB d, the neighbours' d formed from s as the start forms it.  The
+// first nsb work-groups take a row per thread, the others the rows with IB
+// entries (listed; none listed: every row per thread), 16 lanes each: one lane's
+// walk through the longest rows bounded the launch (256^2, 1024 points: 17.1 ->
+// 5.2 us).
 template <typename T>
-__global__ void k_cheb_init_sub(int N, T theta_inv, const T* __restrict__ sv, T* __restrict__ d, T* __restrict__ x,
-                                const T* __restrict__ r, T* __restrict__ rc, StokesCoef<T> c, CsrT<T> tu,
-                                CsrT<T> tv) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 2 * N * N) return;
-  const T di = theta_inv * sv[i];
-  d[i] = di;
-  x[i] = di;
-  rc[i] = r[i] - aib_row_l<T>([=](int k) { return theta_inv * sv[k]; }, i, N, c, tu, tv);
+__global__ void __launch_bounds__(256) k_cheb_init_sub(int N, T theta_inv, const T* __restrict__ sv, T* __restrict__ d,
+                                                       T* __restrict__ x, const T* __restrict__ r, T* __restrict__ rc,
+                                                       StokesCoef<T> c, CsrT<T> tu, CsrT<T> tv,
+                                                       const int* __restrict__ rows, int nrows, int nsb) {
+  const int NN = N * N;
+  auto ds = [=](int k) { return theta_inv * sv[k]; };
+  if ((int)blockIdx.x < nsb) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= 2 * NN) return;
+    const T di = theta_inv * sv[i];
+    d[i] = di;
+    x[i] = di;
+    const CsrT<T>& t = i >= NN ? tv : tu;
+    const int q = i >= NN ? i - NN : i;
+    if (nrows > 0 && t.ptr[q + 1] > t.ptr[q]) return;
+    rc[i] = r[i] - aib_row_l<T>(ds, i, N, c, tu, tv);
+    return;
+  }
+  const int g = ((int)blockIdx.x - nsb) * 16 + threadIdx.x / 16, sub = threadIdx.x % 16;
+  if (g >= nrows) return;
+  const int i = rows[g], comp = i >= NN ? 1 : 0, q = i - comp * NN;
+  const CsrT<T>& t = comp ? tv : tu;
+  T a = 0;
+  for (int k = t.ptr[q] + sub; k < t.ptr[q + 1]; k += 16) a += t.val[k] * ds(t.col[k]);
+  a = row16_sum(a);
+  if (sub != 0) return;
+  const int ii = q % N, jj = q / N, o = comp * NN;
+  const int im = ii == 0 ? N - 1 : ii - 1, ip = ii == N - 1 ? 0 : ii + 1;
+  const int jm = jj == 0 ? N - 1 : jj - 1, jp = jj == N - 1 ? 0 : jj + 1;
+  const T xc = ds(i);
+  const T y = c.alpha * xc - c.beta * (ds(o + jj * N + im) + ds(o + jj * N + ip) + ds(o + jm * N + ii) +
+                                       ds(o + jp * N + ii) - T(4) * xc) + a;
+  rc[i] = r[i] - y;
 }
 
 // A velocity iterate whose last Chebyshev step is still to be added:
@@ -780,9 +808,10 @@ void launch_aib_sub(const T* x, T* y, int N, StokesCoef<T> c, CsrT<T> tu, CsrT<T
 }
 template <typename T>
 void launch_cheb_init_sub(int N, T theta_inv, const T* sv, T* d, T* x, const T* r, T* rc, StokesCoef<T> c,
-                          CsrT<T> tu, CsrT<T> tv, hipStream_t s) {
-  IBMG_KLAUNCH((k_cheb_init_sub<T>), dim3(cdiv(2 * (size_t)N * N, 256)), dim3(256), 0, s, N, theta_inv, sv, d, x, r,
-               rc, c, tu, tv);
+                          CsrT<T> tu, CsrT<T> tv, const int* rows, int nrows, hipStream_t s) {
+  const int nsb = cdiv(2 * (size_t)N * N, 256);
+  IBMG_KLAUNCH((k_cheb_init_sub<T>), dim3(nsb + cdiv(nrows, 16)), dim3(256), 0, s, N, theta_inv, sv, d, x, r, rc, c, tu,
+               tv, rows, nrows, nsb);
   IBMG_LAUNCH_CHECK();
 }
 template <typename T>
@@ -819,7 +848,7 @@ void launch_weyl(T* x, size_t n, hipStream_t s) {
   template void launch_cheb_init<T>(size_t, T, const T*, T*, T*, const T*, T*, hipStream_t);                  \
   template void launch_cheb_step<T>(size_t, T, T, const T*, T*, T*, hipStream_t);                             \
   template void launch_cheb_init_sub<T>(int, T, const T*, T*, T*, const T*, T*, StokesCoef<T>, CsrT<T>, CsrT<T>, \
-                                        hipStream_t);                                                        \
+                                        const int*, int, hipStream_t);                                       \
   template void launch_cheb_div<T>(const T*, const T*, const T*, T, T, const T*, T*, int, T, T, T, hipStream_t); \
   template void launch_cheb_sub<T>(size_t, T, T, const T*, const T*, const T*, const T*, T*, hipStream_t);      \
   template void launch_aib_sub<T>(const T*, T*, int, StokesCoef<T>, CsrT<T>, CsrT<T>, hipStream_t);

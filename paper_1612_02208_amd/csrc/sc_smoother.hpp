@@ -135,7 +135,7 @@ void launch_aib_sub(const T* x, T* y, int N, StokesCoef<T> c, CsrT<T> tu, CsrT<T
 // d = theta_inv s, x = d, rc = r - A_IB d
 template <typename T>
 void launch_cheb_init_sub(int N, T theta_inv, const T* sv, T* d, T* x, const T* r, T* rc, StokesCoef<T> c,
-                          CsrT<T> tu, CsrT<T> tv, hipStream_t s);
+                          CsrT<T> tu, CsrT<T> tv, const int* rows, int nrows, hipStream_t s);
 // out = a D (x + c1 d + c2 s) + b y (the last Chebyshev step folded into D)
 template <typename T>
 void launch_cheb_div(const T* x, const T* d, const T* sv, T c1, T c2, const T* y, T* out, int N, T gi, T a, T b,
@@ -330,6 +330,8 @@ struct ScLevel {
   StokesCoef<T> c{};
   CsrT<T> tu{}, tv{};
   T ih2 = 0;
+  const int* ib_rows = nullptr;   // the level's rows with IB entries, where listed
+  int n_ib_rows = 0;
   ColourLists colu, colp;
   std::vector<BandRun<T>> runs_u;   // LDS runs of the velocity sweep
   DBuf<T> diag, dinv, mdiag;  // A_IB diagonal (and inverse) on faces, -M^ diagonal on cells
@@ -380,7 +382,7 @@ struct ScLevel {
     const size_t n2 = 2 * (size_t)N * N;
     sgs_a(r, as.p, st, grad_p);
     if (its > 1)
-      launch_cheb_init_sub<T>(N, a_theta_inv, as.p, ad.p, x, r, ar.p, c, tu, tv, st);
+      launch_cheb_init_sub<T>(N, a_theta_inv, as.p, ad.p, x, r, ar.p, c, tu, tv, ib_rows, n_ib_rows, st);
     else
       launch_cheb_init<T>(n2, a_theta_inv, as.p, ad.p, x, r, nullptr, st);
     for (int k = 0; k + 1 < its; ++k) {

@@ -1093,6 +1093,8 @@ class Solver final : public SolverBase {
     const size_t n2 = 2 * (size_t)NN, n1 = NN;
     sc.c = coef<T>(lev);
     sc.tu = csr<T>(lev.f[0]);
+    sc.ib_rows = lev.ib_lanes ? lev.d_ib_rows.p : nullptr;
+    sc.n_ib_rows = lev.ib_lanes ? (int)lev.ib_rows.size() : 0;
     sc.tv = csr<T>(lev.f[1]);
     sc.ih2 = (T)((double)N * N);
     launch_sc_diag<T>(N, sc.c, sc.tu, sc.tv, sc.ih2, sc.diag.p, sc.dinv.p, sc.mdiag.p, s);
