@@ -461,8 +461,14 @@ template <typename T>
 void launch_upd_norm(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
                      double* hcol, double* pout, hipStream_t s, int nblk_in = 0, bool store = true);
 template <typename T>
-void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout,
-                      hipStream_t s);
+struct ScaleCopies {   // also v2 = v and dst = src (v2 = null: neither)
+  T* v2 = nullptr;
+  const T* src = nullptr;
+  T* dst = nullptr;
+};
+template <typename T>
+void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout, hipStream_t s,
+                      ScaleCopies<T> cp = {});
 // from those partials: t = (t - V h2) / |t - V h2| with the norm taken as
 // sqrt(|t|^2 - |h2|^2); hcol[0..k) += h2, hcol[k] = the norm
 template <typename T>

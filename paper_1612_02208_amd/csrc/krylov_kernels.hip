@@ -174,7 +174,7 @@ template <typename T>
 __global__ void __launch_bounds__(kThreads) k_scale_red(const T* t, T* v, BSeg sg,
                                                         const double* __restrict__ pin, int nblk_in,
                                                         size_t pstride, double* __restrict__ hout,
-                                                        size_t hstride) {
+                                                        size_t hstride, ScaleCopies<T> cp) {
   __shared__ double red[32];
   __shared__ double nrm;
   const int sy = blockIdx.y;
@@ -188,8 +188,14 @@ __global__ void __launch_bounds__(kThreads) k_scale_red(const T* t, T* v, BSeg s
   const double d = sqrt(nrm);
   if (blockIdx.x == 0 && threadIdx.x == 0) hout[0] = d;
   const double inv = d != 0.0 ? 1.0 / d : 0.0;
-  for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads)
-    v[i] = (T)((double)t[i] * inv);
+  for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
+    const T x = (T)((double)t[i] * inv);
+    v[i] = x;
+    if (cp.v2) {
+      cp.v2[i] = x;
+      cp.dst[i] = cp.src[i];
+    }
+  }
 }
 
 // The second Gram-Schmidt pass finished with the normalisation, from
@@ -663,7 +669,7 @@ void launch_scale_red_b(const T* t, T* v, BSeg sg, int nsys, size_t nmax, const 
                         size_t pstride, double* hout, size_t hstride, hipStream_t s) {
   if (nsys <= 0) return;
   IBMG_KLAUNCH((k_scale_red<T>), dim3(stream_blocks(nmax), nsys), dim3(kThreads), 0, s, t, v, sg, pin,
-                     nblk, pstride, hout, hstride);
+                     nblk, pstride, hout, hstride, ScaleCopies<T>{});
   IBMG_LAUNCH_CHECK();
 }
 
@@ -704,9 +710,12 @@ void launch_upd_norm(T* t, const T* V, int k, size_t stride, size_t n, const dou
 }
 
 template <typename T>
-void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout, hipStream_t s) {
+void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout, hipStream_t s,
+                      ScaleCopies<T> cp) {
   // nblk: blocks of the producer of pin
-  launch_scale_red_b<T>(t, v, seg1(n), 1, n, pin, nblk, 0, hout, 0, s);
+  IBMG_KLAUNCH((k_scale_red<T>), dim3(stream_blocks(n)), dim3(kThreads), 0, s, t, v, seg1(n), pin, nblk, (size_t)0, hout,
+               (size_t)0, cp);
+  IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
@@ -793,7 +802,8 @@ void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k
                                    double*, hipStream_t, int);                                         \
   template void launch_upd_norm<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,     \
                                    double*, hipStream_t, int, bool);                                   \
-  template void launch_scale_red<T>(const T*, T*, size_t, const double*, int, double*, hipStream_t);   \
+  template void launch_scale_red<T>(const T*, T*, size_t, const double*, int, double*, hipStream_t,    \
+                                    ScaleCopies<T>);                                                   \
   template void launch_scale_upd<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,    \
                                     hipStream_t);                                                      \
   template void launch_upd_dots_b<T>(T*, const T*, int, size_t, BSeg, int, const double*, int, size_t, \

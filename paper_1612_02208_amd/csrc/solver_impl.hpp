@@ -1664,10 +1664,15 @@ class Solver final : public SolverBase {
       return;
     }
     const size_t n = 3 * (size_t)d_.N * d_.N;
-    if (!gexec_) build_graph();
     IBMG_HIP(hipMemcpyAsync(vin_.p, r, n * sizeof(double), hipMemcpyDeviceToDevice, s));
-    IBMG_HIP(hipGraphLaunch(gexec_, s));
+    replay(s);
     IBMG_HIP(hipMemcpyAsync(z, vout_.p, n * sizeof(double), hipMemcpyDeviceToDevice, s));
+  }
+
+  // the captured V-cycle, from vin_ to vout_
+  void replay(hipStream_t s) {
+    if (!gexec_) build_graph();
+    IBMG_HIP(hipGraphLaunch(gexec_, s));
   }
 
   double read_scalar(const double* dptr, hipStream_t s) {
@@ -1751,19 +1756,28 @@ class Solver final : public SolverBase {
       launch_scale<double>(V0, V0, osc_.p + 0, n, s);
       launch_fill<double>(g_.p, 0.0, (size_t)o.restart + 2, s);
       IBMG_HIP(hipMemcpyAsync(g_.p, osc_.p + 0, sizeof(double), hipMemcpyDeviceToDevice, s));
+      // Replays read vin_ and write vout_: the operator takes z_k from vout_,
+      // and the launch that normalises the next basis vector also stores it to
+      // vin_ and z_k to its column (two copies fewer an iteration)
+      if (use_graph_) IBMG_HIP(hipMemcpyAsync(vin_.p, V0, n * sizeof(double), hipMemcpyDeviceToDevice, s));
+      auto precondition = [&](const double* v, double* z) {
+        if (use_graph_) replay(s);
+        else vcycle_body(v, z, s);
+      };
       int k = 0;
       bool queued = false;   // z_k's V-cycle already queued by the previous iteration
       for (; k < o.restart && its < o.max_it;) {
         double* vk = Vo_.p + (size_t)k * n;
         double* zk = Zo_.p + (size_t)k * n;
         double* t = Vo_.p + (size_t)(k + 1) * n;
-        if (!queued) vcycle(vk, zk, s);
+        if (!queued) precondition(vk, zk);
         queued = false;
         ++vcycles;
-        op<double>(L_, zk, t, nullptr, trans, Fd_.p, s);
+        op<double>(L_, use_graph_ ? vout_.p : zk, t, nullptr, trans, Fd_.p, s);
         double* hcol = Ho_.p + (size_t)k * ldh;
         orthogonalise_outer(Vo_.p, k + 1, n, t, hcol, gs_nblk, s);
-        launch_scale_red<double>(t, t, n, opart_.p, gs_nblk, hcol + k + 1, s);
+        launch_scale_red<double>(t, t, n, opart_.p, gs_nblk, hcol + k + 1, s,
+                                 use_graph_ ? ScaleCopies<double>{vin_.p, vout_.p, zk} : ScaleCopies<double>{});
         launch_givens(Ho_.p, ldh, k, cs_.p, sn_.p, g_.p, osc_.p + 1, s);
         // The estimate is read on the host after this iteration's work.
         // While the last two estimates say that even one more step at their
@@ -1776,7 +1790,7 @@ class Solver final : public SolverBase {
         IBMG_HIP(hipEventRecord(est_ev_, s));
         const double rate = prev_est > 0.0 ? std::min(1.0, est / prev_est) : 1.0;
         if (k + 1 < o.restart && its + 1 < o.max_it && its >= 2 && est * rate * rate > target) {
-          vcycle(t, Zo_.p + (size_t)(k + 1) * n, s);
+          precondition(t, Zo_.p + (size_t)(k + 1) * n);
           queued = true;
         }
         IBMG_HIP(hipEventSynchronize(est_ev_));
