@@ -34,6 +34,11 @@ constexpr int kScalY = 1;     // scal[1..16]: least-squares solution
 // us, 4.6 M (tangent springs) 36.3 against 24.2.  IBMG_NO_IB_ROWS in the
 // environment takes the other form on every level.
 constexpr size_t kIbRowsMaxEntries = 3500000;
+// Blocks of the outer solve's long reductions up to which the next kernel's
+// blocks reduce the partial sums themselves: the folding launches cost more than
+// the reads (solves with and without folding: 32^2, 3 blocks, 1012 and 982 us;
+// 128^2, 48 blocks, 2188 and 2150; 256^2, 192 blocks, 3095 and 3058).
+constexpr int kFoldBlocks = 256;
 // The IB boxes are kept eliminated (two passes over W and the symmetric owned
 // factor) where their whole rows would take at least this much; see
 // prepare_boxes.
@@ -1536,17 +1541,18 @@ class Solver final : public SolverBase {
   // Classical Gram-Schmidt twice against V[0..k) for the outer solve's long
   // vectors: h (first pass + second pass) into hcol[0..k), the partial sums of
   // |t|^2 left in opart_ for launch_scale_red.  On up to kOuterBlocks blocks:
-  // one block folds each pass's partial sums (the pass-1 dots, then
-  // the pass-2 dots) before the next kernel, so that kernel's blocks read k
-  // values instead of every block's k partials.
+  // beyond kFoldBlocks of them one block folds each pass's partial sums (the
+  // pass-1 dots, then the pass-2 dots) before the next kernel, so that kernel's
+  // blocks read k values instead of every block's k partials.
   void orthogonalise_outer(const double* V, int k, size_t n, double* t, double* hcol, int nblk, hipStream_t s) {
     double* pa = opart_.p;
     double* pb = opart_.p + kOuterPartStride;
+    const bool fold = nblk > kFoldBlocks;
     launch_dots<double>(V, k, n, t, n, pa, nblk, s);
-    launch_dots_finish(pa, k, nblk, ofold_.p, nullptr, 0, s);
-    launch_upd_dots<double>(t, V, k, n, n, ofold_.p, nblk, hcol, pb, s, 1);
-    launch_dots_finish(pb, k, nblk, ofold_.p + 72, nullptr, 0, s);
-    launch_upd_norm<double>(t, V, k, n, n, ofold_.p + 72, nblk, hcol, pa, s, 1);
+    if (fold) launch_dots_finish(pa, k, nblk, ofold_.p, nullptr, 0, s);
+    launch_upd_dots<double>(t, V, k, n, n, fold ? ofold_.p : pa, nblk, hcol, pb, s, fold ? 1 : nblk);
+    if (fold) launch_dots_finish(pb, k, nblk, ofold_.p + 72, nullptr, 0, s);
+    launch_upd_norm<double>(t, V, k, n, n, fold ? ofold_.p + 72 : pb, nblk, hcol, pa, s, fold ? 1 : nblk);
   }
 
   // w = MG(0, b) on level l (Alg. 1)
