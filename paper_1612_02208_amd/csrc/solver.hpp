@@ -21,6 +21,7 @@ struct CompFoot {             // one velocity component on one level
   DBuf<double> tval;
   DBuf<float> tvalf;          // FP32 copy for the FP32 smoother
   int max_list = 0;           // longest face -> point list
+  int max_row = 0;            // longest IB row
 };
 
 struct SolverBase {

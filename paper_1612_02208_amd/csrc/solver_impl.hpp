@@ -86,6 +86,7 @@ struct Level {
   // rows of the IB term (comp N^2 + face) and the faces' flags; ib_lanes = 0:
   // the IB term of L_IB w by interpolation, spring forces and the gather
   std::vector<int> ib_rows;
+  size_t n_ib_v = 0;            // of them component 1's (the last ones)
   int ib_lanes = 0;
   DBuf<int> d_ib_rows;
   DBuf<unsigned char> d_ib_flag;
@@ -411,6 +412,7 @@ class Solver final : public SolverBase {
     const int nn = lev.N * lev.N;
     const size_t nnz = lev.f[0].tcol.size() + lev.f[1].tcol.size();
     lev.ib_rows.clear();
+    lev.n_ib_v = 0;
     lev.ib_lanes = 0;
     // (a batch runs every member's rows in one launch, whatever their number)
     if (!defer_coarse_ && (nnz == 0 || nnz > kIbRowsMaxEntries || std::getenv("IBMG_NO_IB_ROWS"))) return;
@@ -419,6 +421,7 @@ class Solver final : public SolverBase {
       for (int q = 0; q < nn && !lev.f[c].tcol.empty(); ++q)
         if (lev.f[c].tptr[q + 1] > lev.f[c].tptr[q]) {
           lev.ib_rows.push_back(c * nn + q);
+          lev.n_ib_v += c;
           flag[q] |= (unsigned char)(1 << c);
         }
     lev.ib_lanes = nnz > (size_t)kIbLongRow * lev.ib_rows.size() ? 64 : 16;
@@ -611,7 +614,11 @@ class Solver final : public SolverBase {
         for (size_t i = 0; i < clen[t].size(); ++i) f.tptr[tasks[t].r0 + i + 1] = clen[t][i];
         f.tcol.insert(f.tcol.end(), ccols[t].begin(), ccols[t].end());
       }
-      for (size_t r = 0; r < nf; ++r) f.tptr[r + 1] += f.tptr[r];
+      f.max_row = 0;
+      for (size_t r = 0; r < nf; ++r) {
+        f.max_row = std::max(f.max_row, f.tptr[r + 1]);
+        f.tptr[r + 1] += f.tptr[r];
+      }
     });
   }
 
@@ -1024,14 +1031,18 @@ class Solver final : public SolverBase {
         CompFoot& f = lev.f[c];
         if (!f.tcol.empty()) {
           // faces of coarse levels carry thousands of points: their rows'
-          // point lists are shared out over several waves
+          // point lists are shared out over several waves, 16 points each (all
+          // levels' rebuild and solve at 256^2, five passes: 15.5 ms with slices of
+          // 64 points, 15.1 with 32, 14.9 with 16)
           const size_t nnz = f.tcol.size();
-          int nslice = std::min(32, std::max(1, f.max_list / 64));
+          int nslice = std::min(32, std::max(1, f.max_list / 16));
           while (nslice > 1 && (size_t)nslice * nnz > ((size_t)1 << 27)) nslice /= 2;   // <= 1 GiB of slices
           if (nslice > 1 && tpart_.n < (size_t)nslice * nnz) tpart_.alloc((size_t)nslice * nnz);
+          const size_t n_u = lev.ib_rows.size() - lev.n_ib_v;
           launch_t_values(fview<double>(lev.f[0]), fview<double>(lev.f[1]), lev.f[0].d_mask.p, lev.f[1].d_mask.p,
                           sview<double>(), c, lev.N, lev.cd.ibs, f.d_tptr.p, f.d_tcol.p, f.tval.p, nslice, nnz,
-                          tpart_.p, s);
+                          tpart_.p, lev.ib_lanes ? lev.d_ib_rows.p + (c ? n_u : 0) : nullptr,
+                          (int)(c ? lev.n_ib_v : n_u), f.max_row, s);
           if (std::is_same<T, float>::value)
             launch_cast<double, float>(f.tval.p, f.tvalf.p, f.tcol.size(), s);
         }
