@@ -25,7 +25,7 @@ static inline int cdiv(size_t a, int b) { return (int)((a + b - 1) / b); }
 //    first Gram-Schmidt pass (FP64, two vectors) 6.2 us against 21.5 at 64^2
 //    (128 points), 5.1 against 20.6 at 256^2 (1024 points), 18.8 against 24.9
 //    at 512^2 (8192 points).
-// 1: the nodal forces F = K' J u (k_ib_force), gathered through the face ->
+// 1: the nodal forces F = K' J u (k_spring_force), gathered through the face ->
 //    (point, slot) lists, for levels whose explicit rows are too large
 //    (kIbRowsMaxEntries).
 // The transposed form evaluates -D^T p and G^T u directly; the IB block is

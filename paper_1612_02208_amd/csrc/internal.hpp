@@ -456,10 +456,9 @@ int dots_blocks(size_t n, int cap = 256);
 template <typename T>
 void launch_upd_dots(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
                      double* hcol, double* pout, hipStream_t s, int nblk_in = 0);
-// store = false: only the partial sums of |t - V h2|^2, t left unchanged
 template <typename T>
 void launch_upd_norm(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
-                     double* hcol, double* pout, hipStream_t s, int nblk_in = 0, bool store = true);
+                     double* hcol, double* pout, hipStream_t s, int nblk_in = 0);
 template <typename T>
 struct ScaleCopies {   // also v2 = v and dst = src (v2 = null: neither)
   T* v2 = nullptr;
@@ -469,7 +468,7 @@ struct ScaleCopies {   // also v2 = v and dst = src (v2 = null: neither)
 template <typename T>
 void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, double* hout, hipStream_t s,
                       ScaleCopies<T> cp = {});
-// from those partials: t = (t - V h2) / |t - V h2| with the norm taken as
+// from partial sums of h2 = V^T t and |t|^2 (k + 1 a block): t = (t - V h2) / |t - V h2| with the norm taken as
 // sqrt(|t|^2 - |h2|^2); hcol[0..k) += h2, hcol[k] = the norm
 template <typename T>
 void launch_scale_upd(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk_in,
@@ -695,11 +694,10 @@ void launch_block_sums_b(const T* a, int N, size_t bs, double* partial, int nblk
 template <typename T>
 void launch_subtract_means_b(T* a, int N, size_t bs, const double* sums, size_t sstride, int nvel, int nsys,
                              hipStream_t s);
-// with_norm: as launch_upd_dots_n (k + 1 partials per block, |t|^2 last)
 template <typename T>
 void launch_upd_dots_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,
-                       int nblk_in = 0, bool with_norm = false);
+                       int nblk_in = 0);
 // launch_scale_upd on every active system
 template <typename T>
 void launch_scale_upd_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, size_t nmax,
@@ -708,15 +706,10 @@ void launch_scale_upd_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsy
 template <typename T>
 void launch_upd_norm_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,
-                       int nblk_in = 0, bool store = true);
+                       int nblk_in = 0);
 template <typename T>
 void launch_scale_red_b(const T* t, T* v, BSeg sg, int nsys, size_t nmax, const double* pin, int nblk,
                         size_t pstride, double* hout, size_t hstride, hipStream_t s);
-template <typename T>
-void launch_combine_ls_b(T* x, const T* Z, int k, size_t stride, BSeg sg, int nsys, size_t nmax,
-                         double* H, int ldh, size_t hstride, const double* beta, double* yout,
-                         size_t sstride, hipStream_t s, bool assign = false, const double* npart = nullptr,
-                         int nnblk = 0, size_t pstride = 0, bool pass2 = false);
 template <typename T>
 void launch_coarse_apply_batch(const double* inv, int n0, const T* r, T* z, int nsys, hipStream_t s);
 

@@ -69,14 +69,12 @@ __device__ void block_dots(const T* __restrict__ V, int k, size_t stride, const 
 }  // namespace
 
 // t -= V h (h from pass-1 partials, stored into hcol by block 0), then the
-// pass-2 partial dots of the updated t.  with_norm (k <= 8): each block's
-// partials also carry |t|^2 of the updated t after its k dots (k + 1 values
-// per block).
+// pass-2 partial dots of the updated t.
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_upd_dots(T* t, const T* __restrict__ V, int k, size_t stride,
                                                        BSeg sg, const double* __restrict__ pin, int nblk_in,
                                                        size_t pstride, double* __restrict__ hcol,
-                                                       size_t hstride, double* __restrict__ pout, bool with_norm) {
+                                                       size_t hstride, double* __restrict__ pout) {
   __shared__ double red[36];
   __shared__ double h[64];
   const int sy = blockIdx.y;
@@ -93,10 +91,9 @@ __global__ void __launch_bounds__(kThreads) k_upd_dots(T* t, const T* __restrict
     // one pass: each basis value feeds the update and then the pass-2 dot
     // of the updated entry; every thread visits its entries in the order
     // block_dots would, so the sums are those of the two-pass form
-    double acc[9];
+    double acc[8];
 #pragma unroll
-    for (int q = 0; q < 9; ++q) acc[q] = 0.0;
-    double nn = 0.0;
+    for (int q = 0; q < 8; ++q) acc[q] = 0.0;
 #pragma unroll 2
     for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
       double vq[8];
@@ -112,16 +109,8 @@ __global__ void __launch_bounds__(kThreads) k_upd_dots(T* t, const T* __restrict
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if (q < k) acc[q] += vq[q] * ti;
-      nn += ti * ti;
     }
-    if (with_norm) {
-#pragma unroll
-      for (int q = 0; q < 9; ++q)
-        if (q == k) acc[q] = nn;
-      block_sums256<9>(acc, k + 1, red, pout + (size_t)blockIdx.x * (k + 1), threadIdx.x);
-    } else {
-      block_sums256<9>(acc, k, red, pout + (size_t)blockIdx.x * k, threadIdx.x);
-    }
+    block_sums256<8>(acc, k, red, pout + (size_t)blockIdx.x * k, threadIdx.x);
     return;
   }
 #pragma unroll 4
@@ -135,14 +124,12 @@ __global__ void __launch_bounds__(kThreads) k_upd_dots(T* t, const T* __restrict
 }
 
 // t -= V h2 (h2 from pass-2 partials, added into hcol by block 0), then the
-// partial sums of |t|^2.  store = false leaves t as it was and only forms
-// the norm's partial sums (the last basis vector of a smoothing step is
-// never read: its norm alone enters the Hessenberg matrix).
+// partial sums of |t|^2.
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_upd_norm(T* t, const T* __restrict__ V, int k, size_t stride,
                                                        BSeg sg, const double* __restrict__ pin, int nblk_in,
                                                        size_t pstride, double* __restrict__ hcol,
-                                                       size_t hstride, double* __restrict__ pout, bool store) {
+                                                       size_t hstride, double* __restrict__ pout) {
   __shared__ double red[32];
   __shared__ double h[64];
   const int sy = blockIdx.y;
@@ -161,7 +148,7 @@ __global__ void __launch_bounds__(kThreads) k_upd_norm(T* t, const T* __restrict
     double a = (double)t[i];
     for (int q = 0; q < k; ++q) a -= h[q] * (double)V[(size_t)q * stride + i];
     const T tn = (T)a;
-    if (store) t[i] = tn;
+    t[i] = tn;
     acc += (double)tn * (double)tn;
   }
   const double a1[1] = {acc};
@@ -198,8 +185,8 @@ __global__ void __launch_bounds__(kThreads) k_scale_red(const T* t, T* v, BSeg s
   }
 }
 
-// The second Gram-Schmidt pass finished with the normalisation, from
-// k_upd_dots' with_norm partials (h2 = V^T t and |t|^2, k + 1 per block):
+// The second Gram-Schmidt pass finished with the normalisation, from partial
+// sums of h2 = V^T t and |t|^2 (k + 1 per block):
 // t2 = t - V h2, whose norm is sqrt(|t|^2 - |h2|^2) (t2 is orthogonal to the
 // orthonormal V), and t = t2 / |t2| (0 on an exact breakdown); block 0 adds
 // h2 into hcol[0..k) and stores |t2| into hcol[k].
@@ -231,94 +218,6 @@ __global__ void __launch_bounds__(kThreads) k_scale_upd(T* t, const T* __restric
     double a = (double)t[i];
     for (int q = 0; q < k; ++q) a -= h[q] * (double)V[(size_t)q * stride + i];
     t[i] = (T)((double)(T)a * inv);
-  }
-}
-
-// Least squares min || beta e1 - H y || ((k+1) x k Hessenberg, column-major,
-// leading dimension ldh) by Givens rotations in every block, then
-// x += sum_q y_q Z_q (assign: x = sum_q y_q Z_q, the same bits as adding to
-// a zeroed x); block 0 stores y.  npart != null: the last subdiagonal entry
-// H[k][k-1] is the square root of the nnblk partial sums there (reduced as
-// k_scale_red reduces them; block 0 stores it into H).  pass2: npart holds
-// instead k_upd_dots' with_norm partials of the last column (h2 and |t|^2,
-// k + 1 per block): the column gains h2 and its subdiagonal entry is
-// sqrt(|t|^2 - |h2|^2), as k_scale_upd forms it (H itself keeps the first
-// pass's coefficients of that column: no block writes what others read).
-template <typename T>
-__global__ void __launch_bounds__(kThreads) k_combine_ls(T* __restrict__ x, const T* __restrict__ Z, int k,
-                                                         size_t stride, BSeg sg, double* __restrict__ H,
-                                                         int ldh, size_t hstride, const double* __restrict__ beta,
-                                                         double* __restrict__ yout, size_t sstride, bool assign,
-                                                         const double* __restrict__ npart, int nnblk,
-                                                         size_t pstride, bool pass2) {
-  __shared__ double y[16];
-  __shared__ double red[32];
-  __shared__ double nrm;
-  __shared__ double h2[17];
-  const int sy = blockIdx.y;
-  if (!seg_on(sg, sy)) return;
-  const size_t o = seg_begin(sg, sy), n = seg_len(sg, sy);
-  x += o;
-  Z += o;
-  H += sy * hstride;
-  beta += sy * sstride;
-  yout += sy * sstride;
-  double hlast = 0.0;
-  if (npart && pass2) {
-    reduce_partials(npart + sy * pstride, nnblk, k + 1, h2, red);
-    double hh = 0.0;
-    for (int q = 0; q < k; ++q) hh += h2[q] * h2[q];
-    const double r2 = h2[k] - hh;
-    hlast = r2 > 0.0 ? sqrt(r2) : 0.0;
-  } else if (npart) {
-    reduce_partials(npart + sy * pstride, nnblk, 1, &nrm, red);
-    hlast = sqrt(nrm);
-    if (blockIdx.x == 0 && threadIdx.x == 0) H[k + (size_t)(k - 1) * ldh] = hlast;
-  }
-  if (threadIdx.x == 0) {
-    double R[17][16];
-    double g[17], cs[16], sn[16];
-    for (int j = 0; j < k; ++j)
-      for (int i = 0; i <= k; ++i) R[i][j] = H[i + (size_t)j * ldh];
-    if (npart && pass2)
-      for (int i = 0; i < k; ++i) R[i][k - 1] += h2[i];
-    if (npart) R[k][k - 1] = hlast;
-    for (int i = 0; i <= k; ++i) g[i] = 0.0;
-    g[0] = beta[0];
-    for (int j = 0; j < k; ++j) {
-      for (int i = 0; i < j; ++i) {
-        const double a = R[i][j], b = R[i + 1][j];
-        R[i][j] = cs[i] * a + sn[i] * b;
-        R[i + 1][j] = -sn[i] * a + cs[i] * b;
-      }
-      const double a = R[j][j], b = R[j + 1][j];
-      const double d = sqrt(a * a + b * b);
-      double c = 1.0, s = 0.0;
-      if (d != 0.0) {
-        c = a / d;
-        s = b / d;
-      }
-      cs[j] = c;
-      sn[j] = s;
-      R[j][j] = d;
-      R[j + 1][j] = 0.0;
-      const double gj = g[j];
-      g[j] = c * gj;
-      g[j + 1] = -s * gj;
-    }
-    for (int j = k - 1; j >= 0; --j) {
-      double a = g[j];
-      for (int m = j + 1; m < k; ++m) a -= R[j][m] * y[m];
-      y[j] = R[j][j] != 0.0 ? a / R[j][j] : 0.0;
-    }
-    if (blockIdx.x == 0)
-      for (int j = 0; j < k; ++j) yout[j] = y[j];
-  }
-  __syncthreads();
-  for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < n; i += (size_t)gridDim.x * kThreads) {
-    double a = assign ? 0.0 : (double)x[i];
-    for (int q = 0; q < k; ++q) a += y[q] * (double)Z[(size_t)q * stride + i];
-    x[i] = (T)a;
   }
 }
 
@@ -645,22 +544,20 @@ static int stream_blocks(size_t n) {
 template <typename T>
 void launch_upd_dots_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,
-                       int nblk_in, bool with_norm) {
+                       int nblk_in) {
   if (nsys <= 0) return;
-  if (with_norm && (k < 1 || k > 8))
-    throw Error(IBMG_ERR_ARG, "the norm-carrying second pass takes 1..8 basis vectors");
   IBMG_KLAUNCH((k_upd_dots<T>), dim3(nblk, nsys), dim3(kThreads), 0, s, t, V, k, stride, sg, pin,
-                     nblk_in > 0 ? nblk_in : nblk, pstride, hcol, hstride, pout, with_norm);
+                     nblk_in > 0 ? nblk_in : nblk, pstride, hcol, hstride, pout);
   IBMG_LAUNCH_CHECK();
 }
 
 template <typename T>
 void launch_upd_norm_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,
-                       int nblk_in, bool store) {
+                       int nblk_in) {
   if (nsys <= 0) return;
   IBMG_KLAUNCH((k_upd_norm<T>), dim3(nblk, nsys), dim3(kThreads), 0, s, t, V, k, stride, sg, pin,
-                     nblk_in > 0 ? nblk_in : nblk, pstride, hcol, hstride, pout, store);
+                     nblk_in > 0 ? nblk_in : nblk, pstride, hcol, hstride, pout);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -670,19 +567,6 @@ void launch_scale_red_b(const T* t, T* v, BSeg sg, int nsys, size_t nmax, const 
   if (nsys <= 0) return;
   IBMG_KLAUNCH((k_scale_red<T>), dim3(stream_blocks(nmax), nsys), dim3(kThreads), 0, s, t, v, sg, pin,
                      nblk, pstride, hout, hstride, ScaleCopies<T>{});
-  IBMG_LAUNCH_CHECK();
-}
-
-template <typename T>
-void launch_combine_ls_b(T* x, const T* Z, int k, size_t stride, BSeg sg, int nsys, size_t nmax,
-                         double* H, int ldh, size_t hstride, const double* beta, double* yout,
-                         size_t sstride, hipStream_t s, bool assign, const double* npart, int nnblk,
-                         size_t pstride, bool pass2) {
-  if (nsys <= 0) return;
-  if (k < 1 || k > 16 || (pass2 && !npart))
-    throw Error(IBMG_ERR_ARG, "the smoothing least squares takes 1..16 columns");
-  IBMG_KLAUNCH((k_combine_ls<T>), dim3(stream_blocks(nmax), nsys), dim3(kThreads), 0, s, x, Z, k, stride,
-                     sg, H, ldh, hstride, beta, yout, sstride, assign, npart, nnblk, pstride, pass2);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -705,8 +589,8 @@ void launch_upd_dots(T* t, const T* V, int k, size_t stride, size_t n, const dou
 
 template <typename T>
 void launch_upd_norm(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
-                     double* hcol, double* pout, hipStream_t s, int nblk_in, bool store) {
-  launch_upd_norm_b<T>(t, V, k, stride, seg1(n), 1, pin, nblk, 0, hcol, 0, pout, s, nblk_in, store);
+                     double* hcol, double* pout, hipStream_t s, int nblk_in) {
+  launch_upd_norm_b<T>(t, V, k, stride, seg1(n), 1, pin, nblk, 0, hcol, 0, pout, s, nblk_in);
 }
 
 template <typename T>
@@ -801,22 +685,19 @@ void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k
   template void launch_upd_dots<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,     \
                                    double*, hipStream_t, int);                                         \
   template void launch_upd_norm<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,     \
-                                   double*, hipStream_t, int, bool);                                   \
+                                   double*, hipStream_t, int);                                         \
   template void launch_scale_red<T>(const T*, T*, size_t, const double*, int, double*, hipStream_t,    \
                                     ScaleCopies<T>);                                                   \
   template void launch_scale_upd<T>(T*, const T*, int, size_t, size_t, const double*, int, double*,    \
                                     hipStream_t);                                                      \
   template void launch_upd_dots_b<T>(T*, const T*, int, size_t, BSeg, int, const double*, int, size_t, \
-                                     double*, size_t, double*, hipStream_t, int, bool);                \
+                                     double*, size_t, double*, hipStream_t, int);                      \
   template void launch_scale_upd_b<T>(T*, const T*, int, size_t, BSeg, int, size_t, const double*, int, \
                                       size_t, double*, size_t, hipStream_t);                           \
   template void launch_upd_norm_b<T>(T*, const T*, int, size_t, BSeg, int, const double*, int, size_t, \
-                                     double*, size_t, double*, hipStream_t, int, bool);                \
+                                     double*, size_t, double*, hipStream_t, int);                      \
   template void launch_scale_red_b<T>(const T*, T*, BSeg, int, size_t, const double*, int, size_t,     \
-                                      double*, size_t, hipStream_t);                                   \
-  template void launch_combine_ls_b<T>(T*, const T*, int, size_t, BSeg, int, size_t, double*, int,     \
-                                       size_t, const double*, double*, size_t, hipStream_t, bool,      \
-                                       const double*, int, size_t, bool);
+                                      double*, size_t, hipStream_t);
 
 IBMG_INST_KRY(double)
 IBMG_INST_KRY(float)
