@@ -1031,9 +1031,9 @@ class Solver final : public SolverBase {
         CompFoot& f = lev.f[c];
         if (!f.tcol.empty()) {
           // faces of coarse levels carry thousands of points: their rows'
-          // point lists are shared out over several waves, 16 points each (all
-          // levels' rebuild and solve at 256^2, five passes: 15.5 ms with slices of
-          // 64 points, 15.1 with 32, 14.9 with 16)
+          // point lists are shared out over several waves, 16 points each (a
+          // gradient at 256^2, two solves and a rebuild: 15.5 ms with slices of 64
+          // points, 15.1 with 32, 14.9 with 16)
           const size_t nnz = f.tcol.size();
           int nslice = std::min(32, std::max(1, f.max_list / 16));
           while (nslice > 1 && (size_t)nslice * nnz > ((size_t)1 << 27)) nslice /= 2;   // <= 1 GiB of slices
