@@ -356,16 +356,17 @@ class BatchSolver final : public BatchBase {
 
   // Sec. 3.3 smoothing on every active system of level l: w <- w + e, e from
   // nu FGMRES iterations on L e = b - L w, on the unnormalised basis of the
-  // single-system form and with its launches; crs: also the restriction of the
-  // new residual to the next coarser level (from w = 0).
-  void smooth(int l, T* w, const T* b, int nu, T* crs, hipStream_t s) {
+  // single-system form and with its launches.  With w_zero, w is not read; crs
+  // (w_zero only): also the restriction of the new residual to the next coarser
+  // level, by the Arnoldi relation.
+  void smooth(int l, T* w, const T* b, int nu, bool w_zero, T* crs, hipStream_t s) {
     BLevel& L = lv_[l];
     const size_t n = L.n, bn = (size_t)L.nact * n, pn = (size_t)L.nact * L.pst;
     const Many m = many(L);
     const FootView<T> none{};
     T* V = L.V.p;
     const T* u0 = b;
-    if (!crs) {
+    if (!w_zero) {
       launch_apply<T>(w, V, b, nullptr, L.rows, none, none, L.N, 0, L.c, false, s, m);
       u0 = V;
     }
@@ -382,7 +383,7 @@ class BatchSolver final : public BatchBase {
     }
     const double* pl = pu[(nu - 1) & 1];
     if (crs) launch_gs_combine_restrict<T>(w, L.Z.p, u0, V, nu, bn, L.N / 2, pl, L.scal.p, crs, s, m);
-    else launch_gs_combine<T>(w, L.Z.p, nu, bn, n, pl, L.scal.p, false, s, m);
+    else launch_gs_combine<T>(w, L.Z.p, nu, bn, n, pl, L.scal.p, w_zero, s, m);
   }
 
   // Alg. 1 on every system: r and z are ragged batch vectors (FP64).
@@ -391,14 +392,21 @@ class BatchSolver final : public BatchBase {
       BLevel& L = lv_[l];
       const int p0 = nact_[l + 1], p1 = nact_[l];
       if (p1 > p0) launch_cast<double, T>(r + off_[p0], L.b.p + (size_t)p0 * L.n, (size_t)(p1 - p0) * L.n, s);
-      smooth(l, L.w.p, L.b.p, nu1_, lv_[l - 1].b.p, s);
+      BLevel& C = lv_[l - 1];
+      const bool relation = nu1_ <= kArnoldiResidualNu;
+      smooth(l, L.w.p, L.b.p, nu1_, true, relation ? C.b.p : nullptr, s);
+      if (!relation) {
+        const FootView<T> none{};
+        launch_apply<T>(L.w.p, L.r.p, L.b.p, nullptr, L.rows, none, none, L.N, 0, L.c, false, s, many(L));
+        launch_restrict<T>(L.r.p, C.b.p, C.N, s, many(L));
+      }
     }
     launch_coarse_apply_batch<T>(inv0_.p, n0_, lv_[0].b.p, lv_[0].w.p, nact_[0], s);
     for (int l = 1; l <= Lmax_; ++l) {
       BLevel& L = lv_[l];
       const int p0 = nact_[l + 1], p1 = nact_[l];
       launch_prolong_add_batch<T>(lv_[l - 1].w.p, L.w.p, lv_[l - 1].N, p1, d_act_.p, s);
-      smooth(l, L.w.p, L.b.p, nu2_, nullptr, s);
+      smooth(l, L.w.p, L.b.p, nu2_, false, nullptr, s);
       if (p1 > p0) launch_cast<T, double>(L.w.p + (size_t)p0 * L.n, z + off_[p0], (size_t)(p1 - p0) * L.n, s);
     }
   }

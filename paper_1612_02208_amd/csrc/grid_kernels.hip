@@ -425,7 +425,10 @@ void launch_ib_rows(const T* x, T* y, const int* rows, const int* ptr, const int
 // prolongation), R_p = mean of the four fine cells.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc) {
+__global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc, Many m) {
+  if (m.act && !m.act[blockIdx.z]) return;
+  f += blockIdx.z * m.bs;
+  cz += blockIdx.z * (m.bs / 4);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y * blockDim.y + threadIdx.y;
   if (i >= Nc || j >= Nc) return;
@@ -435,10 +438,11 @@ __global__ void k_restrict(const T* __restrict__ f, T* __restrict__ cz, int Nc) 
 }
 
 template <typename T>
-void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s) {
+void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s, Many m) {
+  if (m.nsys <= 0) return;
   dim3 blk(64, 4);
-  dim3 grd((Nc + 63) / 64, (Nc + 3) / 4);
-  IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc);
+  dim3 grd((Nc + 63) / 64, (Nc + 3) / 4, m.nsys);
+  IBMG_KLAUNCH((k_restrict<T>), grd, blk, 0, s, fine, coarse, Nc, m);
   IBMG_LAUNCH_CHECK();
 }
 
@@ -948,7 +952,7 @@ void launch_subtract_means(T* a, int N, const double* sums, int nvel, hipStream_
 #define IBMG_INST_GRID(T)                                                                         \
   template void launch_apply<T>(const T*, T*, const T*, const T*, IbRows<T>, FootView<T>,         \
                                 FootView<T>, int, int, StokesCoef<T>, bool, hipStream_t, Many);         \
-  template void launch_restrict<T>(const T*, T*, int, hipStream_t);                               \
+  template void launch_restrict<T>(const T*, T*, int, hipStream_t, Many);                             \
   template void launch_prolong_add<T>(const T*, T*, int, hipStream_t);                            \
   template void launch_fill<T>(T*, T, size_t, hipStream_t);                                       \
   template void launch_axpy<T>(T*, const T*, size_t, hipStream_t);                                \

@@ -411,7 +411,7 @@ void launch_apply_dots(const T* w, T* y, const T* F, IbRows<T> R, FootView<T> fx
 // of `lanes` lanes each (0: none), at most cap of them for the rows (0: 1024)
 int apply_blocks(int N, int nrows, int lanes, int cap = 0);
 template <typename T>
-void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s);
+void launch_restrict(const T* fine, T* coarse, int Nc, hipStream_t s, Many m = {});
 template <typename T>
 void launch_prolong_add(const T* coarse, T* fine, int Nc, hipStream_t s);
 template <typename Ts, typename Td>

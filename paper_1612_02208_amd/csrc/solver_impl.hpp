@@ -45,6 +45,14 @@ constexpr int kFoldBlocks = 256;
 // factor) where their whole rows would take at least this much; see
 // prepare_boxes.
 constexpr size_t kElimMinBytes = (size_t)192 << 20;
+// Pre-smoothing steps up to which the V-cycle takes the residual it restricts
+// from the Arnoldi relation, without an operator application.  That residual
+// leaves out what rounding did to L z_q and to w, which grows with the basis:
+// 128^2 membrane, kappa = 1e6, FP32 smoother, error of a V-cycle against FP64
+// (geometric mean over 40 right-hand sides), Arnoldi relation and b - L w: 1.5e-7
+// and 1.5e-7 at two iterations, 2.4e-7 and 2.0e-7 at three, 5.2e-7 and 3.3e-7 at
+// four, 3.5e-6 and 5.0e-7 at six, 1.3e-4 and 5.1e-6 at seven.
+constexpr int kArnoldiResidualNu = 2;
 // lanes per explicit row: a wave where rows are long (crowded coarse levels)
 constexpr int kIbLongRow = 96;
 // partial-sum buffers: two of kPartStride doubles (blocks x vectors)
@@ -1553,8 +1561,9 @@ class Solver final : public SolverBase {
   // w <- w + e, e = nu FGMRES iterations (classical Gram-Schmidt twice) on
   // L e = b - L w from e = 0, on an unnormalised basis (krylov_kernels.hip).
   // With w_zero, w is not read (the result is stored into it); crs != null
-  // (w_zero only) also leaves the restriction of b - L w there, and the return
-  // value says whether it did (the Richardson steps do not).
+  // (w_zero only) also leaves the restriction of b - L w there, by the Arnoldi
+  // relation, and the return value says whether it did (the Richardson steps do
+  // not).
   bool smooth_t(int l, T* w, const T* b, int nu, bool w_zero, hipStream_t s, T* crs = nullptr) {
     Level<T>& lev = levels_[l];
     const size_t n = 3 * (size_t)lev.N * lev.N;
@@ -1621,7 +1630,7 @@ class Solver final : public SolverBase {
     }
     Level<T>& lev = levels_[l];
     Level<T>& crs = levels_[l - 1];
-    if (!smooth_t(l, w, b, d_.nu1, true, s, crs.b.p)) {
+    if (!smooth_t(l, w, b, d_.nu1, true, s, d_.nu1 <= kArnoldiResidualNu ? crs.b.p : nullptr)) {
       op<T>(l, w, lev.r.p, b, false, lev.F.p, s);
       launch_restrict<T>(lev.r.p, crs.b.p, crs.N, s);
     }
