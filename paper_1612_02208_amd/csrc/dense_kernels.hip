@@ -188,63 +188,69 @@ struct Mfma<float> {
 // cells) through the rows that n does not reach and ends with those it does
 // (coupled velocities, then the cells beside one).  Every prefix of these orders
 // holds, with each of its cells, faces that lead out of the set of those cells,
-// so the pressure pivots stay definite as in the velocities-first order; the
-// result's error against refined solves is the same (FP64 on boxes of the 512^2
-// annulus and 256^2 membranes: 7e-16 to 7e-15 here, 1e-15 to 7e-15 there).  A 16
+// so the pressure pivots stay definite as in the velocities-first order.  A 16
 // x 16/4 box takes 0.75 GFLOP (1.4 where the structure runs along its edge)
 // instead of 3.4, the whole inverse's 5.8.
+// Stiff structures leave D with rigid and soft directions side by side, so D^{-1}
+// is never applied as a matrix: with D = L D_1 L^T (D_1 diagonal) and Y = S_:K L^{-T},
+//   S_IJ <- S_IJ - Y_I D_1^{-1} Y_J^T,   S_IK <- E_I = Y_I D_1^{-1} L^{-1}.
 // Step K, five launches over every matrix:
-//   diag       (a work-group per matrix): D^{-1} in LDS (128 x 128, the
-//              160 KB of gfx950), to dinv;
+//   pivot      (a work-group per matrix): L and D_1;
 //   panel read (64-row tiles): which tiles of C = S_:K are not zero, and those
 //              above K, stored in K's tile rows, turned round;
-//   scale      (64-row tiles x two column halves): E = C D^{-1};
-//   update     (kept 64 x 64 tiles outside K): S_IJ <- S_IJ - E_I C_J^T;
+//   scale      (64-row tiles): Y and E by substitution in 16-column blocks, and
+//              E_K = D^{-1};
+//   update     (kept 64 x 64 tiles outside K): S_IJ <- S_IJ - Y_I D_1^{-1} Y_J^T;
 //   panel write: S_IK <- E_I below K, S_KI <- E_I^T above it, S_KK <- -D^{-1}.
 // The last block may be narrower (w < 128 columns): D is padded with the
 // identity, and the panel columns beyond w are zero, so they change nothing.
 // Loads run unconditionally from clamped indices and what lies outside is
 // selected away or never stored: a load under a lane condition makes the
 // compiler wait for each one in turn (that alone cost the update kernel 2.5x).
-// The scale and update products are 64 x 64 tiles with a 128-long reduction
-// on the FP64 matrix cores (16x16x4 MFMA, four waves of 2 x 2 tiles): twice
-// the flops per pass over the kept tiles of 64-column steps.
+// All products run on the FP64 matrix cores (16x16x4 MFMA).
 constexpr int GJ_NB = kGjNb;   // 128
 static_assert(GJ_NB == 128, "the sweep kernels are written for 128-column blocks of two 64-wide tiles");
 
-// In-place Gauss-Jordan step K of a 16 x 16 matrix in one wave's accumulator
-// layout (d[v]: row kq + 4 v, column ln).
+// Step K of a 16 x 16 L D L^T factorisation without pivoting, in one wave's
+// accumulator layout (d[v]: row kq + 4 v, column ln): rows below K are reduced by
+// row K, and L^{-1} grows in place of the zeros (d = D on the diagonal).
 template <int K>
-__device__ __forceinline__ void gj16_step(Mfma<double>::acc_t& d, int kq, int ln) {
+__device__ __forceinline__ void ldl16_step(Mfma<double>::acc_t& d, int kq, int ln) {
   const double rk = __shfl(d[K >> 2], (K & 3) * 16 + ln, 64);   // row K at this lane's column
   const double ip = 1.0 / dpp_move<0x150 + K>(rk);              // row_newbcast: lane K of the row of 16
-  const double rip = rk * ip;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const double ck = dpp_move<0x150 + K>(d[v]);   // column K at this lane's row
-    const bool row = v == (K >> 2) && kq == (K & 3);
-    const double off = row ? rip : d[v] - ck * rip;
-    const double col = row ? ip : -ck * ip;
-    d[v] = ln == K ? col : off;
+    const double l = dpp_move<0x150 + K>(d[v]) * ip;   // column K at this lane's row
+    const double x = ln == K ? -l : d[v] - l * rk;
+    d[v] = Mfma<double>::row(kq, v) > K ? x : d[v];
   }
 }
 
-// D^{-1} of the 128 x 128 pivot block, one work-group of 1024 threads per matrix:
-// block sweeps of 16, wave w holding tiles (w / 2, 4 (w mod 2) + t), t < 4, of D
-// in MFMA accumulators.  Per step the wave with the diagonal tile inverts it in
-// registers (DPP and shuffles, no barrier), E = C T^{-1} and the update D -=
-// E C^T run on the matrix cores: 16 barriers in all.  Bound by the eight 16-step
-// chains of divisions.  One pivot per barrier, as scalar Gauss-Jordan through
-// LDS, took 188 us a block (295 us for 300 matrices); this 45 (69) us.
-__global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mats, int n, int kb, int w,
-                                                  double* __restrict__ dinv_all) {
-  constexpr int LD = 18;   // row stride in LDS: operand reads of 16 rows without bank conflicts
-  __shared__ double Cs[2][GJ_NB * LD];
-  __shared__ double Es[GJ_NB * LD];
-  __shared__ double Ts[2][16 * LD];
+// L D L^T of the 128 x 128 pivot block without pivoting, one work-group of 1024
+// threads per matrix, 16 columns at a time; wave w holds tiles (w / 2, 4 (w mod 2)
+// + t), t < 4, in MFMA accumulators, of which those on or right of the diagonal
+// count.  Per step the wave with the diagonal tile factorises it in registers (DPP
+// and shuffles, no barrier), and P = L_kk^{-1} S_k: and the update S_ij -= P_i^T
+// D^{-1} P_j run on the matrix cores: two barriers a step.  Bound by the eight
+// chains of 15 divisions: 59 us for 300 boxes.  Out: piv holds L below its 16 x 16 diagonal blocks,
+// which are L_kk^{-1} (row-major, 128 wide; nothing above them), then 1 / D.
+// (The inverses of the 16 x 16 tiles themselves in place of the factors, which
+// are as ill-conditioned as the block, cost all digits on stiff structures: thin
+// membrane at 256^2, 16 x 16/4 boxes, kappa = 2.6e8, mu = 0.01: a sweep's error
+// 2.5e-2.)
+__global__ void __launch_bounds__(1024) k_sw_pivot(const double* __restrict__ mats, int n, int kb, int w,
+                                                   double* __restrict__ piv_all) {
+  constexpr int LD = 18;            // row stride in LDS: operand reads of 16 rows without bank conflicts
+  constexpr int LP = GJ_NB + 2;
+  __shared__ double Rs[16 * LP], Ps[16 * LP];
+  __shared__ double Ls[2][16 * LD];
+  __shared__ double ri[GJ_NB];
   const double* A = mats + (size_t)blockIdx.x * n * n;
-  double* Di = dinv_all + (size_t)blockIdx.x * GJ_NB * GJ_NB;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kq = lane >> 4, ln = lane & 15;
+  double* Pv = piv_all + (size_t)blockIdx.x * kGjPivot;
+  // (the wave's number as a scalar: a branch on it is then a branch, and no exec
+  // mask changes while products are in flight)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, kq = lane >> 4, ln = lane & 15;
   const int rt = wave >> 1, c0 = 4 * (wave & 1);
   // the padding of a narrow last block is the identity, so the pivots stay
   // nonzero; the padded rows and columns never reach the matrix.  Above the
@@ -262,82 +268,73 @@ __global__ void __launch_bounds__(1024) k_gj_diag(const double* __restrict__ mat
       d[t][v] = a < w && b < w ? x : (a == b ? 1.0 : 0.0);
     }
   for (int kk = 0; kk < GJ_NB / 16; ++kk) {
-    double* C = Cs[kk & 1];
-    double* T = Ts[kk & 1];
-    const bool mine = (kk >> 2) == (wave & 1);   // this wave holds tile (rt, kk)
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      if (mine && t == (kk & 3)) {
-        if (rt == kk) {
-          Mfma<double>::acc_t x = d[t];
-          gj16_step<0>(x, kq, ln);
-          gj16_step<1>(x, kq, ln);
-          gj16_step<2>(x, kq, ln);
-          gj16_step<3>(x, kq, ln);
-          gj16_step<4>(x, kq, ln);
-          gj16_step<5>(x, kq, ln);
-          gj16_step<6>(x, kq, ln);
-          gj16_step<7>(x, kq, ln);
-          gj16_step<8>(x, kq, ln);
-          gj16_step<9>(x, kq, ln);
-          gj16_step<10>(x, kq, ln);
-          gj16_step<11>(x, kq, ln);
-          gj16_step<12>(x, kq, ln);
-          gj16_step<13>(x, kq, ln);
-          gj16_step<14>(x, kq, ln);
-          gj16_step<15>(x, kq, ln);
-          // the lower triangle, mirrored: the sweeps rely on T's symmetry, and
-          // its rounding errors off it would grow
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const int i = Mfma<double>::row(kq, v);
-            if (ln <= i) {
-              T[i * LD + ln] = x[v];
-              T[ln * LD + i] = x[v];
-            }
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) C[(16 * rt + Mfma<double>::row(kq, v)) * LD + ln] = d[t][v];
-      }
-    __syncthreads();
-    if (wave < 8) {   // E for row tile `wave`
-      Mfma<double>::acc_t e = {0, 0, 0, 0};
-#pragma unroll
-      for (int st = 0; st < 4; ++st)
-        e = Mfma<double>::mma(C[(16 * wave + ln) * LD + 4 * st + kq], T[(4 * st + kq) * LD + ln], e);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Es[(16 * wave + Mfma<double>::row(kq, v)) * LD + ln] = e[v];
-    }
-    __syncthreads();
-    // C, E and T of this step are next written two barriers (E: one) later,
-    // after every wave has passed the reads below
-    double ea[4];
-#pragma unroll
-    for (int st = 0; st < 4; ++st) ea[st] = -Es[(16 * rt + ln) * LD + 4 * st + kq];
+    double* L = Ls[kk & 1];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int ct = c0 + t;
-      if (rt == kk) {
+      if (rt != kk) continue;
+      if (c0 + t > kk) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Rs[Mfma<double>::row(kq, v) * LP + 16 * (c0 + t) + ln] = d[t][v];
+      } else if (c0 + t == kk) {
+        Mfma<double>::acc_t x = d[t];
+        ldl16_step<0>(x, kq, ln);
+        ldl16_step<1>(x, kq, ln);
+        ldl16_step<2>(x, kq, ln);
+        ldl16_step<3>(x, kq, ln);
+        ldl16_step<4>(x, kq, ln);
+        ldl16_step<5>(x, kq, ln);
+        ldl16_step<6>(x, kq, ln);
+        ldl16_step<7>(x, kq, ln);
+        ldl16_step<8>(x, kq, ln);
+        ldl16_step<9>(x, kq, ln);
+        ldl16_step<10>(x, kq, ln);
+        ldl16_step<11>(x, kq, ln);
+        ldl16_step<12>(x, kq, ln);
+        ldl16_step<13>(x, kq, ln);
+        ldl16_step<14>(x, kq, ln);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int i = Mfma<double>::row(kq, v);
-          d[t][v] = ct == kk ? -T[i * LD + ln] : Es[(16 * ct + ln) * LD + i];
+          const double l = ln < i ? x[v] : (ln == i ? 1.0 : 0.0);
+          L[i * LD + ln] = l;
+          Pv[(size_t)(16 * kk + i) * GJ_NB + 16 * kk + ln] = l;
+          if (ln == i) ri[16 * kk + i] = 1.0 / x[v];
         }
-      } else if (ct == kk) {
+      }
+    }
+    __syncthreads();
+    if (wave < GJ_NB / 16 && wave > kk) {   // P for column tile `wave`
+      Mfma<double>::acc_t p = {0, 0, 0, 0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) d[t][v] = Es[(16 * rt + Mfma<double>::row(kq, v)) * LD + ln];
-      } else {
+      for (int st = 0; st < 4; ++st)
+        p = Mfma<double>::mma(L[ln * LD + 4 * st + kq], Rs[(4 * st + kq) * LP + 16 * wave + ln], p);
 #pragma unroll
-        for (int st = 0; st < 4; ++st) d[t] = Mfma<double>::mma(ea[st], C[(16 * ct + ln) * LD + 4 * st + kq], d[t]);
+      for (int v = 0; v < 4; ++v) Ps[Mfma<double>::row(kq, v) * LP + 16 * wave + ln] = p[v];
+    }
+    __syncthreads();
+    // R is next written after this barrier, P after the next one; L alternates
+    if (wave < GJ_NB / 16 && wave > kk) {   // L's tile (wave, kk) = (D^{-1} P)^T
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = 16 * wave + (lane >> 4) + 4 * q;
+        Pv[(size_t)i * GJ_NB + 16 * kk + ln] = Ps[ln * LP + i] * ri[16 * kk + ln];
+      }
+    }
+    if (rt > kk) {
+      double a[4];
+#pragma unroll
+      for (int st = 0; st < 4; ++st)
+        a[st] = -Ps[(4 * st + kq) * LP + 16 * rt + ln] * ri[16 * kk + 4 * st + kq];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        if (c0 + t < rt) continue;
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+          d[t] = Mfma<double>::mma(a[st], Ps[(4 * st + kq) * LP + 16 * (c0 + t) + ln], d[t]);
       }
     }
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      Di[(size_t)(16 * rt + Mfma<double>::row(kq, v)) * GJ_NB + 16 * (c0 + t) + ln] = -d[t][v];
+  if (tid < GJ_NB) Pv[(size_t)GJ_NB * GJ_NB + tid] = ri[tid];   // (written before the last barriers)
 }
 
 struct GjTileSmem {
@@ -345,77 +342,16 @@ struct GjTileSmem {
   double Ys[32][65];   // [reduction index of the chunk][column]
 };
 
-// acc = X Y for the wave's 32 x 32 quarter of a 64 x 64 tile: X is a row-major
-// block of 64 rows with row stride ldx (rows from xrows on repeat the last:
-// their results are not used; columns from xcols on read as zero), Y the columns
-// J0 .. J0+63 of a GJ_NB x GJ_NB row-major array; the reduction runs in chunks of
-// 32 through LDS, the next chunk's values loading into registers during the
-// current chunk's MFMA steps.
-__device__ __forceinline__ void gj_tile_product(GjTileSmem& sm, Mfma<double>::acc_t acc[2][2],
-                                                const double* __restrict__ X, size_t ldx, int xrows, int xcols,
-                                                const double* __restrict__ Y, int J0) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = Mfma<double>::acc_t{0, 0, 0, 0};
-  double xr[8], yr[8];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int t = tid + 256 * q;
-      const int row = t >> 5, k = k0 + (t & 31);
-      xr[q] = X[(size_t)(row < xrows ? row : xrows - 1) * ldx + (k < xcols ? k : xcols - 1)];
-      xr[q] = k < xcols ? xr[q] : 0.0;
-      yr[q] = Y[(size_t)(k0 + (t >> 6)) * GJ_NB + J0 + (t & 63)];
-    }
-  };
-  load(0);
-#pragma unroll
-  for (int k0 = 0; k0 < GJ_NB; k0 += 32) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int t = tid + 256 * q;
-      sm.Xs[t & 31][t >> 5] = xr[q];
-      sm.Ys[t >> 6][t & 63] = yr[q];
-    }
-    __syncthreads();
-    if (k0 + 32 < GJ_NB) load(k0 + 32);
-#pragma unroll
-    for (int st = 0; st < 8; ++st) {
-      const int kk = 4 * st + kq;
-      const double a0 = sm.Xs[kk][32 * wr + ln], a1 = sm.Xs[kk][32 * wr + 16 + ln];
-      const double b0 = sm.Ys[kk][32 * wc + ln], b1 = sm.Ys[kk][32 * wc + 16 + ln];
-      acc[0][0] = Mfma<double>::mma(a0, b0, acc[0][0]);
-      acc[0][1] = Mfma<double>::mma(a0, b1, acc[0][1]);
-      acc[1][0] = Mfma<double>::mma(a1, b0, acc[1][0]);
-      acc[1][1] = Mfma<double>::mma(a1, b1, acc[1][1]);
-    }
-    __syncthreads();
-  }
-}
-
-// C_I = S_IK of a 64-row tile I outside K: below K the tiles themselves, above it
-// the copy that k_sw_panel_read makes (row stride 128).
-struct SwPanel {
-  const double* p;
-  size_t ld;
-};
-__device__ __forceinline__ SwPanel sw_panel(const double* A, const double* C, int n, int kb, int Ke, int I) {
-  return I >= Ke ? SwPanel{A + (size_t)I * 64 * n + kb, (size_t)n} : SwPanel{C + (size_t)I * 64 * GJ_NB, GJ_NB};
-}
-
 // flags[I]: whether tile I of S_:K outside K has a nonzero (a NaN counts); above K
 // (S_I,Kh = S_Kh,I^T from tile row Kh) the nonzero tiles are turned round into C,
-// n x 128, one 64-column half at a time.
+// n x 128 (row stride 128), one 64-column half at a time.
 __global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict__ mats, int n, int kb, int w, int lo,
                                                        double* __restrict__ work, int* __restrict__ flags) {
   __shared__ double Ts[64][65];   // [row of the tile][column of the half]
   const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
   if (I >= K0 && I < Ke) return;
   const double* A = mats + (size_t)blockIdx.y * n * n;
-  double* C = work + (size_t)blockIdx.y * 2 * n * GJ_NB;
+  double* C = work + (size_t)blockIdx.y * sweep_panels(n);
   int* flag = flags + (size_t)blockIdx.y * ((n + 63) / 64) + I;
   const int tid = threadIdx.x;
   int any = 0;
@@ -457,48 +393,165 @@ __global__ void __launch_bounds__(256) k_sw_panel_read(const double* __restrict_
   }
 }
 
-// E_I (columns 64 h .. 64 h + 63) = C_I D^{-1} for one 64-row tile I = lo +
-// blockIdx.x outside K (tiles K0 .. Ke - 1) that is not zero
-__global__ void __launch_bounds__(256) k_sw_scale(const double* __restrict__ mats, const double* __restrict__ dinv_all,
-                                                  int n, int kb, int w, int lo, double* __restrict__ work,
-                                                  const int* __restrict__ flags) {
-  const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64, h = blockIdx.z;
-  if ((I >= K0 && I < Ke) || !flags[(size_t)blockIdx.y * ((n + 63) / 64) + I]) return;   // E_K is not used
-  __shared__ GjTileSmem sm;
-  const double* C = work + (size_t)blockIdx.y * 2 * n * GJ_NB;
-  double* E = work + (size_t)blockIdx.y * 2 * n * GJ_NB + (size_t)n * GJ_NB;
-  const double* Di = dinv_all + (size_t)blockIdx.y * GJ_NB * GJ_NB;
-  const int rows = n - I0 < 64 ? n - I0 : 64;
-  const SwPanel c = sw_panel(mats + (size_t)blockIdx.y * n * n, C, n, kb, Ke, I);
-  Mfma<double>::acc_t acc[2][2];
-  gj_tile_product(sm, acc, c.p, c.ld, rows, w, Di, 64 * h);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;
+// Lanes of a wave exchange a 16 x 16 tile through LDS: from the accumulator layout
+// to the MFMA's A operand (a[st]: row ln, column 4 st + kq).
+__device__ __forceinline__ void tile_to_a(double* xs, const Mfma<double>::acc_t& x, double (&a)[4], int kq, int ln) {
+  constexpr int LD = 18;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int v = 0; v < 4; ++v) xs[Mfma<double>::row(kq, v) * LD + ln] = x[v];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = 32 * wr + 16 * a + Mfma<double>::row(kq, v);
-        if (row < rows) E[(size_t)(I0 + row) * GJ_NB + 64 * h + 32 * wc + 16 * b + ln] = acc[a][b][v];
-      }
+  for (int st = 0; st < 4; ++st) a[st] = xs[ln * LD + 4 * st + kq];
 }
 
-// S_IJ <- S_IJ - E_I C_J^T over the kept tiles I >= J >= lo outside K (tiles K0
+// row of entry t of a lower triangle stored row by row
+__host__ __device__ constexpr int tri_row(int t) {
+  int j = 0;
+  while ((j + 1) * (j + 2) / 2 <= t) ++j;
+  return j;
+}
+
+// Every 64-row tile I >= lo that is not zero: Y_I = C_I L^{-T} (to Yw), and for I
+// >= re also E_I = Y_I D^{-1} L^{-1} (in place of C), by substitution in 16-column
+// blocks on the matrix cores, with S_KK = L D L^T from k_sw_pivot (L^{-1} of the 16 x
+// 16 diagonal blocks only).  A tile of K itself (I >= re) takes the identity for C
+// and so gets E_K = S_KK^{-1}.  L's 36 blocks lie in LDS (83 KB); a wave takes 16 rows
+// at a time, whose Y and E blocks stay in registers.  Bound by each wave's chain of
+// products through LDS, so a work-group (one fits a CU; gpm per matrix, on one XCD)
+// has eight waves, which share out the matrix's rows: 121 us a step on average over
+// the sweeps of a 512^2 annulus's rebuild (299 with a work-group of four waves per
+// tile, 220 with the loads of C under conditions).
+constexpr int kSwMaxTiles = 1024;   // most 64-row tiles of a swept matrix
+__global__ void __launch_bounds__(512) k_sw_scale(const double* __restrict__ mats, const double* __restrict__ piv_all,
+                                                  int n, int kb, int w, int lo, int re, int gpm, int count,
+                                                  double* __restrict__ work, const int* __restrict__ flags) {
+  constexpr int NB = GJ_NB / 16, LD = 18;
+  __shared__ double Lb[NB * (NB + 1) / 2][16 * LD];   // block (j, k), k <= j, at j (j + 1) / 2 + k
+  __shared__ double xs[8][16 * LD];
+  __shared__ double ri[GJ_NB];
+  __shared__ unsigned short act[kSwMaxTiles];
+  __shared__ int nact;
+  const int slot = blockIdx.x >> 3, mat = (slot / gpm) * 8 + (blockIdx.x & 7), first = slot % gpm;
+  if (mat >= count) return;
+  // (the wave's number as a scalar: a branch on it is then a branch, and no exec
+  // mask changes while products are in flight)
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63, kq = lane >> 4, ln = lane & 15;
+  const int T = (n + 63) / 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
+  const double* Pv = piv_all + (size_t)mat * kGjPivot;
+  {
+    double l[NB * (NB + 1) / 4];   // half of the threads a block each
+    const int i = (tid >> 4) & 15, c = tid & 15, half = wave >> 2;
+#pragma unroll
+    for (int u = 0; u < NB * (NB + 1) / 4; ++u) {
+      const int j = half ? tri_row(2 * u + 1) : tri_row(2 * u), k = 2 * u + half - j * (j + 1) / 2;
+      l[u] = Pv[(size_t)(16 * j + i) * GJ_NB + 16 * k + c];
+    }
+#pragma unroll
+    for (int u = 0; u < NB * (NB + 1) / 4; ++u) Lb[2 * u + half][i * LD + c] = l[u];
+  }
+  if (tid < GJ_NB) ri[tid] = Pv[(size_t)GJ_NB * GJ_NB + tid];
+  if (wave == 7) {   // the tiles to do, in order
+    int c = 0;
+    for (int i0 = lo; i0 < T; i0 += 64) {
+      const int I = i0 + lane;
+      const bool on = I < T && (I >= K0 && I < Ke ? I >= re : flags[(size_t)mat * T + I] != 0);
+      const unsigned long long m = __ballot(on);
+      if (on) act[c + __popcll(m & ((1ull << lane) - 1))] = (unsigned short)I;
+      c += __popcll(m);
+    }
+    if (lane == 0) nact = c;
+  }
+  __syncthreads();
+  double* C = work + (size_t)mat * sweep_panels(n);
+  double* Y = C + sweep_panels(n) / 2;
+  const double* A = mats + (size_t)mat * n * n;
+  const int q1 = __builtin_amdgcn_readfirstlane(4 * nact);
+  for (int q = first * 8 + wave; q < q1; q += 8 * gpm) {
+    const int I = __builtin_amdgcn_readfirstlane(act[q >> 2]), r0 = 64 * I + 16 * (q & 3);   // the wave's rows r0 ..
+    const bool in_k = I >= K0 && I < Ke;
+    if (r0 >= n) continue;
+    // C in accumulator layout
+    Mfma<double>::acc_t y[NB];
+    if (in_k) {
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[j][v] = r0 + Mfma<double>::row(kq, v) - kb == 16 * j + ln ? 1.0 : 0.0;
+    } else {
+      const double* c = I >= Ke ? A + kb : C;
+      const size_t ld = I >= Ke ? n : GJ_NB;
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = r0 + Mfma<double>::row(kq, v), k = 16 * j + ln;
+          y[j][v] = c[(size_t)(r < n ? r : n - 1) * ld + (k < w ? k : w - 1)];
+        }
+      if (w < GJ_NB)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[j][v] = 16 * j + ln < w ? y[j][v] : 0.0;
+    }
+    double a[NB][4];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      Mfma<double>::acc_t x = y[j];
+#pragma unroll
+      for (int k = 0; k < j; ++k)
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+          x = Mfma<double>::mma(a[k][st], Lb[j * (j + 1) / 2 + k][ln * LD + 4 * st + kq], x);
+      double t[4];
+      tile_to_a(xs[wave], x, t, kq, ln);
+      x = Mfma<double>::acc_t{0, 0, 0, 0};
+#pragma unroll
+      for (int st = 0; st < 4; ++st) x = Mfma<double>::mma(t[st], Lb[j * (j + 1) / 2 + j][ln * LD + 4 * st + kq], x);
+      y[j] = x;
+      // (the panels have whole blocks of 16 rows, so no store needs a condition)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Y[(size_t)(r0 + Mfma<double>::row(kq, v)) * GJ_NB + 16 * j + ln] = x[v];
+      x = -x;   // (the next blocks subtract)
+      tile_to_a(xs[wave], x, a[j], kq, ln);
+    }
+    if (I < re) continue;
+#pragma unroll
+    for (int k = NB - 1; k >= 0; --k) {
+      Mfma<double>::acc_t x = y[k] * ri[16 * k + ln];
+#pragma unroll
+      for (int j = NB - 1; j > k; --j)
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+          x = Mfma<double>::mma(a[j][st], Lb[j * (j + 1) / 2 + k][(4 * st + kq) * LD + ln], x);
+      double t[4];
+      tile_to_a(xs[wave], x, t, kq, ln);
+      x = Mfma<double>::acc_t{0, 0, 0, 0};
+#pragma unroll
+      for (int st = 0; st < 4; ++st) x = Mfma<double>::mma(t[st], Lb[k * (k + 1) / 2 + k][(4 * st + kq) * LD + ln], x);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) C[(size_t)(r0 + Mfma<double>::row(kq, v)) * GJ_NB + 16 * k + ln] = x[v];
+      x = -x;
+      tile_to_a(xs[wave], x, a[k], kq, ln);
+    }
+  }
+}
+
+// S_IJ <- S_IJ - Y_I D^{-1} Y_J^T over the kept tiles I >= J >= lo outside K (tiles K0
 // .. Ke - 1) whose panels are not zero, rows I >= r0 only.  gpm work-groups per
 // matrix share out the pairs of its active tiles in row order; a matrix's
 // work-groups run on one XCD (work-groups go to the eight in turn), whose L2
 // holds its panels.  Both 64 x 128 panels of a pair lie in LDS (133 of its 160
-// KB, E_I kept along a row, rows padded to 130 values so that operand reads meet
+// KB, Y_I D^{-1} kept along a row, rows padded to 130 values so that operand reads meet
 // no bank conflicts), the next pair's panels and tile load into registers during
 // the MFMA steps, and the accumulators start from the old tile.  Bound by the
 // FP64 matrix cores and the turn between pairs: 300 boxes of 55 active pairs
 // take 490 us, 35 TFLOP/s (635 us with loads under lane conditions).
-constexpr int kSwMaxTiles = 1024;   // most 64-row tiles of a swept matrix
 __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, int n, int kb, int w, int lo, int r0,
                                                    int gpm, int count, const double* __restrict__ work,
-                                                   const int* __restrict__ flags) {
+                                                   const double* __restrict__ piv_all, const int* __restrict__ flags) {
   constexpr int LD = GJ_NB + 2;
   __shared__ double Xs[64 * LD], Ys[64 * LD];
   __shared__ unsigned short act[kSwMaxTiles];
@@ -529,27 +582,17 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
   const int p1 = p + per < pa + pairs ? p + per : pa + pairs;
   if (p >= p1) return;
   double* A = mats + (size_t)mat * n * n;
-  const double* C = work + (size_t)mat * 2 * n * GJ_NB;
-  const double* Ew = C + (size_t)n * GJ_NB;
+  const double* Yw = work + (size_t)mat * sweep_panels(n) + sweep_panels(n) / 2;
   const int wr = wave & 1, wc = wave >> 1, kq = lane >> 4, ln = lane & 15;   // rows 32 wr, columns 16 wc
   const int lr = tid >> 7, lk = tid & 127;   // panel loads: rows lr + 4 q, column lk
+  const double md = -piv_all[(size_t)mat * kGjPivot + GJ_NB * GJ_NB + lk];   // -1 / D
   double xr[16], yr[16], old[2][4];
-  auto load_e = [&](int I) {
-    const double* E = Ew + (size_t)I * 64 * GJ_NB;
+  auto load_y = [&](int I, double (&y)[16]) {
+    const double* Y = Yw + (size_t)I * 64 * GJ_NB;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int a = lr + 4 * q;
-      xr[q] = E[(size_t)(I * 64 + a < n ? a : n - 1 - I * 64) * GJ_NB + lk];
-    }
-  };
-  auto load_c = [&](int J) {
-    // (columns from w on meet the zeros of E)
-    const SwPanel c = sw_panel(A, C, n, kb, Ke, J);
-    const int k = lk < w ? lk : w - 1;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int a = lr + 4 * q;
-      yr[q] = c.p[(size_t)(J * 64 + a < n ? a : n - 1 - J * 64) * c.ld + k];
+      y[q] = Y[(size_t)(I * 64 + a < n ? a : n - 1 - I * 64) * GJ_NB + lk];
     }
   };
   auto load_old = [&](int I, int J) {
@@ -565,16 +608,16 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
   while (ri * (ri + 1) / 2 > p) --ri;
   while ((ri + 1) * (ri + 2) / 2 <= p) ++ri;
   int rj = p - ri * (ri + 1) / 2;
-  bool fresh = true;   // E of the current row is in registers, not yet in LDS
-  load_e(act[ri]);
-  load_c(act[rj]);
+  bool fresh = true;   // Y of the current row is in registers, not yet in LDS
+  load_y(act[ri], xr);
+  load_y(act[rj], yr);
   load_old(act[ri], act[rj]);
   for (; p < p1; ++p) {
     const int I0 = act[ri] * 64, J0 = act[rj] * 64;
     __syncthreads();   // the last pair's operand reads are done
     if (fresh)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) Xs[(lr + 4 * q) * LD + lk] = -xr[q];
+      for (int q = 0; q < 16; ++q) Xs[(lr + 4 * q) * LD + lk] = md * xr[q];
 #pragma unroll
     for (int q = 0; q < 16; ++q) Ys[(lr + 4 * q) * LD + lk] = yr[q];
     Mfma<double>::acc_t acc[2];
@@ -586,9 +629,9 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
     fresh = rj == ri;
     ri += fresh ? 1 : 0;
     rj = fresh ? 0 : rj + 1;
-    if (p + 1 < p1) {   // no work-group of this launch writes another's tile, E or C
-      if (fresh) load_e(act[ri]);
-      load_c(act[rj]);
+    if (p + 1 < p1) {   // no work-group of this launch writes another's tile or Y
+      if (fresh) load_y(act[ri], xr);
+      load_y(act[rj], yr);
       load_old(act[ri], act[rj]);
     }
     const double* xa = Xs + (32 * wr + ln) * LD + kq;
@@ -611,29 +654,27 @@ __global__ void __launch_bounds__(512) k_sw_update(double* __restrict__ mats, in
 }
 
 // Row and column K of the swept matrix, one 64-row tile I = lo + blockIdx.x per
-// work-group: the kept tiles of S_KK <- -D^{-1}; below K, S_I,Kh <- E_I's half
-// h; above K, S_Kh,I <- that half transposed.
+// work-group: the kept tiles of S_KK <- -E_K; below K, S_I,Kh <- E_I's half h;
+// above K, S_Kh,I <- that half transposed.
 __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mats, int n, int kb, int w, int lo,
                                                         const double* __restrict__ work,
-                                                        const double* __restrict__ dinv_all,
                                                         const int* __restrict__ flags) {
   __shared__ double Ts[64][65];
   const int I = lo + blockIdx.x, I0 = I * 64, K0 = kb / 64, Ke = (kb + w + 63) / 64;
   if (!(I >= K0 && I < Ke) && !flags[(size_t)blockIdx.y * ((n + 63) / 64) + I]) return;   // stays zero
   double* A = mats + (size_t)blockIdx.y * n * n;
-  const double* E = work + (size_t)blockIdx.y * 2 * n * GJ_NB + (size_t)n * GJ_NB;
-  const double* Di = dinv_all + (size_t)blockIdx.y * GJ_NB * GJ_NB;
+  const double* E = work + (size_t)blockIdx.y * sweep_panels(n);
   const int tid = threadIdx.x;
   if (I >= K0 && I < Ke) {
-    // row tile I of D's kept lower part: columns 0 .. 64 (I - K0) + 63
+    // row tile I of K's kept lower part: columns 0 .. 64 (I - K0) + 63
     const int r0 = 64 * (I - K0);
     for (int h = 0; h <= I - K0; ++h) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         const int t = tid + 256 * q, a = t >> 6, b = t & 63;
-        const int ra = r0 + a, cb = 64 * h + b;
-        const double x = -Di[(size_t)ra * GJ_NB + cb];
-        if (ra < w && cb < w) A[(size_t)(kb + ra) * n + kb + cb] = x;
+        const int cb = 64 * h + b;
+        const double x = -E[(size_t)(r0 + a < w ? I0 + a : n - 1) * GJ_NB + cb];
+        if (r0 + a < w && cb < w) A[(size_t)(I0 + a) * n + kb + cb] = x;
       }
     }
     return;
@@ -674,40 +715,41 @@ __global__ void __launch_bounds__(256) k_sw_panel_write(double* __restrict__ mat
 // One step of the sweeps: block [kb, kb + w) (w <= 128, kb a multiple of 64, w
 // too unless the block ends the matrix) within the tiles from lo on; partial:
 // the rows below the block only.
-static void sweep_step(double* mats, int n, int kb, int w, int lo, bool partial, int count, double* work, double* dinv,
+static void sweep_step(double* mats, int n, int kb, int w, int lo, bool partial, int count, double* work, double* piv,
                        int* flags, hipStream_t s) {
   const int T = (n + 63) / 64, Ke = (kb + w + 63) / 64;
-  IBMG_KLAUNCH(k_gj_diag, dim3(count), dim3(1024), 0, s, mats, n, kb, w, dinv);
+  IBMG_KLAUNCH(k_sw_pivot, dim3(count), dim3(1024), 0, s, mats, n, kb, w, piv);
   IBMG_LAUNCH_CHECK();
   IBMG_KLAUNCH(k_sw_panel_read, dim3(T - lo, count), dim3(256), 0, s, mats, n, kb, w, lo, work, flags);
   IBMG_LAUNCH_CHECK();
-  const int r0 = partial ? Ke : lo;   // first row tile of the scaling and of the panel
+  const int r0 = partial ? Ke : lo;   // first row tile of E and of the panel
   if (T - r0 > 0) {
-    IBMG_KLAUNCH(k_sw_scale, dim3(T - r0, count, 2), dim3(256), 0, s, mats, dinv, n, kb, w, r0, work, flags);
+    const int gps = std::min((T - lo + 1) / 2, std::max(1, 768 / count)), c8 = (count + 7) / 8 * 8;
+    IBMG_KLAUNCH(k_sw_scale, dim3(gps * c8), dim3(512), 0, s, mats, piv, n, kb, w, lo, r0, gps, count, work, flags);
     IBMG_LAUNCH_CHECK();
     // work-groups per matrix (one fits a CU): a pair each for a few matrices,
     // else enough for six rounds of the device, so that matrices with more
     // active pairs even out
     const int t = T - lo, pairs = t * (t + 1) / 2, gpm = std::min(pairs, std::max(4, 1536 / count));
-    IBMG_KLAUNCH(k_sw_update, dim3(gpm * ((count + 7) / 8 * 8)), dim3(512), 0, s, mats, n, kb, w, lo, r0, gpm, count,
-                 work, flags);
+    IBMG_KLAUNCH(k_sw_update, dim3(gpm * c8), dim3(512), 0, s, mats, n, kb, w, lo, r0, gpm, count,
+                 work, piv, flags);
     IBMG_LAUNCH_CHECK();
-    IBMG_KLAUNCH(k_sw_panel_write, dim3(T - r0, count), dim3(256), 0, s, mats, n, kb, w, r0, work, dinv, flags);
+    IBMG_KLAUNCH(k_sw_panel_write, dim3(T - r0, count), dim3(256), 0, s, mats, n, kb, w, r0, work, flags);
     IBMG_LAUNCH_CHECK();
   }
 }
 
 // the parts of a sweep's workspace (sweep_work)
-static double* sweep_dinv(double* work, int n, int count) { return work + (size_t)count * 2 * n * GJ_NB; }
+static double* sweep_piv(double* work, int n, int count) { return work + (size_t)count * sweep_panels(n); }
 static int* sweep_flags(double* work, int n, int count) {
-  return reinterpret_cast<int*>(sweep_dinv(work, n, count) + (size_t)count * GJ_NB * GJ_NB);
+  return reinterpret_cast<int*>(sweep_piv(work, n, count) + (size_t)count * kGjPivot);
 }
 
 void launch_gj_invert(double* mats, int n, int count, double* work, hipStream_t s) {
   if (!count) return;
   if (n > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
   for (int kb = 0; kb < n; kb += GJ_NB)
-    sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, sweep_dinv(work, n, count),
+    sweep_step(mats, n, kb, std::min(GJ_NB, n - kb), 0, false, count, work, sweep_piv(work, n, count),
                sweep_flags(work, n, count), s);
 }
 
@@ -715,12 +757,12 @@ void launch_box_eliminate(double* mats, BoxMat bm, int count, double* work, hipS
   if (!count) return;
   if (bm.nnp % 64) throw Error(IBMG_ERR_ARG, "the owned unknowns start at a tile");
   if (bm.ld > 64 * kSwMaxTiles) throw Error(IBMG_ERR_ARG, "matrix too large for the block sweeps");
-  double* dinv = sweep_dinv(work, bm.ld, count);
+  double* piv = sweep_piv(work, bm.ld, count);
   int* flags = sweep_flags(work, bm.ld, count);
   for (int kb = 0; kb < bm.nnp; kb += GJ_NB)
-    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, dinv, flags, s);
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.nnp - kb), 0, true, count, work, piv, flags, s);
   for (int kb = bm.nnp; kb < bm.ld; kb += GJ_NB)
-    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.ld - kb), bm.nnp / 64, false, count, work, dinv, flags, s);
+    sweep_step(mats, bm.ld, kb, std::min(GJ_NB, bm.ld - kb), bm.nnp / 64, false, count, work, piv, flags, s);
 }
 
 // The inverse's owned rows at the non-owned columns, M_on = S_oo^{-1} (-W), for

@@ -565,9 +565,12 @@ void launch_patch_assemble(const int* patch_ids, int count, BoxGeom g, StokesCoe
 // tiles on or below the diagonal (64 x 64, diagonal tiles in full) hold
 // -A^{-1}.  work: sweep_work(n, count) doubles.
 constexpr int kGjNb = 128;  // block width of the sweeps
+constexpr size_t kGjPivot = (size_t)kGjNb * kGjNb + kGjNb;   // a pivot block's factors
+// the panels C (then E) and Y of a matrix, whole blocks of 16 rows each
+__host__ __device__ inline size_t sweep_panels(size_t n) { return 2 * ((n + 15) / 16 * 16) * kGjNb; }
 inline size_t sweep_work(size_t n, size_t count) {
-  // per matrix: the panels C and E, the pivot block's inverse, a flag per 64 rows
-  return count * (2 * n * kGjNb + (size_t)kGjNb * kGjNb + (n + 127) / 128);
+  // per matrix: the panels, the pivot block's factors, a flag per 64 rows
+  return count * (sweep_panels(n) + kGjPivot + (n + 127) / 128);
 }
 void launch_gj_invert(double* mats, int n, int count, double* work, hipStream_t s);
 // The restricted boxes' elimination: afterwards the rows of the owned unknowns
