@@ -74,7 +74,7 @@ class BatchSolver final : public BatchBase {
       const int n0 = sys_[0]->n0_;
       const size_t stride = (size_t)n0 * n0;
       const int grp = (int)std::max<size_t>(1, std::min<size_t>(nsys, ((size_t)1 << 27) / stride));
-      DBuf<double> mats(stride * grp), work(sweep_work(n0, grp));
+      DBuf<double> mats(stride * grp), work(sweep_work(n0, grp)), res(stride);
       for (int p0 = 0; p0 < nsys; p0 += grp) {
         const int cnt = std::min(grp, nsys - p0);
         for (int p = p0; p < p0 + cnt; ++p) {
@@ -83,7 +83,7 @@ class BatchSolver final : public BatchBase {
                                   hipMemcpyDeviceToDevice, s));
         }
         launch_gj_invert(mats.p, n0, cnt, work.p, s);
-        for (int p = p0; p < p0 + cnt; ++p) sys_[p]->finish_coarse(mats.p + (p - p0) * stride, s);
+        for (int p = p0; p < p0 + cnt; ++p) sys_[p]->finish_coarse(mats.p + (p - p0) * stride, res.p, s);
         IBMG_HIP(hipStreamSynchronize(s));
       }
       for (int p = 0; p < nsys; ++p) sys_[p]->check_breakdown(s, true);

@@ -646,8 +646,8 @@ void launch_ras_apply(const T* r, T* z, BoxGeom g, const T* inv, const int* ib_b
 void launch_coarse_assemble(int N, StokesCoef<double> c, const int* tptr_u, const int* tcol_u,
                             const double* tval_u, const int* tptr_v, const int* tcol_v,
                             const double* tval_v, int nb, double* aug, hipStream_t s);
-// the shifted coarsest matrix for the block sweeps (launch_gj_invert) and the
-// pseudo-inverse from the swept matrix
+// the shifted coarsest matrix A for the block sweeps (launch_gj_invert), and the
+// pseudo-inverse from the swept matrix and A (which inv may hold); R: as large
 struct CoarseShift {
   double vel, p;
 };
@@ -655,7 +655,8 @@ CoarseShift coarse_shift(StokesCoef<double> c, bool rho_zero);
 void launch_coarse_assemble_sym(int N, StokesCoef<double> c, const int* tptr_u, const int* tcol_u,
                                 const double* tval_u, const int* tptr_v, const int* tcol_v, const double* tval_v,
                                 CoarseShift sh, double* mat, hipStream_t s);
-void launch_coarse_extract_sym(const double* mat, int N, CoarseShift sh, double* inv, hipStream_t s);
+void launch_coarse_refine(const double* swept, const double* A, double* R, int N, CoarseShift sh, double* inv,
+                          hipStream_t s);
 // count augmented systems [A | I] (n x 2n each, stride doubles apart), a work-group each
 void launch_coarse_invert(double* aug, int n, int count, size_t stride, hipStream_t s);
 void launch_coarse_extract(const double* aug, int n, int n0, double* inv, hipStream_t s);

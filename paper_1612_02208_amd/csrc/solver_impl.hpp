@@ -1234,7 +1234,7 @@ class Solver final : public SolverBase {
     const int nb = d_.rho == 0.0 ? 3 : 1, nn = n0_ + nb;
     const size_t mat = pivot ? (size_t)nn * 2 * nn : (size_t)n0_ * n0_;
     // (a tangent handle's rebuilds may change between the two)
-    const size_t swept = (size_t)n0_ * n0_ + sweep_work(n0_, 1);
+    const size_t swept = 2 * (size_t)n0_ * n0_ + sweep_work(n0_, 1);
     DBuf<double> aug(tangent_ ? std::max(swept, (size_t)nn * 2 * nn) : swept);
     if (pivot) {
       launch_fill<double>(aug.p, 0.0, mat, s);
@@ -1244,6 +1244,7 @@ class Solver final : public SolverBase {
       assemble_sym(aug.p);
     }
     inv0_.alloc((size_t)n0_ * n0_);
+    if (!pivot) assemble_sym(inv0_.p);   // once more, for the refinement
     if (!dry_run() && !side_) {
       IBMG_HIP(hipStreamCreateWithFlags(&side_, hipStreamNonBlocking));
       IBMG_HIP(hipEventCreateWithFlags(&ev_fork_, hipEventDisableTiming));
@@ -1255,8 +1256,8 @@ class Solver final : public SolverBase {
       launch_coarse_invert(aug.p, nn, 1, 0, side_);
       launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
     } else {
-      launch_gj_invert(aug.p, n0_, 1, aug.p + mat, side_);
-      launch_coarse_extract_sym(aug.p, N, sh, inv0_.p, side_);
+      launch_gj_invert(aug.p, n0_, 1, aug.p + 2 * mat, side_);
+      launch_coarse_refine(aug.p, inv0_.p, aug.p + mat, N, sh, inv0_.p, side_);
     }
     IBMG_HIP(hipEventRecord(ev_join_, side_));
     coarse_aug_ = std::move(aug);
@@ -1270,11 +1271,11 @@ class Solver final : public SolverBase {
     coarse_aug_.release();
   }
 
-  // the coarsest inverse from the caller's swept copy of aug0_
-  void finish_coarse(const double* swept, hipStream_t s) {
+  // the coarsest inverse from the caller's swept copy of aug0_ (R: as large)
+  void finish_coarse(const double* swept, double* R, hipStream_t s) {
     Level<T>& lev = levels_[0];
     inv0_.alloc((size_t)n0_ * n0_);
-    launch_coarse_extract_sym(swept, lev.N, coarse_shift(lev.cd, d_.rho == 0.0), inv0_.p, s);
+    launch_coarse_refine(swept, aug0_.p, R, lev.N, coarse_shift(lev.cd, d_.rho == 0.0), inv0_.p, s);
     aug0_.release();
     defer_coarse_ = false;
   }
