@@ -262,8 +262,8 @@ class BatchSolver final : public BatchBase {
             continue;
           }
           ee.push_back(ent);
-          wt.push_back(lev.wmat.p + (size_t)lev.wptr[i] * lev.w_stride);
-          qt.push_back(lev.inv_sym.p + (size_t)i * sym_box_stride(lev.g));
+          wt.push_back(lev.wmat + (size_t)lev.wptr[i] * lev.w_stride);
+          qt.push_back(lev.inv_sym + (size_t)i * sym_box_stride(lev.g));
           wrow.insert(wrow.end(), lev.wrow.begin() + lev.wptr[i], lev.wrow.begin() + lev.wptr[i + 1]);
           wptr.push_back((int)wrow.size());
           ord.insert(ord.end(), lev.ord.begin() + (size_t)i * lev.g.nown, lev.ord.begin() + (size_t)(i + 1) * lev.g.nown);

@@ -1009,6 +1009,65 @@ void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr,
   IBMG_LAUNCH_CHECK();
 }
 
+// What the eliminated form costs in accuracy in 32 bits: the roundings of W and of
+// r_o - W r_n reach z through Q, so against whole rows the mean square error of a
+// kind of unknown grows by sum_ik Q_ik^2 (1 + |W_k|^2) / sum_ik Q_ik^2, i over its
+// owned positions.  k_w_weight: the weights 1 + |W_k|^2, a wave per row;
+// k_elim_loss: both sums of velocities and pressures, every entry of the symmetric Q
+// read once, kLossParts work-groups a box and no atomics (the host adds their sums).
+__global__ void k_w_weight(const double* __restrict__ mats, BoxMat bm, int nown, double* __restrict__ wt) {
+  const double* A = mats + (size_t)blockIdx.y * bm.ld * bm.ld;
+  const int lane = threadIdx.x & 63;
+  for (int k = blockIdx.x * 4 + (threadIdx.x >> 6); k < nown; k += gridDim.x * 4) {
+    const double* Ar = A + (size_t)(bm.nnp + k) * bm.ld;
+    double v = 0.0;
+    for (int j = lane; j < bm.nn; j += 64) v = fma(Ar[j], Ar[j], v);
+    v = wave_sum(v);
+    if (lane == 0) wt[(size_t)blockIdx.y * nown + k] = 1.0 + v;
+  }
+}
+
+__global__ void __launch_bounds__(256) k_elim_loss(const double* __restrict__ mats, BoxMat bm, int nown, int nvel,
+                                                   const unsigned short* __restrict__ ord,
+                                                   const double* __restrict__ wt, double* __restrict__ out) {
+  __shared__ double red[4][4];
+  const double* A = mats + (size_t)blockIdx.y * bm.ld * bm.ld;
+  const unsigned short* o = ord + (size_t)blockIdx.y * nown;
+  const double* w = wt + (size_t)blockIdx.y * nown;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};   // weighted and plain, of velocities and of pressures
+  for (int i = blockIdx.x; i < nown; i += gridDim.x) {
+    const double* Ar = A + (size_t)(bm.nnp + i) * bm.ld + bm.nnp;
+    const double wi = w[i], ui = o[i] < nvel ? 1.0 : 0.0;
+    for (int k = threadIdx.x; k <= i; k += 256) {
+      const double q = Ar[k] * Ar[k], uk = o[k] < nvel ? 1.0 : 0.0;
+      const double a = q * w[k], b = k < i ? q * wi : 0.0, c = k < i ? q : 0.0;
+      s[0] += ui * a + uk * b;
+      s[1] += ui * q + uk * c;
+      s[2] += (1.0 - ui) * a + (1.0 - uk) * b;
+      s[3] += (1.0 - ui) * q + (1.0 - uk) * c;
+    }
+  }
+  const int wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const double v = wave_sum(s[m]);
+    if ((threadIdx.x & 63) == 0) red[wave][m] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4)
+    out[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + threadIdx.x] =
+        (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+void launch_elim_loss(const double* mats, int count, BoxMat bm, BoxGeom g, const unsigned short* ord, double* wt,
+                      double* out, hipStream_t s) {
+  if (!count) return;
+  IBMG_KLAUNCH(k_w_weight, dim3(16, count), dim3(256), 0, s, mats, bm, g.nown, wt);
+  IBMG_LAUNCH_CHECK();
+  IBMG_KLAUNCH(k_elim_loss, dim3(kLossParts, count), dim3(256), 0, s, mats, bm, g.nown, 2 * g.nown / 3, ord, wt, out);
+  IBMG_LAUNCH_CHECK();
+}
+
 // ---------------------------------------------------------------------------
 // Restricted additive Schwarz (Alg. 2 from a zero guess):
 //   z[G~_k] = (L_k^{-1} R_k r)[G~_k]  for every box k.

@@ -620,6 +620,13 @@ template <typename T>
 void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr, const int* wrow, int ws, T* out,
                       hipStream_t s);
 
+// Four sums per box and part of kLossParts, of eliminated boxes before
+// launch_extract_*: velocities' sum of Q_ik^2 (1 + |W_k|^2), of Q_ik^2, and
+// pressures' (out: count kLossParts 4; wt: count nown)
+constexpr int kLossParts = 8;
+void launch_elim_loss(const double* mats, int count, BoxMat bm, BoxGeom g, const unsigned short* ord, double* wt,
+                      double* out, hipStream_t s);
+
 // The interior boxes' shared inverse in its four parity classes (ras_int_block):
 // M (T[4][nrt][Kp][16]), the orbits' representatives kcode[K] and the rows'
 // rcode[R] (comp << 24 | jj << 12 | ii; rcode with the owned images' bits 1 e,

@@ -45,6 +45,15 @@ constexpr int kFoldBlocks = 256;
 // factor) where their whole rows would take at least this much; see
 // prepare_boxes.
 constexpr size_t kElimMinBytes = (size_t)192 << 20;
+// An FP32 smoother takes the eliminated form only where it is no less accurate
+// than whole rows: its two roundings, amplified as launch_elim_loss measures (the
+// sums' ratio), against the whole rows' longer sums.  Error of one sweep against
+// FP64, eliminated over whole rows, by that ratio (16 x 16/4 and 8 x 8/2 boxes,
+// annuli and the thin and thick structures over stiffnesses): velocities 0.55 to
+// 0.65 at 1.4 to 1.6, 0.95 at 3.3, 0.98 at 5.0, 1.14 at 8.3, 1.24 at 10, 1.41 at
+// 7.3, 6.2 to 33 on the stiffest; pressures 0.6 to 0.8 at 1.1 to 1.3, 0.65 at 1.6,
+// 1.7 at 4.2 and 4.4.
+constexpr double kElimMaxLossVel = 5.0, kElimMaxLossPre = 1.6;
 // Pre-smoothing steps up to which the V-cycle takes the residual it restricts
 // from the Arnoldi relation, without an operator application.  That residual
 // leaves out what rounding did to L z_q and to w, which grows with the basis:
@@ -106,7 +115,7 @@ struct Level {
   std::vector<int> uniq;  // unique box ids (IB boxes, then one interior representative)
   std::vector<int> ib_list, int_list;
   DBuf<int> d_ib, d_int;
-  DBuf<T> inv;            // [n_unique][nch][nloc][64]
+  DBuf<T> inv;            // [n_unique][nch][nloc][64], or W and Q
   // the interior boxes' shared inverse in its four parity classes (ras_int_block)
   std::vector<int> kcode, rcode, klocal, rlocal;
   DBuf<int> d_kcode, d_rcode, d_klocal, d_rlocal;
@@ -122,13 +131,15 @@ struct Level {
   DBuf<unsigned short> d_ord, d_own;
   // eliminated storage of the IB boxes: the W rows, the symmetric factor, the
   // first pass's result and the per-box partials
-  bool use_sym = false;
+  bool use_sym = false, may_sym = false;
+  double loss[4] = {0, 0, 0, 0};   // launch_elim_loss's sums (FP32 smoothers)
   std::vector<int> wptr, wrow;
   std::vector<unsigned char> coupled;
   DBuf<int> d_wptr, d_wrow;
   DBuf<unsigned char> d_coupled;
   int w_max = 0, w_stride = 0;
-  DBuf<T> wmat, inv_sym, w_res, sym_part;
+  T *wmat = nullptr, *inv_sym = nullptr;   // W and Q, within inv
+  DBuf<T> w_res, sym_part;
   // restricted multiplicative Schwarz: box colours; ib_list and int_list
   // sorted by colour, colour c spanning [ib_off[c], ib_off[c+1]) and
   // [int_off[c], int_off[c+1])
@@ -277,10 +288,13 @@ class Solver final : public SolverBase {
     if (inv0_.n) scan(inv0_.p, inv0_.n, "the coarsest inverse");
     for (int l = 1; l <= L_ && !coarse_only; ++l) {
       Level<T>& lev = levels_[l];
-      if (lev.inv.n) scan(lev.inv.p, lev.inv.n, ("the box inverses of level " + std::to_string(l)).c_str());
+      if (lev.use_sym) {
+        scan(lev.inv_sym, (size_t)lev.n_ib * sym_box_stride(lev.g), ("the IB box inverses of level " + std::to_string(l)).c_str());
+        scan(lev.wmat, lev.wrow.size() * (size_t)lev.w_stride, ("the IB box factors of level " + std::to_string(l)).c_str());
+      } else {
+        scan(lev.inv.p, rows_held(lev) * box_stride(lev), ("the box inverses of level " + std::to_string(l)).c_str());
+      }
       if (lev.cls.n) scan(lev.cls.p, lev.cls.n, ("the interior box inverse of level " + std::to_string(l)).c_str());
-      if (lev.inv_sym.n) scan(lev.inv_sym.p, lev.inv_sym.n, ("the IB box inverses of level " + std::to_string(l)).c_str());
-      if (lev.wmat.n) scan(lev.wmat.p, lev.wmat.n, ("the IB box factors of level " + std::to_string(l)).c_str());
       if (lev.sc)
         if (!(std::isfinite(lev.sc->lamA) && lev.sc->lamA > 0.0 && std::isfinite(lev.sc->lamM) && lev.sc->lamM > 0.0))
           throw Error(IBMG_ERR_BREAKDOWN, "Schur-complement Chebyshev bound of level " + std::to_string(l) +
@@ -1328,22 +1342,30 @@ class Solver final : public SolverBase {
     const size_t l = &lev - levels_.data();
     const int per_launch = d_.smoother == IBMG_RMS ? lev.n_ib / std::max(1, lev.ncolour)
                                                    : lev.n_ib * (l < members_.size() ? members_[l] : 1);
-    lev.use_sym = lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
+    // An FP32 level keeps room for both forms: which one it takes follows from the
+    // eliminated boxes (kElimMaxLossVel), in build_boxes.
+    lev.may_sym = lev.n_ib > 0 && lev.bm.nn <= kElimMaxNn &&
                   (size_t)per_launch * box_stride(lev) * sizeof(T) >= kElimMinBytes &&
                   std::getenv("IBMG_NO_SYM") == nullptr;
-    if (lev.use_sym) {
-      list_w_rows(lev);
-      lev.d_wptr.upload(lev.wptr, s);
-      lev.d_wrow.upload(lev.wrow, s);
-      lev.d_coupled.upload(lev.coupled, s);
-      lev.wmat.alloc(lev.wrow.size() * (size_t)lev.w_stride);
-      lev.inv_sym.alloc((size_t)lev.n_ib * sym_box_stride(g));
-      if (!defer_coarse_) {   // (a batch has its own for all members)
-        lev.w_res.alloc((size_t)lev.n_ib * g.nown);
-        lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
-      }
+    lev.use_sym = lev.may_sym;
+    const size_t rows = rows_held(lev) * box_stride(lev);
+    if (!lev.may_sym) {
+      lev.inv.alloc(rows);
+      return;
     }
-    lev.inv.alloc((size_t)(inv_end(lev) - inv_base(lev)) * box_stride(lev));
+    list_w_rows(lev);
+    lev.d_wptr.upload(lev.wptr, s);
+    lev.d_wrow.upload(lev.wrow, s);
+    lev.d_coupled.upload(lev.coupled, s);
+    const size_t wlen = (lev.wrow.size() * (size_t)lev.w_stride + 63) / 64 * 64;
+    const size_t both = wlen + (size_t)lev.n_ib * sym_box_stride(g);
+    lev.inv.alloc(sizeof(T) == 4 ? std::max(rows, both) : both);
+    lev.wmat = lev.inv.p;
+    lev.inv_sym = lev.inv.p + wlen;
+    if (!defer_coarse_) {   // (a batch has its own for all members)
+      lev.w_res.alloc((size_t)lev.n_ib * g.nown);
+      lev.sym_part.alloc((size_t)lev.n_ib * sym_part_len(g));
+    }
   }
 
   // the box matrices' order from unique box u0 on
@@ -1356,21 +1378,36 @@ class Solver final : public SolverBase {
   // the eliminated storage from IB box i0 on
   SymIB sym_of(Level<T>& lev, int i0) {
     if (!lev.use_sym) return SymIB{};
-    return SymIB{lev.inv_sym.p + (size_t)i0 * sym_box_stride(lev.g), nullptr, lev.sym_part.p,
-                 WBoxView{lev.wmat.p, nullptr, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
+    return SymIB{lev.inv_sym + (size_t)i0 * sym_box_stride(lev.g), nullptr, lev.sym_part.p,
+                 WBoxView{lev.wmat, nullptr, lev.d_wptr.p + i0, lev.d_wrow.p, lev.d_nonown.p,
                           lev.d_coupled.p + (size_t)i0 * lev.g.nown, lev.d_ord.p + (size_t)i0 * lev.g.nown, lev.bm.nn,
                           lev.w_stride, lev.w_max},
                  lev.w_res.p};
   }
 
-  // The unique boxes [inv_base, inv_end) whose owned rows lev.inv holds in
-  // chunks: the IB boxes unless they are in eliminated storage, and the
-  // interior boxes' shared inverse where no parity classes hold it.
-  static int inv_base(const Level<T>& lev) { return lev.use_sym ? lev.n_ib : 0; }
-  int inv_end(const Level<T>& lev) const { return has_classes(lev) ? lev.n_ib : lev.n_unique; }
+  // The unique boxes whose rows lev.inv holds in chunks where none are eliminated:
+  // the IB boxes, and the interior boxes' shared inverse where no parity classes
+  // hold it.
+  size_t rows_held(const Level<T>& lev) const { return has_classes(lev) ? lev.n_ib : lev.n_unique; }
   // the single-system restricted sweeps take the interior boxes in parity
   // classes; the summed combination and the batched form read whole rows
   bool has_classes(const Level<T>& lev) const { return !lev.sum_mode && !lev.int_list.empty(); }
+
+  // Adds what the eliminated form costs `count` IB boxes from u0 on (m: their
+  // matrices, eliminated) to the level's sums, and takes the level to whole rows
+  // where that is too much (a NaN from a breakdown included).
+  void elim_loss(Level<T>& lev, int u0, int count, const double* m, BoxMat bm, hipStream_t s) {
+    const size_t nsum = (size_t)count * kLossParts * 4;
+    DBuf<double> buf(nsum + (size_t)count * lev.g.nown);
+    if (dry_run()) return;
+    launch_elim_loss(m, count, bm, lev.g, order_of(lev, u0).ord, buf.p + nsum, buf.p, s);
+    std::vector<double> h(nsum);
+    IBMG_HIP(hipMemcpyAsync(h.data(), buf.p, nsum * sizeof(double), hipMemcpyDeviceToHost, s));
+    IBMG_HIP(hipStreamSynchronize(s));
+    if (u0 == 0) std::fill(lev.loss, lev.loss + 4, 0.0);
+    for (size_t i = 0; i < nsum; ++i) lev.loss[i % 4] += h[i];
+    lev.use_sym = lev.loss[0] <= kElimMaxLossVel * lev.loss[1] && lev.loss[2] <= kElimMaxLossPre * lev.loss[3];
+  }
 
   // The unique box inverses of every Schwarz level: assembled per level,
   // eliminated (or, for the summed combination, inverted) in batches that mix
@@ -1397,7 +1434,7 @@ class Solver final : public SolverBase {
       const size_t nbatch = (items.size() + cap - 1) / cap;
       const int batch = (int)((items.size() + nbatch - 1) / nbatch);
       DBuf<double> mats((size_t)batch * n * n), work(sweep_work(n, batch));
-      for (size_t b0 = 0; b0 < items.size(); b0 += batch) {
+      for (size_t b0 = 0; b0 < items.size();) {
         const int cnt = (int)std::min<size_t>(batch, items.size() - b0);
         // runs of one level with consecutive unique indices
         auto for_runs = [&](auto fn) {
@@ -1417,6 +1454,19 @@ class Solver final : public SolverBase {
         });
         if (bm.nnp) launch_box_eliminate(mats.p, bm, cnt, work.p, s);
         else launch_gj_invert(mats.p, n, cnt, work.p, s);
+        // (boxes that an earlier batch put down in the other form come again)
+        bool again = false;
+        if (sizeof(T) == 4)
+          for_runs([&](int l, int u0, int count, size_t slot) {
+            Level<T>& lev = levels_[l];
+            if (!lev.use_sym || u0 >= lev.n_ib) return;
+            elim_loss(lev, u0, std::min(count, lev.n_ib - u0), mats.p + slot * n * n, bm, s);
+            again = again || (!lev.use_sym && u0 > 0);
+          });
+        if (again) {
+          b0 = 0;
+          continue;
+        }
         for_runs([&](int l, int u0, int count, size_t slot) {
           Level<T>& lev = levels_[l];
           double* m0 = mats.p + slot * n * n;
@@ -1425,19 +1475,20 @@ class Solver final : public SolverBase {
           // representative (the last) get whole rows
           const int nsym = lev.use_sym ? std::min(count, std::max(0, lev.n_ib - u0)) : 0;
           if (bm.nnp) launch_box_on(m0 + (size_t)nsym * n * n, bm, count - nsym, s);
-          const int c0 = std::max(u0, inv_base(lev)), c1 = std::min(u0 + count, inv_end(lev));
-          if (c1 > c0)
-            launch_extract_rows<T>(m0 + (size_t)(c0 - u0) * n * n, c1 - c0, lev.g, bm, order_of(lev, c0),
-                                   lev.inv.p + (size_t)(c0 - inv_base(lev)) * box_stride(lev), s);
+          const int c1 = std::min(u0 + count, (int)rows_held(lev));
+          if (!lev.use_sym && c1 > u0)
+            launch_extract_rows<T>(m0, c1 - u0, lev.g, bm, order_of(lev, u0), lev.inv.p + (size_t)u0 * box_stride(lev),
+                                   s);
           if (has_classes(lev) && u0 + count > lev.n_ib)
             launch_extract_classes<T>(m0 + (size_t)(lev.n_ib - u0) * n * n, bm,
                                       lev.d_own.p + (size_t)lev.n_ib * lev.g.nown, lev.clsv, lev.d_klocal.p,
                                       lev.d_rlocal.p, lev.cls.p, s);
           if (nsym > 0) {
-            launch_extract_sym<T>(m0, nsym, lev.g, bm, lev.inv_sym.p + (size_t)u0 * sym_box_stride(lev.g), s);
-            launch_extract_w<T>(m0, nsym, bm, lev.d_wptr.p + u0, lev.d_wrow.p, lev.w_stride, lev.wmat.p, s);
+            launch_extract_sym<T>(m0, nsym, lev.g, bm, lev.inv_sym + (size_t)u0 * sym_box_stride(lev.g), s);
+            launch_extract_w<T>(m0, nsym, bm, lev.d_wptr.p + u0, lev.d_wrow.p, lev.w_stride, lev.wmat, s);
           }
         });
+        b0 += batch;
       }
       IBMG_HIP(hipStreamSynchronize(s));
     }
