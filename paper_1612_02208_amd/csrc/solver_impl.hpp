@@ -27,15 +27,24 @@ namespace detail {
 
 constexpr int kMaxNu = 8;
 constexpr int kMaxRestart = 64;
-constexpr int kScalY = 1;     // scal[1..16]: least-squares solution
 // The IB term of L_IB w comes from a level's explicit Galerkin rows (in the
-// operator's own launch) up to this many entries.  Beyond the bare stencil the
-// rows cost about 4.2 to 5.9 us per million entries (12 bytes each, FP64), the
-// other form (interpolate, spring forces, gather: three launches) about 15 us
-// at any size measured: 512^2 annulus, FP64, 2.35 M entries 18.8 against 24.9
-// us, 4.6 M (tangent springs) 36.3 against 24.2.  IBMG_NO_IB_ROWS in the
-// environment takes the other form on every level.
-constexpr size_t kIbRowsMaxEntries = 3500000;
+// operator's own launch) up to this many entries for the level's longest face list
+// and its number of points.  The rows cost about 4 to 5.9 us per million entries
+// (12 bytes each, FP64; 8 in FP32); the other form (interpolate, spring forces,
+// gather: three launches) at least 12 to 15 us, and more with the points and with
+// the longest list, which one thread walks.  Rows and the other form, FP64 us (FP32):
+// 512^2, 2000 scattered points, 3.32 M entries, list 4: 21.7 and 16.2 (17.0, 11.8);
+// annuli, 4 x 2048, 2.35 M, 17: 15.3 and 19.5 (10.7, 15.9), with tangent springs
+// 4.59 M, 17: 31.5 and 19.9 (26.1, 15.6), 8 x 4096, 4.03 M, 51: 19.5 and 47.3
+// (15.1, 34.3); thick shell of 59584 points, 4.57 M, 40: 23.6 and 75.6 (18.7, 52.7);
+// 1024^2, suspension of 32768 points, 6.50 M, 10: 55.0 and 42.6 (43.1, 30.9); thick
+// shell of 235904 points, 17.65 M, 41: 106 and 368 (56, 339).  Over 244 such levels
+// the line costs 0.7 % against the better form each time (3.5 M entries whatever the
+// lists: 7.2 %, eleven times at the worst).  IBMG_NO_IB_ROWS in the environment
+// takes the other form on every level.
+inline size_t ib_rows_max_entries(int longest, int points) {
+  return 1500000 + 100000 * (size_t)longest + 100 * (size_t)points;
+}
 // Blocks of the outer solve's long reductions up to which the next kernel's
 // blocks reduce the partial sums themselves: the folding launches cost more than
 // the reads (solves with and without folding: 32^2, 3 blocks, 1012 and 982 us;
@@ -429,15 +438,16 @@ class Solver final : public SolverBase {
   }
 
   // The level's rows with IB entries, the faces' flags and the lanes a row
-  // gets in the operator's launch (0: too many entries, see kIbRowsMaxEntries).
+  // gets in the operator's launch (0: too many entries, see ib_rows_max_entries).
   void list_ib_rows(Level<T>& lev, std::vector<unsigned char>& flag) const {
     const int nn = lev.N * lev.N;
     const size_t nnz = lev.f[0].tcol.size() + lev.f[1].tcol.size();
     lev.ib_rows.clear();
     lev.n_ib_v = 0;
     lev.ib_lanes = 0;
+    const int longest = std::max(lev.f[0].max_list, lev.f[1].max_list);
     // (a batch runs every member's rows in one launch, whatever their number)
-    if (!defer_coarse_ && (nnz == 0 || nnz > kIbRowsMaxEntries || std::getenv("IBMG_NO_IB_ROWS"))) return;
+    if (!defer_coarse_ && (nnz == 0 || nnz > ib_rows_max_entries(longest, M_) || std::getenv("IBMG_NO_IB_ROWS"))) return;
     flag.assign(nn, 0);
     for (int c = 0; c < 2; ++c)
       for (int q = 0; q < nn && !lev.f[c].tcol.empty(); ++q)
