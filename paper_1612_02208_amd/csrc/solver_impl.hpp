@@ -47,9 +47,11 @@ inline size_t ib_rows_max_entries(int longest, int points) {
 }
 // Blocks of the outer solve's long reductions up to which the next kernel's
 // blocks reduce the partial sums themselves: the folding launches cost more than
-// the reads (solves with and without folding: 32^2, 3 blocks, 1012 and 982 us;
-// 128^2, 48 blocks, 2188 and 2150; 256^2, 192 blocks, 3095 and 3058).
-constexpr int kFoldBlocks = 256;
+// the reads until every block reads them all from many.  30 iterations of one
+// restart cycle with and without folding, in us: 256^2 (192 blocks) 16301 and 15889,
+// 320^2 (300) 22191 and 21796, 416^2 (507) 28024 and 27679, 480^2 (675) 36768 and
+// 36482, 512^2 (768) 26055 and 26121, 640^2 (1024) 39678 and 40490.
+constexpr int kFoldBlocks = 704;
 // The IB boxes are kept eliminated (two passes over W and the symmetric owned
 // factor) where their whole rows would take at least this much; see
 // prepare_boxes.
