@@ -1270,7 +1270,8 @@ class Solver final : public SolverBase {
       assemble_sym(aug.p);
     }
     inv0_.alloc((size_t)n0_ * n0_);
-    if (!pivot) assemble_sym(inv0_.p);   // once more, for the refinement
+    if (!pivot)   // the matrix stays, for the refinement
+      IBMG_HIP(hipMemcpyAsync(inv0_.p, aug.p, mat * sizeof(double), hipMemcpyDeviceToDevice, s));
     if (!dry_run() && !side_) {
       IBMG_HIP(hipStreamCreateWithFlags(&side_, hipStreamNonBlocking));
       IBMG_HIP(hipEventCreateWithFlags(&ev_fork_, hipEventDisableTiming));
