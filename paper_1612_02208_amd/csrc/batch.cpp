@@ -18,11 +18,6 @@
 
 namespace ibmg {
 
-namespace {
-
-
-}  // namespace
-
 // Host checks of a batch's descriptors (every one valid, the shared
 // parameters equal, the options the batched form runs).
 void validate_batch(int nsys, const ibmg_desc* d) {
@@ -157,17 +152,16 @@ class BatchSolver final : public BatchBase {
     else return f.tvalf.p;
   }
 
-  // Concatenate the IB rows of system positions [0, count) at level l (or
-  // at each system's finest level when l < 0) with indices shifted by base.
+  // Concatenate the finest levels' IB rows of system positions [0, count) with
+  // indices shifted by base.
   template <typename U>
-  void gather_rows(int l, int count, const std::vector<size_t>& base, DBuf<int>& rows, DBuf<int>& ptr,
-                   DBuf<int>& col, DBuf<U>& val, int* nrows, hipStream_t s) {
+  void gather_rows(int count, const std::vector<size_t>& base, DBuf<int>& rows, DBuf<int>& ptr, DBuf<int>& col,
+                   DBuf<U>& val, int* nrows, hipStream_t s) {
     std::vector<int> hr, hp(1, 0), hc;
     std::vector<std::pair<const U*, size_t>> pieces;
     for (int p = 0; p < count; ++p) {
       Solver<T>& S = *sys_[p];
-      const int lv = l < 0 ? S.L_ : l;
-      Level<T>& lev = S.levels_[lv];
+      Level<T>& lev = S.levels_[S.L_];
       const size_t nn = (size_t)lev.N * lev.N;
       for (int c = 0; c < 2; ++c) {
         const CompFoot& f = lev.f[c];
@@ -307,7 +301,7 @@ class BatchSolver final : public BatchBase {
   void build_outer_rows(hipStream_t s) {
     std::vector<size_t> base(ns_);
     for (int p = 0; p < ns_; ++p) base[p] = (size_t)off_[p];
-    gather_rows<double>(-1, ns_, base, orows_, optr_, ocol_, oval_, &onrows_, s);
+    gather_rows<double>(ns_, base, orows_, optr_, ocol_, oval_, &onrows_, s);
   }
 
   void build_coarse(hipStream_t s) {

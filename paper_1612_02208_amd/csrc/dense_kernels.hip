@@ -940,7 +940,8 @@ void launch_extract_rows(const double* mats, int count, BoxGeom g, BoxMat bm, Bo
 // box keeps the two factors the elimination leaves (above):
 //   W rows: the owned rows coupled to a non-owned unknown (by the stencil along
 //           the box's edge or by the IB rows), nn columns each, row-major with
-//           a row stride of nn rounded up to even;
+//           a row stride of nn rounded up to a multiple of 4 (the first pass
+//           loads 16 bytes: four FP32 values or two FP64 ones);
 //   Q:      S_oo^{-1}, symmetric: chunk c (owned rows 64c .. 64c+63) holds the
 //           columns 0 .. 64 (c + 1) - 1 of 64 rows each (the tiles on and below
 //           the diagonal; zero beyond nown); the others are the transposes of
@@ -2008,12 +2009,11 @@ void launch_coarse_refine(const double* swept, const double* A, double* R, int N
 // results; the row swap; the scaled pivot row and the column's factors
 // staged in LDS; then the elimination over the whole matrix as one flat
 // loop, so each thread keeps several independent loads in flight.
-__global__ void __launch_bounds__(1024) k_coarse_invert(double* __restrict__ aug, int nn, size_t stride) {
+__global__ void __launch_bounds__(1024) k_coarse_invert(double* __restrict__ aug, int nn) {
   __shared__ double wmax[16];
   __shared__ int wimax[16];
   __shared__ double fac[1024];
   __shared__ double rowk[2048];   // the scaled pivot row (2 nn <= 2048)
-  aug += blockIdx.x * stride;     // one system per work-group
   const int ld = 2 * nn;
   const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6;
   for (int k = 0; k < nn; ++k) {
@@ -2068,10 +2068,9 @@ __global__ void __launch_bounds__(1024) k_coarse_invert(double* __restrict__ aug
   }
 }
 
-void launch_coarse_invert(double* aug, int nn, int count, size_t stride, hipStream_t s) {
+void launch_coarse_invert(double* aug, int nn, hipStream_t s) {
   if (nn > 1024) throw Error(IBMG_ERR_ARG, "coarsest system too large for one work-group");
-  if (count < 1) return;
-  IBMG_KLAUNCH(k_coarse_invert, dim3(count), dim3(1024), 0, s, aug, nn, stride);
+  IBMG_KLAUNCH(k_coarse_invert, dim3(1), dim3(1024), 0, s, aug, nn);
   IBMG_LAUNCH_CHECK();
 }
 

@@ -664,8 +664,8 @@ void launch_coarse_assemble_sym(int N, StokesCoef<double> c, const int* tptr_u, 
                                 CoarseShift sh, double* mat, hipStream_t s);
 void launch_coarse_refine(const double* swept, const double* A, double* R, int N, CoarseShift sh, double* inv,
                           hipStream_t s);
-// count augmented systems [A | I] (n x 2n each, stride doubles apart), a work-group each
-void launch_coarse_invert(double* aug, int n, int count, size_t stride, hipStream_t s);
+// the augmented system [A | I] (n x 2n) by one work-group
+void launch_coarse_invert(double* aug, int n, hipStream_t s);
 void launch_coarse_extract(const double* aug, int n, int n0, double* inv, hipStream_t s);
 template <typename T>
 void launch_coarse_apply(const double* inv, int n0, const T* r, T* z, hipStream_t s);
@@ -709,11 +709,6 @@ template <typename T>
 void launch_upd_dots_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,
                        int nblk_in = 0);
-// launch_scale_upd on every active system
-template <typename T>
-void launch_scale_upd_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, size_t nmax,
-                        const double* pin, int nblk_in, size_t pstride, double* hcol, size_t hstride,
-                        hipStream_t s);
 template <typename T>
 void launch_upd_norm_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, const double* pin,
                        int nblk, size_t pstride, double* hcol, size_t hstride, double* pout, hipStream_t s,

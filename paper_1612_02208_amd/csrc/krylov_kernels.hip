@@ -185,25 +185,18 @@ __global__ void __launch_bounds__(kThreads) k_scale_red(const T* t, T* v, BSeg s
   }
 }
 
-// The second Gram-Schmidt pass finished with the normalisation, from partial
-// sums of h2 = V^T t and |t|^2 (k + 1 per block):
+// A second Gram-Schmidt pass finished with the normalisation, from partial
+// sums of h2 = V^T t and |t|^2 (k + 1 per block), for the kernel timer (the solves
+// store the updated t before they scale it):
 // t2 = t - V h2, whose norm is sqrt(|t|^2 - |h2|^2) (t2 is orthogonal to the
 // orthonormal V), and t = t2 / |t2| (0 on an exact breakdown); block 0 adds
 // h2 into hcol[0..k) and stores |t2| into hcol[k].
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_scale_upd(T* t, const T* __restrict__ V, int k, size_t stride,
-                                                        BSeg sg, const double* __restrict__ pin, int nblk_in,
-                                                        size_t pstride, double* __restrict__ hcol,
-                                                        size_t hstride) {
+                                                        size_t n, const double* __restrict__ pin, int nblk_in,
+                                                        double* __restrict__ hcol) {
   __shared__ double red[32];
   __shared__ double h[64];
-  const int sy = blockIdx.y;
-  if (!seg_on(sg, sy)) return;
-  const size_t o = seg_begin(sg, sy), n = seg_len(sg, sy);
-  t += o;
-  V += o;
-  pin += sy * pstride;
-  hcol += sy * hstride;
   reduce_partials(pin, nblk_in, k + 1, h, red);
   double hh = 0.0;
   for (int q = 0; q < k; ++q) hh += h[q] * h[q];
@@ -571,17 +564,6 @@ void launch_scale_red_b(const T* t, T* v, BSeg sg, int nsys, size_t nmax, const 
 }
 
 template <typename T>
-void launch_scale_upd_b(T* t, const T* V, int k, size_t stride, BSeg sg, int nsys, size_t nmax,
-                        const double* pin, int nblk_in, size_t pstride, double* hcol, size_t hstride,
-                        hipStream_t s) {
-  if (nsys <= 0) return;
-  if (k < 1 || k > 8) throw Error(IBMG_ERR_ARG, "the norm-carrying second pass takes 1..8 basis vectors");
-  IBMG_KLAUNCH((k_scale_upd<T>), dim3(stream_blocks(nmax), nsys), dim3(kThreads), 0, s, t, V, k, stride, sg, pin,
-               nblk_in, pstride, hcol, hstride);
-  IBMG_LAUNCH_CHECK();
-}
-
-template <typename T>
 void launch_upd_dots(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk,
                      double* hcol, double* pout, hipStream_t s, int nblk_in) {
   launch_upd_dots_b<T>(t, V, k, stride, seg1(n), 1, pin, nblk, 0, hcol, 0, pout, s, nblk_in);
@@ -605,7 +587,9 @@ void launch_scale_red(const T* t, T* v, size_t n, const double* pin, int nblk, d
 template <typename T>
 void launch_scale_upd(T* t, const T* V, int k, size_t stride, size_t n, const double* pin, int nblk_in,
                       double* hcol, hipStream_t s) {
-  launch_scale_upd_b<T>(t, V, k, stride, seg1(n), 1, n, pin, nblk_in, 0, hcol, 0, s);
+  if (k < 1 || k > 8) throw Error(IBMG_ERR_ARG, "the norm-carrying second pass takes 1..8 basis vectors");
+  IBMG_KLAUNCH((k_scale_upd<T>), dim3(stream_blocks(n)), dim3(kThreads), 0, s, t, V, k, stride, n, pin, nblk_in, hcol);
+  IBMG_LAUNCH_CHECK();
 }
 
 int gs_blocks(size_t n) {
@@ -692,8 +676,6 @@ void launch_gs_combine_restrict(T* x, const T* Z, const T* u0, const T* V, int k
                                     hipStream_t);                                                      \
   template void launch_upd_dots_b<T>(T*, const T*, int, size_t, BSeg, int, const double*, int, size_t, \
                                      double*, size_t, double*, hipStream_t, int);                      \
-  template void launch_scale_upd_b<T>(T*, const T*, int, size_t, BSeg, int, size_t, const double*, int, \
-                                      size_t, double*, size_t, hipStream_t);                           \
   template void launch_upd_norm_b<T>(T*, const T*, int, size_t, BSeg, int, const double*, int, size_t, \
                                      double*, size_t, double*, hipStream_t, int);                      \
   template void launch_scale_red_b<T>(const T*, T*, BSeg, int, size_t, const double*, int, size_t,     \

@@ -1280,7 +1280,7 @@ class Solver final : public SolverBase {
     IBMG_HIP(hipEventRecord(ev_fork_, s));
     IBMG_HIP(hipStreamWaitEvent(side_, ev_fork_, 0));
     if (pivot) {
-      launch_coarse_invert(aug.p, nn, 1, 0, side_);
+      launch_coarse_invert(aug.p, nn, side_);
       launch_coarse_extract(aug.p, nn, n0_, inv0_.p, side_);
     } else {
       launch_gj_invert(aug.p, n0_, 1, aug.p + 2 * mat, side_);
@@ -2129,8 +2129,8 @@ class Solver final : public SolverBase {
       }
     } else if (kernel >= IBMG_KERNEL_APPLY_DOTS && kernel <= IBMG_KERNEL_SCALE_UPD) {
       // one smoothing step's Krylov kernels with the basis at its largest
-      // (k = nu vectors), and the outer solve's (and the batched smoothing's)
-      // kernels of a normalised basis: zero dots leave t as it is and unit
+      // (k = nu vectors), and the kernels of a normalised basis (the outer
+      // solve's, and k_scale_upd): zero dots leave t as it is and unit
       // norms keep the small algebra well posed, so repeated launches see the
       // same values
       require(level >= 1, "the smoothing kernels run on levels >= 1");
