@@ -164,8 +164,8 @@ typedef struct {
 /* Bytes of device workspace ibmg_create needs for ``desc``: the exact
  * high-water mark of the set-up's buffers (every level's operators, box
  * inverses and work vectors, the outer FGMRES basis for max_restart, and the
- * set-up's temporaries, among them up to 8 GiB of box matrices inverted in
- * one batch).  Runs the set-up's host planning (no device work).  A rebuild
+ * set-up's temporaries, among them up to 10 GiB of box matrices, with the
+ * elimination's work space, taken in one batch).  Runs the set-up's host planning (no device work).  A rebuild
  * at moved positions (ibmg_time_step) re-lays the position-dependent buffers
  * and needs more when the structure touches more boxes, so time-stepping
  * callers add headroom.  Errors: IBMG_ERR_ARG as ibmg_create. */
@@ -343,17 +343,19 @@ ibmg_status ibmg_sc_info(const ibmg_handle* h, int32_t level, double* lam, int32
  *   IBMG_KERNEL_APPLY_DOTS    L_IB^l z with the first Gram-Schmidt pass fused:
  *                             z read, the product written, k vectors read
  *                             ((k + 2) n values)
- *   IBMG_KERNEL_UPD_DOTS      t -= V h, then the second pass's dots and |t|^2:
- *                             t read and written, k vectors read ((k + 2) n)
- *   IBMG_KERNEL_SCALE_UPD     t = (t - V h2) / |t - V h2|, the norm taken as
- *                             sqrt(|t|^2 - |h2|^2) from those sums: t read and
- *                             written, k vectors read ((k + 2) n)
+ *   IBMG_KERNEL_UPD_DOTS      u = t - V h, then the second pass's dots and |u|^2
+ *                             (carried as coefficients: the basis is neither
+ *                             rescaled nor swept again): t read, u written, k
+ *                             vectors read ((k + 2) n)
  *   IBMG_KERNEL_COMBINE_LS    w += sum_q y_q Z_q after the small least squares:
  *                             k vectors and w read, w written ((k + 2) n)
- * and two kernels of the outer solve's (and the batched smoothing's) second
- * pass, timed on the same vectors:
+ * and, timed on the same vectors, two kernels of the outer solve's second pass
  *   IBMG_KERNEL_UPD_NORM      t -= V h2, then |t|^2: (k + 2) n
  *   IBMG_KERNEL_SCALE_RED     v = t / |t|: 2 n
+ * and one that joins the two, which no solve launches:
+ *   IBMG_KERNEL_SCALE_UPD     t = (t - V h2) / |t - V h2|, the norm taken as
+ *                             sqrt(|t|^2 - |h2|^2) from sums given: t read and
+ *                             written, k vectors read ((k + 2) n)
  * Synchronises ``stream``; IBMG_ERR_ARG if the level has no such work. */
 typedef enum {
   IBMG_KERNEL_RAS_IB = 0,

@@ -307,9 +307,9 @@ class StokesIB:
         this handle's stream, with its algorithmic bytes and flops per launch.
         kernel: "ras_ib", "ras_interior", "stencil", "restrict", "prolong",
         "spread", "interp", the smoothing step's Krylov kernels "apply_dots",
-        "upd_dots", "scale_upd", "combine_ls", the outer solve's second-pass
-        kernels "upd_norm", "scale_red" (single handles) or "ras_batch"
-        (batch handles)."""
+        "upd_dots", "combine_ls", the outer solve's second-pass kernels
+        "upd_norm", "scale_red", "scale_upd", which joins those two and which
+        no solve launches (single handles) or "ras_batch" (batch handles)."""
         k = {"ras_ib": _lib.KERNEL_RAS_IB, "ras_interior": _lib.KERNEL_RAS_INTERIOR,
              "stencil": _lib.KERNEL_STENCIL, "ras_batch": _lib.KERNEL_RAS_BATCH,
              "restrict": _lib.KERNEL_RESTRICT, "prolong": _lib.KERNEL_PROLONG,
