@@ -232,7 +232,8 @@ __device__ __forceinline__ void ldl16_step(Mfma<double>::acc_t& d, int kq, int l
 // count.  Per step the wave with the diagonal tile factorises it in registers (DPP
 // and shuffles, no barrier), and P = L_kk^{-1} S_k: and the update S_ij -= P_i^T
 // D^{-1} P_j run on the matrix cores: two barriers a step.  Bound by the eight
-// chains of 15 divisions: 59 us for 300 boxes.  Out: piv holds L below its 16 x 16 diagonal blocks,
+// chains of 15 divisions: 51 us for 300 boxes, 41 on average over the sweeps of a
+// 512^2 annulus's rebuild.  Out: piv holds L below its 16 x 16 diagonal blocks,
 // which are L_kk^{-1} (row-major, 128 wide; nothing above them), then 1 / D.
 // (The inverses of the 16 x 16 tiles themselves in place of the factors, which
 // are as ill-conditioned as the block, cost all digits on stiff structures: thin
@@ -420,9 +421,9 @@ __host__ __device__ constexpr int tri_row(int t) {
 // and so gets E_K = S_KK^{-1}.  L's 36 blocks lie in LDS (83 KB); a wave takes 16 rows
 // at a time, whose Y and E blocks stay in registers.  Bound by each wave's chain of
 // products through LDS, so a work-group (one fits a CU; gpm per matrix, on one XCD)
-// has eight waves, which share out the matrix's rows: 121 us a step on average over
-// the sweeps of a 512^2 annulus's rebuild (299 with a work-group of four waves per
-// tile, 220 with the loads of C under conditions).
+// has eight waves, which share out the matrix's rows: 207 us a step for 300 boxes,
+// 121 to 141 on average over the sweeps of a 512^2 annulus's rebuild (299 with a
+// work-group of four waves per tile, 220 with the loads of C under conditions).
 constexpr int kSwMaxTiles = 1024;   // most 64-row tiles of a swept matrix
 __global__ void __launch_bounds__(512) k_sw_scale(const double* __restrict__ mats, const double* __restrict__ piv_all,
                                                   int n, int kb, int w, int lo, int re, int gpm, int count,
